@@ -701,7 +701,6 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             ma.out_f32 = epi == EPI_QKV ? L.sub_q : L.sub_x;
             ma.out_s = epi == EPI_SWIGLU ? L.sub_hs : L.sub_xs;
             ma.pss_out = L.sub_pss;
-            ma.q_s = L.sub_q_s;
             HIP_TRY(timed(x, kc, (uint64_t)m.O * m.K * 2, [&] { return launch_gemm(epi, m, ma, x->n_cu, x->gemm_rgw, s); }));
         } else {
             const MvArgs &m = list[i].mv;

@@ -17,15 +17,16 @@
 // share activations (the other row tiles) are given consecutive positions on one die, so that what one of
 // them pulls from memory the others find in that die's L2.
 //
-// The epilogue is the block kernel's (mv_epilogue), run per (row group, sub-block) on that sub-block's
-// buffers: every sub-block ends up exactly as laid out for a 64-row block of the bulk layout.
+// The epilogue works on the accumulators in registers and leaves every sub-block exactly as laid out for a 64-row block
+// of the bulk layout.
 //
-// Where the tiles alone would leave compute units idle -- a matrix of few rows (o_proj, down_proj) under a macro
-// block of two to four sub-blocks: a prompt of 65-256 tokens, a candidate-evaluation window of more than 64 -- the
-// depth is split over two or four workgroups per tile as well (gridDim.y): each publishes its results, the
-// workgroup that arrives last at the tile's counter adds them in part order and runs the epilogue.
+// Workgroups come in rounds of one per compute unit.  Where the last round (or the only one: a matrix of few rows, a
+// macro block of few sub-blocks) would leave compute units idle, its tiles are split in depth over up to four
+// workgroups each: every wavefront publishes its results, and of the wavefronts that share a piece of a tile the one
+// that arrives last adds them in part order and runs the epilogue.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "swift_device.h"
@@ -37,38 +38,267 @@ namespace swift {
 namespace {
 
 constexpr int kRingBytes = 144 * 1024;   // most of LDS: what is in flight bounds what a compute unit takes in
+constexpr int kDeviceScope = 16;              // cache policy of buffer loads and stores: sc1
 constexpr int kNormFloats = 2 * 16 * 64;  // scratch of gemm_norm_scales
 
 // RMSNorm scales of the workgroup's two sub-blocks: rs[64 wn + r].  Thread (wn, q, r4) adds the partials q, q + 16,
 // .. of rows 4 r4 .. 4 r4 + 3 of sub-block wn (16 loads of 16 bytes in flight at a time); then one thread per row
-// adds the sixteen sums in order.
-__device__ inline void gemm_norm_scales(const MvArgs &a, const MacroArgs &ma, int sub0, float *rs, float *scratch) {
-    const int tid = threadIdx.x, r4 = tid & 15, q = (tid >> 4) & 15, wn = tid >> 8;
-    const int sub = min(sub0 + wn, ma.S - 1);
-    if (a.pss) {
-        const float *p = a.pss + (size_t)sub * ma.pss + 4 * r4;
-        f32x4 ss = {0.f, 0.f, 0.f, 0.f};
-        for (int p0 = 0; p0 < a.n_pss; p0 += 256) {
-            f32x4 v[16];
+// adds the sixteen sums in order.  The first 256 partials (hidden <= 4096: all of them) are requested by
+// gemm_norm_load, ahead of the ring's first stages, so that they do not queue behind 140 KB of tiles; the scales are
+// read by the epilogue only, so no barrier here waits for more than LDS.
+struct GemmNorm {
+    f32x4 v[16];
+};
+__device__ inline const float *gemm_norm_base(const MvArgs &a, const MacroArgs &ma, int sub0) {
+    const int tid = threadIdx.x;
+    return a.pss + (size_t)min(sub0 + (tid >> 8), ma.S - 1) * ma.pss + 4 * (tid & 15);
+}
+__device__ inline void gemm_norm_load(const MvArgs &a, const float *p, int p0, GemmNorm &n) {
+    const int q = (threadIdx.x >> 4) & 15;
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int i = p0 + q + 16 * u;
-                v[u] = i < a.n_pss ? *(const f32x4 *)(p + (size_t)i * a.rp) : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) ss += v[u];
-        }
-        *(f32x4 *)(scratch + (wn * 16 + q) * 64 + 4 * r4) = ss;
-    }
-    __syncthreads();
-    if (tid < 128) {
-        const int w2 = tid >> 6, r2 = tid & 63;
-        float ss = 0.f;
-        if (a.pss)
-            for (int q2 = 0; q2 < 16; ++q2) ss += scratch[(w2 * 16 + q2) * 64 + r2];
-        rs[tid] = a.pss ? 1.0f / sqrtf(ss / (float)a.norm_dim + a.eps) : 1.0f;
+    for (int u = 0; u < 16; ++u) {
+        const int i = p0 + q + 16 * u;
+        const f32x4 v = *(const f32x4 *)(p + (size_t)min(i, a.n_pss - 1) * a.rp);
+        n.v[u] = i < a.n_pss ? v : f32x4{0.f, 0.f, 0.f, 0.f};
     }
 }
+__device__ inline void gemm_norm_finish(const MvArgs &a, const float *p, GemmNorm &n, float *rs, float *scratch) {
+    const int tid = threadIdx.x, r4 = tid & 15, q = (tid >> 4) & 15, wn = tid >> 8;
+    f32x4 ss = {0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0;;) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) ss += n.v[u];
+        p0 += 256;
+        if (p0 >= a.n_pss) break;
+        gemm_norm_load(a, p, p0, n);
+    }
+    *(f32x4 *)(scratch + (wn * 16 + q) * 64 + 4 * r4) = ss;
+    lds_barrier();
+    if (tid < 128) {
+        const int w2 = tid >> 6, r2 = tid & 63;
+        float sum = 0.f;
+#pragma unroll
+        for (int q2 = 0; q2 < 16; ++q2) sum += scratch[(w2 * 16 + q2) * 64 + r2];
+        rs[tid] = 1.0f / sqrtf(sum / (float)a.norm_dim + a.eps);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// epilogue
+// ------------------------------------------------------------------------------------------
+// It works on the accumulators where they are: a wavefront's 8 accumulator tiles of a row group hold column 16 cb + col
+// = 2 r + term in lane column col, tile rows 4 kg .. 4 kg + 3 in the lane's four registers.  The two terms of a block
+// row sit in neighbouring lanes; the even lane keeps the even column blocks, the odd lane the odd ones, so that a lane
+// ends up with four block rows r(c) = 16 c + 8 (col & 1) + col / 2, c = 0 .. 3, and four consecutive tile rows of
+// each: 16-byte reads and writes of everything that is laid out along the rows of W, and no trip through LDS.  (The
+// block kernel's epilogue, which this replaces here, walks a row group in sixteen dependent rounds of a load, a few
+// LDS reads and 2-byte stores: about 10 us per row group and wavefront, 20-43 us per workgroup, a third of a 512-row
+// launch; now 4-9 us.)
+__device__ inline float dpp_xor1(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));  // quad_perm [1,0,3,2]
+}
+__device__ inline int gemm_row(int c, int col) { return 16 * c + 8 * (col & 1) + (col >> 1); }
+__device__ inline void fold_terms(const f32x4 (&acc)[8], int col, f32x4 (&y)[4]) {
+    const bool odd = col & 1;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float own = odd ? acc[2 * c + 1][i] : acc[2 * c][i], other = odd ? acc[2 * c][i] : acc[2 * c + 1][i];
+            y[c][i] = own + dpp_xor1(other);
+        }
+}
+// Exchanges the odd 16-lane rows of a with the even ones of b.
+__device__ inline void swap16(uint32_t &a, uint32_t &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+// Exchanges the upper 32 lanes of a with the lower ones of b.
+__device__ inline void swap32(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+// Lanes kg and kg ^ 1 hold values 0..3 and 4..7 of two eight-value units (x, y: two packed words each): afterwards the
+// lane with the even kg holds all of x, the other one all of y.
+__device__ inline u32x4 join8(uint32_t x0, uint32_t x1, uint32_t y0, uint32_t y1) {
+    swap16(x0, y0);
+    swap16(x1, y1);
+    return u32x4{x0, x1, y0, y1};
+}
+__device__ inline uint32_t pack2(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
+// The two-term split of the four values of lanes kg, kg ^ 1 (values 4 (kg & 1) .. of eight), to unit
+// [chunk][128 columns][8]: columns 2 r and 2 r + 1.
+__device__ inline void store_split(uint16_t *out_s, int chunk, int r, int kg, bool ok, const f32x4 &v) {
+    uint32_t h[4], m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        h[i] = f32_to_bf16_rne_finite(v[i]);
+        m[i] = f32_to_bf16_rne_finite(v[i] - __uint_as_float(h[i] << 16));
+    }
+    const u32x4 u = join8(pack2(h[0], h[1]), pack2(h[2], h[3]), pack2(m[0], m[1]), pack2(m[2], m[3]));
+    if (ok) *(u32x4 *)(out_s + ((size_t)chunk * 128 + 2 * r + (kg & 1)) * 8) = u;
+}
+
+// x += y for RGW row groups from rg0: the residual values and gains of all of them are requested together.
+// y(g, out): finished sums of row group g.
+template <int RGW, typename YF>
+__device__ inline void gemm_resid(const MvArgs &a, int rg0, int lane, YF y) {
+    const int col = lane & 15, kg = lane >> 4;
+    f32x4 x[RGW][4], gain[RGW];
+#pragma unroll
+    for (int g = 0; g < RGW; ++g) {
+        const int row = 16 * (rg0 + g) + 4 * kg;
+        const bool in = row < a.O;  // (O is a multiple of 8: a lane's four rows are all real or all padding)
+        gain[g] = in ? *(const f32x4 *)(a.gain_next + row) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int r = gemm_row(c, col);
+            x[g][c] = in && r < a.R ? *(const f32x4 *)(a.out_f32 + (size_t)r * a.ld_out + row) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < RGW; ++g) {
+        const int rg = rg0 + g, row = 16 * rg + 4 * kg;
+        if (rg >= a.n_rg) break;  // (wavefront-uniform)
+        const bool in = row < a.O;
+        f32x4 v[4];
+        y(g, v);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int r = gemm_row(c, col);
+            const bool ok = in && r < a.R;
+            const f32x4 xn = x[g][c] + v[c];
+            if (ok) *(f32x4 *)(a.out_f32 + (size_t)r * a.ld_out + row) = xn;
+            store_split(a.out_s, 2 * rg + (kg >> 1), r, kg, ok, xn * gain[g]);
+            float ss = in ? (xn[0] * xn[0] + xn[1] * xn[1]) + (xn[2] * xn[2] + xn[3] * xn[3]) : 0.f;
+            ss += __shfl_xor(ss, 16, 64);
+            ss += __shfl_xor(ss, 32, 64);
+            if (kg == 0 && r < a.R) a.pss_out[(size_t)rg * a.rp + r] = ss;
+        }
+    }
+}
+
+// A lane's four block rows paired up: the first eight tile rows (gate, or the first half of rotary pairs) of c = 2 p +
+// (kg >> 1) end up in lo, the other eight of the same block row in hi (tile rows 4 (kg & 1) .. of each), scaled.
+__device__ inline void pair_halves(const f32x4 (&v)[4], const float (&sc)[4], int p, f32x4 &lo, f32x4 &hi) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x = v[2 * p][i] * sc[2 * p], y = v[2 * p + 1][i] * sc[2 * p + 1];
+        swap32(x, y);
+        lo[i] = x;
+        hi[i] = y;
+    }
+}
+
+__device__ inline void gemm_swiglu(const MvArgs &a, int rg, int lane, const float (&sc)[4], const f32x4 (&v)[4]) {
+    const int col = lane & 15, kg = lane >> 4;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        f32x4 ga, up, h;
+        pair_halves(v, sc, p, ga, up);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[i] = ga[i] / (1.0f + expf(-ga[i])) * up[i];
+        const int r = gemm_row(2 * p + (kg >> 1), col);
+        store_split(a.out_s, rg, r, kg, r < a.R && 16 * rg < a.O, h);
+    }
+}
+
+// Queries to fp32 rows, keys to their slots, values to the grouped layout: there, eight consecutive slots of an element
+// are one 16-byte unit, so the values cross the lanes through a wavefront's own 2.3 KB of LDS (vsh).
+template <int RGW, typename YF>
+__device__ inline void gemm_qkv(const MvArgs &a, int rg0, int lane, const float (&sc)[4], uint16_t *vsh, YF y) {
+    constexpr int VP = 64 + 8;  // pitch of an element's slots in vsh
+    const int col = lane & 15, kg = lane >> 4;
+    const int d = a.head_dim, half = d >> 1, gph = half >> 3, nq = a.n_q_heads, nkv = a.n_kv_heads;
+    f32x4 cs[RGW][2], sn[RGW][2];
+#pragma unroll
+    for (int g = 0; g < RGW; ++g) {
+        const int rg = min(rg0 + g, a.n_rg - 1), i0 = 8 * (rg % gph) + 4 * (kg & 1);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int r = min(gemm_row(2 * p + (kg >> 1), col), a.R - 1);
+            cs[g][p] = *(const f32x4 *)(a.cos_tab + (size_t)(a.pos0 + r) * half + i0);
+            sn[g][p] = *(const f32x4 *)(a.sin_tab + (size_t)(a.pos0 + r) * half + i0);
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < RGW; ++g) {
+        const int rg = rg0 + g;
+        if (rg >= a.n_rg) break;  // (wavefront-uniform)
+        const int hh = rg / gph, e0 = 8 * (rg - hh * gph);  // head; first element of the row group's eight pairs
+        f32x4 v[4];
+        y(g, v);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            f32x4 ya, yb;
+            pair_halves(v, sc, p, ya, yb);
+            const int r = gemm_row(2 * p + (kg >> 1), col);
+            const bool ok = r < a.R;
+            const int pos = a.pos0 + r;
+            if (hh < nq + nkv) {
+                const f32x4 qa = ya * cs[g][p] - yb * sn[g][p], qb = yb * cs[g][p] + ya * sn[g][p];
+                if (hh < nq) {
+                    float *qp = a.out_f32 + (size_t)r * a.ld_out + hh * d + e0 + 4 * (kg & 1);
+                    if (ok) {
+                        *(f32x4 *)qp = qa;
+                        *(f32x4 *)(qp + half) = qb;
+                    }
+                    continue;
+                }
+                ya = qa;
+                yb = qb;
+            }
+            uint32_t ha[4], hb[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ha[i] = f32_to_bf16_rne(ya[i]);
+                hb[i] = f32_to_bf16_rne(yb[i]);
+            }
+            if (hh < nq + nkv || a.nb32 <= 0) {
+                const int head = hh < nq + nkv ? hh - nq : hh - nq - nkv;
+                uint16_t *plane = (uint16_t *)(hh < nq + nkv ? a.kcache : a.vcache);
+                const u32x4 u = join8(pack2(ha[0], ha[1]), pack2(ha[2], ha[3]), pack2(hb[0], hb[1]), pack2(hb[2], hb[3]));
+                if (ok) *(u32x4 *)(plane + ((size_t)head * a.max_seq + pos) * d + e0 + (kg & 1) * half) = u;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    vsh[(4 * (kg & 1) + i) * VP + r] = (uint16_t)ha[i];
+                    vsh[(8 + 4 * (kg & 1) + i) * VP + r] = (uint16_t)hb[i];
+                }
+            }
+        }
+        if (hh >= nq + nkv && a.nb32 > 0) {
+            // (one wavefront's LDS instructions are carried out in order: only the compiler has to keep it)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int e = lane & 15, elem = e0 + (e & 7) + (e >> 3) * half;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int r = 8 * ((lane >> 4) + 4 * u);  // eight slots from block row r on
+                const u32x4 w = *(const u32x4 *)(vsh + e * VP + r);
+                uint16_t *vp = (uint16_t *)a.vcache;
+                if ((a.pos0 & 7) == 0 && r + 8 <= a.R) {
+                    *(u32x4 *)(vp + kv_vt_index(hh - nq - nkv, a.nb32, d, a.pos0 + r, elem)) = w;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (r + i < a.R)
+                            vp[kv_vt_index(hh - nq - nkv, a.nb32, d, a.pos0 + r + i, elem)] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+
+// Which workgroups do what.  Row tiles [0, MTF) are computed whole, one workgroup each per column tile (grid ids below
+// n_full); the rest are split in depth over ksp workgroups of TS k tiles each.
+struct GemmPlan {
+    int MT, NN, MTF, n_full, ksp, TS;
+};
 
 template <int RGW>
 struct GemmOperands {
@@ -76,15 +306,16 @@ struct GemmOperands {
 };
 
 template <int EPI, int WN, int RGW>
-__global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, int NN, int TS) {
+__global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan pl) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int WM = 8 / WN;                    // wavefronts along the rows; WN sub-blocks side by side
     constexpr int TRG = WM * RGW;                 // row groups of the workgroup's tile
     constexpr int A_BYTES = TRG * 1024;
     constexpr int ST_BYTES = A_BYTES + WN * 8192;
-    constexpr int NST = kRingBytes / ST_BYTES;   // stages of the ring
+        constexpr int NST = kRingBytes / ST_BYTES;   // stages of the ring
     constexpr int NP = TRG + 8 * WN;              // 1 KB pieces of a stage
     constexpr int PW = (NP + 7) / 8;              // pieces a wavefront copies per stage (PW - 1 past the remainder)
+    constexpr bool kNorm = EPI != EPI_RESID;      // the input is a normalised one: scales from the producer's partial sums
     static_assert(NST >= 3 && NST * PW < 64, "ring depth against the load counter");
     unsigned char *ring = smem;
     float *rs = (float *)(smem + kRingBytes);     // [2][64]
@@ -93,19 +324,31 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, in
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    // workgroup -> tile: the NN column tiles of a row tile sit next to each other on one die (consecutive
-    // workgroup ids go round the 8 dies)
-    const int id = blockIdx.x, die = id & 7, qd = id >> 3;
-    const int nt = qd % NN, mt = (qd / NN) * 8 + die;
-    if (mt >= MT) return;
+    // workgroup -> tile: the NN column tiles of a row tile (for tiles split in depth: of one of its parts) sit next to
+    // each other on one die (consecutive workgroup ids go round the 8 dies)
+    const int NN = pl.NN, id = (int)blockIdx.x < pl.n_full ? blockIdx.x : blockIdx.x - pl.n_full;
+    const int die = id & 7, qd = id >> 3;
+    const int nt = qd % NN, pair = (qd / NN) * 8 + die;
+    int mt = pair, kz = 0, KSP = 1, TS = a.T;
+    if ((int)blockIdx.x < pl.n_full) {
+        if (mt >= pl.MTF) return;
+    } else {
+        const int tail = pl.MT - pl.MTF;
+        if (pair >= tail * pl.ksp) return;
+        kz = pair / tail;
+        mt = pl.MTF + pair - kz * tail;
+        KSP = pl.ksp;
+        TS = pl.TS;
+    }
     const int sub0 = WN * nt;
     const int T = a.T;
     const int col = lane & 15, kg = lane >> 4;
-    // gridDim.y > 1: the depth is split over workgroups, TS k tiles each (matrices of few rows under a macro block of
-    // few sub-blocks would otherwise leave most compute units idle); the parts' results are added at the end
-    const int KSP = gridDim.y, kz = blockIdx.y;
     const int t_lo = kz * TS, t_hi = min(T, t_lo + TS);  // (every part holds tiles: the launcher)
 
+    // A ragged last k tile (depth not a multiple of 32) is not part of the pipeline: it is handled at the end (by
+    // the part that holds it).  TF: full tiles of this workgroup's part; TR: the ragged tile's number, if it is here.
+    const bool ragged = (a.K & 31) != 0 && t_hi == T;
+    const int TF = t_hi - t_lo - (ragged ? 1 : 0), TR = T - 1;
     // ---- what this wavefront copies per stage: pieces p = wave + 8 i, each 64 lanes x 16 bytes from a
     // wavefront-uniform address
     const unsigned char *src[PW];   // tile 0 of the piece (wavefront-uniform)
@@ -158,10 +401,6 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, in
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // A ragged last k tile (depth not a multiple of 32) is not part of the pipeline: it is handled at the end (by
-    // the part that holds it).  TF: full tiles of this workgroup's part; TR: the ragged tile's number, if it is here.
-    const bool ragged = (a.K & 31) != 0 && t_hi == T;
-    const int TF = t_hi - t_lo - (ragged ? 1 : 0), TR = T - 1;
     const unsigned char *a_base = ring + (wm * RGW) * 1024 + lane * 16;
     const unsigned char *b_base = ring + A_BYTES + wn * 8192 + (kg * 128 + col) * 16;
     // (wavefronts without a sub-block -- an odd sub-block count leaves half of the last column tile empty -- go
@@ -181,6 +420,20 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, in
                                                                      __builtin_bit_cast(bf16x8, o.bv[cb]), acc[g][cb], 0, 0, 0);
     };
 
+    // The order of a step's instructions: two matrix instructions, the copies, then the next stage's operand reads one by
+    // one between the other matrix instructions.  (All reads in front, as it was: they queue up at LDS, 88 KB per step
+    // of a compute unit, and hold the matrix cores up; all behind: LDS and the matrix cores take turns.  7B, 512 rows:
+    // gate/up 184 -> 163 us, q|k|v 117 -> 107.)
+    auto interleave = [&]() {
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, PW, 0);
+#pragma unroll
+        for (int i = 0; i < RGW + 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
     // The pipeline.  Step t: the operands of stage t are in registers (read during step t - 1).  Once stage t + 1
     // has landed for everybody -- and everybody's reads of stage t have completed: the barrier waits for them --
     // stage t + NST is requested into the slot stage t leaves, the operands of stage t + 1 are read into the other
@@ -190,13 +443,24 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, in
     auto pipeline = [&](auto FULL) {
         constexpr auto ALL = std::integral_constant<int, 0>();
         constexpr auto AHEAD = std::integral_constant<int, NST - 2>();  // stages t + 2 .. t + NST - 1 may stay in flight
+        GemmNorm nv;
+        const float *np = nullptr;
+        if (kNorm) {
+            np = gemm_norm_base(a, ma, sub0);
+            gemm_norm_load(a, np, 0, nv);
+        }
+        if (TF >= NST) {
 #pragma unroll
-        for (int t = 0; t < NST; ++t)
-            if (t < TF) issue(t * ST_BYTES, FULL);
-        gemm_norm_scales(a, ma, sub0, rs, nscratch);
-        if (TF == 0) return;
+            for (int t = 0; t < NST; ++t) issue(t * ST_BYTES, FULL);
+            if (kNorm) gemm_norm_finish(a, np, nv, rs, nscratch);
+            wait_all_but(std::integral_constant<int, NST - 1>(), FULL);
+        } else {
+            for (int t = 0; t < TF; ++t) issue(t * ST_BYTES, FULL);
+            if (kNorm) gemm_norm_finish(a, np, nv, rs, nscratch);
+            if (TF == 0) return;
+            wait_all_but(ALL, FULL);
+        }
         GemmOperands<RGW> o0, o1;
-        wait_all_but(ALL, FULL);
         lds_sync();
         read_operands(0, o0);
         int t = 0, slot = 0;
@@ -205,12 +469,11 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, in
             const int nslot = next_slot(slot);
             wait_all_but(AHEAD, FULL);
             lds_sync();
+            __builtin_amdgcn_sched_barrier(0);
             issue(slot, FULL);
             read_operands(nslot, nxt);
-            // (the reads stay in front of the matrix instructions: left alone, the scheduler sinks them behind to
-            // save registers, and LDS and the matrix cores then take turns instead of working side by side)
-            __builtin_amdgcn_sched_barrier(0);
             multiply(cur);
+            interleave();
             slot = nslot;
         };
         // (the last step reads a slot nobody needs: no harm)
@@ -218,9 +481,10 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, in
             const int nslot = next_slot(slot);
             wait_all_but(ALL, FULL);
             lds_sync();
-            read_operands(nslot, nxt);
             __builtin_amdgcn_sched_barrier(0);
+            read_operands(nslot, nxt);
             multiply(cur);
+            interleave();
             slot = nslot;
         };
         for (; t + NST + 1 < TF; t += 2) {  // both steps issue a stage
@@ -261,97 +525,85 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, int MT, in
         multiply(o);
     }
 
-    // ---- epilogue per row group: results to LDS (dump[wave][column][tile row]), then the block kernel's epilogue
-    // on the sub-block's own buffers
+    // ---- epilogue on the sub-block's own buffers
     const int sub = min(sub0 + wn, ma.S - 1);
     MvArgs as = a;
     as.R = sub == ma.S - 1 ? ma.rows_last : 64;
     as.pos0 = a.pos0 + 64 * sub;
-    as.in_s = a.in_s + (size_t)sub * ma.in_s;
     if (a.out_f32) as.out_f32 = a.out_f32 + (size_t)sub * ma.out_f32;
     if (a.out_s) as.out_s = a.out_s + (size_t)sub * ma.out_s;
     if (a.pss_out) as.pss_out = a.pss_out + (size_t)sub * ma.pss_out;
-    if (a.q_s) as.q_s = a.q_s + (size_t)sub * ma.q_s;
-    float *dw = (float *)ring + (size_t)wave * 2048;
     const bool wave_live = sub0 + wn < ma.S;
-    const float *rsw = rs + 64 * wn;
-    auto dump = [&](int g) {
-        __syncthreads();  // the ring / the previous dump is no longer read
+    const int rg0 = (mt * WM + wm) * RGW;
+    auto finish = [&](auto y) {
+        if (EPI == EPI_RESID) {
+            gemm_resid<RGW>(as, rg0, lane, y);
+        } else {
+            float sc[4];
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb)
+            for (int c = 0; c < 4; ++c) sc[c] = rs[64 * wn + gemm_row(c, col)];
+            if (EPI == EPI_QKV) {
+                gemm_qkv<RGW>(as, rg0, lane, sc, (uint16_t *)ring + (size_t)wave * 2048, y);
+            } else {
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) dw[(16 * cb + col) * 16 + 4 * kg + r4] = acc[g][cb][r4];
-        __syncthreads();
-    };
-    if (KSP == 1) {
-#pragma unroll
-        for (int g = 0; g < RGW; ++g) {
-            const int rg = (mt * WM + wm) * RGW + g;
-            dump(g);
-            if (wave_live && rg < a.n_rg)
-                mv_epilogue<EPI>(as, rg, lane, rsw, nullptr,
-                                 [&](int r, int j) { return dw[(2 * r) * 16 + j] + dw[(2 * r + 1) * 16 + j]; });
+                for (int g = 0; g < RGW; ++g) {
+                    if (rg0 + g >= a.n_rg) break;
+                    f32x4 v[4];
+                    y(g, v);
+                    gemm_swiglu(as, rg0 + g, lane, sc, v);
+                }
+            }
         }
+    };
+    __syncthreads();  // the ring is no longer read (and the scales are visible where no step had a barrier)
+    if (KSP == 1) {
+        if (wave_live) finish([&](int g, f32x4(&v)[4]) { fold_terms(acc[g], col, v); });
         return;
     }
-    // ---- depth split over workgroups: every part publishes its results, the two terms combined, as
-    // part[(kz n_rg + rg) S + sub][row][tile row]; the workgroup that arrives last at the tile's counter adds the
-    // parts in part order (so the result does not depend on who is last) and runs the epilogue.
-    // (device-scope atomic stores write through, so thread 0's release has nothing to flush; the barrier orders every
-    // wavefront's stores before it)
-    const size_t pslot = 1024;
+    // ---- depth split over workgroups.  Every wavefront publishes its results, the two terms combined, as
+    // part[kz][row group][sub-block] (lane by lane: its partners in the other parts read them back into the same lanes),
+    // and counts itself in; the one that arrives last of its KSP partners adds the parts in part order (so the result
+    // does not depend on who is last) and runs the epilogue.  No barrier: the wavefronts of a tile are independent, and
+    // partners arrive in any order, so the adding is spread over the parts.  Stores and loads of the parts are device
+    // scope (sc1: written through, read past this die's L2), so once a wavefront's stores are acknowledged (vmcnt 0) a
+    // relaxed count publishes them, and no cache has to be written back or invalidated.  (One counter per workgroup,
+    // 8-byte stores and an acquire-release count cost 25-30 us per launch; this ~10.)
+    const int rgt0 = rg0 - pl.MTF * TRG, n_rgt = a.n_rg - pl.MTF * TRG;  // row groups of the split tiles
+    if (!wave_live) return;
+    const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(a.part, 0, 0x7fffffff, 0x00020000);
+    auto part_off = [&](int k2, int g, int c) { return (uint32_t)((((k2 * n_rgt + rgt0 + g) * ma.S + sub) * 4 + c) * 1024 + lane * 16); };
 #pragma unroll
     for (int g = 0; g < RGW; ++g) {
-        const int rg = (mt * WM + wm) * RGW + g;
-        dump(g);
-        if (wave_live && rg < a.n_rg) {
-            float *pp = a.part + (((size_t)kz * a.n_rg + rg) * ma.S + sub) * pslot;
+        if (rg0 + g >= a.n_rg) break;
+        f32x4 v[4];
+        fold_terms(acc[g], col, v);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int idx = lane + 64 * i, r = idx >> 4, j = idx & 15;
-                __hip_atomic_store(pp + idx, dw[(2 * r) * 16 + j] + dw[(2 * r + 1) * 16 + j], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
+        for (int c = 0; c < 4; ++c)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[c]), part, part_off(kz, g, c), 0, kDeviceScope);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    int *counter = a.counters + ((mt - pl.MTF) * NN + nt) * 8 + wave;
+    int arrived = 0;
+    if (lane == 0) arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(arrived) != KSP - 1) return;
+    asm volatile("" ::: "memory");
+    finish([&](int g, f32x4(&v)[4]) {
+        if (rg0 + g >= a.n_rg) return;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(0, g, c), 0, kDeviceScope));
+        for (int k2 = 1; k2 < KSP; ++k2) {
+            f32x4 w[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(k2, g, c), 0, kDeviceScope));
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] += w[c];
         }
-    }
-    int *flag = (int *)nscratch;
-    __syncthreads();
-    if (tid == 0) {
-        const int old = __hip_atomic_fetch_add(a.counters + mt * NN + nt, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = (old == KSP - 1) ? 1 : 0;
-    }
-    __syncthreads();
-    if (*flag == 0) return;
-    // (plain loads below: ordered after thread 0's acquire by the barrier)
-#pragma unroll
-    for (int g = 0; g < RGW; ++g) {
-        const int rg = (mt * WM + wm) * RGW + g;
-        const bool live = wave_live && rg < a.n_rg;
-        __syncthreads();  // the previous dump is no longer read
-        if (live) {
-            const float *p0 = a.part + ((size_t)rg * ma.S + sub) * pslot + lane * 4;
-            const size_t kstride = (size_t)a.n_rg * ma.S * pslot;
-            f32x4 sum[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sum[q] = *(const f32x4 *)(p0 + 256 * q);
-            for (int k2 = 1; k2 < KSP; ++k2) {
-                f32x4 v[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = *(const f32x4 *)(p0 + k2 * kstride + 256 * q);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) sum[q] += v[q];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) *(f32x4 *)(dw + lane * 4 + 256 * q) = sum[q];
-        }
-        __syncthreads();
-        if (live) mv_epilogue<EPI>(as, rg, lane, rsw, nullptr, [&](int r, int j) { return dw[r * 16 + j]; });
-    }
-    if (tid == 0) a.counters[mt * NN + nt] = 0;
+    });
+    if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int EPI, int WN, int RGW>
-hipError_t launch_gemm_t(const MvArgs &a, const MacroArgs &ma, int ksp, hipStream_t s) {
+hipError_t launch_gemm_t(const MvArgs &a, const MacroArgs &ma, const GemmPlan &pl, hipStream_t s) {
     static bool attr_set = false;
     const size_t lds = kRingBytes + 128 * 4 + kNormFloats * 4;
     if (!attr_set) {
@@ -359,14 +611,9 @@ hipError_t launch_gemm_t(const MvArgs &a, const MacroArgs &ma, int ksp, hipStrea
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    constexpr int TRG = (8 / WN) * RGW;
-    const int MT = (a.n_rg + TRG - 1) / TRG, NN = (ma.S + WN - 1) / WN;
-    const int grid = ((MT + 7) / 8) * 8 * NN;
-    const int TS = (a.T + ksp - 1) / ksp;
-    ksp = (a.T + TS - 1) / TS;  // parts that hold tiles
-    if (ksp > 1 && (!a.part || !a.counters || (int64_t)ksp * a.n_rg * ma.S > a.part_capacity || MT * NN > 4096))
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_gemm<EPI, WN, RGW>), dim3(grid, ksp), dim3(512), lds, s, a, ma, MT, NN, TS);
+    const int tail = pl.MT - pl.MTF;
+    const int grid = pl.n_full + (tail * pl.ksp + 7) / 8 * 8 * pl.NN;
+    hipLaunchKernelGGL((k_gemm<EPI, WN, RGW>), dim3(grid), dim3(512), lds, s, a, ma, pl);
     return hipGetLastError();
 }
 
@@ -378,61 +625,71 @@ struct GemmTiling {
 };
 constexpr GemmTiling kGemmTilings[7] = {{0, 0}, {2, 1}, {2, 2}, {2, 3}, {2, 4}, {1, 1}, {1, 2}};
 
-// Depth parts for a tiling: 1 unless the tiles leave compute units idle; then the largest of 2, 4 that still gives
-// at most one workgroup per compute unit, parts of at least 16 k tiles, and partial results that fit the scratch.
-// Only for macro blocks of up to four sub-blocks: with more, the parts' results are too many bytes (measured at
-// eight sub-blocks, same machine: down_proj 128-131 us with four parts against 113 us unsplit).
-int gemm_depth_parts(const MvArgs &a, const MacroArgs &ma, int n_cu, int code) {
-    const int wn = kGemmTilings[code].wn, rgw = kGemmTilings[code].rgw, trg = (8 / wn) * rgw;
-    const int MT = (a.n_rg + trg - 1) / trg, NN = (ma.S + wn - 1) / wn;
-    int ksp = 1;
-    while (ma.S <= 4 && ksp < 4 && MT * NN * ksp * 2 <= n_cu && a.T / (ksp * 2) >= 16 && a.part && a.counters &&
-           (int64_t)ksp * 2 * a.n_rg * ma.S <= a.part_capacity && MT * NN <= 4096)
-        ksp *= 2;
-    return ksp;
-}
+// What a workgroup costs, measured with all compute units at work (7B and 13B shapes, 128-512 rows): us per k tile, and us
+// per workgroup for its start, the first stages' arrival and the epilogue.  (A 256 x 256 tile's matrix instructions take
+// 0.54 us per k tile at the ~1.9 GHz the part holds with all matrix cores busy.)
+struct GemmCost {
+    double stage, fixed;
+};
+constexpr GemmCost kGemmCosts[7] = {{0, 0}, {0.305, 9.0}, {0.37, 10.0}, {0.54, 12.0}, {0.58, 14.0}, {0.26, 8.0}, {0.385, 9.0}};
+constexpr double kPartBytesPerUs = 1.3e6;  // publishing and adding the parts of tiles split in depth
 
-int gemm_tiling(const MvArgs &a, const MacroArgs &ma, int n_cu) {
-    // The one that finishes first by a simple count: rounds of workgroups (one per compute unit) times the k tiles
-    // of a workgroup times the longer of a stage's multiply time and the time to take its bytes in (about 21 bytes
-    // per cycle and compute unit when the units of a die stream the same data: measured), plus, with the depth
-    // split, what publishing and adding the parts costs (measured: about 20 us, and the parts' bytes written and read
-    // at about 3 TB/s).
-    int best = 1;
-    double best_t = 1e30;
-    for (int code = 1; code <= 6; ++code) {
-        const int wn = kGemmTilings[code].wn, rgw = kGemmTilings[code].rgw, trg = (8 / wn) * rgw;
-        const int MT = (a.n_rg + trg - 1) / trg, NN = (ma.S + wn - 1) / wn;
-        const int ksp = gemm_depth_parts(a, ma, n_cu, code);
-        const int rounds = (MT * NN * ksp + n_cu - 1) / n_cu;
-        const double mfma = 256.0 * rgw, intake = (trg + 8.0 * wn) * 1024.0 / 21.0;  // cycles per stage
-        const double parts = ksp > 1 ? 45000.0 + 2.0 * ksp * a.n_rg * ma.S * 4096.0 * 0.0007 : 0.0;
-        const double t = rounds * ((a.T + ksp - 1) / ksp) * (mfma > intake ? mfma : intake) + parts;
-        if (t < best_t) {
-            best_t = t;
-            best = code;
-        }
-    }
-    return best;
+// The plan of a tiling with its last tiles split ksp ways, and what it costs; false if the partial results would not fit
+// the scratch or a part would hold fewer than 16 k tiles.
+bool gemm_plan(const MvArgs &a, const MacroArgs &ma, int n_cu, int code, int ksp, GemmPlan &pl, double &us) {
+    const int wn = kGemmTilings[code].wn, rgw = kGemmTilings[code].rgw, trg = (8 / wn) * rgw;
+    pl.MT = (a.n_rg + trg - 1) / trg;
+    pl.NN = (ma.S + wn - 1) / wn;
+    const int per_round = std::max(1, n_cu / pl.NN / 8) * 8;  // row tiles of a round (whole dies)
+    const int whole_rounds = pl.MT / per_round;
+    pl.MTF = ksp == 1 ? pl.MT : whole_rounds * per_round;
+    pl.TS = (a.T + ksp - 1) / ksp;
+    pl.ksp = (a.T + pl.TS - 1) / pl.TS;  // parts that hold tiles
+    pl.n_full = (pl.MTF + 7) / 8 * 8 * pl.NN;
+    const int tail = pl.MT - pl.MTF;
+    const GemmCost c = kGemmCosts[code];
+    us = (double)((pl.MTF * pl.NN + n_cu - 1) / n_cu) * (a.T * c.stage + c.fixed);
+    if (tail == 0 || pl.ksp == 1) return ksp == 1;
+    const double bytes = (double)pl.ksp * (a.n_rg - pl.MTF * trg) * ma.S * 4096.0;
+    us += (double)((tail * pl.NN * pl.ksp + n_cu - 1) / n_cu) * (pl.TS * c.stage + c.fixed) + bytes / kPartBytesPerUs;
+    return pl.TS >= 16 && a.part && a.counters && (int64_t)pl.ksp * (a.n_rg - pl.MTF * trg) * ma.S <= a.part_capacity &&
+           tail * pl.NN * 8 <= 4096;
 }
 
 }  // namespace
 
 hipError_t launch_gemm(int epi, const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, hipStream_t s) {
     if (ma.S < 1 || ma.S > kMacroSub || ma.rows_last < 1 || ma.rows_last > 64 || a.RL != (64 | kBulkLayout) || a.rp != 64 ||
-        (a.K & 7) != 0 || a.T != (a.K + 31) / 32 || a.n_rg < 1 || !a.Wt || !a.in_s || a.tree)
+        (a.K & 7) != 0 || a.T != (a.K + 31) / 32 || a.n_rg < 1 || !a.Wt || !a.in_s || a.tree || a.q_s ||
+        (epi == EPI_RESID ? !a.gain_next || !a.pss_out || (a.O & 7) != 0 : !a.pss || a.n_pss < 1))
         return hipErrorInvalidValue;
-    const int code = (tiling_override >= 1 && tiling_override <= 6) ? tiling_override : gemm_tiling(a, ma, n_cu);
-    const int ksp = gemm_depth_parts(a, ma, n_cu, code);
+    // The tile shape and the depth split that finish first by the measured costs: workgroups come in rounds of one per
+    // compute unit, and splitting the last round's tiles in depth fills the units that would idle in it, for the price
+    // of the parts' results.
+    GemmPlan pl{};
+    int code = 0;
+    double best = 1e30;
+    for (int c = 1; c <= 6; ++c) {
+        if (tiling_override >= 1 && tiling_override <= 6 && c != tiling_override) continue;
+        for (int ksp = 1; ksp <= 4; ++ksp) {
+            GemmPlan p;
+            double us;
+            if (!gemm_plan(a, ma, n_cu, c, ksp, p, us) || us >= best) continue;
+            best = us;
+            pl = p;
+            code = c;
+        }
+    }
+    if (code == 0) return hipErrorInvalidValue;
 #define SWIFT_GEMM_CASE(E)                                                \
     case E:                                                               \
         switch (code) {                                                   \
-            case 1: return launch_gemm_t<E, 2, 1>(a, ma, ksp, s);         \
-            case 2: return launch_gemm_t<E, 2, 2>(a, ma, ksp, s);         \
-            case 3: return launch_gemm_t<E, 2, 3>(a, ma, ksp, s);         \
-            case 4: return launch_gemm_t<E, 2, 4>(a, ma, ksp, s);         \
-            case 5: return launch_gemm_t<E, 1, 1>(a, ma, ksp, s);         \
-            default: return launch_gemm_t<E, 1, 2>(a, ma, ksp, s);        \
+            case 1: return launch_gemm_t<E, 2, 1>(a, ma, pl, s);         \
+            case 2: return launch_gemm_t<E, 2, 2>(a, ma, pl, s);         \
+            case 3: return launch_gemm_t<E, 2, 3>(a, ma, pl, s);         \
+            case 4: return launch_gemm_t<E, 2, 4>(a, ma, pl, s);         \
+            case 5: return launch_gemm_t<E, 1, 1>(a, ma, pl, s);         \
+            default: return launch_gemm_t<E, 1, 2>(a, ma, pl, s);        \
         }
     switch (epi) {
         SWIFT_GEMM_CASE(EPI_QKV)

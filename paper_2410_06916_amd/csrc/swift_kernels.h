@@ -293,10 +293,11 @@ constexpr int kMacroSub = 8;
 struct MacroArgs {
     int S;          // sub-blocks, 1..kMacroSub
     int rows_last;  // rows of the last one, 1..64 (the others hold 64)
-    int64_t in_s, pss, out_f32, out_s, pss_out, q_s;  // strides, in elements of the respective buffer
+    int64_t in_s, pss, out_f32, out_s, pss_out;  // strides, in elements of the respective buffer
 };
 // epilogue: EPI_QKV, EPI_RESID or EPI_SWIGLU; a.R is ignored, a.RL must be the 64-row bulk layout, a.rp = 64, a.K a
-// multiple of 8.  tiling_override: 0 = automatic, else the tile shape (tuning runs): 1..4 = that many row groups per
+// multiple of 8; a.q_s is null; a.part and a.counters (4096 words, zero between launches) may be null: no depth split.
+// tiling_override: 0 = automatic, else the tile shape (tuning runs): 1..4 = that many row groups per
 // wavefront on two sub-blocks side by side, 5 / 6 = one / two row groups per wavefront on one sub-block.
 hipError_t launch_gemm(int epilogue, const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, hipStream_t s);
 

@@ -188,6 +188,35 @@ def test_prefill_tilings_against_oracle(oracle_lib, subs, rgw):
     g.close()
 
 
+@pytest.mark.parametrize("n_prompt", [129, 200, 330, 512])
+def test_prefill_depth_split_against_64_row_blocks(n_prompt):
+    """The blocked matrix product at the 7B width where it splits tiles in depth over workgroups: all of them (short
+    macro blocks, o_proj and down_proj), and only those past the whole rounds of workgroups (gate/up at 512 rows).  The
+    same prompt in 64-row blocks takes another kernel: the last row's logits agree to what two-term activations (2^-17
+    per element) and a bf16 cache allow, cache slots up to one bf16 rounding step (2^-7 of a value, 2^-10 of the
+    vector's largest for the cancelled ones).  Twice: the arrival counters are zero again after a launch."""
+    import paper_2410_06916_amd as P
+    shape = si.LLAMA2_7B.with_layers(1)
+    g = P.SwiftModel(shape, 600)
+    g.load_weights(si.iter_weights(shape, 5, "cuda:0", gain_jitter=0.1))
+    prompt = si.uniform_ids(71, n_prompt, shape.vocab)
+    slots = sorted({0, 7, n_prompt // 2, n_prompt - 65, n_prompt - 1})
+
+    def after():
+        g.prefill(prompt)
+        return g.read_logits((n_prompt - 1) % 64), [g.read_kv(0, p) for p in slots]
+    g.prefill_blocks(-1)
+    want, kv = after()
+    g.prefill_blocks(0)
+    for _ in range(2):
+        got, kv2 = after()
+        assert hp.rel_err_rowmax(got, want)[0] <= 2e-3
+        for pair, pair2 in zip(kv, kv2):
+            for a, b in zip(pair, pair2):
+                assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(a) + 2.0 ** -10 * np.abs(a).max())
+    g.close()
+
+
 BLOCK_ATTN_SHAPES = {
     # head_dim 64, two query heads per kv head
     "d64-gqa2": si.ModelShape("d64-gqa2", 2, 256, 4, 2, 64, 344, 384, "bf16", 1e-5),
