@@ -349,41 +349,43 @@ char *kv_base(swift_ctx *x, int layer, int which) {
 // one with children).
 typedef TreeTab TreeRows;
 
-// ---- storage-generic path: one token through the network at position `pos`; row = which row of
-// the activation / logits buffers to use.  skip == nullptr: full model.  want_logits: run the LM
-// head and the arg-max for this row.  tree: the row is block row `row` of a token tree whose first row
-// sits in slot tree_base; `pos` is then the row's cache slot and it is rotated for its level's position.
-int forward_row(swift_ctx *x, int32_t token, int pos, const uint8_t *skip, int row, bool want_logits,
-                bool reuse_kv = false, const TreeRows *tree = nullptr, int tree_base = 0) {
+// ---- storage-generic path: a block of R rows (tokens[0..R) at positions pos0..pos0+R-1) through the network, one
+// launch per stage for all of them; row r uses row r of the activation / logits buffers.  skip == nullptr: full model.
+// want_logits: run the LM head and the arg-max.  tree: the rows are those of a token tree whose first row sits in slot
+// pos0; row r goes to slot pos0 + r and is rotated for its level's position.
+int forward_block_rows(swift_ctx *x, const int32_t *tokens, int R, int pos0, const uint8_t *skip, bool want_logits,
+                       bool reuse_kv, const TreeRows *tree) {
     const swift_model_config &c = x->c;
     const Layout &L = x->L;
     const int H = c.hidden, d = c.head_dim, Q = c.n_q_heads * d, KV = c.n_kv_heads * d, F = c.ffn, V = c.vocab;
     const uint64_t eb = elem_bytes(c.dtype);
     hipStream_t s = x->stream;
-    float *xr = dptr<float>(x, L.x) + (size_t)row * H;
-    float *qr = dptr<float>(x, L.q) + (size_t)row * Q;
-    float *ar = dptr<float>(x, L.att) + (size_t)row * Q;
-    float *hr = dptr<float>(x, L.h) + (size_t)row * F;
-    float *lr = dptr<float>(x, L.logits) + (size_t)row * V;
+    float *xr = dptr<float>(x, L.x), *qr = dptr<float>(x, L.q), *ar = dptr<float>(x, L.att), *hr = dptr<float>(x, L.h);
+    float *lr = dptr<float>(x, L.logits);
 
-    auto linear = [&](int kc, int epi, uint64_t w_off, int O, int K, const float *xin, const float *gain, float *out,
+    auto linear = [&](int kc, int epi, uint64_t w_off, int O, int K, const float *xin, const float *gain, float *out, int ld_out,
                       int layer) -> int {
         GemvArgs g{};
         g.W = x->base + w_off;
         g.O = O;
         g.K = K;
+        g.R = R;
         g.xin = xin;
         g.gain = gain;
         g.eps = c.rms_eps;
         g.out = out;
+        g.ld_out = ld_out;
         if (epi == EPI_QKV) {
             g.kcache = kv_base(x, layer, 0);
             g.vcache = kv_base(x, layer, 1);
-            const int rope_pos = tree ? tree_base + tree->depth[row] : pos;
-            g.cos_row = dptr<float>(x, L.cos) + (size_t)rope_pos * (d / 2);
-            g.sin_row = dptr<float>(x, L.sin) + (size_t)rope_pos * (d / 2);
+            g.cos_tab = dptr<float>(x, L.cos);
+            g.sin_tab = dptr<float>(x, L.sin);
+            if (tree) {
+                g.tree = 1;
+                memcpy(g.depth, tree->depth, sizeof(g.depth));
+            }
         }
-        g.pos = pos;
+        g.pos0 = pos0;
         g.max_seq = c.max_seq;
         g.head_dim = d;
         g.n_q_heads = c.n_q_heads;
@@ -392,50 +394,57 @@ int forward_row(swift_ctx *x, int32_t token, int pos, const uint8_t *skip, int r
         return SWIFT_OK;
     };
     int rc;
-    EmbedArgs ea{x->base + L.embed, H, token, xr};
-    HIP_TRY(timed(x, SWIFT_KC_OTHER, H * eb, [&] { return launch_embed(c.dtype, ea, s); }));
+    EmbedArgs ea{};
+    ea.E = x->base + L.embed;
+    ea.H = H;
+    ea.R = R;
+    memcpy(ea.tokens, tokens, R * sizeof(int32_t));
+    ea.x = xr;
+    HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)R * H * eb, [&] { return launch_embed(c.dtype, ea, s); }));
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerOff &y = L.layers[l];
         if (!(skip && skip[2 * l])) {
-            // (reuse_kv: only the query rows of the fused matrix; the cache slot keeps what it holds)
-            if ((rc = linear(SWIFT_KC_QKV, EPI_QKV, y.wqkv, reuse_kv ? Q : Q + 2 * KV, H, xr, dptr<float>(x, y.attn_norm), qr,
+            // (reuse_kv: only the query rows of the fused matrix; the cache slots keep what they hold)
+            if ((rc = linear(SWIFT_KC_QKV, EPI_QKV, y.wqkv, reuse_kv ? Q : Q + 2 * KV, H, xr, dptr<float>(x, y.attn_norm), qr, Q,
                              l)))
                 return rc;
-            AttnArgs a{};
-            a.q = qr;
-            a.kcache = kv_base(x, l, 0);
-            a.vcache = kv_base(x, l, 1);
-            a.n_ctx = pos + 1;
-            a.rows = 1;
-            a.max_seq = c.max_seq;
-            a.head_dim = d;
-            a.n_q_heads = c.n_q_heads;
-            a.n_kv_heads = c.n_kv_heads;
-            a.part_o = x->scr.part_o;
-            a.part_ml = x->scr.part_ml;
-            a.max_split = L.n_split_max;
-            a.out = ar;
-            a.out_s = nullptr;
-            if (tree) {
-                a.tree = 1;
-                a.n_base = tree_base;
-                a.row_base = row;
-                a.tt = *tree;
+            // (a launch of the split kernel covers up to kMaxRows rows: its partial buffers)
+            for (int row0 = 0; row0 < R; row0 += kMaxRows) {
+                AttnArgs a{};
+                a.q = qr + (size_t)row0 * Q;
+                a.kcache = kv_base(x, l, 0);
+                a.vcache = kv_base(x, l, 1);
+                a.n_ctx = pos0 + row0 + 1;
+                a.rows = std::min((int)kMaxRows, R - row0);
+                a.max_seq = c.max_seq;
+                a.head_dim = d;
+                a.n_q_heads = c.n_q_heads;
+                a.n_kv_heads = c.n_kv_heads;
+                a.part_o = x->scr.part_o;
+                a.part_ml = x->scr.part_ml;
+                a.max_split = L.n_split_max;
+                a.out = ar + (size_t)row0 * Q;
+                if (tree) {
+                    a.tree = 1;
+                    a.n_base = pos0;
+                    a.row_base = row0;
+                    a.tt = *tree;
+                }
+                HIP_TRY(timed(x, SWIFT_KC_ATTN, (uint64_t)2 * KV * eb * (pos0 + row0 + a.rows),
+                              [&] { return launch_attn_decode(c.dtype, a, x->n_cu, s); }));
             }
-            HIP_TRY(timed(x, SWIFT_KC_ATTN, (uint64_t)2 * KV * eb * (pos + 1),
-                          [&] { return launch_attn_decode(c.dtype, a, x->n_cu, s); }));
-            if ((rc = linear(SWIFT_KC_OPROJ, EPI_RESID, y.wo, H, Q, ar, nullptr, xr, l))) return rc;
+            if ((rc = linear(SWIFT_KC_OPROJ, EPI_RESID, y.wo, H, Q, ar, nullptr, xr, H, l))) return rc;
         }
         if (!(skip && skip[2 * l + 1])) {
-            if ((rc = linear(SWIFT_KC_GATEUP, EPI_SWIGLU, y.wgu, 2 * F, H, xr, dptr<float>(x, y.mlp_norm), hr, l))) return rc;
-            if ((rc = linear(SWIFT_KC_DOWN, EPI_RESID, y.wd, H, F, hr, nullptr, xr, l))) return rc;
+            if ((rc = linear(SWIFT_KC_GATEUP, EPI_SWIGLU, y.wgu, 2 * F, H, xr, dptr<float>(x, y.mlp_norm), hr, F, l))) return rc;
+            if ((rc = linear(SWIFT_KC_DOWN, EPI_RESID, y.wd, H, F, hr, nullptr, xr, H, l))) return rc;
         }
     }
     if (want_logits) {
-        if ((rc = linear(SWIFT_KC_LMHEAD, EPI_LOGITS, L.lm_head, V, H, xr, dptr<float>(x, L.final_norm), lr, 0))) return rc;
-        ArgmaxArgs m{lr, V, 1, dptr<int32_t>(x, L.out_tok) + row, dptr<float>(x, L.out_conf) + row,
-                     x->want_topk ? dptr<int32_t>(x, L.out_topk) + (size_t)row * kTopK : nullptr, kTopK};
-        HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)V * 4, [&] { return launch_argmax_conf(m, s); }));
+        if ((rc = linear(SWIFT_KC_LMHEAD, EPI_LOGITS, L.lm_head, V, H, xr, dptr<float>(x, L.final_norm), lr, V, 0))) return rc;
+        ArgmaxArgs m{lr, V, R, dptr<int32_t>(x, L.out_tok), dptr<float>(x, L.out_conf),
+                     x->want_topk ? dptr<int32_t>(x, L.out_topk) : nullptr, kTopK};
+        HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)R * V * 4, [&] { return launch_argmax_conf(m, s); }));
     }
     return SWIFT_OK;
 }
@@ -763,11 +772,7 @@ int forward_block(swift_ctx *x, const int32_t *tokens, int R, int pos0, const ui
     if (tree && R > kMaxRows) return fail(SWIFT_EINVAL, "a token tree has at most SWIFT_MAX_BLOCK rows");
     if (exact && R > kMaxRows) return fail(SWIFT_EINVAL, "a verify block has at most SWIFT_MAX_BLOCK rows");
     if (x->L.tiled) return forward_block_tiled(x, tokens, R, pos0, skip, want_logits, reuse_kv, tree, exact);
-    for (int r = 0; r < R; ++r) {
-        int rc = forward_row(x, tokens[r], pos0 + r, skip, r, want_logits, reuse_kv, tree, pos0);
-        if (rc) return rc;
-    }
-    return SWIFT_OK;
+    return forward_block_rows(x, tokens, R, pos0, skip, want_logits, reuse_kv, tree);
 }
 
 // Copies rows [0, rows) of the token / confidence results to the pinned staging area and waits.

@@ -44,27 +44,31 @@ enum Epilogue : int {
 };
 
 // ------------------------------------------------------------------------------------------
-// storage-generic path (fp32 or bf16 row-major weights, one activation row)
+// storage-generic path (fp32 or bf16 row-major weights): a block of R activation rows
 // ------------------------------------------------------------------------------------------
 struct GemvArgs {
     const void *W;      // [O][K] in the model's storage dtype, row-major
     int O, K;
-    const float *xin;   // [K] fp32
+    int R;              // rows, 1..kMaxBlockRows
+    const float *xin;   // [R][K] fp32
     const float *gain;  // [K] fp32 RMSNorm gain, or nullptr: no normalisation
     float eps;
-    float *out;
+    float *out;         // [R][ld_out]
+    int ld_out;
     // EPI_QKV only
     void *kcache, *vcache;           // this layer's [n_kv][max_seq][d]
-    const float *cos_row, *sin_row;  // rotary table rows for `pos`: [d/2] each
-    int pos, max_seq, head_dim, n_q_heads, n_kv_heads;  // pos: the cache slot the keys/values go to
+    const float *cos_tab, *sin_tab;  // [max_seq][d/2]
+    int pos0, max_seq, head_dim, n_q_heads, n_kv_heads;  // row r's keys/values go to slot pos0 + r, ...
+    int tree;                        // ... it is rotated for position pos0 + r, or, tree != 0, for pos0 + depth[r]
+    uint8_t depth[kMaxRows];
 };
 hipError_t launch_gemv(int dtype, int epilogue, const GemvArgs &a, int n_cu, hipStream_t s);
 
 struct EmbedArgs {
     const void *E;  // [V][H]
-    int H;
-    int32_t token;
-    float *x;  // [H]
+    int H, R;
+    int32_t tokens[kMaxBlockRows];
+    float *x;  // [R][H]
 };
 hipError_t launch_embed(int dtype, const EmbedArgs &a, hipStream_t s);
 

@@ -13,6 +13,8 @@
 #include <math.h>
 #include <stdio.h>
 
+#include <algorithm>
+
 #include "swift_device.h"
 
 namespace swift {
@@ -28,28 +30,40 @@ __device__ inline float block_sum_256(float v, float *red /* >= 4 floats of LDS 
 }
 
 // ------------------------------------------------------------------------------------------
-// weight-streaming pass, one activation row
+// weight-streaming pass, a block of activation rows
 // ------------------------------------------------------------------------------------------
-template <typename T, int EPI>
+// A workgroup takes RB consecutive rows (blockIdx.y): a weight loaded once feeds all of them, and a block is one launch
+// instead of one per row.  What bounds the small models that run here is the launch (3-4 us each, whatever it computes):
+// a 5-row verification of the tiny model takes 27 launches instead of 135, a 32-row prompt 27 instead of 860.  A row's
+// products are added in the same order whatever RB is (lane l takes 16-byte chunks l, l + 64, .., then a butterfly), so
+// its result does not depend on the rows it shares a pass with.
+template <typename T, int EPI, int RB>
 __global__ __launch_bounds__(kGemvThreads) void k_gemv(GemvArgs a) {
-    extern __shared__ __align__(16) float xs[];  // [K] activation (normalised if gain != null)
+    extern __shared__ __align__(16) float xs[];  // [RB][K] activations (normalised if gain != null)
     __shared__ float red[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int K = a.K;
+    const int row0 = (int)blockIdx.y * RB, n_rows = min(RB, a.R - row0);
 
-    // ---- prologue: stage the activation row in LDS, RMS-normalised when a gain is given
-    if (a.gain) {
-        float ss = 0.f;
-        for (int i = tid; i < K; i += kGemvThreads) {
-            float v = a.xin[i];
-            xs[i] = v;
-            ss += v * v;
+    // ---- prologue: stage the activation rows in LDS, RMS-normalised when a gain is given (rows past the block: the
+    // last row once more, dropped at the end)
+#pragma unroll
+    for (int rr = 0; rr < RB; ++rr) {
+        const float *xin = a.xin + (size_t)(row0 + min(rr, n_rows - 1)) * K;
+        float *x = xs + (size_t)rr * K;
+        if (a.gain) {
+            float ss = 0.f;
+            for (int i = tid; i < K; i += kGemvThreads) {
+                float v = xin[i];
+                x[i] = v;
+                ss += v * v;
+            }
+            ss = block_sum_256(ss, red);
+            const float r = 1.0f / sqrtf(ss / (float)K + a.eps);
+            for (int i = tid; i < K; i += kGemvThreads) x[i] = x[i] * r * a.gain[i];
+        } else {
+            for (int i = tid; i < K; i += kGemvThreads) x[i] = xin[i];
         }
-        ss = block_sum_256(ss, red);
-        const float r = 1.0f / sqrtf(ss / (float)K + a.eps);
-        for (int i = tid; i < K; i += kGemvThreads) xs[i] = xs[i] * r * a.gain[i];
-    } else {
-        for (int i = tid; i < K; i += kGemvThreads) xs[i] = a.xin[i];
     }
     __syncthreads();
 
@@ -72,84 +86,116 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(GemvArgs a) {
         }
         const u32x4 *wa = (const u32x4 *)(W + (size_t)ra * K);
         const u32x4 *wb = (const u32x4 *)(W + (size_t)rb * K);
-        float acc_a = 0.f, acc_b = 0.f;
-#pragma unroll 4
+        constexpr int kUnroll = RB == 1 ? 4 : 2;
+        float acc_a[RB], acc_b[RB];
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) acc_a[rr] = acc_b[rr] = 0.f;
+#pragma unroll kUnroll
         for (int c = lane; c < chunks; c += 64) {
-            const u32x4 va = __builtin_nontemporal_load(wa + c);
-            const u32x4 vb = __builtin_nontemporal_load(wb + c);
+            // (weights that every row group of a block reads again stay in the caches)
+            const u32x4 va = RB == 1 ? __builtin_nontemporal_load(wa + c) : wa[c];
+            const u32x4 vb = RB == 1 ? __builtin_nontemporal_load(wb + c) : wb[c];
             float fa[T::VEC], fb[T::VEC];
             T::unpack(va, fa);
             T::unpack(vb, fb);
-            const float *xp = xs + c * T::VEC;
 #pragma unroll
-            for (int j = 0; j < T::VEC; ++j) {
-                acc_a = fmaf(fa[j], xp[j], acc_a);
-                acc_b = fmaf(fb[j], xp[j], acc_b);
+            for (int rr = 0; rr < RB; ++rr) {
+                const float *xp = xs + (size_t)rr * K + c * T::VEC;
+#pragma unroll
+                for (int j = 0; j < T::VEC; ++j) {
+                    acc_a[rr] = fmaf(fa[j], xp[j], acc_a[rr]);
+                    acc_b[rr] = fmaf(fb[j], xp[j], acc_b[rr]);
+                }
             }
         }
-        acc_a = wave_sum(acc_a);
-        acc_b = wave_sum(acc_b);
-        if (lane != 0) continue;
+        // lane rr ends up with row rr's two sums
+        float ya0 = 0.f, yb0 = 0.f;
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) {
+            const float sa = wave_sum(acc_a[rr]), sb = wave_sum(acc_b[rr]);
+            if (lane == rr) {
+                ya0 = sa;
+                yb0 = sb;
+            }
+        }
+        if (lane >= n_rows) continue;
+        const int r = row0 + lane;
+        float *out = a.out + (size_t)r * a.ld_out;
 
         if (EPI == EPI_QKV) {
             const int hh = u / half, i = u - hh * half;
-            const int nq = a.n_q_heads, nkv = a.n_kv_heads;
+            const int nq = a.n_q_heads, nkv = a.n_kv_heads, pos = a.pos0 + r;
             if (hh < nq + nkv) {  // rotary pair (i, i + d/2)
-                const float c = a.cos_row[i], s = a.sin_row[i];
-                const float ya = acc_a * c - acc_b * s;
-                const float yb = acc_b * c + acc_a * s;
+                const int rpos = a.pos0 + (a.tree ? (int)a.depth[r & (kMaxRows - 1)] : r);
+                const float c = a.cos_tab[(size_t)rpos * half + i], s = a.sin_tab[(size_t)rpos * half + i];
+                const float ya = ya0 * c - yb0 * s;
+                const float yb = yb0 * c + ya0 * s;
                 if (hh < nq) {
-                    a.out[hh * d + i] = ya;
-                    a.out[hh * d + i + half] = yb;
+                    out[hh * d + i] = ya;
+                    out[hh * d + i + half] = yb;
                 } else {
-                    typename T::elem *kc =
-                        (typename T::elem *)a.kcache + ((size_t)(hh - nq) * a.max_seq + a.pos) * d;
+                    typename T::elem *kc = (typename T::elem *)a.kcache + ((size_t)(hh - nq) * a.max_seq + pos) * d;
                     T::store1(kc + i, ya);
                     T::store1(kc + i + half, yb);
                 }
             } else {
-                typename T::elem *vc =
-                    (typename T::elem *)a.vcache + ((size_t)(hh - nq - nkv) * a.max_seq + a.pos) * d;
-                T::store1(vc + i, acc_a);
-                T::store1(vc + i + half, acc_b);
+                typename T::elem *vc = (typename T::elem *)a.vcache + ((size_t)(hh - nq - nkv) * a.max_seq + pos) * d;
+                T::store1(vc + i, ya0);
+                T::store1(vc + i + half, yb0);
             }
         } else if (EPI == EPI_RESID) {
-            a.out[ra] += acc_a;
-            a.out[rb] += acc_b;
+            out[ra] += ya0;
+            out[rb] += yb0;
         } else if (EPI == EPI_SWIGLU) {
-            a.out[u] = acc_a / (1.0f + expf(-acc_a)) * acc_b;
+            out[u] = ya0 / (1.0f + expf(-ya0)) * yb0;
         } else {
-            a.out[ra] = acc_a;
-            a.out[rb] = acc_b;
+            out[ra] = ya0;
+            out[rb] = yb0;
         }
     }
 }
 
-template <typename T, int EPI>
+template <typename T, int EPI, int RB>
 static hipError_t launch_gemv_t(const GemvArgs &a, int n_cu, hipStream_t s) {
-    const size_t lds = (size_t)a.K * sizeof(float);
+    const size_t lds = (size_t)RB * a.K * sizeof(float);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemv<T, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        hipError_t e = hipFuncSetAttribute((const void *)k_gemv<T, EPI, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            160 * 1024 - 64);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int n_units = a.O / 2;
     const int wg_needed = (n_units + 3) / 4;
-    // a few workgroups per compute unit; each one stages the activation row once
+    // a few workgroups per compute unit; each one stages the activation rows once
     int occupancy = lds > 48 * 1024 ? (lds > 76 * 1024 ? 1 : 2) : 4;
     int grid = n_cu * occupancy;
     if (grid > wg_needed) grid = wg_needed;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL((k_gemv<T, EPI>), dim3(grid), dim3(kGemvThreads), lds, s, a);
+    hipLaunchKernelGGL((k_gemv<T, EPI, RB>), dim3(grid, (a.R + RB - 1) / RB), dim3(kGemvThreads), lds, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_gemv(int dtype, int epi, const GemvArgs &a, int n_cu, hipStream_t s) {
-#define SWIFT_CASE(E)                                                      \
-    case E:                                                                \
-        return dtype == F32 ? launch_gemv_t<F32T, E>(a, n_cu, s) : launch_gemv_t<BF16T, E>(a, n_cu, s);
+    if (a.R < 1 || a.R > kMaxBlockRows || (a.tree && a.R > kMaxRows)) return hipErrorInvalidValue;
+    // Rows per workgroup.  A matrix that the caches hold is read again cheaply, and what counts is the length of a
+    // workgroup: two rows (the tiny model's matrices, 0.3-1.4 MB, 32 rows: gate/up 11.2, 10.7, 11.4 and 13.5 us with 1, 2,
+    // 4 and 8 rows; q|k|v 7.9, 7.1, 8.4, 12.4).  A larger one is worth reading once: as many rows as the block has and LDS
+    // takes, up to eight.
+    const int fit = (int)((160 * 1024 - 64) / ((size_t)a.K * sizeof(float)));
+    const int want = std::min(fit, (int64_t)a.O * a.K * 4 <= (16 << 20) ? 2 : 8);
+    const int rb = a.R == 1 || want < 2 ? 1 : a.R == 2 || want < 4 ? 2 : a.R <= 4 || want < 8 ? 4 : 8;
+#define SWIFT_ROWS(T, E)                                        \
+    switch (rb) {                                               \
+        case 1: return launch_gemv_t<T, E, 1>(a, n_cu, s);      \
+        case 2: return launch_gemv_t<T, E, 2>(a, n_cu, s);      \
+        case 4: return launch_gemv_t<T, E, 4>(a, n_cu, s);      \
+        default: return launch_gemv_t<T, E, 8>(a, n_cu, s);     \
+    }
+#define SWIFT_CASE(E)                  \
+    case E:                            \
+        if (dtype != F32) return hipErrorInvalidValue; /* bf16 models run on the tiled kernels */ \
+        SWIFT_ROWS(F32T, E)
     switch (epi) {
         SWIFT_CASE(EPI_QKV)
         SWIFT_CASE(EPI_RESID)
@@ -157,6 +203,7 @@ hipError_t launch_gemv(int dtype, int epi, const GemvArgs &a, int n_cu, hipStrea
         SWIFT_CASE(EPI_LOGITS)
     }
 #undef SWIFT_CASE
+#undef SWIFT_ROWS
     return hipErrorInvalidValue;
 }
 
@@ -165,17 +212,19 @@ hipError_t launch_gemv(int dtype, int epi, const GemvArgs &a, int n_cu, hipStrea
 // ------------------------------------------------------------------------------------------
 template <typename T>
 __global__ void k_embed(EmbedArgs a) {
-    const typename T::elem *row = (const typename T::elem *)a.E + (size_t)a.token * a.H;
+    const int r = blockIdx.y;
+    const typename T::elem *row = (const typename T::elem *)a.E + (size_t)a.tokens[r] * a.H;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.H; i += gridDim.x * blockDim.x)
-        a.x[i] = T::load1(row + i);
+        a.x[(size_t)r * a.H + i] = T::load1(row + i);
 }
 
 hipError_t launch_embed(int dtype, const EmbedArgs &a, hipStream_t s) {
-    const int grid = (a.H + 255) / 256;
+    if (a.R < 1 || a.R > kMaxBlockRows) return hipErrorInvalidValue;
+    const dim3 grid((a.H + 255) / 256, a.R);
     if (dtype == F32)
-        hipLaunchKernelGGL(k_embed<F32T>, dim3(grid), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_embed<F32T>, grid, dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL(k_embed<BF16T>, dim3(grid), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_embed<BF16T>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -422,6 +471,8 @@ static AttnPlan attn_plan(const AttnArgs &a, int n_cu) {
     if (want > a.max_split) want = a.max_split;
     if (want < 1) want = 1;
     p.chunk = (a.max_seq + want - 1) / want;
+    // (a short cache: at least 128 slots, so that up to there a context is one range and needs no merge launch)
+    if (a.max_seq <= 1024 && p.chunk < 128) p.chunk = 128;
     p.chunk = (p.chunk + gran - 1) / gran * gran;
     p.n_split = (ctx + p.chunk - 1) / p.chunk;  // <= want <= max_split
     // Block rows that share their key/value loads in one workgroup (the more, the less cache traffic; bounded

@@ -217,6 +217,34 @@ def test_prefill_depth_split_against_64_row_blocks(n_prompt):
     g.close()
 
 
+@pytest.mark.parametrize("shape", [
+    si.TINY.with_layers(2),
+    si.ModelShape("fp32-wide", 1, 2048, 16, 8, 128, 10240, 384, "fp32", 1e-6),   # 8 rows per workgroup, 4 in down_proj
+    si.ModelShape("fp32-tall", 1, 256, 4, 4, 64, 32768, 384, "fp32", 1e-6),      # one row per workgroup in down_proj
+], ids=lambda s: s.name)
+def test_fp32_block_rows_equal_single_rows_bit_for_bit(shape):
+    """fp32 models take the rows of a block in one launch per stage, 1, 2, 4 or 8 of them per workgroup: every row's
+    logits equal those of the same token decoded alone, bit for bit (blocks on either side of the group sizes, prompts
+    and caches on either side of one attention range)."""
+    import paper_2410_06916_amd as P
+    g = P.SwiftModel(shape, 300)
+    g.load_weights(si.iter_weights(shape, 4, "cuda:0", gain_jitter=0.1))
+    ids = si.uniform_ids(12, 32, shape.vocab)
+    for n_prompt in (1, 33, 120):
+        first = g.prefill(si.uniform_ids(13, n_prompt, shape.vocab))
+        toks = np.concatenate([[first], ids[1:]]).astype(np.int32)
+        single = []
+        for i in range(32):
+            g.rollback(n_prompt + i, int(toks[i]))
+            single.append(g.verify([toks[i]], True)[1][0])
+            g.accept()
+        g.rollback(n_prompt, int(first))
+        for rows in (2, 3, 4, 5, 8, 9, 17, 32):
+            _, lg = g.verify(toks[:rows], True)
+            assert np.array_equal(lg, np.stack(single[:rows])), (n_prompt, rows)
+    g.close()
+
+
 BLOCK_ATTN_SHAPES = {
     # head_dim 64, two query heads per kv head
     "d64-gqa2": si.ModelShape("d64-gqa2", 2, 256, 4, 2, 64, 344, 384, "bf16", 1e-5),
