@@ -29,6 +29,11 @@ __device__ inline bf16x8 pack_bf16x8(const uint16_t (&v)[8]) {
     return __builtin_bit_cast(bf16x8, u);
 }
 
+// What bounds it: a wavefront's 80 matrix instructions per 64-slot chunk (1280 clocks) and the vector arithmetic around them
+// (softmax, conversions) hardly overlap, ~3500 clocks a chunk.  Hence hardware bf16 conversions, one fused multiply-add
+// per exponent, masks only in the chunk where a range ends, contiguous loads elsewhere and 16-byte stores: 7B, 512-row
+// macro blocks, 27 us + 10 us of merging -> 24 us at 512 slots, 69 + 13 -> 64 at 2048.
+//
 // Lane layout of v_mfma_f32_16x16x32_bf16 (C = A B): lane = 16 g + col.
 //   A (16 x 32): row col,    k = 8 g .. 8 g + 7        B (32 x 16): column col, k = 8 g .. 8 g + 7
 //   C (16 x 16): column col, rows 4 g .. 4 g + 3
@@ -38,7 +43,7 @@ __device__ inline bf16x8 pack_bf16x8(const uint16_t (&v)[8]) {
 // A prompt macro block (a.sub_rows = 64) is one launch too: blockIdx.z is the sub-block, which is treated as a block
 // of its own whose partial results sit at the macro block's row numbers.
 template <int D>
-__global__ __launch_bounds__(256) void k_attn_block(AttnArgs am, int chunk) {
+__global__ __launch_bounds__(256, 2) void k_attn_block(AttnArgs am, int chunk) {
     constexpr int DC = D / 32;   // k steps of a score tile
     constexpr int DT = D / 16;   // 16-row tiles of O^T
     constexpr int PPR = D / 8;   // 16-byte pieces per cache row
@@ -88,7 +93,17 @@ __global__ __launch_bounds__(256) void k_attn_block(AttnArgs am, int chunk) {
     // slot (an unwritten slot may hold anything).  Values come from the cache that groups eight slots per element
     // (kv_vt_index): piece p = (8-slot group p / D of the chunk, element p % D); slots past the range are zeroed in the
     // registers (0 x NaN is NaN in the second product).
+    // A chunk that lies wholly inside the range is two runs of contiguous 16-byte pieces.
     auto load_chunk = [&](int k0) {
+        if (k0 + 64 <= hi_all) {
+            const u32x4 *kp = (const u32x4 *)(kc + (size_t)k0 * D), *vp = (const u32x4 *)(vt + (size_t)k0 * D);
+#pragma unroll
+            for (int u = 0; u < NPC; ++u) {
+                kr[u] = (kp + 256 * u)[tid];
+                vr[u] = (vp + 256 * u)[tid];
+            }
+            return;
+        }
 #pragma unroll
         for (int u = 0; u < NPC; ++u) {
             const int p = tid + 256 * u, key = p / PPR, dj = p - key * PPR;
@@ -118,7 +133,8 @@ __global__ __launch_bounds__(256) void k_attn_block(AttnArgs am, int chunk) {
         }
     };
 
-    const float scale = 1.0f / sqrtf((float)D);
+    const float scale = 1.0f / sqrtf((float)D), c_exp = scale * 1.4426950408889634f;
+    const int first_lim = a.n_ctx + 16 * wave;  // range of the tile's first row
     float m_run = -INFINITY, l_run = 0.f;
     f32x4 o[DT];
 #pragma unroll
@@ -130,106 +146,109 @@ __global__ __launch_bounds__(256) void k_attn_block(AttnArgs am, int chunk) {
         __syncthreads();
         if (k0 + 64 < hi_all) load_chunk(k0 + 64);
         if (tile_live && k0 < tile_lim) {  // wavefront-uniform: some row of the tile reaches this chunk
+            // (scores stay unscaled; the scale and log2 e meet them in the exponent: e^(scale (s - max)) = 2^(c s - c max))
             float s[2][2][4];
             float mx = -INFINITY;
+            const bool ragged = k0 + 64 > first_lim;  // wavefront-uniform: some row's range ends inside this chunk
+            // (the four tiles side by side: four independent chains of matrix instructions)
+            f32x4 acc[4];
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf)
+            for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int tt = 0; tt < 2; ++tt) {
-                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-                    const uint16_t *kp = Ks + (32 * hf + 8 * (col >> 2) + 4 * tt + (col & 3)) * KP + 8 * g;
+            for (int c = 0; c < DC; ++c) {
+                bf16x8 av[4];
 #pragma unroll
-                    for (int c = 0; c < DC; ++c) {
-                        const bf16x8 av = __builtin_bit_cast(bf16x8, *(const u32x4 *)(kp + 32 * c));
+                for (int q = 0; q < 4; ++q)
+                    av[q] = __builtin_bit_cast(
+                        bf16x8, *(const u32x4 *)(Ks + (32 * (q >> 1) + 8 * (col >> 2) + 4 * (q & 1) + (col & 3)) * KP + 8 * g + 32 * c));
 #pragma unroll
-                        for (int t = 0; t < 3; ++t)
-                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, qop[c][t], acc, 0, 0, 0);
-                    }
+                for (int t = 0; t < 3; ++t)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int key = k0 + 32 * hf + 8 * g + 4 * tt + i;
-                        const float v = key < lim ? acc[i] * scale : -INFINITY;
-                        s[hf][tt][i] = v;
-                        mx = fmaxf(mx, v);
-                    }
+                    for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[q], qop[c][t], acc[q], 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int hf = q >> 1, tt = q & 1;
+                    if (ragged && k0 + 32 * hf + 8 * g + 4 * tt + i >= lim) acc[q][i] = -INFINITY;
+                    s[hf][tt][i] = acc[q][i];
+                    mx = fmaxf(mx, acc[q][i]);
                 }
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             const float mn = fmaxf(m_run, mx);
             const float ms = mn == -INFINITY ? 0.f : mn;  // nothing live yet: every exponential below is 0
-            const float corr = __expf(m_run - ms);
+            const float mc = ms * c_exp;
+            const float corr = __builtin_amdgcn_exp2f(fmaf(m_run, c_exp, -mc));
             float ps = 0.f;
             bf16x8 phi[2], plo[2];
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
-                uint16_t h[8], l[8];
+                f32x8 p;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const float p = __expf(s[hf][j >> 2][j & 3] - ms);
-                    ps += p;
-                    const uint32_t hb = f32_to_bf16_rne_finite(p);
-                    h[j] = (uint16_t)hb;
-                    l[j] = (uint16_t)f32_to_bf16_rne_finite(p - __uint_as_float(hb << 16));
+                    p[j] = __builtin_amdgcn_exp2f(fmaf(s[hf][j >> 2][j & 3], c_exp, -mc));
+                    ps += p[j];
                 }
-                phi[hf] = pack_bf16x8(h);
-                plo[hf] = pack_bf16x8(l);
+                split2(p, phi[hf], plo[hf]);
             }
             l_run = l_run * corr + ps;
             m_run = mn;
+            if (!__all(corr == 1.f)) {  // (most chunks leave every row's maximum where it is)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                o[dt] *= corr;
-                const int dd = 16 * dt + col;
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf) {
-                    const bf16x8 av = __builtin_bit_cast(
-                        bf16x8, *(const u32x4 *)(Vt + dd * VP + 8 * ((4 * hf + g) ^ ((dd >> 3) & 7))));
-                    o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, phi[hf], o[dt], 0, 0, 0);
-                    o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, plo[hf], o[dt], 0, 0, 0);
-                }
+                for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
             }
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                for (int d4 = 0; d4 < DT; d4 += 4) {
+                    bf16x8 av[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int dd = 16 * (d4 + q) + col;
+                        av[q] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(Vt + dd * VP + 8 * ((4 * hf + g) ^ ((dd >> 3) & 7))));
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) o[d4 + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[q], phi[hf], o[d4 + q], 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) o[d4 + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[q], plo[hf], o[d4 + q], 0, 0, 0);
+                }
         }
         __syncthreads();
     }
     // a row's sum is spread over its four lanes (the running maximum is common to them)
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
-    if (row >= a.rows) return;
     const int ns_row = (a.n_ctx + row + chunk - 1) / chunk;  // ranges this row reaches
-    if (sp >= ns_row) return;
-    if (ns_row == 1) {  // the row ends in the first range: normalise and write
-        const float inv = 1.0f / l_run;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            const int e = head * D + 16 * dt + 4 * g;
-            uint16_t hi[4], mid[4], lw[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float y = o[dt][i] * inv;
-                if (a.out) a.out[(size_t)row * nq * D + e + i] = y;
-                split3(y, hi[i], mid[i], lw[i]);
-            }
-            if (a.out_s) {
-                const int ocode = a.out_rows ? a.out_rows : a.rows, orows = layout_rows(ocode), nt = block_terms(ocode);
-                uint16_t *p = a.out_s + ((size_t)(e >> 3) * (nt * orows) + nt * row) * 8 + (e & 7);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    p[i] = hi[i];
-                    p[8 + i] = mid[i];
-                    if (nt == 3) p[16 + i] = lw[i];
-                }
-            }
-        }
-    } else {  // partial result of this range; k_attn_combine merges the ranges in order
+    const bool mine = row < a.rows && sp < ns_row;
+    const float inv = 1.0f / l_run;
+    const int orows = a.out_s ? layout_rows(a.out_rows) : 0;
+    if (mine && ns_row > 1 && g == 0) {
         const size_t base = ((size_t)(row_base + row) * nq + head) * n_split + sp;
-        if (g == 0) {
-            a.part_ml[base * 2] = m_run;
-            a.part_ml[base * 2 + 1] = l_run;
+        a.part_ml[base * 2] = m_run * scale;
+        a.part_ml[base * 2 + 1] = l_run;
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+        const int e = head * D + 16 * dt + 4 * g;
+        const f32x4 y = o[dt] * inv;
+        uint32_t h[4], m[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h[i] = f32_to_bf16_rne_finite(y[i]);
+            m[i] = f32_to_bf16_rne_finite(y[i] - __uint_as_float(h[i] << 16));
         }
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a.part_o[base * D + 16 * dt + 4 * g + i] = o[dt][i];
+        // (the lane with the even g ends up with eight elements' first terms, its neighbour with their second terms)
+        const u32x4 u = join8(pack2(h[0], h[1]), pack2(h[2], h[3]), pack2(m[0], m[1]), pack2(m[2], m[3]));
+        if (!mine) continue;
+        if (ns_row == 1) {  // the row ends in the first range: write the result
+            if (a.out) *(f32x4 *)(a.out + (size_t)row * nq * D + e) = y;
+            if (a.out_s) *(u32x4 *)(a.out_s + ((size_t)(e >> 3) * (2 * orows) + 2 * row + (g & 1)) * 8) = u;
+        } else {            // partial result of this range; k_attn_combine merges the ranges in order
+            const size_t base = ((size_t)(row_base + row) * nq + head) * n_split + sp;
+            *(f32x4 *)(a.part_o + base * D + 16 * dt + 4 * g) = o[dt];
+        }
     }
 }
 
@@ -243,14 +262,15 @@ hipError_t launch_attn_block(const AttnArgs &a, int n_cu, hipStream_t s) {
     const int n_sub = a.sub_rows ? (a.rows + 63) / 64 : 1;
     if (a.tree || a.rows < 1 || a.rows > 64 * n_sub || (a.sub_rows != 0 && a.sub_rows != 64) || n_sub > kMacroSub ||
         (a.sub_rows && a.out) || (a.head_dim != 64 && a.head_dim != 128) || a.n_ctx < 1 ||
-        a.n_kv_heads < 1 || a.n_q_heads % a.n_kv_heads != 0 || a.n_ctx + a.rows - 1 > a.max_seq || (!a.out && !a.out_s) ||
+        a.n_kv_heads < 1 || a.n_q_heads % a.n_kv_heads != 0 || a.n_ctx + a.rows - 1 > a.max_seq || (!a.out && !a.out_s) || (a.out_s && block_terms(a.out_rows) != 2) ||
         a.nb32 < (a.max_seq + 31) / 32 ||
         !a.part_o || !a.part_ml)
         return hipErrorInvalidValue;
     const int ctx = a.n_ctx + a.rows - 1;
-    // ranges: about two workgroups per compute unit, at least two chunks each, and no more partial results
-    // than the buffers hold (they are sized for kMaxRows rows times max_split ranges)
-    int want = (2 * n_cu + a.n_q_heads * n_sub - 1) / (a.n_q_heads * n_sub);
+    // ranges: about one workgroup per compute unit (a second one takes as much longer as it adds: 7B, 512 rows at 2048
+    // slots 69 us in two ranges + 13 us to merge them, 73 us in one), at least two chunks each, and no more partial
+    // results than the buffers hold (they are sized for kMaxRows rows times max_split ranges)
+    int want = (n_cu + a.n_q_heads * n_sub - 1) / (a.n_q_heads * n_sub);
     const int cap = kMaxRows * a.max_split / a.rows;
     if (want > cap) want = cap;
     if (want < 1) want = 1;

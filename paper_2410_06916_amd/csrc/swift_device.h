@@ -8,6 +8,13 @@ namespace swift {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // one 128-bit load
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+
+// Eight probabilities as two bf16 terms (relative error 2^-17), converted in pairs.
+__device__ inline void split2(const f32x8 &p, bf16x8 &hi, bf16x8 &lo) {
+    hi = __builtin_convertvector(p, bf16x8);
+    lo = __builtin_convertvector(p - __builtin_convertvector(hi, f32x8), bf16x8);
+}
 
 // fp32 -> bf16 bits, round to nearest even (NaN stays NaN)
 __device__ inline uint16_t f32_to_bf16_rne(float f) {
@@ -16,12 +23,8 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
     u += 0x7fffu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
 }
-// same for finite inputs only (no NaN test)
-__device__ inline uint32_t f32_to_bf16_rne_finite(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
+// same for finite inputs only: the hardware's conversion (v_cvt_pk_bf16_f32), one instruction instead of four
+__device__ inline uint32_t f32_to_bf16_rne_finite(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 // v = hi + mid + lo exactly (three bf16 terms carry the 24-bit significand of an fp32 value)
 __device__ inline void split3(float v, uint16_t &hi, uint16_t &mid, uint16_t &lo) {
@@ -33,6 +36,21 @@ __device__ inline void split3(float v, uint16_t &hi, uint16_t &mid, uint16_t &lo
     mid = (uint16_t)m;
     lo = (uint16_t)f32_to_bf16_rne_finite(r2);
 }
+
+// Exchanges the odd 16-lane rows of a with the even ones of b.
+__device__ inline void swap16(uint32_t &a, uint32_t &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+// Lanes kg and kg ^ 1 hold values 0..3 and 4..7 of two eight-value units (x, y: two packed words each): afterwards the
+// lane with the even kg holds all of x, the other one all of y.
+__device__ inline u32x4 join8(uint32_t x0, uint32_t x1, uint32_t y0, uint32_t y1) {
+    swap16(x0, y0);
+    swap16(x1, y1);
+    return u32x4{x0, x1, y0, y1};
+}
+__device__ inline uint32_t pack2(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every global
 // load and store of the wavefront (its release fence covers global memory), which would drain a

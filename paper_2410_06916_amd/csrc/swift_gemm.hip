@@ -108,26 +108,12 @@ __device__ inline void fold_terms(const f32x4 (&acc)[8], int col, f32x4 (&y)[4])
             y[c][i] = own + dpp_xor1(other);
         }
 }
-// Exchanges the odd 16-lane rows of a with the even ones of b.
-__device__ inline void swap16(uint32_t &a, uint32_t &b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
 // Exchanges the upper 32 lanes of a with the lower ones of b.
 __device__ inline void swap32(float &a, float &b) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     a = __uint_as_float(r[0]);
     b = __uint_as_float(r[1]);
 }
-// Lanes kg and kg ^ 1 hold values 0..3 and 4..7 of two eight-value units (x, y: two packed words each): afterwards the
-// lane with the even kg holds all of x, the other one all of y.
-__device__ inline u32x4 join8(uint32_t x0, uint32_t x1, uint32_t y0, uint32_t y1) {
-    swap16(x0, y0);
-    swap16(x1, y1);
-    return u32x4{x0, x1, y0, y1};
-}
-__device__ inline uint32_t pack2(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
 // The two-term split of the four values of lanes kg, kg ^ 1 (values 4 (kg & 1) .. of eight), to unit
 // [chunk][128 columns][8]: columns 2 r and 2 r + 1.
 __device__ inline void store_split(uint16_t *out_s, int chunk, int r, int kg, bool ok, const f32x4 &v) {
