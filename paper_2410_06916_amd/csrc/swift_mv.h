@@ -26,14 +26,14 @@ __device__ inline void mv_touch_value_lines(const MvArgs &a, int rg, int lane) {
 // What follows the dot products of one 16-row group, run by one whole wavefront.
 // Y(r, j): finished dot product of block row r and tile row j (before the norm scale).
 // rot: optional LDS copy of the rotary rows, [R][d/2 cos | d/2 sin]; nullptr = read the tables.
-// ONE_PASS: the caller guarantees R <= 4, so that one pass of the wavefront covers the row group
-// (no loop around the loads and stores below).
-template <int EPI, bool ONE_PASS = false, typename YF>
-__device__ inline void mv_epilogue(const MvArgs &a, int rg, int lane, const float *rs, const float *rot, YF Y) {
+// Several wavefronts may share a row group: wavefront it0 of it_step takes every it_step-th pass of 64 results.
+template <int EPI, typename YF>
+__device__ inline void mv_epilogue(const MvArgs &a, int rg, int lane, const float *rs, const float *rot, YF Y, int it0 = 0,
+                                   int it_step = 1) {
     const int R = a.R, NT = block_terms(a.RL), NC = NT * layout_rows(a.RL);  // NC: column pitch of the split outputs
     if (EPI == EPI_RESID || EPI == EPI_LOGITS) {
-        const int iters = ONE_PASS ? 1 : (16 * R + 63) >> 6;
-        for (int it = 0; it < iters; ++it) {
+        const int iters = (16 * R + 63) >> 6;
+        for (int it = it0; it < iters; it += it_step) {
             const int idx = it * 64 + lane;
             const int r = idx >> 4, j = idx & 15;
             const int row = 16 * rg + j;
@@ -60,8 +60,8 @@ __device__ inline void mv_epilogue(const MvArgs &a, int rg, int lane, const floa
             }
         }
     } else {
-        const int iters = ONE_PASS ? 1 : (8 * R + 63) >> 6;
-        for (int it = 0; it < iters; ++it) {
+        const int iters = (8 * R + 63) >> 6;
+        for (int it = it0; it < iters; it += it_step) {
             const int idx = it * 64 + lane;
             const int r = idx >> 3, j = idx & 7;
             if (r >= R) continue;

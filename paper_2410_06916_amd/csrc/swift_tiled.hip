@@ -1,7 +1,7 @@
 // gfx950 kernels of the bf16 path: tiled weights streamed once from HBM into MFMA, activations
 // kept in fp32 precision as three bf16 terms (two in blocks of more than 16 rows).  k_mv1 handles blocks of 1-5 activation rows whose
-// activation fits in LDS (draft pass, plain decoding, short verify blocks), k_mvN blocks of up to
-// 64 rows (longer verify blocks, prefill, candidate evaluation).
+// activation fits in LDS (draft pass, plain decoding, short verify blocks), k_mvR and k_mvN blocks of up to
+// 32 and 64 rows (longer verify blocks, prefill, candidate evaluation).
 #include <math.h>
 
 #include <algorithm>
@@ -244,6 +244,51 @@ __device__ inline void mv_norm_rows32(const MvArgs &a, float *rs /* LDS [64] */,
         if (a.pss)
             for (int q2 = 0; q2 < 32; ++q2) ss += scratch[q2 * 32 + tid];
         rs[tid] = a.pss ? 1.0f / sqrtf(ss / (float)a.norm_dim + a.eps) : 1.0f;
+    }
+}
+
+// mv_norm_rows32 in two parts: the loads of the first 256 partials (hidden <= 4096: all of them), and the rest with an
+// LDS-only barrier.
+struct NormPart32 {
+    float v[2][8];
+};
+__device__ inline void mv_norm32_load(const MvArgs &a, int p0, NormPart32 &np) {
+    const int tid = threadIdx.x, r = tid & 31, q0 = tid >> 5;
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int p = p0 + q0 + 16 * half + 32 * u;
+            np.v[half][u] = (a.pss && p < a.n_pss) ? a.pss[(size_t)p * a.rp + r] : 0.f;
+        }
+}
+__device__ inline void mv_norm32_finish(const MvArgs &a, NormPart32 &np, float *rs /* LDS [32] */, float *scratch /* LDS [1024] */) {
+    const int tid = threadIdx.x, r = tid & 31, q0 = tid >> 5;
+    float ss[2] = {0.f, 0.f};
+    for (int p0 = 0;;) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            float t = 0.f;
+            if (p0 == 0) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t += np.v[half][u];
+                ss[half] = t;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) ss[half] += np.v[half][u];
+            }
+        }
+        p0 += 256;
+        if (p0 >= a.n_pss) break;
+        mv_norm32_load(a, p0, np);
+    }
+    scratch[q0 * 32 + r] = ss[0];
+    scratch[(q0 + 16) * 32 + r] = ss[1];
+    lds_barrier();
+    if (tid < 32) {
+        float t = 0.f;
+        for (int q2 = 0; q2 < 32; ++q2) t += scratch[q2 * 32 + tid];
+        rs[tid] = a.pss ? 1.0f / sqrtf(t / (float)a.norm_dim + a.eps) : 1.0f;
     }
 }
 
@@ -611,7 +656,7 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 }
 
 // ------------------------------------------------------------------------------------------
-// a block of 2..64 activation rows: Y = W . X, MFMA, K chunked through LDS, optional split-K
+// a block of up to 64 activation rows: Y = W . X, MFMA, K chunked through LDS, optional split-K
 // ------------------------------------------------------------------------------------------
 // Each of the 8 wavefronts of a workgroup owns RG 16-row groups of W; the workgroup walks its K
 // range in chunks of CT tiles.  The B operand of a chunk (4 CT k-chunks x NC = 3R columns x 16 B,
@@ -943,6 +988,209 @@ static hipError_t launch_mvN_t(const MvArgs &a, int n_cu, hipStream_t s) {
     return launch_maybe_timed(k_mvN<EPI, NCB, CT, RG, DMA, CANON>, dim3(grid_x, ksp), dim3(512), lds, s, a, TS, rpw);
 }
 
+// ------------------------------------------------------------------------------------------
+// 6..32 activation rows (and any number whose activation is too deep for k_mv1): every wavefront on its own
+// ------------------------------------------------------------------------------------------
+// As in k_mv1, eight wavefronts share RG row groups of W, each streaming one of the eight K slices through a rolling window
+// of NS steps (a step: the tile of each of the RG row groups and the NCB column blocks of B that meet it), and the slice
+// sums are added in LDS in the one fixed order.  B is not staged: it comes straight from L2, which holds it (27 columns x
+// 4096: 221 KB) and delivers 128 B/ns to a compute unit that takes in about 26 B/ns of weights, so that nothing couples
+// the wavefronts between the ends of a round.
+// (the slice sums of two rounds, where LDS holds them: one barrier a round)
+template <int NCB, int RG>
+constexpr bool kMvrTwoBuffers = 2 * 8 * RG * 16 * NCB * 16 * 4 <= 150 * 1024;
+template <int EPI, int NCB, int RG, int NS>
+__global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int NCP = 16 * NCB;                 // columns as computed
+    constexpr int kRed = 8 * RG * NCP * 16;       // floats of one round's slice sums
+    constexpr bool kTwo = kMvrTwoBuffers<NCB, RG>;
+    float *red = (float *)smem;                   // [kTwo ? 2 : 1][8 slices][RG][NCP][16]
+    float *rs = red + (kTwo ? 2 : 1) * kRed;      // [32]
+    float *nscratch = rs + 32;                    // [1024]
+    constexpr bool kNorm = EPI != EPI_RESID;
+    const int NT = block_terms(a.RL), NC = NT * layout_rows(a.RL);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, kg = lane >> 4;
+    const int T = a.T;
+    const int n = (T + 7) >> 3;                // k tiles of a slice
+    const int t0 = min(ks * n, T - 1);
+    const int nv = max(0, min(n, T - ks * n)); // ... of which exist
+    const int nvm1 = max(nv - 1, 0);
+    const int W = a.n_wg, last_rg = a.n_rg - 1;
+    const u32x4 *Wt = (const u32x4 *)a.Wt;
+    const unsigned char *bb = (const unsigned char *)a.in_s;
+    // this lane's byte offset of B for tile t0 (columns past NC read what lies there: results nobody reads); in a ragged
+    // last tile the lanes past the real depth read its last chunk, and meet zero weights
+    const uint32_t bstride = 64u * NC;
+    const uint32_t boff = ((uint32_t)(4 * t0 + kg) * NC + col) * 16u;
+    const uint32_t bmax = ((uint32_t)((a.K >> 3) - 1) * NC + col) * 16u;
+
+    u32x4 A[NS][RG], B[NS][NCB];
+    const u32x4 *base[RG];
+    auto load_step = [&](int i, u32x4(&Av)[RG], u32x4(&Bv)[NCB]) {
+        const int ii = min(i, nvm1);
+#pragma unroll
+        for (int g = 0; g < RG; ++g) Av[g] = __builtin_nontemporal_load(base[g] + (size_t)ii * 64);
+        const uint32_t off = min(boff + (uint32_t)ii * bstride, bmax);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) Bv[cb] = *(const u32x4 *)(bb + off + 256 * cb);
+    };
+    auto set_base = [&](int seg) {
+#pragma unroll
+        for (int g = 0; g < RG; ++g) {
+            const int rg = min((seg * W + (int)blockIdx.x) * RG + g, last_rg);
+            base[g] = Wt + ((size_t)rg * T + t0) * 64 + lane;
+        }
+    };
+    // (the norm partials go out first; the scales are read by the epilogue only, so an LDS-only barrier will do)
+    NormPart np;
+    NormPart32 np32;
+    if (kNorm) {
+        if (a.rp == 16)
+            np = mv_norm_load(a);
+        else
+            mv_norm32_load(a, 0, np32);
+    }
+    set_base(0);
+#pragma unroll
+    for (int u = 0; u < NS; ++u) load_step(u, A[u], B[u]);
+    if (EPI == EPI_QKV) {
+        // the lines the epilogues of this workgroup's rounds will write values into (wavefront s: round s)
+        if (ks < a.S)
+            for (int g = 0; g < RG; ++g) mv_touch_value_lines(a, min((ks * W + (int)blockIdx.x) * RG + g, last_rg), lane);
+    }
+    if (kNorm) {
+        if (a.rp == 16)
+            mv_norm_finish<true>(a, np, rs, nscratch);
+        else
+            mv_norm32_finish(a, np32, rs, nscratch);
+    }
+
+    f32x4 acc[RG][NCB];
+    auto mma_step = [&](int i, const u32x4(&Av)[RG], const u32x4(&Bv)[NCB]) {
+        if (i >= nv) return;  // (wavefront-uniform)
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb)
+                acc[g][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Av[g]), __builtin_bit_cast(bf16x8, Bv[cb]),
+                                                                     acc[g][cb], 0, 0, 0);
+    };
+    const int nb = (n + NS - 1) / NS;
+    for (int seg = 0; seg < a.S; ++seg) {
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b + 1 < nb; ++b) {
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                mma_step(b * NS + u, A[u], B[u]);
+                load_step((b + 1) * NS + u, A[u], B[u]);
+            }
+        }
+        if (seg + 1 < a.S) {
+            // the window rolls on into the next round's row groups: the stream never drains
+            set_base(seg + 1);
+#pragma unroll
+            for (int u = 0; u < NS; ++u) {
+                mma_step((nb - 1) * NS + u, A[u], B[u]);
+                load_step(u, A[u], B[u]);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < NS; ++u) mma_step((nb - 1) * NS + u, A[u], B[u]);
+        }
+        // ---- end of the round: slice sums to LDS, then all wavefronts share the epilogue
+        if (!kTwo && seg > 0) lds_barrier();  // (the previous round's sums are no longer read)
+        float *rp = red + (kTwo ? (size_t)(seg & 1) * kRed : 0);
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) *(f32x4 *)(rp + ((ks * RG + g) * NCP + 16 * cb + col) * 16 + 4 * kg) = acc[g][cb];
+        lds_barrier();  // (the next round's loads stay in flight)
+        constexpr int share = 8 / RG;              // wavefronts per row group
+        const int g = ks / share;
+        const int rg = (seg * W + (int)blockIdx.x) * RG + g;
+        if (g < RG && rg <= last_rg) {
+            mv_epilogue<EPI>(a, rg, lane, rs, nullptr, [&](int r, int j) {
+                // (the order of k_mv1: per term in groups of kgroup slices, the terms of a group combined, groups in order)
+                const int kgroup = a.kgroup;
+                const float *w = rp + (g * NCP + NT * r) * 16 + j;
+                constexpr int ss = RG * NCP * 16;  // from one slice to the next
+                float y = 0.f;
+#pragma unroll 1
+                for (int k0 = 0; k0 < 8; k0 += kgroup) {
+                    float hi = w[0], mid = w[16], lo = NT == 3 ? w[32] : 0.f;
+                    w += ss;
+#pragma unroll 1
+                    for (int k2 = 1; k2 < kgroup; ++k2) {
+                        hi += w[0];
+                        mid += w[16];
+                        if (NT == 3) lo += w[32];
+                        w += ss;
+                    }
+                    const float gs = (hi + mid) + lo;
+                    y = k0 == 0 ? gs : y + gs;
+                }
+                return y;
+            }, ks - g * share, share);
+        }
+    }
+}
+
+// Steps in flight per wavefront: what 256 registers hold beside the accumulators.
+constexpr int mvr_steps(int ncb, int rg) {
+    const int n = ((rg * ncb >= 8 ? 184 : 200) - 4 * rg * ncb) / (4 * (rg + ncb));
+    return n > 10 ? 10 : n;
+}
+
+template <int EPI, int NCB, int RG>
+static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
+    constexpr int NS = mvr_steps(NCB, RG);
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_mvR<EPI, NCB, RG, NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const size_t lds = (size_t)(kMvrTwoBuffers<NCB, RG> ? 2 : 1) * 8 * RG * 16 * NCB * 16 * 4 + 32 * 4 + 1024 * 4;
+    const int units = (a.n_rg + RG - 1) / RG;
+    a.S = (units + n_cu - 1) / n_cu;
+    a.n_wg = (units + a.S - 1) / a.S;
+    a.kgroup = mv_slice_group(a, n_cu);
+    return launch_maybe_timed(k_mvR<EPI, NCB, RG, NS>, dim3(a.n_wg), dim3(512), lds, s, a);
+}
+
+// Row groups per workgroup round for k_mvR, or 0: k_mvN is the faster kernel.  Both sides by costs fitted to launches of
+// the 7B, 13B and 70B shapes (us, kernel durations).  k_mvR: start and end of a launch 5, then what a compute unit takes in --
+// weights and its own reading of B -- at 46-60 KB per us; a row-group count that leaves units idle in its last round pays for
+// whole rounds.  k_mvN: 7.5, the weights at 6.1 TB/s, 3 where it splits K over workgroups, 8.5 % more per column block past
+// the second.  (9 rows, 7B, k_mvN -> k_mvR: q|k|v 27.8 -> 20.5, o_proj 15.6 -> 11.4, gate/up 37.9 -> 32.9, down_proj 26.0 ->
+// 24.4, LM head 47.2 -> 45.8; 31 rows: 38.5 -> 30.7, 22.4 -> 18.8, and k_mvN 53.8 against 62.7 for gate/up; 70B, one row,
+// down_proj 83 -> 72.)
+static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
+    if (ncb < 1 || ncb > 6 || a.R > kMaxRows) return 0;
+    static const double kRate[3] = {57.0, 50.0, 45.5};
+    const double mb = (double)a.n_rg * a.T / 1024.0;
+    double best = (7.5 + mb * 1.0486 / 6.1 + (mv_slice_group(a, n_cu) < 8 ? 3.0 : 0.0)) * (1.0 + 0.085 * (ncb - 2));
+    if (ncb == 1) best = 1e30;  // (activations too deep for k_mv1)
+    int rg = 0;
+    for (int c = 1; c <= 3; ++c) {
+        if (ncb > 4 && c == 2) continue;
+        const int units = (a.n_rg + c - 1) / c, S = (units + n_cu - 1) / n_cu;
+        const double us = 5.0 + (double)S * a.T * (c + ncb) / (ncb == 6 && c == 3 && S > 1 ? 40.0 : kRate[c - 1]);
+        if (us < best) {
+            best = us;
+            rg = c;
+        }
+    }
+    return rg;
+}
+
 int mv_split_slots(const MvArgs &a, int n_cu) {
     if (a.RL & kBulkLayout) return a.part_capacity;  // (bulk layouts: not needed by callers)
     if (a.R <= kMvSmallRows && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds) return 0;  // LDS-resident kernel
@@ -960,10 +1208,37 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
     // small blocks (in their own exact layout) whose whole activation fits in LDS take the single-pass kernel
     if (!bulk && a.R <= kMvSmallRows && ks_override != 16 && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds)
         return launch_mv1(epi, a, n_cu, ks_override, wg_override, s);
-    // exact layouts (up to 32 rows): 1-6 column blocks of three-term columns, K chunks of 8 tiles, the fixed
+    // exact layouts (up to 32 rows): 2-6 column blocks of three-term columns, K chunks of 8 tiles, the fixed
     // summation order; bulk layouts of 32 / 64 rows (prefill, candidate evaluation): 4 / 8 column blocks of
     // two-term columns
     const int ncb = (block_terms(a.RL) * lrows + 15) / 16;
+    if (const int rg = mvr_row_groups(a, n_cu, ncb)) {
+#define SWIFT_MVR_RG(E, N)                                          \
+    case N:                                                         \
+        if (rg == 1) return launch_mvR_t<E, N, 1>(a, n_cu, s);      \
+        if (rg == 2) return launch_mvR_t<E, N, 2>(a, n_cu, s);      \
+        return launch_mvR_t<E, N, 3>(a, n_cu, s);
+#define SWIFT_MVR_CASE(E)                                                                     \
+    case E:                                                                                   \
+        switch (ncb) {                                                                        \
+            SWIFT_MVR_RG(E, 1)                                                                \
+            SWIFT_MVR_RG(E, 2)                                                                \
+            SWIFT_MVR_RG(E, 3)                                                                \
+            SWIFT_MVR_RG(E, 4)                                                                \
+            case 5: return rg == 1 ? launch_mvR_t<E, 5, 1>(a, n_cu, s) : launch_mvR_t<E, 5, 3>(a, n_cu, s); \
+            case 6: return rg == 1 ? launch_mvR_t<E, 6, 1>(a, n_cu, s) : launch_mvR_t<E, 6, 3>(a, n_cu, s); \
+            default: return hipErrorInvalidValue;                                             \
+        }
+        switch (epi) {
+            SWIFT_MVR_CASE(EPI_QKV)
+            SWIFT_MVR_CASE(EPI_RESID)
+            SWIFT_MVR_CASE(EPI_SWIGLU)
+            SWIFT_MVR_CASE(EPI_LOGITS)
+        }
+#undef SWIFT_MVR_CASE
+#undef SWIFT_MVR_RG
+        return hipErrorInvalidValue;
+    }
 #define SWIFT_MVN_CASE(E)                                                                \
     case E:                                                                              \
         if (bulk) switch (ncb) {                                                         \
@@ -972,7 +1247,6 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
                 default: return hipErrorInvalidValue;                                    \
             }                                                                            \
         switch (ncb) {                                                                   \
-            case 1: return launch_mvN_t<E, 1, 8, 1, false, true>(a, n_cu, s);            \
             case 2: return launch_mvN_t<E, 2, 8, 1, false, true>(a, n_cu, s);            \
             case 3: return launch_mvN_t<E, 3, 8, 1, false, true>(a, n_cu, s);            \
             case 4: return launch_mvN_t<E, 4, 8, 1, false, true>(a, n_cu, s);            \
