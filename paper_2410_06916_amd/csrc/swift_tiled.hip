@@ -1147,9 +1147,17 @@ constexpr int mvr_steps(int ncb, int rg) {
     return n > 10 ? 10 : n;
 }
 
-template <int EPI, int NCB, int RG>
-static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
-    constexpr int NS = mvr_steps(NCB, RG);
+// A second depth for slices that the first one cuts badly (slots past the end of a slice load its last tile again): 16, 20,
+// 32 and 43 tiles are 2 x 8, 2 x 10 or 5 x 4, 4 x 8 and 5 x 9 or 11 x 4.
+constexpr int mvr_other_steps(int ns) { return ns > 8 ? 8 : ns == 8 ? 7 : ns > 4 ? 4 : ns == 3 ? 2 : ns; }
+// Steps of a slice of n tiles as walked, with the better of the two depths.
+static int mvr_slots(int n, int ncb, int rg) {
+    const int a = mvr_steps(ncb, rg), b = mvr_other_steps(a);
+    return std::min((n + a - 1) / a * a, (n + b - 1) / b * b);
+}
+
+template <int EPI, int NCB, int RG, int NS>
+static hipError_t launch_mvR_ns(const MvArgs &a, hipStream_t s) {
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void *)k_mvR<EPI, NCB, RG, NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1158,23 +1166,30 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
         attr_set = true;
     }
     const size_t lds = (size_t)(kMvrTwoBuffers<NCB, RG> ? 2 : 1) * 8 * RG * 16 * NCB * 16 * 4 + 32 * 4 + 1024 * 4;
+    return launch_maybe_timed(k_mvR<EPI, NCB, RG, NS>, dim3(a.n_wg), dim3(512), lds, s, a);
+}
+template <int EPI, int NCB, int RG>
+static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
     const int units = (a.n_rg + RG - 1) / RG;
     a.S = (units + n_cu - 1) / n_cu;
     a.n_wg = (units + a.S - 1) / a.S;
     a.kgroup = mv_slice_group(a, n_cu);
-    return launch_maybe_timed(k_mvR<EPI, NCB, RG, NS>, dim3(a.n_wg), dim3(512), lds, s, a);
+    constexpr int NS = mvr_steps(NCB, RG), NS2 = mvr_other_steps(NS);
+    const int n = (a.T + 7) / 8, slots = (n + NS - 1) / NS * NS, slots2 = (n + NS2 - 1) / NS2 * NS2;
+    return slots <= slots2 ? launch_mvR_ns<EPI, NCB, RG, NS>(a, s) : launch_mvR_ns<EPI, NCB, RG, NS2>(a, s);
 }
 
 // Row groups per workgroup round for k_mvR, or 0: k_mvN is the faster kernel.  Both sides by costs fitted to launches of
-// the 7B, 13B and 70B shapes (us, kernel durations).  k_mvR: start and end of a launch 5, then what a compute unit takes in --
-// weights and its own reading of B -- at 46-60 KB per us; a row-group count that leaves units idle in its last round pays for
-// whole rounds.  k_mvN: 7.5, the weights at 6.1 TB/s, 3 where it splits K over workgroups, 8.5 % more per column block past
-// the second.  (9 rows, 7B, k_mvN -> k_mvR: q|k|v 27.8 -> 20.5, o_proj 15.6 -> 11.4, gate/up 37.9 -> 32.9, down_proj 26.0 ->
-// 24.4, LM head 47.2 -> 45.8; 31 rows: 38.5 -> 30.7, 22.4 -> 18.8, and k_mvN 53.8 against 62.7 for gate/up; 70B, one row,
-// down_proj 83 -> 72.)
+// the 7B, 13B and 70B shapes (us, kernel durations).  k_mvR: 5 for the start and end of a launch, then what a compute unit
+// takes in -- weights and its own reading of B, slots past the end of a slice among them -- at 45-70 KB per us; a row-group
+// count that leaves units idle in its last round pays for whole rounds.  k_mvN: 7.5, the weights at 6.1 TB/s, 3 where it
+// splits K over workgroups, 8.5 % more per column block past the second.  (9 rows, 7B, k_mvN -> k_mvR: q|k|v 27.8 -> 20.6,
+// o_proj 15.6 -> 10.6, gate/up 37.9 -> 32.9, down_proj 26.0 -> 23.9, LM head 47.2 -> 45.9; 15 rows: 28.8 -> 22.4, 18.2 ->
+// 12.3, 40.5 -> 35.6, 29.3 -> 28.6; 31 rows: 38.5 -> 31.3, 22.4 -> 17.6, and k_mvN 53.8 against 63.0 for gate/up; 70B, one
+// row, down_proj 83 -> 72.)
 static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     if (ncb < 1 || ncb > 6 || a.R > kMaxRows) return 0;
-    static const double kRate[3] = {57.0, 50.0, 45.5};
+    static const double kRate[3][6] = {{57, 61, 64, 66, 68, 70}, {45, 48, 52, 52, 52, 52}, {45, 47, 49.5, 48.5, 47, 46}};
     const double mb = (double)a.n_rg * a.T / 1024.0;
     double best = (7.5 + mb * 1.0486 / 6.1 + (mv_slice_group(a, n_cu) < 8 ? 3.0 : 0.0)) * (1.0 + 0.085 * (ncb - 2));
     if (ncb == 1) best = 1e30;  // (activations too deep for k_mv1)
@@ -1182,7 +1197,7 @@ static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     for (int c = 1; c <= 3; ++c) {
         if (ncb > 4 && c == 2) continue;
         const int units = (a.n_rg + c - 1) / c, S = (units + n_cu - 1) / n_cu;
-        const double us = 5.0 + (double)S * a.T * (c + ncb) / (ncb == 6 && c == 3 && S > 1 ? 40.0 : kRate[c - 1]);
+        const double us = 5.0 + (double)S * 8 * mvr_slots((a.T + 7) / 8, ncb, c) * (c + ncb) / kRate[c - 1][ncb - 1];
         if (us < best) {
             best = us;
             rg = c;
