@@ -547,21 +547,66 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
         m.part_capacity = L.mv_part_capacity;  // (decides the K split, hence the summation order: one value everywhere)
         return m;
     };
-    // ---- the pass as a list of launches
-    struct Launch {
-        int kc;       // kernel class (profiling, launch-shape overrides)
-        int epi;      // projections: Epilogue; attention: -1
-        MvArgs mv;
-        AttnArgs at;
+    const int last = n_sub > 0 ? n_sub - 1 : 0;
+    MacroArgs ma{};
+    ma.S = n_sub;
+    ma.rows_last = R;
+    auto sub_rows = [&](int sb) { return sb == last ? R : kMaxBlockRows; };
+    for (int sb = 0; sb <= last; ++sb) {
+        EmbedRowsArgs ea{};
+        ea.E = dptr<uint16_t>(x, L.embed);
+        ea.H = H;
+        ea.R = sub_rows(sb);
+        for (int r = 0; r < ea.R; ++r) ea.tokens[r] = tokens[sb * kMaxBlockRows + r];
+        ea.x = xf + sb * L.sub_x;
+        ea.xs = xs + sb * L.sub_xs;
+        ea.gain_next = gain_of(0);
+        ea.pss = pss + sb * L.sub_pss;
+        ea.rp = n_sub > 0 ? kMaxBlockRows : block_row_pitch(R);
+        ea.RL = RLC;
+        HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)ea.R * H * 2, [&] { return launch_embed_rows(ea, s); }));
+    }
+
+    // ---- one launch per stage, issued as soon as its arguments stand: the device starts on the first one while the host
+    // prepares the others
+    auto run_mv = [&](int kc, int epi, const MvArgs &m) -> int {
+        if (n_sub > 0 && epi != EPI_LOGITS) {
+            // (sub-block strides: which buffers a launch reads and writes follows from its epilogue)
+            ma.in_s = kc == SWIFT_KC_OPROJ ? L.sub_as : kc == SWIFT_KC_DOWN ? L.sub_hs : L.sub_xs;
+            ma.pss = L.sub_pss;
+            ma.out_f32 = epi == EPI_QKV ? L.sub_q : L.sub_x;
+            ma.out_s = epi == EPI_SWIGLU ? L.sub_hs : L.sub_xs;
+            ma.pss_out = L.sub_pss;
+            HIP_TRY(timed(x, kc, (uint64_t)m.O * m.K * 2, [&] { return launch_gemm(epi, m, ma, x->n_cu, x->gemm_rgw, s); }));
+        } else {
+            HIP_TRY(timed(x, kc, (uint64_t)m.O * m.K * 2,
+                          [&] { return launch_mv(epi, m, x->n_cu, x->tune_ks[kc], x->tune_wg[kc], s); }, true));
+        }
+        return SWIFT_OK;
     };
-    std::vector<Launch> list;
-    list.reserve(5 * stages.size() + 1);
-    auto push_mv = [&](int kc, int epi, const MvArgs &m) {
-        Launch st{};
-        st.kc = kc;
-        st.epi = epi;
-        st.mv = m;
-        list.push_back(st);
+    auto run_attn = [&](const AttnArgs &at) -> int {
+        if (n_sub > 0 && L.mfma_attn) {
+            // (the block attention kernel takes the whole macro block in one launch)
+            AttnArgs a = at;
+            a.rows = last * kMaxBlockRows + R;
+            a.sub_rows = kMaxBlockRows;
+            a.sub_q = L.sub_q;
+            a.sub_out_s = L.sub_as;
+            a.out_rows = RLC;
+            HIP_TRY(timed(x, SWIFT_KC_ATTN, (uint64_t)2 * KV * 2 * (pos0 + a.rows), [&] { return launch_attn_block(a, x->n_cu, s); }));
+            return SWIFT_OK;
+        }
+        for (int sb = 0; sb <= last; ++sb) {
+            AttnArgs a = at;
+            a.rows = sub_rows(sb);
+            a.n_ctx += sb * kMaxBlockRows;
+            a.q += sb * L.sub_q;
+            a.q_s += sb * L.sub_q_s;
+            a.out_s += sb * L.sub_as;
+            int rc = block_attention(x, a, RLC);
+            if (rc) return rc;
+        }
+        return SWIFT_OK;
     };
     for (size_t i = 0; i < stages.size(); ++i) {
         const int l = stages[i].layer;
@@ -592,12 +637,9 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
                 m.pf_heads = c.n_kv_heads;
                 m.pf_rows = pos0;
             }
-            push_mv(SWIFT_KC_QKV, EPI_QKV, m);
+            if (int rc = run_mv(SWIFT_KC_QKV, EPI_QKV, m)) return rc;
 
-            Launch at{};
-            at.kc = SWIFT_KC_ATTN;
-            at.epi = -1;
-            AttnArgs &a = at.at;
+            AttnArgs a{};
             a.q = qf;
             a.kcache = kv_base(x, l, 0);
             a.vcache = kv_base(x, l, 1);
@@ -620,7 +662,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
                 a.row_base = 0;
                 a.tt = *tree;
             }
-            list.push_back(at);
+            if (int rc = run_attn(a)) return rc;
 
             MvArgs o = base_args(y.wo, H, Q, (H + 15) / 16);
             o.in_s = as_;
@@ -629,14 +671,14 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             o.out_s = xs;
             o.gain_next = gnext;
             o.pss_out = pss;
-            push_mv(SWIFT_KC_OPROJ, EPI_RESID, o);
+            if (int rc = run_mv(SWIFT_KC_OPROJ, EPI_RESID, o)) return rc;
         } else {
             MvArgs m = base_args(y.wgu, 2 * F, H, (F + 7) / 8);
             m.in_s = xs;
             m.pss = pss;
             m.n_pss = n_pss;
             m.out_s = hs;
-            push_mv(SWIFT_KC_GATEUP, EPI_SWIGLU, m);
+            if (int rc = run_mv(SWIFT_KC_GATEUP, EPI_SWIGLU, m)) return rc;
             MvArgs w = base_args(y.wd, H, F, (H + 15) / 16);
             w.in_s = hs;
             w.out_f32 = xf;
@@ -644,11 +686,10 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             w.out_s = xs;
             w.gain_next = gnext;
             w.pss_out = pss;
-            push_mv(SWIFT_KC_DOWN, EPI_RESID, w);
+            if (int rc = run_mv(SWIFT_KC_DOWN, EPI_RESID, w)) return rc;
         }
     }
     // (macro block: the LM head reads the last sub-block's buffers)
-    const int last = n_sub > 0 ? n_sub - 1 : 0;
     if (want_logits) {
         MvArgs m = base_args(L.lm_head, V, H, (V + 15) / 16);
         m.in_s = xs + last * L.sub_xs;
@@ -656,68 +697,9 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
         m.n_pss = n_pss;
         m.out_f32 = dptr<float>(x, L.logits);
         m.ld_out = V;
-        push_mv(SWIFT_KC_LMHEAD, EPI_LOGITS, m);
+        if (int rc = run_mv(SWIFT_KC_LMHEAD, EPI_LOGITS, m)) return rc;
     }
 
-    MacroArgs ma{};
-    ma.S = n_sub;
-    ma.rows_last = R;
-    auto sub_rows = [&](int sb) { return sb == last ? R : kMaxBlockRows; };
-    for (int sb = 0; sb <= last; ++sb) {
-        EmbedRowsArgs ea{};
-        ea.E = dptr<uint16_t>(x, L.embed);
-        ea.H = H;
-        ea.R = sub_rows(sb);
-        for (int r = 0; r < ea.R; ++r) ea.tokens[r] = tokens[sb * kMaxBlockRows + r];
-        ea.x = xf + sb * L.sub_x;
-        ea.xs = xs + sb * L.sub_xs;
-        ea.gain_next = gain_of(0);
-        ea.pss = pss + sb * L.sub_pss;
-        ea.rp = n_sub > 0 ? kMaxBlockRows : block_row_pitch(R);
-        ea.RL = RLC;
-        HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)ea.R * H * 2, [&] { return launch_embed_rows(ea, s); }));
-    }
-
-    // ---- one launch per stage
-    for (size_t i = 0; i < list.size(); ++i) {
-        const int kc = list[i].kc;
-        if (list[i].epi < 0 && n_sub > 0 && L.mfma_attn) {
-            // (the block attention kernel takes the whole macro block in one launch)
-            AttnArgs a = list[i].at;
-            a.rows = last * kMaxBlockRows + R;
-            a.sub_rows = kMaxBlockRows;
-            a.sub_q = L.sub_q;
-            a.sub_out_s = L.sub_as;
-            a.out_rows = RLC;
-            HIP_TRY(timed(x, SWIFT_KC_ATTN, (uint64_t)2 * KV * 2 * (pos0 + a.rows), [&] { return launch_attn_block(a, x->n_cu, s); }));
-        } else if (list[i].epi < 0) {
-            for (int sb = 0; sb <= last; ++sb) {
-                AttnArgs a = list[i].at;
-                a.rows = sub_rows(sb);
-                a.n_ctx += sb * kMaxBlockRows;
-                a.q += sb * L.sub_q;
-                a.q_s += sb * L.sub_q_s;
-                a.out_s += sb * L.sub_as;
-                int rc = block_attention(x, a, RLC);
-                if (rc) return rc;
-            }
-        } else if (n_sub > 0 && list[i].epi != EPI_LOGITS) {
-            // (sub-block strides: which buffers a launch reads and writes follows from its epilogue)
-            const MvArgs &m = list[i].mv;
-            const int epi = list[i].epi;
-            ma.in_s = kc == SWIFT_KC_OPROJ ? L.sub_as : kc == SWIFT_KC_DOWN ? L.sub_hs : L.sub_xs;
-            ma.pss = L.sub_pss;
-            ma.out_f32 = epi == EPI_QKV ? L.sub_q : L.sub_x;
-            ma.out_s = epi == EPI_SWIGLU ? L.sub_hs : L.sub_xs;
-            ma.pss_out = L.sub_pss;
-            HIP_TRY(timed(x, kc, (uint64_t)m.O * m.K * 2, [&] { return launch_gemm(epi, m, ma, x->n_cu, x->gemm_rgw, s); }));
-        } else {
-            const MvArgs &m = list[i].mv;
-            const int epi = list[i].epi;
-            HIP_TRY(timed(x, kc, (uint64_t)m.O * m.K * 2,
-                          [&] { return launch_mv(epi, m, x->n_cu, x->tune_ks[kc], x->tune_wg[kc], s); }, true));
-        }
-    }
     if (want_logits) {
         ArgmaxArgs am{dptr<float>(x, L.logits), V, R, dptr<int32_t>(x, L.out_tok), dptr<float>(x, L.out_conf),
                       x->want_topk ? dptr<int32_t>(x, L.out_topk) : nullptr, kTopK};
