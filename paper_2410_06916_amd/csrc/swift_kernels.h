@@ -1,5 +1,5 @@
 // Launch interface between the C-ABI layer (swift_api.hip) and the gfx950 kernels
-// (swift_kernels.hip: storage-generic single-row path; swift_tiled.hip: bf16 tiled MFMA path).
+// (swift_kernels.hip: storage-generic path; swift_tiled.hip: bf16 tiled MFMA path).
 // Plain structs and functions; every launcher enqueues on the given stream and returns the
 // hipError_t of the launch.
 #pragma once

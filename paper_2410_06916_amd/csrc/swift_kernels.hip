@@ -1,8 +1,8 @@
-// gfx950 kernels of the draft / verify forward pass: storage-generic single-row projections,
+// gfx950 kernels of the draft / verify forward pass: storage-generic projections (fp32 models),
 // attention over the cache, arg-max/confidence, utilities.
 //
 // Every projection of the decoder is a weight-streaming pass: the weight matrix is read
-// from HBM exactly once with 128-bit loads, the activation vector lives in LDS, and the
+// with 128-bit loads, once for all rows of a workgroup, the activations live in LDS, and the
 // operation that follows the projection (rotation + cache append, SwiGLU, residual add)
 // runs in the same kernel on the finished dot products.  Wavefronts are 64 lanes wide;
 // one wavefront owns two output rows at a time so that the rows an epilogue needs

@@ -668,7 +668,7 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 // workgroup that arrives last at a counter adds the partials in split order (so the result does
 // not depend on arrival order) and runs the epilogue.
 //
-// CANON (exact layouts: verify blocks of up to 32 rows, 1-6 column blocks) reproduces the LDS-resident kernel
+// CANON (exact layouts: verify blocks of up to 32 rows, 2-6 column blocks) reproduces the LDS-resident kernel
 // bit for bit: the K range of a row group is cut into the same 8 slices of ceil(T/8) tiles, a slice is
 // accumulated from zero tile by tile, a workgroup covers a group of 8, 4, 2 or 1 whole slices (mv_slice_group: a
 // function of the matrix alone, not of the row count) and adds their sums per term in slice order, combines
