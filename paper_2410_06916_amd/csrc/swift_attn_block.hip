@@ -180,7 +180,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(AttnArgs am, int chunk) {
             const float mn = fmaxf(m_run, mx);
             const float ms = mn == -INFINITY ? 0.f : mn;  // nothing live yet: every exponential below is 0
             const float mc = ms * c_exp;
-            const float corr = __builtin_amdgcn_exp2f(fmaf(m_run, c_exp, -mc));
+            // (not 2^(c m_run - mc): the rounding of mc would stay in it, a factor beside 1 in every chunk with the same sign)
+            const float corr = __builtin_amdgcn_exp2f((m_run - ms) * c_exp);
             float ps = 0.f;
             bf16x8 phi[2], plo[2];
 #pragma unroll

@@ -304,6 +304,57 @@ def test_block_attention_on_matrix_cores_against_oracle(oracle_lib, case):
     g.close()
 
 
+def test_long_prompt_attention_keeps_early_slots_weights():
+    """A prompt's last row over 128 chunks of 64 cache slots, the largest score in the first chunk and the running
+    maximum unchanged ever after: the first chunk's weight may not drift with the number of chunks behind it.  32 heads
+    with largest scores of 2.4 .. 64; every number but the softmax is exact by construction (inputs +-1, no norm epsilon,
+    keys and values that bf16 holds, a rotation by less than 1e-4), so a head's output gives the weight p of the 64 slots
+    of token 0 (two values v = +-1: output 2 p - 1) and is compared with its value in closed form.
+
+    Tolerance on the odds p / (1 - p), relative: probabilities as two bf16 terms, 2^-17 on either side; two fp32 sums
+    (weights, weighted values) over 128 chunks, 128 x 2^-24 each; the fp32 exponent of a score of up to 64 (92 in base 2),
+    half a step of 2^-17 x ln 2."""
+    import paper_2410_06916_amd as P
+    H, n_heads, d, n, n_first = 256, 32, 128, 8192, 64
+    shape = si.ModelShape("attn-odds", 1, H, n_heads, 4, d, 64, 64, "bf16", 0.0, 1.0e9)
+    Q, KV = n_heads * d, 4 * d
+    bf = torch.bfloat16
+    w = {name: torch.zeros(dims, dtype=torch.float32 if kind == "gain" else bf) for name, dims, kind in si.tensor_specs(shape)}
+    for name in w:
+        if name.endswith("norm"):
+            w[name].fill_(1.0)
+    w["embed"].fill_(1.0)             # coordinate 1 tells token 0 from the others
+    w["embed"][1:, 1] = -1.0
+    k_common, k_token, q_token = 22.5, 6.75, 4.0
+    for h in range(n_heads):          # raw score of head h: h x 22.5 +- 27
+        w["l0.wq"][h * d + 63, 0] = float(h)
+        w["l0.wq"][h * d + 62, 0] = q_token
+    for h in range(4):
+        w["l0.wk"][h * d + 63, 0] = k_common
+        w["l0.wk"][h * d + 62, 1] = k_token
+        w["l0.wv"][h * d, 1] = 1.0
+    for h in range(n_heads):          # head h's output onto coordinate 100 + h, 64-fold
+        w["l0.wo"][100 + h, h * d] = 64.0
+        w["lm_head"][h, 100 + h] = 1.0
+    w["lm_head"][n_heads, 99] = 1.0   # an untouched coordinate: the final norm's scale
+    assert Q == w["l0.wo"].shape[1] and KV == w["l0.wk"].shape[0]
+    g = P.SwiftModel(shape, n + 8)
+    g.load_weights(w)
+    prompt = np.ones(n, np.int32)
+    prompt[:n_first] = 0
+    g.prefill(prompt)
+    lg = g.read_logits((n - 1) % 64).astype(np.float64)
+    g.close()
+    out = (lg[:n_heads] / lg[n_heads] - 1.0) / 64.0
+    odds = (1.0 + out) / (1.0 - out)
+    want = n_first / (n - n_first) * np.exp(2.0 * q_token * k_token / np.sqrt(d))
+    err = np.abs(odds / want - 1.0)
+    tol = 2 * 2.0 ** -17 + 2 * 128 * 2.0 ** -24 + 0.5 * 2.0 ** -17 * np.log(2.0)
+    # (reading them off: the output as two bf16 terms, then 1 + 64 x output as two bf16 terms, 2^-17 each)
+    tol += 2 * 2.0 ** -17 * (1.0 / 64.0 + 2.0 * np.abs(out).max())
+    assert err.max() <= tol, (tol, err)
+
+
 @pytest.mark.parametrize("blocks", ["macro-block", "64-row-blocks"])
 def test_prefill_at_7b_width_against_oracle(oracle_lib, blocks):
     """The 7B workload's widths (hidden 4096, 32 heads of 128, ffn 11008), two layers deep, a 200-token prompt.
