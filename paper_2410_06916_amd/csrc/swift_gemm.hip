@@ -43,35 +43,23 @@ constexpr int kNormFloats = 2 * 16 * 64;  // scratch of gemm_norm_scales
 
 // RMSNorm scales of the workgroup's two sub-blocks: rs[64 wn + r].  Thread (wn, q, r4) adds the partials q, q + 16,
 // .. of rows 4 r4 .. 4 r4 + 3 of sub-block wn (16 loads of 16 bytes in flight at a time); then one thread per row
-// adds the sixteen sums in order.  The first 256 partials (hidden <= 4096: all of them) are requested by
-// gemm_norm_load, ahead of the ring's first stages, so that they do not queue behind 140 KB of tiles; the scales are
-// read by the epilogue only, so no barrier here waits for more than LDS.
-struct GemmNorm {
-    f32x4 v[16];
-};
-__device__ inline const float *gemm_norm_base(const MvArgs &a, const MacroArgs &ma, int sub0) {
-    const int tid = threadIdx.x;
-    return a.pss + (size_t)min(sub0 + (tid >> 8), ma.S - 1) * ma.pss + 4 * (tid & 15);
-}
-__device__ inline void gemm_norm_load(const MvArgs &a, const float *p, int p0, GemmNorm &n) {
-    const int q = (threadIdx.x >> 4) & 15;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const int i = p0 + q + 16 * u;
-        const f32x4 v = *(const f32x4 *)(p + (size_t)min(i, a.n_pss - 1) * a.rp);
-        n.v[u] = i < a.n_pss ? v : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-}
-__device__ inline void gemm_norm_finish(const MvArgs &a, const float *p, GemmNorm &n, float *rs, float *scratch) {
-    const int tid = threadIdx.x, r4 = tid & 15, q = (tid >> 4) & 15, wn = tid >> 8;
+// adds the sixteen sums in order.  The partials are read ahead of the ring's first stages, so that they do not queue
+// behind 140 KB of tiles; the scales are read by the epilogue only, so no barrier here waits for more than LDS.
+__device__ inline f32x4 gemm_norm_sum(const MvArgs &a, const MacroArgs &ma, int sub0) {
+    const int tid = threadIdx.x, q = (tid >> 4) & 15;
+    const float *p = a.pss + (size_t)min(sub0 + (tid >> 8), ma.S - 1) * ma.pss + 4 * (tid & 15);
     f32x4 ss = {0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0;;) {
+    for (int p0 = 0; p0 < a.n_pss; p0 += 256) {
+        f32x4 v[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) ss += n.v[u];
-        p0 += 256;
-        if (p0 >= a.n_pss) break;
-        gemm_norm_load(a, p, p0, n);
+        for (int u = 0; u < 16; ++u) v[u] = *(const f32x4 *)(p + (size_t)min(p0 + q + 16 * u, a.n_pss - 1) * a.rp);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) ss += p0 + q + 16 * u < a.n_pss ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    return ss;
+}
+__device__ inline void gemm_norm_scales(const MvArgs &a, const f32x4 &ss, float *rs, float *scratch) {
+    const int tid = threadIdx.x, r4 = tid & 15, q = (tid >> 4) & 15, wn = tid >> 8;
     *(f32x4 *)(scratch + (wn * 16 + q) * 64 + 4 * r4) = ss;
     lds_barrier();
     if (tid < 128) {
@@ -298,7 +286,7 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     constexpr int TRG = WM * RGW;                 // row groups of the workgroup's tile
     constexpr int A_BYTES = TRG * 1024;
     constexpr int ST_BYTES = A_BYTES + WN * 8192;
-        constexpr int NST = kRingBytes / ST_BYTES;   // stages of the ring
+    constexpr int NST = kRingBytes / ST_BYTES;   // stages of the ring
     constexpr int NP = TRG + 8 * WN;              // 1 KB pieces of a stage
     constexpr int PW = (NP + 7) / 8;              // pieces a wavefront copies per stage (PW - 1 past the remainder)
     constexpr bool kNorm = EPI != EPI_RESID;      // the input is a normalised one: scales from the producer's partial sums
@@ -426,23 +414,18 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     // register set, and the matrix cores work on stage t meanwhile.  `slot`: byte offset of stage t's ring slot.
     // The loop body is kept free of conditions: a wavefront issues at most one scalar instruction every few cycles,
     // and whatever the loop needs beyond the matrix instructions is paid for in full.
+    f32x4 norm_ss = {0.f, 0.f, 0.f, 0.f};
     auto pipeline = [&](auto FULL) {
         constexpr auto ALL = std::integral_constant<int, 0>();
         constexpr auto AHEAD = std::integral_constant<int, NST - 2>();  // stages t + 2 .. t + NST - 1 may stay in flight
-        GemmNorm nv;
-        const float *np = nullptr;
-        if (kNorm) {
-            np = gemm_norm_base(a, ma, sub0);
-            gemm_norm_load(a, np, 0, nv);
-        }
         if (TF >= NST) {
 #pragma unroll
             for (int t = 0; t < NST; ++t) issue(t * ST_BYTES, FULL);
-            if (kNorm) gemm_norm_finish(a, np, nv, rs, nscratch);
+            if (kNorm) gemm_norm_scales(a, norm_ss, rs, nscratch);
             wait_all_but(std::integral_constant<int, NST - 1>(), FULL);
         } else {
             for (int t = 0; t < TF; ++t) issue(t * ST_BYTES, FULL);
-            if (kNorm) gemm_norm_finish(a, np, nv, rs, nscratch);
+            if (kNorm) gemm_norm_scales(a, norm_ss, rs, nscratch);
             if (TF == 0) return;
             wait_all_but(ALL, FULL);
         }
@@ -487,6 +470,7 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
             if (t + 1 < TF) drain(o1, o0);
         }
     };
+    if (kNorm) norm_ss = gemm_norm_sum(a, ma, sub0);
     if (full_share)
         pipeline(std::true_type());
     else

@@ -1141,9 +1141,9 @@ __global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
     }
 }
 
-// Steps in flight per wavefront: what 256 registers hold beside the accumulators.
+// Steps in flight per wavefront: what 256 registers hold beside the accumulators (3 x 6 tiles: two steps, three spill).
 constexpr int mvr_steps(int ncb, int rg) {
-    const int n = ((rg * ncb >= 8 ? 184 : 200) - 4 * rg * ncb) / (4 * (rg + ncb));
+    const int n = ((rg * ncb >= 18 ? 144 : rg * ncb >= 8 ? 184 : 200) - 4 * rg * ncb) / (4 * (rg + ncb));
     return n > 10 ? 10 : n;
 }
 

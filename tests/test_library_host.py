@@ -137,6 +137,35 @@ def test_new_entry_points_reject_null_contexts_without_a_device(P):
     assert [L.swift_topk_width(p) for p in (0.01, 0.5, 0.51, 0.8, 0.81, 0.95, 0.96, 1.0)] == [10, 10, 5, 5, 3, 3, 1, 1]
 
 
+def test_projection_kernels_hold_their_windows_in_registers(P):
+    """The streaming kernels keep what is in flight in registers: no instance of them spills one (the compiler's own count
+    in the library's gfx950 code objects; each object is a bundle entry: count, then offset, size and name of each)."""
+    import shutil
+    import struct
+    import subprocess
+    import tempfile
+    from paper_2410_06916_amd import build as hip_build
+    readelf = shutil.which("llvm-readelf", path="/opt/rocm/llvm/bin")
+    if readelf is None:
+        pytest.skip("no llvm-readelf")
+    data, at, spills = open(hip_build.lib_path(), "rb").read(), 0, {}
+    while (at := data.find(b"__CLANG_OFFLOAD_BUNDLE__", at)) >= 0:
+        p = at + 32
+        for _ in range(struct.unpack_from("<Q", data, at + 24)[0]):
+            off, size, n = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + n]:
+                with tempfile.NamedTemporaryFile(suffix=".co") as f:
+                    f.write(data[at + off:at + off + size])
+                    f.flush()
+                    notes = subprocess.run([readelf, "--notes", f.name], capture_output=True, text=True, check=True).stdout
+                spills.update((k, int(v)) for k, v in re.findall(r"\.name:\s+(_Z\S+).*?\.vgpr_spill_count:\s+(\d+)", notes, re.S))
+            p += 24 + n
+        at += 24
+    kernels = {k: v for k, v in spills.items() if "k_mvR" in k or "k_gemm" in k}
+    assert len(kernels) > 100
+    assert not [k for k, v in kernels.items() if v], {k: v for k, v in kernels.items() if v}
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
