@@ -345,6 +345,14 @@ int swift_debug_attn_path(swift_ctx *ctx, int rows, int tree, char *out, int cap
 #define SWIFT_KC_OTHER 6    /* embedding gather, arg-max finalisation */
 #define SWIFT_KC_COUNT 7
 
+/* Names the kernel instance a projection (kernel_class: SWIFT_KC_QKV, _OPROJ, _GATEUP, _DOWN or _LMHEAD) of a bf16 model
+ * takes in a block of `rows` rows on a device of n_cu compute units, e.g. "mvR<columns 2, row groups 3, steps 8, rounds 2>".
+ * exact != 0: draft, decode, verify and tree blocks (up to SWIFT_MAX_BLOCK rows); else prefill and candidate-evaluation
+ * blocks of up to 64 rows.  out: host, capacity bytes, NUL-terminated.  Needs no device; for tests that must know what they
+ * covered. */
+int swift_debug_projection_path(const swift_model_config *cfg, int n_cu, int kernel_class, int rows, int exact, char *out,
+                                int capacity);
+
 /* Overrides the launch shape of the tiled single-row projection kernel of one class: wavefronts
  * that share a 16-row group (0 = automatic, else 1, 2, 4 or 8) and workgroups (0 = automatic).
  * Results do not depend on it bit for bit only within one setting; it exists for tuning runs. */

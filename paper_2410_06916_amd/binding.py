@@ -105,6 +105,7 @@ def lib():
     L.swift_debug_tune.argtypes = [vp, C.c_int, C.c_int, C.c_int]
     L.swift_debug_prefill.argtypes = [vp, C.c_int, C.c_int]
     L.swift_debug_attn_path.argtypes = [vp, C.c_int, C.c_int, C.c_char_p, C.c_int]
+    L.swift_debug_projection_path.argtypes = [C.POINTER(ModelConfig), C.c_int, C.c_int, C.c_int, C.c_int, C.c_char_p, C.c_int]
     L.swift_profile_class.argtypes = [vp, C.c_int]
     L.swift_profile_read.argtypes = [vp, C.POINTER(C.c_int64), C.POINTER(C.c_double), C.POINTER(C.c_uint64)]
     _lib = L
@@ -145,6 +146,14 @@ def match_prefix(draft: Sequence[int], target: Sequence[int]) -> int:
     d = np.ascontiguousarray(draft, np.int32)
     t = np.ascontiguousarray(target, np.int32)
     return lib().swift_match_prefix(_p(d, C.c_int32), _p(t, C.c_int32), min(d.size, t.size))
+
+
+def projection_path(cfg: ModelConfig, name: str, rows: int, exact: bool = True, n_cu: int = 256) -> str:
+    """Name of the kernel instance projection `name` takes in a block of `rows` rows (see swift_debug_projection_path)."""
+    buf = C.create_string_buffer(96)
+    _chk(lib().swift_debug_projection_path(C.byref(cfg), n_cu, KERNEL_CLASSES[name], rows, 1 if exact else 0, buf, 96),
+         "swift_debug_projection_path")
+    return buf.value.decode()
 
 
 def pass_bytes(cfg: ModelConfig, skip: Optional[np.ndarray], n_ctx: int, rows: int = 1) -> int:

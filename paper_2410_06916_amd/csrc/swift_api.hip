@@ -1608,6 +1608,33 @@ extern "C" int swift_debug_attn_path(swift_ctx *x, int rows, int tree, char *out
     return SWIFT_OK;
 }
 
+extern "C" int swift_debug_projection_path(const swift_model_config *cfg, int n_cu, int kernel_class, int rows, int exact,
+                                          char *out, int capacity) {
+    if (!out || capacity < 1 || n_cu < 1 || rows < 1 || rows > (exact ? kMaxRows : kMaxBlockRows))
+        return fail(SWIFT_EINVAL, "bad argument");
+    int rc = swift_check_config(cfg);
+    if (rc) return rc;
+    if (cfg->dtype != SWIFT_BF16) return fail(SWIFT_EINVAL, "fp32 models have one projection kernel");
+    const int H = cfg->hidden, Q = cfg->n_q_heads * cfg->head_dim, KV = cfg->n_kv_heads * cfg->head_dim, F = cfg->ffn;
+    MvArgs m{};
+    switch (kernel_class) {
+        case SWIFT_KC_QKV: m.O = Q + 2 * KV, m.K = H, m.n_rg = m.O / 16; break;
+        case SWIFT_KC_OPROJ: m.O = H, m.K = Q, m.n_rg = (H + 15) / 16; break;
+        case SWIFT_KC_GATEUP: m.O = 2 * F, m.K = H, m.n_rg = (F + 7) / 8; break;
+        case SWIFT_KC_DOWN: m.O = H, m.K = F, m.n_rg = (H + 15) / 16; break;
+        case SWIFT_KC_LMHEAD: m.O = cfg->vocab, m.K = H, m.n_rg = (cfg->vocab + 15) / 16; break;
+        default: return fail(SWIFT_EINVAL, "not a projection");
+    }
+    m.T = (m.K + 31) / 32;
+    m.R = rows;
+    m.RL = block_row_layout(rows, exact != 0);
+    m.rp = block_row_pitch(rows);
+    m.head_dim = cfg->head_dim;
+    m.part_capacity = make_layout(*cfg).mv_part_capacity;
+    mv_path_name(m, n_cu, out, capacity);
+    return SWIFT_OK;
+}
+
 extern "C" int swift_debug_tune(swift_ctx *x, int kernel_class, int waves_per_row_group, int workgroups) {
     if (!x || kernel_class < 0 || kernel_class >= SWIFT_KC_COUNT) return fail(SWIFT_EINVAL, "bad argument");
     if (!(waves_per_row_group == 0 || waves_per_row_group == 1 || waves_per_row_group == 2 ||

@@ -288,6 +288,8 @@ hipError_t launch_mv(int epilogue, MvArgs a, int n_cu, int ks_override, int wg_o
 // Row-group-splits of `part` (16 * R floats each) that launch_mv writes for a block of up to 16 rows
 // described by `a` (0: the launch splits K inside workgroups only and uses neither `part` nor `counters`).
 int mv_split_slots(const MvArgs &a, int n_cu);
+// Writes the name of the kernel instance launch_mv takes for `a` into out; returns the length snprintf reports.  Host only.
+int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity);
 
 // Prompt macro blocks: up to kMacroSub consecutive sub-blocks of 64 rows (the last one may hold fewer) go through a
 // projection in one launch.  Each sub-block has buffers of its own, laid out as for a 64-row block in the bulk

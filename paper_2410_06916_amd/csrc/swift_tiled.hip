@@ -3,6 +3,7 @@
 // activation fits in LDS (draft pass, plain decoding, short verify blocks), k_mvR and k_mvN blocks of up to
 // 32 and 64 rows (longer verify blocks, prefill, candidate evaluation).
 #include <math.h>
+#include <stdio.h>
 
 #include <algorithm>
 
@@ -948,6 +949,40 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS, int rpw) {
     if (tid == 0) a.counters[blockIdx.x] = 0;
 }
 
+// How k_mvN cuts a matrix over workgroups: grid (row blocks, K parts), tiles per part, wavefronts with work.
+struct MvnPlan {
+    int grid_x, ksp, TS, rpw;
+};
+static MvnPlan mvn_plan(const MvArgs &a, int n_cu, int RG, bool canon) {
+    MvnPlan p;
+    const int n_rb = (a.n_rg + 8 * RG - 1) / (8 * RG);
+    // split K over workgroups until about one workgroup per compute unit exists
+    // (never more workgroups than compute units: one workgroup fills a compute unit's registers,
+    // so a partial second round would double the kernel's duration)
+    int ksp = n_cu / n_rb;
+    if (ksp < 1) ksp = 1;
+    if (ksp > 8) ksp = 8;
+    if (canon) {
+        p.TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
+    } else {
+        while (ksp > 1 && ((a.T + ksp - 1) / ksp < 8 || (int64_t)a.n_rg * ksp > a.part_capacity)) --ksp;
+        p.TS = (a.T + ksp - 1) / ksp;
+    }
+    p.ksp = (a.T + p.TS - 1) / p.TS;  // workgroups whose K range holds tiles
+    // With fewer workgroups than compute units, a workgroup takes fewer row groups, so that every compute unit
+    // gets about the same share: what bounds these launches is what ONE compute unit can take in (weights plus
+    // its copy of the activation), not the chip's HBM rate.
+    p.rpw = 8;
+    p.grid_x = n_rb;
+    if (n_rb * p.ksp < n_cu) {
+        p.rpw = (a.n_rg * p.ksp + RG * n_cu - 1) / (RG * n_cu);
+        if (p.rpw < 4) p.rpw = 4;
+        if (p.rpw > 8) p.rpw = 8;
+        p.grid_x = (a.n_rg + p.rpw * RG - 1) / (p.rpw * RG);
+    }
+    return p;
+}
+
 template <int EPI, int NCB, int CT, int RG, bool DMA, bool CANON>
 static hipError_t launch_mvN_t(const MvArgs &a, int n_cu, hipStream_t s) {
     static bool attr_set = false;
@@ -960,32 +995,8 @@ static hipError_t launch_mvN_t(const MvArgs &a, int n_cu, hipStream_t s) {
     const int NC = block_terms(a.RL) * layout_rows(a.RL);
     const size_t buf2 = 2 * (size_t)4 * CT * NC * 16;
     const size_t lds = 16 + (buf2 > (size_t)NCB * 8192 ? buf2 : (size_t)NCB * 8192) + 320 + 4096;
-    const int n_rb = (a.n_rg + 8 * RG - 1) / (8 * RG);
-    // split K over workgroups until about one workgroup per compute unit exists
-    // (never more workgroups than compute units: one workgroup fills a compute unit's registers,
-    // so a partial second round would double the kernel's duration)
-    int ksp = n_cu / n_rb;
-    if (ksp < 1) ksp = 1;
-    if (ksp > 8) ksp = 8;
-    int TS;
-    if (CANON) {
-        TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
-    } else {
-        while (ksp > 1 && ((a.T + ksp - 1) / ksp < 8 || (int64_t)a.n_rg * ksp > a.part_capacity)) --ksp;
-        TS = (a.T + ksp - 1) / ksp;
-    }
-    ksp = (a.T + TS - 1) / TS;  // workgroups whose K range holds tiles
-    // With fewer workgroups than compute units, a workgroup takes fewer row groups, so that every compute unit
-    // gets about the same share: what bounds these launches is what ONE compute unit can take in (weights plus
-    // its copy of the activation), not the chip's HBM rate.
-    int rpw = 8, grid_x = n_rb;
-    if (n_rb * ksp < n_cu) {
-        rpw = (a.n_rg * ksp + RG * n_cu - 1) / (RG * n_cu);
-        if (rpw < 4) rpw = 4;
-        if (rpw > 8) rpw = 8;
-        grid_x = (a.n_rg + rpw * RG - 1) / (rpw * RG);
-    }
-    return launch_maybe_timed(k_mvN<EPI, NCB, CT, RG, DMA, CANON>, dim3(grid_x, ksp), dim3(512), lds, s, a, TS, rpw);
+    const MvnPlan p = mvn_plan(a, n_cu, RG, CANON);
+    return launch_maybe_timed(k_mvN<EPI, NCB, CT, RG, DMA, CANON>, dim3(p.grid_x, p.ksp), dim3(512), lds, s, a, p.TS, p.rpw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1150,10 +1161,14 @@ constexpr int mvr_steps(int ncb, int rg) {
 // A second depth for slices that the first one cuts badly (slots past the end of a slice load its last tile again): 16, 20,
 // 32 and 43 tiles are 2 x 8, 2 x 10 or 5 x 4, 4 x 8 and 5 x 9 or 11 x 4.
 constexpr int mvr_other_steps(int ns) { return ns > 8 ? 8 : ns == 8 ? 7 : ns > 4 ? 4 : ns == 3 ? 2 : ns; }
-// Steps of a slice of n tiles as walked, with the better of the two depths.
-static int mvr_slots(int n, int ncb, int rg) {
+// The better of the two depths for a slice of n tiles, and the steps of the slice as walked with it.
+static int mvr_depth(int n, int ncb, int rg) {
     const int a = mvr_steps(ncb, rg), b = mvr_other_steps(a);
-    return std::min((n + a - 1) / a * a, (n + b - 1) / b * b);
+    return (n + a - 1) / a * a <= (n + b - 1) / b * b ? a : b;
+}
+static int mvr_slots(int n, int ncb, int rg) {
+    const int d = mvr_depth(n, ncb, rg);
+    return (n + d - 1) / d * d;
 }
 
 template <int EPI, int NCB, int RG, int NS>
@@ -1175,29 +1190,39 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
     a.n_wg = (units + a.S - 1) / a.S;
     a.kgroup = mv_slice_group(a, n_cu);
     constexpr int NS = mvr_steps(NCB, RG), NS2 = mvr_other_steps(NS);
-    const int n = (a.T + 7) / 8, slots = (n + NS - 1) / NS * NS, slots2 = (n + NS2 - 1) / NS2 * NS2;
-    return slots <= slots2 ? launch_mvR_ns<EPI, NCB, RG, NS>(a, s) : launch_mvR_ns<EPI, NCB, RG, NS2>(a, s);
+    return mvr_depth((a.T + 7) / 8, NCB, RG) == NS ? launch_mvR_ns<EPI, NCB, RG, NS>(a, s) : launch_mvR_ns<EPI, NCB, RG, NS2>(a, s);
 }
 
-// Row groups per workgroup round for k_mvR, or 0: k_mvN is the faster kernel.  Both sides by costs fitted to launches of
-// the 7B, 13B and 70B shapes (us, kernel durations).  k_mvR: 5 for the start and end of a launch, then what a compute unit
-// takes in -- weights and its own reading of B, slots past the end of a slice among them -- at 45-70 KB per us; a row-group
-// count that leaves units idle in its last round pays for whole rounds.  k_mvN: 7.5, the weights at 6.1 TB/s, 3 where it
-// splits K over workgroups, 8.5 % more per column block past the second.  (9 rows, 7B, k_mvN -> k_mvR: q|k|v 27.8 -> 20.6,
-// o_proj 15.6 -> 10.6, gate/up 37.9 -> 32.9, down_proj 26.0 -> 23.9, LM head 47.2 -> 45.9; 15 rows: 28.8 -> 22.4, 18.2 ->
-// 12.3, 40.5 -> 35.6, 29.3 -> 28.6; 31 rows: 38.5 -> 31.3, 22.4 -> 17.6, and k_mvN 53.8 against 63.0 for gate/up; 70B, one
-// row, down_proj 83 -> 72.)
+// Row groups per workgroup round for k_mvR, or 0: k_mvN is the faster kernel.  Both sides by what one compute unit has to
+// walk, in us per k tile, fitted to 709 sets of launch durations of both kernels (rows 1-32 of both layouts, seven widths
+// from 1024 to 8192, matrices of 6 to 1300 MB).  c: column blocks, 0.4 x those computed + 0.6 x the columns' own share.
+//   k_mvR   3.7 + rounds x 8 slices x steps of a slice as walked x (weights of 1, 2 or 3 row groups + c columns of B)
+//   k_mvN   6.1 (+ 2.8 + 0.96 c where K is split over workgroups) + rounds x tiles (a slice's last chunk of eight, where it
+//           is partial, counts half of what it lacks) x (row groups + c columns), by the root of the share of units in use
+// The picks add up to 0.3 % more than the faster kernel of every set; the worst ones are launches of 7-13 us and, at the
+// 7B, 13B and 70B widths, o_proj of 3-5 rows (70B, 27.5 against 25) and down_proj of 6-9 (13B, 36.9 against 34.0).
+// (us, k_mvN / the best k_mvR.  7B: 9 rows q|k|v 27.8 / 20.8, o_proj 15.3 / 10.4, gate/up 37.8 / 32.9, down_proj 26.0 /
+// 23.8; 15 rows down_proj 29.0 / 29.6; 31 rows q|k|v 37.9 / 30.3, gate/up 52.2 / 51.5, down_proj 35.2 / 41.3, LM head
+// 60.0 / 74.9.  70B, 16 rows: LM head 90.3 / 97.7.  13B, 32 bulk rows: q|k|v 40.9 / 45.2.)
 static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     if (ncb < 1 || ncb > 6 || a.R > kMaxRows) return 0;
-    static const double kRate[3][6] = {{57, 61, 64, 66, 68, 70}, {45, 48, 52, 52, 52, 52}, {45, 47, 49.5, 48.5, 47, 46}};
-    const double mb = (double)a.n_rg * a.T / 1024.0;
-    double best = (7.5 + mb * 1.0486 / 6.1 + (mv_slice_group(a, n_cu) < 8 ? 3.0 : 0.0)) * (1.0 + 0.085 * (ncb - 2));
-    if (ncb == 1) best = 1e30;  // (activations too deep for k_mv1)
+    static const double kWeights[3] = {0.0213, 0.0467, 0.0603}, kColumns[3] = {0.0147, 0.0178, 0.0226};
+    const bool bulk = (a.RL & kBulkLayout) != 0;
+    const double cols = 0.4 * ncb + 0.6 * (block_terms(a.RL) * layout_rows(a.RL)) / 16.0;
+    double best = 1e30;
     int rg = 0;
+    if (ncb > 1) {  // (one column block: activations too deep for k_mv1, which k_mvN does not take)
+        const MvnPlan p = mvn_plan(a, n_cu, 1, !bulk);
+        const int n = bulk ? p.TS : (a.T + 7) / 8;  // tiles of a slice
+        const double walked = p.TS + 0.5 * (p.TS / n) * ((n + 7) / 8 * 8 - n);
+        const int wgs = p.grid_x * p.ksp, rounds = (wgs + n_cu - 1) / n_cu;
+        best = 6.05 + (p.ksp > 1 ? 2.83 + 0.964 * cols : 0.0) +
+               rounds * walked * (p.rpw * 0.0349 + cols * (bulk ? 0.0212 : 0.0284)) * sqrt((double)wgs / (rounds * n_cu));
+    }
     for (int c = 1; c <= 3; ++c) {
         if (ncb > 4 && c == 2) continue;
         const int units = (a.n_rg + c - 1) / c, S = (units + n_cu - 1) / n_cu;
-        const double us = 5.0 + (double)S * 8 * mvr_slots((a.T + 7) / 8, ncb, c) * (c + ncb) / kRate[c - 1][ncb - 1];
+        const double us = 3.68 + (double)S * 8 * mvr_slots((a.T + 7) / 8, ncb, c) * (kWeights[c - 1] + cols * kColumns[c - 1]);
         if (us < best) {
             best = us;
             rg = c;
@@ -1206,9 +1231,26 @@ static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     return rg;
 }
 
+// Small blocks (in their own exact layout) whose whole activation fits in LDS take the single-pass kernel.
+static bool mv_takes_mv1(const MvArgs &a, int ks_override) {
+    return !(a.RL & kBulkLayout) && a.R <= kMvSmallRows && ks_override != 16 && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds;
+}
+static int mv_column_blocks(const MvArgs &a) { return (block_terms(a.RL) * layout_rows(a.RL) + 15) / 16; }
+
+int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity) {
+    if (mv_takes_mv1(a, 0)) return snprintf(out, (size_t)capacity, "mv1<rows %d>", a.R);
+    const int ncb = mv_column_blocks(a), rg = mvr_row_groups(a, n_cu, ncb);
+    if (rg == 0) return snprintf(out, (size_t)capacity, "mvN<columns %d, parts %d>", ncb, mvn_plan(a, n_cu, 1, !(a.RL & kBulkLayout)).ksp);
+    const int units = (a.n_rg + rg - 1) / rg;
+    return snprintf(out, (size_t)capacity, "mvR<columns %d, row groups %d, steps %d, rounds %d>", ncb, rg,
+                    mvr_depth((a.T + 7) / 8, ncb, rg), (units + n_cu - 1) / n_cu);
+}
+
 int mv_split_slots(const MvArgs &a, int n_cu) {
     if (a.RL & kBulkLayout) return a.part_capacity;  // (bulk layouts: not needed by callers)
-    if (a.R <= kMvSmallRows && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds) return 0;  // LDS-resident kernel
+    if (mv_takes_mv1(a, 0)) return 0;
+    // (what k_mvN needs, also where k_mvR, which needs none, is the faster kernel: what a caller's scratch has to hold does
+    // not hang on a rule about speed)
     const int TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
     const int ksp = (a.T + TS - 1) / TS;
     return ksp > 1 ? ksp * a.n_rg : 0;
@@ -1220,13 +1262,11 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
     if (a.R < 1 || a.R > kMaxBlockRows || (a.rp != 16 && a.rp != 64) || a.R > a.rp || a.R > lrows ||
         (bulk ? (lrows != 32 && lrows != 64) : (lrows != a.R || lrows > kMaxRows)))
         return hipErrorInvalidValue;
-    // small blocks (in their own exact layout) whose whole activation fits in LDS take the single-pass kernel
-    if (!bulk && a.R <= kMvSmallRows && ks_override != 16 && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds)
-        return launch_mv1(epi, a, n_cu, ks_override, wg_override, s);
+    if (mv_takes_mv1(a, ks_override)) return launch_mv1(epi, a, n_cu, ks_override, wg_override, s);
     // exact layouts (up to 32 rows): 2-6 column blocks of three-term columns, K chunks of 8 tiles, the fixed
     // summation order; bulk layouts of 32 / 64 rows (prefill, candidate evaluation): 4 / 8 column blocks of
     // two-term columns
-    const int ncb = (block_terms(a.RL) * lrows + 15) / 16;
+    const int ncb = mv_column_blocks(a);
     if (const int rg = mvr_row_groups(a, n_cu, ncb)) {
 #define SWIFT_MVR_RG(E, N)                                          \
     case N:                                                         \

@@ -166,6 +166,45 @@ def test_projection_kernels_hold_their_windows_in_registers(P):
     assert not [k for k, v in kernels.items() if v], {k: v for k, v in kernels.items() if v}
 
 
+_R = "mvR<columns %d, row groups %d"
+# (kernel class, rows) -> the kernel that was the faster one by 4 % and more, each launch timed on the MI355X
+_FASTER_PROJECTION = {
+    "7b": {("qkv", 9): _R % (2, 3), ("oproj", 9): _R % (2, 1), ("gateup", 9): _R % (2, 3), ("down", 9): _R % (2, 1),
+           ("down", 11): _R % (3, 1), ("qkv", 31): _R % (6, 3), ("oproj", 31): _R % (6, 1), ("down", 31): "mvN", ("lmhead", 31): "mvN",
+           ("lmhead", 19): "mvN", ("down", 5): _R % (1, 1)},
+    "13b": {("qkv", 9): _R % (2, 2), ("oproj", 11): _R % (3, 2), ("oproj", 16): _R % (3, 2), ("oproj", 21): _R % (4, 2),
+            ("gateup", 9): _R % (2, 2), ("lmhead", 9): _R % (2, 2), ("qkv", 24): "mvN", ("gateup", 24): "mvN",
+            ("down", 24): "mvN", ("down", 5): _R % (1, 2)},
+    "70b": {("qkv", 9): _R % (2, 3), ("qkv", 24): _R % (5, 3), ("qkv", 31): _R % (6, 3), ("gateup", 9): _R % (2, 3),
+            ("down", 9): _R % (2, 2), ("oproj", 16): _R % (3, 2), ("lmhead", 15): "mvN", ("lmhead", 16): "mvN",
+            ("down", 31): "mvN", ("gateup", 31): "mvN", ("oproj", 31): "mvN"},
+}
+# the same for candidate-evaluation and prompt blocks of 17-32 rows (two terms per row: four column blocks)
+_FASTER_PROJECTION_BULK = {
+    "7b": {"qkv": _R % (4, 3), "oproj": _R % (4, 1), "lmhead": "mvN"},
+    "13b": {"qkv": "mvN", "oproj": _R % (4, 2), "gateup": "mvN", "down": "mvN", "lmhead": "mvN"},
+    "70b": {"qkv": _R % (4, 3), "oproj": _R % (4, 2), "down": "mvN", "lmhead": "mvN"},
+}
+
+
+@pytest.mark.parametrize("width", sorted(_FASTER_PROJECTION))
+def test_projection_kernel_of_a_block_is_the_faster_one(P, width):
+    """The rule that chooses between the two block projection kernels, against launch durations of both (7B, 13B and 70B
+    widths, 256 compute units; profiles/block_projection_sweep.txt holds all of them)."""
+    from paper_2410_06916_amd import binding as B
+    cfg = B.make_config({"7b": si.LLAMA2_7B, "13b": si.LLAMA2_13B, "70b": si.LLAMA2_70B}[width], 777)
+    for (name, rows), want in _FASTER_PROJECTION[width].items():
+        got = B.projection_path(cfg, name, rows)
+        assert got.startswith(want), (name, rows, got)
+    for name, want in _FASTER_PROJECTION_BULK[width].items():
+        got = B.projection_path(cfg, name, 32, exact=False)
+        assert got.startswith(want), (name, "bulk", got)
+    with pytest.raises(P.SwiftError):
+        B.projection_path(cfg, "attn", 4)
+    with pytest.raises(P.SwiftError):
+        B.projection_path(cfg, "qkv", 33)
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
