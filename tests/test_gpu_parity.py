@@ -992,6 +992,54 @@ def test_block_rows_equal_single_rows_bit_for_bit(case):
     g.close()
 
 
+# projection kernel instances that the bit-for-bit test at the other widths is meant to reach, by block rows
+_EXPECTED_PROJECTION_PATHS = {
+    "13b": {("qkv", 10): "mvR<columns 2, row groups 2, steps 10, rounds 2>", ("qkv", 17): "mvR<columns 4, row groups 2, steps 4, rounds 2>",
+            ("oproj", 11): "mvR<columns 3, row groups 2, steps 7, rounds 1>", ("gateup", 6): "mvR<columns 2, row groups 2, steps 10, rounds 4>",
+            ("qkv", 22): "mvN<columns 5, parts 2>", ("down", 32): "mvN<columns 6, parts 4>",
+            ("down", 2): "mvR<columns 1, row groups 2, steps 8, rounds 1>", ("lmhead", 17): "mvR<columns 4, row groups 3, steps 4, rounds 3>"},
+    "70b": {("down", 1): "mvR<columns 1, row groups 2, steps 8, rounds 1>", ("down", 16): "mvR<columns 3, row groups 2, steps 8, rounds 1>",
+            ("gateup", 17): "mvR<columns 4, row groups 3, steps 4, rounds 5>", ("qkv", 26): "mvR<columns 5, row groups 3, steps 2, rounds 1>",
+            ("qkv", 27): "mvR<columns 6, row groups 3, steps 2, rounds 1>", ("oproj", 21): "mvR<columns 4, row groups 2, steps 4, rounds 1>",
+            ("lmhead", 16): "mvN<columns 3, parts 1>", ("qkv", 3): "mvR<columns 1, row groups 3, steps 8, rounds 1>"},
+    # a hidden size past the first 256 norm partials and not a multiple of 256: ragged slices, every depth shallow
+    "wide-ragged": {("qkv", 32): "mvR<columns 6, row groups 1, steps 6, rounds 1>", ("qkv", 26): "mvN<columns 5, parts 8>",
+                    ("qkv", 21): "mvR<columns 4, row groups 1, steps 9, rounds 1>", ("down", 22): "mvR<columns 5, row groups 3, steps 3, rounds 1>",
+                    ("oproj", 27): "mvR<columns 6, row groups 3, steps 2, rounds 1>", ("down", 11): "mvR<columns 3, row groups 2, steps 7, rounds 1>"},
+}
+
+
+@pytest.mark.parametrize("width", ["13b", "70b", "wide-ragged"])
+def test_block_rows_equal_single_rows_bit_for_bit_at_other_widths(width):
+    """The bit-for-bit property of the verify blocks where the projections take other instances than at the 7B width: one
+    layer of the 13B and 70B widths and of a narrow model with hidden > 4096 (norm partials past the first 256), row counts
+    on either side of every column-block boundary of the three-term layout (16 columns: 5.33 rows)."""
+    import paper_2410_06916_amd as P
+    from paper_2410_06916_amd import binding as B
+    if width == "wide-ragged":
+        shape = si.ModelShape("wide-ragged", 1, 4200, 4, 4, 128, 1400, 1000, "bf16", 1e-5)
+    else:
+        shape = _WIDTHS[width].with_layers(1)
+    g = P.SwiftModel(shape, 80)
+    cfg = B.make_config(shape, 80)
+    for (name, rows), want in _EXPECTED_PROJECTION_PATHS[width].items():
+        assert B.projection_path(cfg, name, rows) == want, (name, rows, B.projection_path(cfg, name, rows))
+    g.load_weights(si.iter_weights(shape, 6, "cuda:0", gain_jitter=0.1))
+    n0, toks = 20, si.uniform_ids(44, 32, shape.vocab)
+    toks[0] = g.prefill(si.uniform_ids(43, n0, shape.vocab))
+    single = []
+    for i in range(32):
+        g.rollback(n0 + i, int(toks[i]))
+        single.append(g.verify([toks[i]], True)[1][0])
+        g.accept()
+    for rows in (2, 3, 5, 6, 10, 11, 16, 17, 21, 22, 26, 27, 32):
+        g.rollback(n0, int(toks[0]))
+        _, lg = g.verify(toks[:rows], True)
+        for r in range(rows):
+            assert np.array_equal(lg[r], single[r]), (width, rows, r, np.abs(lg[r] - single[r]).max())
+    g.close()
+
+
 def test_long_context_uses_split_attention(oracle_lib):
     """A context beyond the single-workgroup attention range (1536 slots): the split kernel and
     its merge, for one row and for a block, with a ragged last chunk."""
