@@ -481,8 +481,18 @@ static AttnPlan attn_plan(const AttnArgs &a, int n_cu) {
     if (want > a.max_split) want = a.max_split;
     if (want < 1) want = 1;
     p.chunk = (a.max_seq + want - 1) / want;
-    // (a short cache: at least 128 slots, so that up to there a context is one range and needs no merge launch)
-    if (a.max_seq <= 1024 && p.chunk < 128) p.chunk = 128;
+    // ... but no shorter than what costs about as much to walk as the merge launch that a second range brings (3-5 us): 128
+    // slots, fewer where a step covers few of them (fp32, heads of 128: eight a step) or a lane serves eight query heads.
+    // us a decode call of four layers over 60 / 250 slots, shortest ranges of 16, 32, 64, 128 slots: fp32, heads of 64, one
+    // query head per kv head 126, 129, 112, 117 / 135, 131, 126, 118; five rows 143, 147, 145, 136 / 153, 154, 147, 140;
+    // heads of 128, one 172, 176, 167, 167 / 178, 178, 180, 190; five rows 215, 215, 236, 245 / 231, 224, 240, 285; four
+    // 184, 198, 210, 208 / 201, 206, 226, 276; five rows 201, 218, 242, 234 / 215, 222, 244, 298.
+    int least = 128;
+    if (VEC == 4 && d == 128)
+        least = p.group >= 4 ? 16 : 32;
+    else if (VEC == 4 && d >= 32 && p.group == 8)
+        least = 64;
+    if (p.chunk < least) p.chunk = least;
     p.chunk = (p.chunk + gran - 1) / gran * gran;
     p.n_split = (ctx + p.chunk - 1) / p.chunk;  // <= want <= max_split
     // Block rows that share their key/value loads in one workgroup (the more, the less cache traffic; bounded

@@ -1040,6 +1040,37 @@ def test_block_rows_equal_single_rows_bit_for_bit_at_other_widths(width):
     g.close()
 
 
+@pytest.mark.parametrize("heads,kv,d,caps", [(8, 8, 128, (900, 1100)), (8, 2, 128, (300, 1000)), (8, 1, 128, (300, 1000)),
+                                             (8, 1, 64, (900, 1100)), (16, 2, 32, (900, 1100)), (4, 4, 64, (900, 1100))])
+def test_fp32_attention_ranges_do_not_hang_on_a_capacity_limit(oracle_lib, heads, kv, d, caps):
+    """How many cache slots a workgroup of the row-at-a-time attention walks follows from what a slot costs there, not from
+    the capacity being short: up to where 64 ranges of the shortest length fill it, a cache's capacity (either side of 1024
+    slots) does not show in the bits of any row (blocks of one, five and twelve rows over one and several ranges), and the
+    rows agree with the oracle."""
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape(f"ranges-{heads}-{kv}-{d}", 1, 256, heads, kv, d, 344, 384, "fp32", 1e-6)
+    weights = hp.shaped_weights(shape, seed=5)
+    ids = si.uniform_ids(91, 300, shape.vocab)
+    got = []
+    for cap in caps:
+        g = P.SwiftModel(shape, cap)
+        g.load_weights(weights)
+        out = []
+        for ctx in (20, 63, 130, 260):
+            first = g.prefill(ids[:ctx])
+            out += [g.verify(np.concatenate([[first], ids[260:259 + rows]]).astype(np.int32), True)[1] for rows in (1, 5, 12)]
+        got.append(out)
+        g.close()
+    o = oracle_lib.Oracle(shape, 300, threads=4)
+    o.set_weights(weights)
+    first = o.prefill(ids[:260])[0]
+    want = o.verify(np.concatenate([[first], ids[260:271]]).astype(np.int32), True)[1]
+    o.close()
+    assert np.all(hp.rel_err_rowmax(got[0][-1], want) <= TOL["fp32"])
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 def test_long_context_uses_split_attention(oracle_lib):
     """A context beyond the single-workgroup attention range (1536 slots): the split kernel and
     its merge, for one row and for a block, with a ragged last chunk."""
