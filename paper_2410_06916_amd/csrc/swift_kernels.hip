@@ -34,7 +34,8 @@ __device__ inline float block_sum_256(float v, float *red /* >= 4 floats of LDS 
 // ------------------------------------------------------------------------------------------
 // A workgroup takes RB consecutive rows (blockIdx.y): a weight loaded once feeds all of them, and a block is one launch
 // instead of one per row.  What bounds the small models that run here is the launch (3-4 us each, whatever it computes):
-// a 5-row verification of the tiny model takes 27 launches instead of 135, a 32-row prompt 27 instead of 860.  A row's
+// a 5-row verification of the tiny model takes 23 launches (27 where its context spans several ranges and the attention
+// merges them) instead of 135, a 32-row prompt 23 instead of 860.  A row's
 // products are added in the same order whatever RB is (lane l takes 16-byte chunks l, l + 64, .., then a butterfly), so
 // its result does not depend on the rows it shares a pass with.
 template <typename T, int EPI, int RB>
@@ -219,12 +220,8 @@ __global__ void k_embed(EmbedArgs a) {
 }
 
 hipError_t launch_embed(int dtype, const EmbedArgs &a, hipStream_t s) {
-    if (a.R < 1 || a.R > kMaxBlockRows) return hipErrorInvalidValue;
-    const dim3 grid((a.H + 255) / 256, a.R);
-    if (dtype == F32)
-        hipLaunchKernelGGL(k_embed<F32T>, grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_embed<BF16T>, grid, dim3(256), 0, s, a);
+    if (dtype != F32 || a.R < 1 || a.R > kMaxBlockRows) return hipErrorInvalidValue;  // (bf16 models: launch_embed_rows)
+    hipLaunchKernelGGL(k_embed<F32T>, dim3((a.H + 255) / 256, a.R), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
