@@ -32,7 +32,7 @@ __device__ inline bf16x8 pack_bf16x8(const uint16_t (&v)[8]) {
 // What bounds it: a wavefront's 80 matrix instructions per 64-slot chunk (1280 clocks) and the vector arithmetic around them
 // (softmax, conversions) hardly overlap, ~3500 clocks a chunk.  Hence hardware bf16 conversions, one fused multiply-add
 // per exponent, masks only in the chunk where a range ends, contiguous loads elsewhere and 16-byte stores: 7B, 512-row
-// macro blocks, 27 us + 10 us of merging -> 24 us at 512 slots, 69 + 13 -> 64 at 2048.
+// macro blocks, 27 us + 10 us of merging -> 22 us at 512 slots, 69 + 13 -> 64 at 2048.
 //
 // Lane layout of v_mfma_f32_16x16x32_bf16 (C = A B): lane = 16 g + col.
 //   A (16 x 32): row col,    k = 8 g .. 8 g + 7        B (32 x 16): column col, k = 8 g .. 8 g + 7

@@ -396,8 +396,8 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
 
     // The order of a step's instructions: two matrix instructions, the copies, then the next stage's operand reads one by
     // one between the other matrix instructions.  (All reads in front, as it was: they queue up at LDS, 88 KB per step
-    // of a compute unit, and hold the matrix cores up; all behind: LDS and the matrix cores take turns.  7B, 512 rows:
-    // gate/up 184 -> 163 us, q|k|v 117 -> 107.)
+    // of a compute unit, and hold the matrix cores up; all behind: LDS and the matrix cores take turns.  7B, 512 rows, this
+    // change alone: gate/up 184 -> 163 us, q|k|v 117 -> 107.)
     auto interleave = [&]() {
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x020, PW, 0);
