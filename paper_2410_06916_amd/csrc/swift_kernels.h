@@ -6,10 +6,17 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/swift.h"
+
 namespace swift {
 
 constexpr int kMaxRows = 32;       // rows of one verify block or token tree (SWIFT_MAX_BLOCK)
 constexpr int kMaxBlockRows = 64;  // rows of one prefill block
+// The static scratch array of swift_verify_static: [arrival counters][split-K partial sums][attention partials].
+constexpr size_t kStaticCounterBytes = 4096 * 4;
+constexpr int kStaticPartSlots = 8192;  // row-group-splits of kMaxRows rows, as the arena's area holds for such blocks
+constexpr size_t kStaticPartBytes = (size_t)kStaticPartSlots * 16 * kMaxRows * 4;  // 16 MiB
+constexpr size_t kStaticAttnBytes = SWIFT_STATIC_SCRATCH_BYTES - kStaticCounterBytes - kStaticPartBytes;
 // How the split activations of a block are laid out: a code that holds the rows the layout is pitched for and
 // how many bf16 terms an fp32 activation is split into.
 //  * exact layouts (draft, verify and tree blocks of up to kMaxRows rows; any block of up to 16 rows): pitched for

@@ -489,6 +489,10 @@ static AttnPlan attn_plan(const AttnArgs &a, int n_cu) {
         least = p.group >= 4 ? 16 : 32;
     else if (VEC == 4 && d >= 32 && p.group == 8)
         least = 64;
+    // (many query heads: up to 128 slots, so that the partial results of a block of kMaxRows rows over a short cache -- 1024
+    // slots -- fit what swift_verify_static has for them)
+    const int fit = (int)((kStaticAttnBytes - 256) / ((size_t)kMaxRows * a.n_q_heads * (4 * d + 8)));  // ranges
+    least = std::max(least, std::min(128, (a.max_seq + std::max(fit, 1) - 1) / std::max(fit, 1)));
     if (p.chunk < least) p.chunk = least;
     p.chunk = (p.chunk + gran - 1) / gran * gran;
     p.n_split = (ctx + p.chunk - 1) / p.chunk;  // <= want <= max_split

@@ -91,3 +91,20 @@ def test_static_scratch_verify_against_oracle_and_limits(oracle_lib):
         g.verify_static([g.pending, wide.vocab])      # the argument checks are swift_verify's
     assert e.value.code == -1
     g.close()
+
+
+@pytest.mark.parametrize("heads,kv", [(32, 4), (64, 8), (46, 23)])
+def test_static_scratch_holds_full_blocks_of_fp32_models_over_short_caches(heads, kv):
+    """fp32 models take the row-at-a-time attention, whose shortest ranges follow from what a slot costs: with many query
+    heads they still leave the partial results of a 32-row block over a cache of up to 1024 slots in the static array."""
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape(f"static-{heads}", 1, 256, heads, kv, 128, 256, 512, "fp32", 1e-6)
+    g = P.SwiftModel(shape, 1000)
+    g.load_weights(si.iter_weights(shape, 2, "cuda:0"))
+    t = g.prefill(si.uniform_ids(3, 900, shape.vocab))
+    block = np.concatenate([[t], si.uniform_ids(4, 31, shape.vocab)]).astype(np.int32)
+    _, want = g.verify(block, True)
+    g.rollback(900, t)
+    _, got = g.verify_static(block, True)
+    assert np.array_equal(got, want)
+    g.close()
