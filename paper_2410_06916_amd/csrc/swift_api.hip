@@ -487,9 +487,12 @@ int block_attention(swift_ctx *x, const AttnArgs &at, int RLC) {
 //
 // n_sub > 0: a prompt macro block instead: n_sub sub-blocks of kMaxBlockRows rows, the last one with R rows, at
 // positions pos0 .. (tokens holds all their rows).  Every projection is one launch of the blocked matrix product
-// over all sub-blocks; attention, the embedding and the LM head (last sub-block only: results land in rows
+// over all sub-blocks; the embedding and the LM head (last sub-block only: results land in rows
 // [0, R)) go sub-block by sub-block.  Bulk layouts; no tree.  With reuse_kv (a candidate-evaluation window of more
 // than one sub-block) the caller asks for every sub-block's predictions afterwards (macro_sub_logits).
+// Without it (a prompt), nothing but the cache and the last sub-block's logits is left of the pass.  Past the last attention
+// sublayer's keys and values no row meets another one, so from there on the pass goes on with the last sub-block alone
+// (through the block kernels), or, without logits, ends.
 int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, const uint8_t *skip, bool want_logits,
                         bool reuse_kv, const TreeRows *tree, bool exact, int n_sub = 0) {
     if (n_sub > 0 && (tree || exact || n_sub > kMacroSub)) return fail(SWIFT_EINVAL, "bad macro block");
@@ -563,10 +566,18 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
         HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)ea.R * H * 2, [&] { return launch_embed_rows(ea, s); }));
     }
 
+    // The stage from which on a prompt's macro block is its last sub-block only (7B, 512 rows: the last layer 207 us instead of
+    // 388; 3990 rows in eight macro blocks: 60 us for all but the last one).
+    size_t tail_stage = stages.size();
+    bool tail = false;
+    if (n_sub > 0 && !reuse_kv)
+        for (size_t i = 0; i < stages.size(); ++i)
+            if (stages[i].kind == 0) tail_stage = i;
+
     // ---- one launch per stage, issued as soon as its arguments stand: the device starts on the first one while the host
     // prepares the others
     auto run_mv = [&](int kc, int epi, const MvArgs &m) -> int {
-        if (n_sub > 0 && epi != EPI_LOGITS) {
+        if (n_sub > 0 && epi != EPI_LOGITS && !tail) {
             // (sub-block strides: which buffers a launch reads and writes follows from its epilogue)
             ma.in_s = kc == SWIFT_KC_OPROJ ? L.sub_as : kc == SWIFT_KC_DOWN ? L.sub_hs : L.sub_xs;
             ma.pss = L.sub_pss;
@@ -584,6 +595,11 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
         if (n_sub > 0 && L.mfma_attn) {
             // (the block attention kernel takes the whole macro block in one launch)
             AttnArgs a = at;
+            if (tail) {
+                a.out_rows = RLC;
+                HIP_TRY(timed(x, SWIFT_KC_ATTN, (uint64_t)2 * KV * 2 * (a.n_ctx - 1 + R), [&] { return launch_attn_block(a, x->n_cu, s); }));
+                return SWIFT_OK;
+            }
             a.rows = last * kMaxBlockRows + R;
             a.sub_rows = kMaxBlockRows;
             a.sub_q = L.sub_q;
@@ -592,6 +608,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             HIP_TRY(timed(x, SWIFT_KC_ATTN, (uint64_t)2 * KV * 2 * (pos0 + a.rows), [&] { return launch_attn_block(a, x->n_cu, s); }));
             return SWIFT_OK;
         }
+        if (tail) return block_attention(x, at, RLC);
         for (int sb = 0; sb <= last; ++sb) {
             AttnArgs a = at;
             a.rows = sub_rows(sb);
@@ -608,9 +625,32 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
         const int l = stages[i].layer;
         const LayerOff &y = L.layers[l];
         const float *gnext = gain_of(i + 1);
+        if (i == tail_stage) {
+            // keys and values of all rows: the row groups behind the query heads'
+            MvArgs m = base_args(y.wqkv + tiled_bytes(Q / 16, H), 2 * KV, H, 2 * KV / 16);
+            m.head0 = c.n_q_heads;
+            m.in_s = xs;
+            m.pss = pss;
+            m.n_pss = n_pss;
+            m.kcache = kv_base(x, l, 0);
+            m.vcache = kv_base(x, l, 1);
+            m.nb32 = L.nb32;
+            if (int rc = run_mv(SWIFT_KC_QKV, EPI_QKV, m)) return rc;
+            if (!want_logits) return SWIFT_OK;
+            // from here on: the last sub-block's rows and buffers
+            tail = true;
+            pos0 += last * kMaxBlockRows;
+            xf += last * L.sub_x;
+            qf += last * L.sub_q;
+            xs += last * L.sub_xs;
+            as_ += last * L.sub_as;
+            hs += last * L.sub_hs;
+            pss += last * L.sub_pss;
+        }
         if (stages[i].kind == 0) {
-            // (reuse_kv: the query heads' row groups only; they come first in the fused matrix)
-            MvArgs m = reuse_kv ? base_args(y.wqkv, Q, H, Q / 16) : base_args(y.wqkv, Q + 2 * KV, H, (Q + 2 * KV) / 16);
+            // (reuse_kv, tail: the query heads' row groups only; they come first in the fused matrix)
+            const bool q_only = reuse_kv || tail;
+            MvArgs m = q_only ? base_args(y.wqkv, Q, H, Q / 16) : base_args(y.wqkv, Q + 2 * KV, H, (Q + 2 * KV) / 16);
             m.in_s = xs;
             m.pss = pss;
             m.n_pss = n_pss;
@@ -629,7 +669,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             // the committed keys/values the attention launch will read: warmed into L2 by spare workgroups of
             // this launch (one-workgroup-per-head attention only: its workgroup-to-head mapping is what the
             // warm-up relies on)
-            if (!reuse_kv && attn_uses_head_kernel(c.max_seq, c.n_kv_heads)) {
+            if (!q_only && attn_uses_head_kernel(c.max_seq, c.n_kv_heads)) {
                 m.pf_heads = c.n_kv_heads;
                 m.pf_rows = pos0;
             }
@@ -688,8 +728,8 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
     // (macro block: the LM head reads the last sub-block's buffers)
     if (want_logits) {
         MvArgs m = base_args(L.lm_head, V, H, (V + 15) / 16);
-        m.in_s = xs + last * L.sub_xs;
-        m.pss = pss + last * L.sub_pss;
+        m.in_s = tail ? xs : xs + last * L.sub_xs;
+        m.pss = tail ? pss : pss + last * L.sub_pss;
         m.n_pss = n_pss;
         m.out_f32 = dptr<float>(x, L.logits);
         m.ld_out = V;

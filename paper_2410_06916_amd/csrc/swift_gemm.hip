@@ -201,7 +201,7 @@ __device__ inline void gemm_qkv(const MvArgs &a, int rg0, int lane, const float 
     for (int g = 0; g < RGW; ++g) {
         const int rg = rg0 + g;
         if (rg >= a.n_rg) break;  // (wavefront-uniform)
-        const int hh = rg / gph, e0 = 8 * (rg - hh * gph);  // head; first element of the row group's eight pairs
+        const int hl = rg / gph, hh = a.head0 + hl, e0 = 8 * (rg - hl * gph);  // head; first element of the row group's eight pairs
         f32x4 v[4];
         y(g, v);
 #pragma unroll

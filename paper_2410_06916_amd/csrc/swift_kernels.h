@@ -256,6 +256,7 @@ struct MvArgs {
     void *kcache, *vcache;   // QKV: this layer's [n_kv][max_seq][d]
     const float *cos_tab, *sin_tab;  // QKV: [max_seq][d/2]
     int pos0, max_seq, head_dim, n_q_heads, n_kv_heads;
+    int head0;             // QKV, blocked matrix product only: the fused matrix's head that row group 0 belongs to
     // QKV: row r's keys/values go to slot pos0 + r; it is rotated for position pos0 + r, or, for the rows
     // of a token tree (tree != 0, R <= kMaxRows), for position pos0 + depth[r] (the row's level)
     int tree;

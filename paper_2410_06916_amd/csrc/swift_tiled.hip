@@ -1260,7 +1260,7 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
     const bool bulk = (a.RL & kBulkLayout) != 0;
     const int lrows = layout_rows(a.RL);
     if (a.R < 1 || a.R > kMaxBlockRows || (a.rp != 16 && a.rp != 64) || a.R > a.rp || a.R > lrows ||
-        (bulk ? (lrows != 32 && lrows != 64) : (lrows != a.R || lrows > kMaxRows)))
+        (bulk ? (lrows != 32 && lrows != 64) : (lrows != a.R || lrows > kMaxRows)) || a.head0 != 0)
         return hipErrorInvalidValue;
     if (mv_takes_mv1(a, ks_override)) return launch_mv1(epi, a, n_cu, ks_override, wg_override, s);
     // exact layouts (up to 32 rows): 2-6 column blocks of three-term columns, K chunks of 8 tiles, the fixed

@@ -218,6 +218,34 @@ def test_prefill_depth_split_against_64_row_blocks(n_prompt):
 
 
 @pytest.mark.parametrize("shape", [
+    si.LLAMA2_7B.with_layers(2),
+    si.ModelShape("tail-gqa-d128", 2, 512, 8, 2, 128, 344, 384, "bf16", 1e-5),
+    si.ModelShape("tail-d32", 1, 96, 3, 3, 32, 136, 200, "bf16", 1e-5),   # attention row by row
+], ids=lambda s: s.name)
+def test_prefill_last_layer_of_macro_blocks_against_64_row_blocks(shape):
+    """Past the last attention sublayer's keys and values a macro block goes on with its last sub-block alone (or ends): every
+    row of the last sub-block and the last layer's cache slots of all sub-blocks against the same prompt in 64-row blocks,
+    which compute every row of every layer.  Bounds as for the depth split above."""
+    import paper_2410_06916_amd as P
+    g = P.SwiftModel(shape, 700)
+    g.load_weights(si.iter_weights(shape, 6, "cuda:0", gain_jitter=0.1))
+    for n_prompt in (65, 128, 205, 512, 513, 600):
+        prompt = si.uniform_ids(72, n_prompt, shape.vocab)
+        slots = sorted({0, 63, 64, n_prompt // 2, n_prompt - 1})
+        last_rows = n_prompt - (n_prompt - 1) // 64 * 64
+        res = []
+        for blocks in (-1, 0):
+            g.prefill_blocks(blocks)
+            g.prefill(prompt)
+            res.append((np.stack([g.read_logits(r) for r in range(last_rows)]),
+                        [x for p in slots for x in g.read_kv(shape.n_layers - 1, p)]))
+        assert np.all(hp.rel_err_rowmax(res[1][0], res[0][0]) <= 2e-3), n_prompt
+        for a, b in zip(res[0][1], res[1][1]):
+            assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(a) + 2.0 ** -10 * np.abs(a).max()), n_prompt
+    g.close()
+
+
+@pytest.mark.parametrize("shape", [
     si.TINY.with_layers(2),
     si.ModelShape("fp32-wide", 1, 2048, 16, 8, 128, 10240, 384, "fp32", 1e-6),   # 8 rows per workgroup, 4 in down_proj
     si.ModelShape("fp32-tall", 1, 256, 4, 4, 64, 32768, 384, "fp32", 1e-6),      # one row per workgroup in down_proj
