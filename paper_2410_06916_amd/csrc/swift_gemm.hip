@@ -3,12 +3,13 @@
 // that fills the cache before drafting starts; Section 3.1: the rows of a block are independent given the
 // cache, so any number of them may share one sweep over the weights).
 //
-// A workgroup of 8 wavefronts owns a tile of WM RGW 16-row groups of W times WN sub-blocks (WN x 64 rows x 2
-// bf16 terms = 128 WN columns; WM WN = 8, WN = 2 or 1).  Wavefront (wm, wn) = (w % WM, w / WM) owns RGW row groups
-// times the 128 columns of sub-block wn: 8 RGW accumulator tiles.  Both operands reach LDS straight from global
-// memory (no registers in between) through a ring of NST stages of one 32-deep k tile each: WM RGW weight tiles
+// A workgroup of 8 wavefronts owns a tile of WM RGW 16-row groups of W times WN / 2 sub-blocks (a sub-block: 64 rows x 2
+// bf16 terms = 128 columns; WM WN = 8, WN = 4 or 2).  Wavefront (wm, wn) = (w % WM, w / WM) owns RGW row groups
+// times 64 columns, half wn % 2 of sub-block wn / 2 (32 of its rows): 4 RGW accumulator tiles.  Both operands reach LDS straight
+// from global memory (no registers in between) through a ring of NST stages of one 32-deep k tile each: WM RGW weight tiles
 // of 1 KB (already in A-operand order) and the sub-blocks' 8 KB of split activations each (already in B-operand
-// order).  In step t the operands of stage t + 1 are read from LDS and stage t is multiplied while stages
+// order).  LDS moves 128 bytes a clock, and it is what bounds all but the 256 x 256 tile: a wavefront reads RGW + 4 KB a stage,
+// so its tile is kept near a square (as RGW / 2 row groups times 128 columns, it read RGW / 2 + 8 KB for the same products).  In step t the operands of stage t + 1 are read from LDS and stage t is multiplied while stages
 // t + 2 .. t + NST - 1 are on their way and stage t + NST is requested: what a compute unit can take in is
 // bounded by the bytes it keeps in flight, and the ring is what keeps most of LDS in flight.  One barrier per
 // stage.
@@ -74,22 +75,22 @@ __device__ inline void gemm_norm_scales(const MvArgs &a, const f32x4 &ss, float 
 // ------------------------------------------------------------------------------------------
 // epilogue
 // ------------------------------------------------------------------------------------------
-// It works on the accumulators where they are: a wavefront's 8 accumulator tiles of a row group hold column 16 cb + col
+// It works on the accumulators where they are: a wavefront's 4 accumulator tiles of a row group hold column 16 cb + col
 // = 2 r + term in lane column col, tile rows 4 kg .. 4 kg + 3 in the lane's four registers.  The two terms of a block
 // row sit in neighbouring lanes; the even lane keeps the even column blocks, the odd lane the odd ones, so that a lane
-// ends up with four block rows r(c) = 16 c + 8 (col & 1) + col / 2, c = 0 .. 3, and four consecutive tile rows of
-// each: 16-byte reads and writes of everything that is laid out along the rows of W, and no trip through LDS.  (The
+// ends up with two block rows r(c) = r0 + 16 c + 8 (col & 1) + col / 2, c = 0, 1 (r0: first row of the wavefront's half of
+// the sub-block), and four consecutive tile rows of each: 16-byte reads and writes of everything that is laid out along the rows of W, and no trip through LDS.  (The
 // block kernel's epilogue, which this replaces here, walks a row group in sixteen dependent rounds of a load, a few
 // LDS reads and 2-byte stores: about 10 us per row group and wavefront, 20-43 us per workgroup, a third of a 512-row
 // launch; now 4-9 us.)
 __device__ inline float dpp_xor1(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));  // quad_perm [1,0,3,2]
 }
-__device__ inline int gemm_row(int c, int col) { return 16 * c + 8 * (col & 1) + (col >> 1); }
-__device__ inline void fold_terms(const f32x4 (&acc)[8], int col, f32x4 (&y)[4]) {
+__device__ inline int gemm_row(int c, int col) { return 16 * c + 8 * (col & 1) + (col >> 1); }  // within the wavefront's 32 rows
+__device__ inline void fold_terms(const f32x4 (&acc)[4], int col, f32x4 (&y)[2]) {
     const bool odd = col & 1;
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float own = odd ? acc[2 * c + 1][i] : acc[2 * c][i], other = odd ? acc[2 * c][i] : acc[2 * c + 1][i];
@@ -115,152 +116,139 @@ __device__ inline void store_split(uint16_t *out_s, int chunk, int r, int kg, bo
     if (ok) *(u32x4 *)(out_s + ((size_t)chunk * 128 + 2 * r + (kg & 1)) * 8) = u;
 }
 
-// x += y for RGW row groups from rg0: the residual values and gains of all of them are requested together.
-// y(g, out): finished sums of row group g.
+// x += y for RGW row groups from rg0 and rows r0 .. r0 + 31: the residual values and gains of up to four of them are
+// requested together.  y(g, out): finished sums of row group g.
 template <int RGW, typename YF>
-__device__ inline void gemm_resid(const MvArgs &a, int rg0, int lane, YF y) {
+__device__ inline void gemm_resid(const MvArgs &a, int rg0, int r0, int lane, YF y) {
     const int col = lane & 15, kg = lane >> 4;
-    f32x4 x[RGW][4], gain[RGW];
 #pragma unroll
-    for (int g = 0; g < RGW; ++g) {
-        const int row = 16 * (rg0 + g) + 4 * kg;
-        const bool in = row < a.O;  // (O is a multiple of 8: a lane's four rows are all real or all padding)
-        gain[g] = in ? *(const f32x4 *)(a.gain_next + row) : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int g0 = 0; g0 < RGW; g0 += 4) {
+        constexpr int G = RGW < 4 ? RGW : 4;
+        f32x4 x[G][2], gain[G];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int r = gemm_row(c, col);
-            x[g][c] = in && r < a.R ? *(const f32x4 *)(a.out_f32 + (size_t)r * a.ld_out + row) : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < G && g0 + g < RGW; ++g) {
+            const int row = 16 * (rg0 + g0 + g) + 4 * kg;
+            const bool in = row < a.O;  // (O is a multiple of 8: a lane's four rows are all real or all padding)
+            gain[g] = in ? *(const f32x4 *)(a.gain_next + row) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int r = r0 + gemm_row(c, col);
+                x[g][c] = in && r < a.R ? *(const f32x4 *)(a.out_f32 + (size_t)r * a.ld_out + row) : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
         }
-    }
 #pragma unroll
-    for (int g = 0; g < RGW; ++g) {
-        const int rg = rg0 + g, row = 16 * rg + 4 * kg;
-        if (rg >= a.n_rg) break;  // (wavefront-uniform)
-        const bool in = row < a.O;
-        f32x4 v[4];
-        y(g, v);
+        for (int g = 0; g < G && g0 + g < RGW; ++g) {
+            const int rg = rg0 + g0 + g, row = 16 * rg + 4 * kg;
+            if (rg >= a.n_rg) return;  // (wavefront-uniform)
+            const bool in = row < a.O;
+            f32x4 v[2];
+            y(g0 + g, v);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int r = gemm_row(c, col);
-            const bool ok = in && r < a.R;
-            const f32x4 xn = x[g][c] + v[c];
-            if (ok) *(f32x4 *)(a.out_f32 + (size_t)r * a.ld_out + row) = xn;
-            store_split(a.out_s, 2 * rg + (kg >> 1), r, kg, ok, xn * gain[g]);
-            float ss = in ? (xn[0] * xn[0] + xn[1] * xn[1]) + (xn[2] * xn[2] + xn[3] * xn[3]) : 0.f;
-            ss += __shfl_xor(ss, 16, 64);
-            ss += __shfl_xor(ss, 32, 64);
-            if (kg == 0 && r < a.R) a.pss_out[(size_t)rg * a.rp + r] = ss;
+            for (int c = 0; c < 2; ++c) {
+                const int r = r0 + gemm_row(c, col);
+                const bool ok = in && r < a.R;
+                const f32x4 xn = x[g][c] + v[c];
+                if (ok) *(f32x4 *)(a.out_f32 + (size_t)r * a.ld_out + row) = xn;
+                store_split(a.out_s, 2 * rg + (kg >> 1), r, kg, ok, xn * gain[g]);
+                float ss = in ? (xn[0] * xn[0] + xn[1] * xn[1]) + (xn[2] * xn[2] + xn[3] * xn[3]) : 0.f;
+                ss += __shfl_xor(ss, 16, 64);
+                ss += __shfl_xor(ss, 32, 64);
+                if (kg == 0 && r < a.R) a.pss_out[(size_t)rg * a.rp + r] = ss;
+            }
         }
     }
 }
 
-// A lane's four block rows paired up: the first eight tile rows (gate, or the first half of rotary pairs) of c = 2 p +
-// (kg >> 1) end up in lo, the other eight of the same block row in hi (tile rows 4 (kg & 1) .. of each), scaled.
-__device__ inline void pair_halves(const f32x4 (&v)[4], const float (&sc)[4], int p, f32x4 &lo, f32x4 &hi) {
+// A lane's two block rows paired up: the first eight tile rows (gate, or the first half of rotary pairs) of c =
+// kg >> 1 end up in lo, the other eight of the same block row in hi (tile rows 4 (kg & 1) .. of each), scaled.
+__device__ inline void pair_halves(const f32x4 (&v)[2], const float (&sc)[2], f32x4 &lo, f32x4 &hi) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float x = v[2 * p][i] * sc[2 * p], y = v[2 * p + 1][i] * sc[2 * p + 1];
+        float x = v[0][i] * sc[0], y = v[1][i] * sc[1];
         swap32(x, y);
         lo[i] = x;
         hi[i] = y;
     }
 }
 
-__device__ inline void gemm_swiglu(const MvArgs &a, int rg, int lane, const float (&sc)[4], const f32x4 (&v)[4]) {
+__device__ inline void gemm_swiglu(const MvArgs &a, int rg, int r0, int lane, const float (&sc)[2], const f32x4 (&v)[2]) {
     const int col = lane & 15, kg = lane >> 4;
+    f32x4 ga, up, h;
+    pair_halves(v, sc, ga, up);
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        f32x4 ga, up, h;
-        pair_halves(v, sc, p, ga, up);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) h[i] = ga[i] / (1.0f + expf(-ga[i])) * up[i];
-        const int r = gemm_row(2 * p + (kg >> 1), col);
-        store_split(a.out_s, rg, r, kg, r < a.R && 16 * rg < a.O, h);
-    }
+    for (int i = 0; i < 4; ++i) h[i] = ga[i] / (1.0f + expf(-ga[i])) * up[i];
+    const int r = r0 + gemm_row(kg >> 1, col);
+    store_split(a.out_s, rg, r, kg, r < a.R && 16 * rg < a.O, h);
 }
 
 // Queries to fp32 rows, keys to their slots, values to the grouped layout: there, eight consecutive slots of an element
-// are one 16-byte unit, so the values cross the lanes through a wavefront's own 2.3 KB of LDS (vsh).
+// are one 16-byte unit, so the values cross the lanes through a wavefront's own 1.3 KB of LDS (vsh).
 template <int RGW, typename YF>
-__device__ inline void gemm_qkv(const MvArgs &a, int rg0, int lane, const float (&sc)[4], uint16_t *vsh, YF y) {
-    constexpr int VP = 64 + 8;  // pitch of an element's slots in vsh
+__device__ inline void gemm_qkv(const MvArgs &a, int rg0, int r0, int lane, const float (&sc)[2], uint16_t *vsh, YF y) {
+    constexpr int VP = 32 + 8;  // pitch of an element's slots in vsh
     const int col = lane & 15, kg = lane >> 4;
     const int d = a.head_dim, half = d >> 1, gph = half >> 3, nq = a.n_q_heads, nkv = a.n_kv_heads;
-    f32x4 cs[RGW][2], sn[RGW][2];
+    const int rl = gemm_row(kg >> 1, col), r = r0 + rl, pos = a.pos0 + r;  // the lane's block row, once paired up
+    const bool ok = r < a.R;
+    f32x4 cs[RGW], sn[RGW];
 #pragma unroll
     for (int g = 0; g < RGW; ++g) {
         const int rg = min(rg0 + g, a.n_rg - 1), i0 = 8 * (rg % gph) + 4 * (kg & 1);
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int r = min(gemm_row(2 * p + (kg >> 1), col), a.R - 1);
-            cs[g][p] = *(const f32x4 *)(a.cos_tab + (size_t)(a.pos0 + r) * half + i0);
-            sn[g][p] = *(const f32x4 *)(a.sin_tab + (size_t)(a.pos0 + r) * half + i0);
-        }
+        cs[g] = *(const f32x4 *)(a.cos_tab + (size_t)(a.pos0 + min(r, a.R - 1)) * half + i0);
+        sn[g] = *(const f32x4 *)(a.sin_tab + (size_t)(a.pos0 + min(r, a.R - 1)) * half + i0);
     }
 #pragma unroll
     for (int g = 0; g < RGW; ++g) {
         const int rg = rg0 + g;
         if (rg >= a.n_rg) break;  // (wavefront-uniform)
         const int hl = rg / gph, hh = a.head0 + hl, e0 = 8 * (rg - hl * gph);  // head; first element of the row group's eight pairs
-        f32x4 v[4];
+        f32x4 v[2], ya, yb;
         y(g, v);
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            f32x4 ya, yb;
-            pair_halves(v, sc, p, ya, yb);
-            const int r = gemm_row(2 * p + (kg >> 1), col);
-            const bool ok = r < a.R;
-            const int pos = a.pos0 + r;
-            if (hh < nq + nkv) {
-                const f32x4 qa = ya * cs[g][p] - yb * sn[g][p], qb = yb * cs[g][p] + ya * sn[g][p];
-                if (hh < nq) {
-                    float *qp = a.out_f32 + (size_t)r * a.ld_out + hh * d + e0 + 4 * (kg & 1);
-                    if (ok) {
-                        *(f32x4 *)qp = qa;
-                        *(f32x4 *)(qp + half) = qb;
-                    }
-                    continue;
+        pair_halves(v, sc, ya, yb);
+        if (hh < nq + nkv) {
+            const f32x4 qa = ya * cs[g] - yb * sn[g], qb = yb * cs[g] + ya * sn[g];
+            if (hh < nq) {
+                float *qp = a.out_f32 + (size_t)r * a.ld_out + hh * d + e0 + 4 * (kg & 1);
+                if (ok) {
+                    *(f32x4 *)qp = qa;
+                    *(f32x4 *)(qp + half) = qb;
                 }
-                ya = qa;
-                yb = qb;
+                continue;
             }
-            uint32_t ha[4], hb[4];
+            ya = qa;
+            yb = qb;
+        }
+        uint32_t ha[4], hb[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ha[i] = f32_to_bf16_rne(ya[i]);
+            hb[i] = f32_to_bf16_rne(yb[i]);
+        }
+        if (hh < nq + nkv || a.nb32 <= 0) {
+            const int head = hh < nq + nkv ? hh - nq : hh - nq - nkv;
+            uint16_t *plane = (uint16_t *)(hh < nq + nkv ? a.kcache : a.vcache);
+            const u32x4 u = join8(pack2(ha[0], ha[1]), pack2(ha[2], ha[3]), pack2(hb[0], hb[1]), pack2(hb[2], hb[3]));
+            if (ok) *(u32x4 *)(plane + ((size_t)head * a.max_seq + pos) * d + e0 + (kg & 1) * half) = u;
+        } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                ha[i] = f32_to_bf16_rne(ya[i]);
-                hb[i] = f32_to_bf16_rne(yb[i]);
+                vsh[(4 * (kg & 1) + i) * VP + rl] = (uint16_t)ha[i];
+                vsh[(8 + 4 * (kg & 1) + i) * VP + rl] = (uint16_t)hb[i];
             }
-            if (hh < nq + nkv || a.nb32 <= 0) {
-                const int head = hh < nq + nkv ? hh - nq : hh - nq - nkv;
-                uint16_t *plane = (uint16_t *)(hh < nq + nkv ? a.kcache : a.vcache);
-                const u32x4 u = join8(pack2(ha[0], ha[1]), pack2(ha[2], ha[3]), pack2(hb[0], hb[1]), pack2(hb[2], hb[3]));
-                if (ok) *(u32x4 *)(plane + ((size_t)head * a.max_seq + pos) * d + e0 + (kg & 1) * half) = u;
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    vsh[(4 * (kg & 1) + i) * VP + r] = (uint16_t)ha[i];
-                    vsh[(8 + 4 * (kg & 1) + i) * VP + r] = (uint16_t)hb[i];
-                }
-            }
-        }
-        if (hh >= nq + nkv && a.nb32 > 0) {
             // (one wavefront's LDS instructions are carried out in order: only the compiler has to keep it)
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             const int e = lane & 15, elem = e0 + (e & 7) + (e >> 3) * half;
+            const int u8 = 8 * (lane >> 4), ru = r0 + u8;  // eight slots from block row ru on
+            const u32x4 w = *(const u32x4 *)(vsh + e * VP + u8);
+            uint16_t *vp = (uint16_t *)a.vcache;
+            if ((a.pos0 & 7) == 0 && ru + 8 <= a.R) {
+                *(u32x4 *)(vp + kv_vt_index(hh - nq - nkv, a.nb32, d, a.pos0 + ru, elem)) = w;
+            } else {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int r = 8 * ((lane >> 4) + 4 * u);  // eight slots from block row r on
-                const u32x4 w = *(const u32x4 *)(vsh + e * VP + r);
-                uint16_t *vp = (uint16_t *)a.vcache;
-                if ((a.pos0 & 7) == 0 && r + 8 <= a.R) {
-                    *(u32x4 *)(vp + kv_vt_index(hh - nq - nkv, a.nb32, d, a.pos0 + r, elem)) = w;
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        if (r + i < a.R)
-                            vp[kv_vt_index(hh - nq - nkv, a.nb32, d, a.pos0 + r + i, elem)] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
-                }
+                for (int i = 0; i < 8; ++i)
+                    if (ru + i < a.R)
+                        vp[kv_vt_index(hh - nq - nkv, a.nb32, d, a.pos0 + ru + i, elem)] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -276,18 +264,18 @@ struct GemmPlan {
 
 template <int RGW>
 struct GemmOperands {
-    u32x4 av[RGW], bv[8];
+    u32x4 av[RGW], bv[4];
 };
 
 template <int EPI, int WN, int RGW>
 __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan pl) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int WM = 8 / WN;                    // wavefronts along the rows; WN sub-blocks side by side
+    constexpr int WM = 8 / WN, SB = WN / 2;       // wavefronts along the rows; SB sub-blocks side by side
     constexpr int TRG = WM * RGW;                 // row groups of the workgroup's tile
     constexpr int A_BYTES = TRG * 1024;
-    constexpr int ST_BYTES = A_BYTES + WN * 8192;
+    constexpr int ST_BYTES = A_BYTES + SB * 8192;
     constexpr int NST = kRingBytes / ST_BYTES;   // stages of the ring
-    constexpr int NP = TRG + 8 * WN;              // 1 KB pieces of a stage
+    constexpr int NP = TRG + 8 * SB;              // 1 KB pieces of a stage
     constexpr int PW = (NP + 7) / 8;              // pieces a wavefront copies per stage (PW - 1 past the remainder)
     constexpr bool kNorm = EPI != EPI_RESID;      // the input is a normalised one: scales from the producer's partial sums
     static_assert(NST >= 3 && NST * PW < 64, "ring depth against the load counter");
@@ -297,7 +285,7 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % WM, wn = wave / WM;
+    const int wm = wave % WM, wn = wave / WM, ws = wn >> 1, wh = wn & 1;  // its sub-block of the tile, its half of that
     // workgroup -> tile: the NN column tiles of a row tile (for tiles split in depth: of one of its parts) sit next to
     // each other on one die (consecutive workgroup ids go round the 8 dies)
     const int NN = pl.NN, id = (int)blockIdx.x < pl.n_full ? blockIdx.x : blockIdx.x - pl.n_full;
@@ -314,7 +302,7 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
         KSP = pl.ksp;
         TS = pl.TS;
     }
-    const int sub0 = WN * nt;
+    const int sub0 = SB * nt;
     const int T = a.T;
     const int col = lane & 15, kg = lane >> 4;
     const int t_lo = kz * TS, t_hi = min(T, t_lo + TS);  // (every part holds tiles: the launcher)
@@ -369,27 +357,27 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
         asm volatile("s_barrier" ::: "memory");
     };
 
-    f32x4 acc[RGW][8];
+    f32x4 acc[RGW][4];
 #pragma unroll
     for (int g = 0; g < RGW; ++g)
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int cb = 0; cb < 4; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const unsigned char *a_base = ring + (wm * RGW) * 1024 + lane * 16;
-    const unsigned char *b_base = ring + A_BYTES + wn * 8192 + (kg * 128 + col) * 16;
+    const unsigned char *b_base = ring + A_BYTES + ws * 8192 + (kg * 128 + 64 * wh + col) * 16;
     // (wavefronts without a sub-block -- an odd sub-block count leaves half of the last column tile empty -- go
     // through the motions on the last sub-block's data; their results are dropped)
     auto read_operands = [&](int slot_bytes, GemmOperands<RGW> &o) {
 #pragma unroll
         for (int g = 0; g < RGW; ++g) o.av[g] = *(const u32x4 *)(a_base + slot_bytes + g * 1024);
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb) o.bv[cb] = *(const u32x4 *)(b_base + slot_bytes + cb * 256);
+        for (int cb = 0; cb < 4; ++cb) o.bv[cb] = *(const u32x4 *)(b_base + slot_bytes + cb * 256);
     };
     auto multiply = [&](const GemmOperands<RGW> &o) {
 #pragma unroll
         for (int g = 0; g < RGW; ++g)
 #pragma unroll
-            for (int cb = 0; cb < 8; ++cb)
+            for (int cb = 0; cb < 4; ++cb)
                 acc[g][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, o.av[g]),
                                                                      __builtin_bit_cast(bf16x8, o.bv[cb]), acc[g][cb], 0, 0, 0);
     };
@@ -402,7 +390,7 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x020, PW, 0);
 #pragma unroll
-        for (int i = 0; i < RGW + 8; ++i) {
+        for (int i = 0; i < RGW + 4; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }
@@ -496,38 +484,38 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     }
 
     // ---- epilogue on the sub-block's own buffers
-    const int sub = min(sub0 + wn, ma.S - 1);
+    const int sub = min(sub0 + ws, ma.S - 1), r0 = 32 * wh;  // the wavefront's rows of it: r0 .. r0 + 31
     MvArgs as = a;
     as.R = sub == ma.S - 1 ? ma.rows_last : 64;
     as.pos0 = a.pos0 + 64 * sub;
     if (a.out_f32) as.out_f32 = a.out_f32 + (size_t)sub * ma.out_f32;
     if (a.out_s) as.out_s = a.out_s + (size_t)sub * ma.out_s;
     if (a.pss_out) as.pss_out = a.pss_out + (size_t)sub * ma.pss_out;
-    const bool wave_live = sub0 + wn < ma.S;
+    const bool wave_live = sub0 + ws < ma.S && r0 < as.R;
     const int rg0 = (mt * WM + wm) * RGW;
     auto finish = [&](auto y) {
         if (EPI == EPI_RESID) {
-            gemm_resid<RGW>(as, rg0, lane, y);
+            gemm_resid<RGW>(as, rg0, r0, lane, y);
         } else {
-            float sc[4];
+            float sc[2];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) sc[c] = rs[64 * wn + gemm_row(c, col)];
+            for (int c = 0; c < 2; ++c) sc[c] = rs[64 * ws + r0 + gemm_row(c, col)];
             if (EPI == EPI_QKV) {
-                gemm_qkv<RGW>(as, rg0, lane, sc, (uint16_t *)ring + (size_t)wave * 2048, y);
+                gemm_qkv<RGW>(as, rg0, r0, lane, sc, (uint16_t *)ring + (size_t)wave * 1024, y);
             } else {
 #pragma unroll
                 for (int g = 0; g < RGW; ++g) {
                     if (rg0 + g >= a.n_rg) break;
-                    f32x4 v[4];
+                    f32x4 v[2];
                     y(g, v);
-                    gemm_swiglu(as, rg0 + g, lane, sc, v);
+                    gemm_swiglu(as, rg0 + g, r0, lane, sc, v);
                 }
             }
         }
     };
     __syncthreads();  // the ring is no longer read (and the scales are visible where no step had a barrier)
     if (KSP == 1) {
-        if (wave_live) finish([&](int g, f32x4(&v)[4]) { fold_terms(acc[g], col, v); });
+        if (wave_live) finish([&](int g, f32x4(&v)[2]) { fold_terms(acc[g], col, v); });
         return;
     }
     // ---- depth split over workgroups.  Every wavefront publishes its results, the two terms combined, as
@@ -541,14 +529,14 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     const int rgt0 = rg0 - pl.MTF * TRG, n_rgt = a.n_rg - pl.MTF * TRG;  // row groups of the split tiles
     if (!wave_live) return;
     const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(a.part, 0, 0x7fffffff, 0x00020000);
-    auto part_off = [&](int k2, int g, int c) { return (uint32_t)((((k2 * n_rgt + rgt0 + g) * ma.S + sub) * 4 + c) * 1024 + lane * 16); };
+    auto part_off = [&](int k2, int g, int c) { return (uint32_t)((((k2 * n_rgt + rgt0 + g) * ma.S + sub) * 4 + 2 * wh + c) * 1024 + lane * 16); };
 #pragma unroll
     for (int g = 0; g < RGW; ++g) {
         if (rg0 + g >= a.n_rg) break;
-        f32x4 v[4];
+        f32x4 v[2];
         fold_terms(acc[g], col, v);
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < 2; ++c)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[c]), part, part_off(kz, g, c), 0, kDeviceScope);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -557,16 +545,16 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     if (lane == 0) arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__builtin_amdgcn_readfirstlane(arrived) != KSP - 1) return;
     asm volatile("" ::: "memory");
-    finish([&](int g, f32x4(&v)[4]) {
+    finish([&](int g, f32x4(&v)[2]) {
         if (rg0 + g >= a.n_rg) return;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(0, g, c), 0, kDeviceScope));
+        for (int c = 0; c < 2; ++c) v[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(0, g, c), 0, kDeviceScope));
         for (int k2 = 1; k2 < KSP; ++k2) {
-            f32x4 w[4];
+            f32x4 w[2];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) w[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(k2, g, c), 0, kDeviceScope));
+            for (int c = 0; c < 2; ++c) w[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(k2, g, c), 0, kDeviceScope));
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] += w[c];
+            for (int c = 0; c < 2; ++c) v[c] += w[c];
         }
     });
     if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -587,31 +575,35 @@ hipError_t launch_gemm_t(const MvArgs &a, const MacroArgs &ma, const GemmPlan &p
     return hipGetLastError();
 }
 
-// Tilings: code 1..4 = two sub-blocks side by side (workgroup tile 64 RGW rows x 256 columns, RGW = the code),
-// 5, 6 = one sub-block (tile 128 or 256 rows x 128 columns: for matrices with few rows, where the narrower tile
-// gives as many workgroups with fewer bytes to copy per product).
+// Tilings: wavefronts along the columns (4: two sub-blocks side by side, 2: one) and row groups per wavefront.  Codes 1..4:
+// workgroup tiles of 64, 128, 192, 256 rows x 256 columns; 5, 6: 128, 256 rows x 128 columns (for matrices with few rows, where
+// the narrower tile gives as many workgroups with fewer bytes to copy per product); 7..9: 96, 160, 224 rows x 256 columns; 10:
+// 192 rows x 128 columns.  The odd heights fit more matrices into whole rounds of workgroups: without them the fastest launches
+// of the sweep below add up to 1.8 % more.
 struct GemmTiling {
     int wn, rgw;
 };
-constexpr GemmTiling kGemmTilings[7] = {{0, 0}, {2, 1}, {2, 2}, {2, 3}, {2, 4}, {1, 1}, {1, 2}};
+constexpr int kGemmCodes = 10;
+constexpr GemmTiling kGemmTilings[kGemmCodes + 1] = {{0, 0}, {4, 2}, {4, 4}, {4, 6}, {4, 8}, {2, 2}, {2, 4}, {4, 3}, {4, 5}, {4, 7}, {2, 3}};
 
-// What a workgroup costs, measured with all compute units at work (7B and 13B shapes, 128-512 rows): us per k tile, and us
-// per workgroup for its start, the first stages' arrival and the epilogue.  Over 140 launches (five widths from 2048 to
-// 8192, 128-512 rows, profiles/blocked_product_sweep.txt) the shapes and splits chosen by them add up to 0.9 % more than the
-// fastest of each launch; single launches up to 16 % (13B, seven sub-blocks, gate/up).  (A 256 x 256 tile's matrix instructions take
-// 0.54 us per k tile at the ~1.9 GHz the part holds with all matrix cores busy.)
+// What a workgroup costs, measured with all compute units at work (7B, 13B and 70B shapes, 128-1024 rows): us per k tile, and us
+// per workgroup for its start, the first stages' arrival and the epilogue.  Over 105 launches (profiles/blocked_product_sweep.txt)
+// the shapes and splits chosen by them add up to 0.3 % more than the fastest of each launch; single launches up to 11 % (13B
+// q|k|v).  (A 256 x 256 tile's matrix instructions take 0.54 us per k tile at 1.9 GHz; a whole chip of them is held to less by
+// its power, 1.6 PFLOP/s.)
 struct GemmCost {
     double stage, fixed;
 };
-constexpr GemmCost kGemmCosts[7] = {{0, 0}, {0.305, 9.0}, {0.37, 10.0}, {0.54, 12.0}, {0.58, 14.0}, {0.26, 8.0}, {0.385, 9.0}};
-constexpr double kPartBytesPerUs = 1.3e6;  // publishing and adding the parts of tiles split in depth
+constexpr GemmCost kGemmCosts[kGemmCodes + 1] = {{0, 0},       {0.286, 5.4}, {0.393, 5.6}, {0.513, 8.3}, {0.670, 6.1}, {0.276, 4.6},
+                                                {0.425, 4.8}, {0.329, 5.0}, {0.445, 7.3}, {0.594, 6.7}, {0.347, 5.1}};
+constexpr double kPartBytesPerUs = 1.43e6;  // publishing and adding the parts of tiles split in depth
 
 // The plan of a tiling with its last tiles split ksp ways, and what it costs; false if the partial results would not fit
 // the scratch or a part would hold fewer than 16 k tiles.
 bool gemm_plan(const MvArgs &a, const MacroArgs &ma, int n_cu, int code, int ksp, GemmPlan &pl, double &us) {
-    const int wn = kGemmTilings[code].wn, rgw = kGemmTilings[code].rgw, trg = (8 / wn) * rgw;
+    const int wn = kGemmTilings[code].wn, rgw = kGemmTilings[code].rgw, trg = (8 / wn) * rgw, sb = wn / 2;
     pl.MT = (a.n_rg + trg - 1) / trg;
-    pl.NN = (ma.S + wn - 1) / wn;
+    pl.NN = (ma.S + sb - 1) / sb;
     const int per_round = std::max(1, n_cu / pl.NN / 8) * 8;  // row tiles of a round (whole dies)
     const int whole_rounds = pl.MT / per_round;
     pl.MTF = ksp == 1 ? pl.MT : whole_rounds * per_round;
@@ -620,10 +612,12 @@ bool gemm_plan(const MvArgs &a, const MacroArgs &ma, int n_cu, int code, int ksp
     pl.n_full = (pl.MTF + 7) / 8 * 8 * pl.NN;
     const int tail = pl.MT - pl.MTF;
     const GemmCost c = kGemmCosts[code];
-    us = (double)((pl.MTF * pl.NN + n_cu - 1) / n_cu) * (a.T * c.stage + c.fixed);
+    // (rounds by the fullest die: all column tiles of a row tile, or of one of its parts, are on one)
+    auto rounds = [&](int groups) { return (double)(((groups + 7) / 8 * pl.NN + n_cu / 8 - 1) / std::max(1, n_cu / 8)); };
+    us = rounds(pl.MTF) * (a.T * c.stage + c.fixed);
     if (tail == 0 || pl.ksp == 1) return ksp == 1;
     const double bytes = (double)pl.ksp * (a.n_rg - pl.MTF * trg) * ma.S * 4096.0;
-    us += (double)((tail * pl.NN * pl.ksp + n_cu - 1) / n_cu) * (pl.TS * c.stage + c.fixed) + bytes / kPartBytesPerUs;
+    us += rounds(tail * pl.ksp) * (pl.TS * c.stage + c.fixed) + bytes / kPartBytesPerUs;
     return pl.TS >= 16 && a.part && a.counters && (int64_t)pl.ksp * (a.n_rg - pl.MTF * trg) * ma.S <= a.part_capacity &&
            tail * pl.NN * 8 <= 4096;
 }
@@ -641,9 +635,11 @@ hipError_t launch_gemm(int epi, const MvArgs &a, const MacroArgs &ma, int n_cu, 
     GemmPlan pl{};
     int code = 0;
     double best = 1e30;
-    for (int c = 1; c <= 6; ++c) {
-        if (tiling_override >= 1 && tiling_override <= 6 && c != tiling_override) continue;
+    const int only = tiling_override & 15, parts = tiling_override >> 4;  // (parts: 0 = any)
+    for (int c = 1; c <= kGemmCodes; ++c) {
+        if (only && c != only) continue;
         for (int ksp = 1; ksp <= 4; ++ksp) {
+            if (parts && ksp != parts) continue;
             GemmPlan p;
             double us;
             if (!gemm_plan(a, ma, n_cu, c, ksp, p, us) || us >= best) continue;
@@ -656,12 +652,16 @@ hipError_t launch_gemm(int epi, const MvArgs &a, const MacroArgs &ma, int n_cu, 
 #define SWIFT_GEMM_CASE(E)                                                \
     case E:                                                               \
         switch (code) {                                                   \
-            case 1: return launch_gemm_t<E, 2, 1>(a, ma, pl, s);         \
-            case 2: return launch_gemm_t<E, 2, 2>(a, ma, pl, s);         \
-            case 3: return launch_gemm_t<E, 2, 3>(a, ma, pl, s);         \
-            case 4: return launch_gemm_t<E, 2, 4>(a, ma, pl, s);         \
-            case 5: return launch_gemm_t<E, 1, 1>(a, ma, pl, s);         \
-            default: return launch_gemm_t<E, 1, 2>(a, ma, pl, s);        \
+            case 1: return launch_gemm_t<E, 4, 2>(a, ma, pl, s);         \
+            case 2: return launch_gemm_t<E, 4, 4>(a, ma, pl, s);         \
+            case 3: return launch_gemm_t<E, 4, 6>(a, ma, pl, s);         \
+            case 4: return launch_gemm_t<E, 4, 8>(a, ma, pl, s);         \
+            case 5: return launch_gemm_t<E, 2, 2>(a, ma, pl, s);         \
+            case 6: return launch_gemm_t<E, 2, 4>(a, ma, pl, s);         \
+            case 7: return launch_gemm_t<E, 4, 3>(a, ma, pl, s);         \
+            case 8: return launch_gemm_t<E, 4, 5>(a, ma, pl, s);         \
+            case 9: return launch_gemm_t<E, 4, 7>(a, ma, pl, s);         \
+            default: return launch_gemm_t<E, 2, 3>(a, ma, pl, s);        \
         }
     switch (epi) {
         SWIFT_GEMM_CASE(EPI_QKV)

@@ -219,17 +219,19 @@ def test_prefill_depth_split_against_64_row_blocks(n_prompt):
 
 @pytest.mark.parametrize("shape", [
     si.LLAMA2_7B.with_layers(2),
+    si.LLAMA2_13B.with_layers(2),
     si.ModelShape("tail-gqa-d128", 2, 512, 8, 2, 128, 344, 384, "bf16", 1e-5),
     si.ModelShape("tail-d32", 1, 96, 3, 3, 32, 136, 200, "bf16", 1e-5),   # attention row by row
 ], ids=lambda s: s.name)
 def test_prefill_last_layer_of_macro_blocks_against_64_row_blocks(shape):
     """Past the last attention sublayer's keys and values a macro block goes on with its last sub-block alone (or ends): every
     row of the last sub-block and the last layer's cache slots of all sub-blocks against the same prompt in 64-row blocks,
-    which compute every row of every layer.  Bounds as for the depth split above."""
+    which compute every row of every layer.  The lengths are those of 2, 4, 5, 8, 9 and 16 sub-blocks (where the blocked matrix
+    product takes each of its tile heights and column widths) and of a second macro block.  Bounds as for the depth split."""
     import paper_2410_06916_amd as P
-    g = P.SwiftModel(shape, 700)
+    g = P.SwiftModel(shape, 1300)
     g.load_weights(si.iter_weights(shape, 6, "cuda:0", gain_jitter=0.1))
-    for n_prompt in (65, 128, 205, 512, 513, 600):
+    for n_prompt in (65, 128, 205, 310, 512, 513, 1025, 1200):
         prompt = si.uniform_ids(72, n_prompt, shape.vocab)
         slots = sorted({0, 63, 64, n_prompt // 2, n_prompt - 1})
         last_rows = n_prompt - (n_prompt - 1) // 64 * 64
