@@ -359,7 +359,7 @@ int swift_debug_projection_path(const swift_model_config *cfg, int n_cu, int ker
 int swift_debug_tune(swift_ctx *ctx, int kernel_class, int waves_per_row_group, int workgroups);
 
 /* How swift_prefill walks a prompt on bf16 models (tuning and test runs; every setting gives results within the
- * library's tolerance, not the same bits).  sub_blocks: 0 = the default (macro blocks of up to 8 sub-blocks of 64
+ * library's tolerance, not the same bits).  sub_blocks: 0 = the default (macro blocks of up to 16 sub-blocks of 64
  * rows per sweep over the weights), 1..8 = macro blocks of at most that many sub-blocks, -1 = one 64-row block per
  * sweep.  tiling: 0 = automatic, else the workgroup tile of the blocked matrix product: 1..4 = 64, 128, 192 or 256
  * weight rows x two sub-blocks, 5 / 6 = 128 / 256 weight rows x one sub-block. */

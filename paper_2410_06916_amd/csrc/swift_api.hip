@@ -487,8 +487,8 @@ int block_attention(swift_ctx *x, const AttnArgs &at, int RLC) {
 //
 // n_sub > 0: a prompt macro block instead: n_sub sub-blocks of kMaxBlockRows rows, the last one with R rows, at
 // positions pos0 .. (tokens holds all their rows).  Every projection is one launch of the blocked matrix product
-// over all sub-blocks; the embedding and the LM head (last sub-block only: results land in rows
-// [0, R)) go sub-block by sub-block.  Bulk layouts; no tree.  With reuse_kv (a candidate-evaluation window of more
+// over all sub-blocks, as is attention with heads of 64 or 128 (else it goes sub-block by sub-block); the LM head runs for the
+// last sub-block (results land in rows [0, R)).  Bulk layouts; no tree.  With reuse_kv (a candidate-evaluation window of more
 // than one sub-block) the caller asks for every sub-block's predictions afterwards (macro_sub_logits).
 // Without it (a prompt), nothing but the cache and the last sub-block's logits is left of the pass.  Past the last attention
 // sublayer's keys and values no row meets another one, so from there on the pass goes on with the last sub-block alone
@@ -551,19 +551,21 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
     ma.S = n_sub;
     ma.rows_last = R;
     auto sub_rows = [&](int sb) { return sb == last ? R : kMaxBlockRows; };
-    for (int sb = 0; sb <= last; ++sb) {
+    {
         EmbedRowsArgs ea{};
         ea.E = dptr<uint16_t>(x, L.embed);
         ea.H = H;
-        ea.R = sub_rows(sb);
-        for (int r = 0; r < ea.R; ++r) ea.tokens[r] = tokens[sb * kMaxBlockRows + r];
-        ea.x = xf + sb * L.sub_x;
-        ea.xs = xs + sb * L.sub_xs;
+        ea.R = last * kMaxBlockRows + R;
+        ea.x = xf;
+        ea.xs = xs;
         ea.gain_next = gain_of(0);
-        ea.pss = pss + sb * L.sub_pss;
+        ea.pss = pss;
         ea.rp = n_sub > 0 ? kMaxBlockRows : block_row_pitch(R);
         ea.RL = RLC;
-        HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)ea.R * H * 2, [&] { return launch_embed_rows(ea, s); }));
+        ea.sub_x = L.sub_x;
+        ea.sub_xs = L.sub_xs;
+        ea.sub_pss = L.sub_pss;
+        HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)ea.R * H * 2, [&] { return launch_embed_rows(ea, tokens, s); }));
     }
 
     // The stage from which on a prompt's macro block is its last sub-block only (7B, 512 rows: the last layer 207 us instead of
@@ -1683,7 +1685,7 @@ extern "C" int swift_debug_tune(swift_ctx *x, int kernel_class, int waves_per_ro
 }
 
 extern "C" int swift_debug_prefill(swift_ctx *x, int sub_blocks, int tiling) {
-    if (!x || sub_blocks < -1 || sub_blocks > kMacroSub || tiling < 0 || tiling > 6)
+    if (!x || sub_blocks < -1 || sub_blocks > 8 || tiling < 0 || tiling > 6)
         return fail(SWIFT_EINVAL, "bad argument");
     x->prefill_sub = sub_blocks;
     x->gemm_rgw = tiling;

@@ -303,7 +303,9 @@ int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity);
 // projection in one launch.  Each sub-block has buffers of its own, laid out as for a 64-row block in the bulk
 // layout; sub-block s is found at the given element strides from sub-block 0's pointers in MvArgs, its rows sit at
 // positions pos0 + 64 s ..
-constexpr int kMacroSub = 8;
+// (sixteen: the tiles of 1024 rows leave fewer compute units idle in their last round than two times those of 512; 7B, per
+// layer q|k|v + o_proj + gate/up + down_proj 651 us against 2 x 356)
+constexpr int kMacroSub = 16;
 struct MacroArgs {
     int S;          // sub-blocks, 1..kMacroSub
     int rows_last;  // rows of the last one, 1..64 (the others hold 64)
@@ -311,22 +313,23 @@ struct MacroArgs {
 };
 // epilogue: EPI_QKV, EPI_RESID or EPI_SWIGLU; a.R is ignored, a.RL must be the 64-row bulk layout, a.rp = 64, a.K a
 // multiple of 8; a.q_s is null; a.part and a.counters (4096 words, zero between launches) may be null: no depth split.
-// tiling_override: 0 = automatic, else the tile shape (tuning runs): 1..4 = that many row groups per
-// wavefront on two sub-blocks side by side, 5 / 6 = one / two row groups per wavefront on one sub-block.
+// tiling_override: 0 = automatic, else the tile shape (tuning runs; kGemmTilings) + 16 x the parts of a depth split (0: any).
 hipError_t launch_gemm(int epilogue, const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, hipStream_t s);
 
-// x[r] = E[token r] (fp32), split of x * gain_next, partial sums of squares per 16 elements.
+// x[r] = E[token r] (fp32), split of x * gain_next, partial sums of squares per 16 elements.  More than kMaxBlockRows rows:
+// those of a macro block, row r at row r % 64 of sub-block r / 64, found at the given element strides.
 struct EmbedRowsArgs {
     const uint16_t *E;  // [V][H] bf16 row-major
     int H, R;
     int RL;             // layout code of xs: block_row_layout
-    int32_t tokens[kMaxBlockRows];
     float *x;           // [R][H]
     uint16_t *xs;       // [H/8][3 RL][8]
     const float *gain_next;
     float *pss;         // [ceil(H/16)][rp]
     int rp;             // row pitch of pss (16 or 64)
+    int64_t sub_x, sub_xs, sub_pss;
 };
-hipError_t launch_embed_rows(const EmbedRowsArgs &a, hipStream_t s);
+constexpr int kEmbedRows = 512;  // rows of one launch (their token ids travel in its arguments)
+hipError_t launch_embed_rows(const EmbedRowsArgs &a, const int32_t *tokens, hipStream_t s);
 
 }  // namespace swift

@@ -4,6 +4,7 @@
 // 32 and 64 rows (longer verify blocks, prefill, candidate evaluation).
 #include <math.h>
 #include <stdio.h>
+#include <string.h>
 
 #include <algorithm>
 
@@ -89,38 +90,79 @@ hipError_t launch_tile_weights(const TileArgs &a, hipStream_t s) {
 // ------------------------------------------------------------------------------------------
 // embedding gather for R rows: fp32 residual, split of x * gain_next, partial sums of squares
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_embed_rows(EmbedRowsArgs a) {
-    // one thread per (row r, element i); 16 consecutive lanes share a 16-element group
+// One thread per row and eight elements (16 bytes in, 32 + 16 per term out); the two threads of a 16-element group add its
+// squares.  A prompt's macro block is one launch for every 512 rows, as many token ids as the launch arguments carry (512 rows
+// of 4096: 9.9 us, against 33 as eight launches of 64 rows with a thread per element).
+template <int N>
+struct EmbedTokens {
+    int32_t id[N];
+};
+template <int N>
+__global__ __launch_bounds__(256) void k_embed_rows(EmbedRowsArgs a, EmbedTokens<N> tok) {
     const int NT = block_terms(a.RL), NC = NT * layout_rows(a.RL);
-    const int Hp = (a.H + 15) & ~15;
-    const int total = a.R * Hp;
-    for (int idx0 = blockIdx.x * 256; idx0 < total; idx0 += gridDim.x * 256) {
-        const int idx = idx0 + threadIdx.x;
-        const int r = idx / Hp, i = idx - r * Hp;
-        float v = 0.f;
-        const bool ok = idx < total && i < a.H;
-        if (ok) {
-            v = __uint_as_float((uint32_t)a.E[(size_t)a.tokens[r] * a.H + i] << 16);
-            a.x[(size_t)r * a.H + i] = v;
-            uint16_t hi, mid, lo;
-            split3(v * a.gain_next[i], hi, mid, lo);
-            uint16_t *p = a.xs + ((size_t)(i >> 3) * NC + NT * r) * 8 + (i & 7);
-            p[0] = hi;
-            p[8] = mid;
-            if (NT == 3) p[16] = lo;
-        }
-        float ss = v * v;
+    const int cpr = ((a.H + 15) >> 4) * 2;  // 8-element chunks of a row (whole 16-element groups)
+    const int total = a.R * cpr, idx = blockIdx.x * 256 + threadIdx.x;
+    const int r = min(idx, total - 1) / cpr, c = min(idx, total - 1) - r * cpr;
+    const int sub = r >> 6, rs = N > kMaxBlockRows ? r & 63 : r;  // sub-block, row of it
+    const bool ok = idx < total && 8 * c < a.H;                   // (H is a multiple of 8)
+    float v[8];
 #pragma unroll
-        for (int off = 8; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
-        if (idx < total && (i & 15) == 0) a.pss[(size_t)(i >> 4) * a.rp + r] = ss;
+    for (int i = 0; i < 8; ++i) v[i] = 0.f;
+    if (ok) {
+        const u32x4 e = *(const u32x4 *)(a.E + (size_t)tok.id[r] * a.H + 8 * c);
+        const f32x4 g0 = *(const f32x4 *)(a.gain_next + 8 * c), g1 = *(const f32x4 *)(a.gain_next + 8 * c + 4);
+        float *x = a.x + sub * a.sub_x + (size_t)rs * a.H + 8 * c;
+        u32x4 t[3];
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            v[i] = __uint_as_float(e[i >> 1] << 16);
+            v[i + 1] = __uint_as_float(e[i >> 1] & 0xffff0000u);
+            uint16_t h[2], m[2], l[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) split3(v[i + j] * (i < 4 ? g0[i + j & 3] : g1[i + j & 3]), h[j], m[j], l[j]);
+            t[0][i >> 1] = pack2(h[0], h[1]);
+            t[1][i >> 1] = pack2(m[0], m[1]);
+            t[2][i >> 1] = pack2(l[0], l[1]);
+        }
+        *(f32x4 *)x = f32x4{v[0], v[1], v[2], v[3]};
+        *(f32x4 *)(x + 4) = f32x4{v[4], v[5], v[6], v[7]};
+        u32x4 *p = (u32x4 *)(a.xs + sub * a.sub_xs) + (size_t)c * NC + NT * rs;
+        p[0] = t[0];
+        p[1] = t[1];
+        if (NT == 3) p[2] = t[2];
     }
+    float q[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) q[i] = v[i] * v[i];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) q[i] += __shfl_xor(q[i], 1, 64);
+    const float ss = ((q[0] + q[4]) + (q[2] + q[6])) + ((q[1] + q[5]) + (q[3] + q[7]));
+    if (idx < total && (c & 1) == 0) a.pss[sub * a.sub_pss + (size_t)(c >> 1) * a.rp + rs] = ss;
 }
 
-hipError_t launch_embed_rows(const EmbedRowsArgs &a, hipStream_t s) {
-    const int Hp = (a.H + 15) & ~15;
-    const int grid = (a.R * Hp + 255) / 256;
-    hipLaunchKernelGGL(k_embed_rows, dim3(grid), dim3(256), 0, s, a);
+template <int N>
+static hipError_t launch_embed_rows_n(const EmbedRowsArgs &a, const int32_t *tokens, hipStream_t s) {
+    EmbedTokens<N> tok;
+    memcpy(tok.id, tokens, sizeof(int32_t) * a.R);
+    const int grid = (a.R * ((a.H + 15) / 16 * 2) + 255) / 256;
+    hipLaunchKernelGGL(k_embed_rows<N>, dim3(grid), dim3(256), 0, s, a, tok);
     return hipGetLastError();
+}
+
+hipError_t launch_embed_rows(const EmbedRowsArgs &a, const int32_t *tokens, hipStream_t s) {
+    if (a.R < 1 || (a.H & 7) != 0) return hipErrorInvalidValue;
+    if (a.R <= kMaxBlockRows) return launch_embed_rows_n<kMaxBlockRows>(a, tokens, s);
+    for (int r0 = 0; r0 < a.R; r0 += kEmbedRows) {
+        EmbedRowsArgs b = a;
+        const int sub = r0 / kMaxBlockRows;
+        b.R = std::min(kEmbedRows, a.R - r0);
+        b.x += sub * a.sub_x;
+        b.xs += sub * a.sub_xs;
+        b.pss += sub * a.sub_pss;
+        const hipError_t e = launch_embed_rows_n<kEmbedRows>(b, tokens + r0, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // ------------------------------------------------------------------------------------------
