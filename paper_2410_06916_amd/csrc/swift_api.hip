@@ -80,8 +80,8 @@ struct Layout {
     // tiled path: split activations (three bf16 terms, MFMA B layout), RMSNorm partials, split-K scratch
     uint64_t xs, as_, hs, pss, mv_part, mv_counters;
     // elements from one sub-block of a prompt macro block to the next, per activation buffer
-    uint64_t sub_x, sub_q, sub_q_s, sub_xs, sub_as, sub_hs, sub_pss;
-    int mv_part_capacity;
+    uint64_t sub_x, sub_q, sub_xs, sub_as, sub_hs, sub_pss;
+    int mv_part_capacity, gemm_part_slots;
     uint64_t stage, stage_bytes;  // staging for host tensors that are re-tiled on the device
     uint64_t total;
     int n_split_max;
@@ -135,15 +135,15 @@ Layout make_layout(const swift_model_config &c) {
     const uint64_t subs = L.tiled ? kMacroSub : 1;
     L.sub_x = kMaxBlockRows * H;
     L.sub_q = kMaxBlockRows * Q;
-    L.sub_q_s = kMaxBlockRows * Q * 2;
-    L.sub_xs = ceil_div(H, 32) * 4 * 3 * kMaxBlockRows * 8;
-    L.sub_as = ceil_div(Q, 32) * 4 * 3 * kMaxBlockRows * 8;
-    L.sub_hs = ceil_div(F, 32) * 4 * 3 * kMaxBlockRows * 8;
+    // (64 rows of two terms; exact layouts of three terms have up to 32 rows)
+    L.sub_xs = ceil_div(H, 32) * 4 * 2 * kMaxBlockRows * 8;
+    L.sub_as = ceil_div(Q, 32) * 4 * 2 * kMaxBlockRows * 8;
+    L.sub_hs = ceil_div(F, 32) * 4 * 2 * kMaxBlockRows * 8;
     L.sub_pss = ceil_div(H, 16) * kMaxBlockRows;
     L.x = take(subs * L.sub_x * 4);
     L.q = take(subs * L.sub_q * 4);
     L.att = take(kMaxBlockRows * Q * 4);
-    L.q_s = take(subs * L.sub_q_s * 2);
+    L.q_s = take((uint64_t)kMaxBlockRows * Q * 2 * 2);
     L.h = take(kMaxBlockRows * F * 4);
     L.logits = take(kMaxBlockRows * V * 4);
     L.part_o = take((uint64_t)kMaxRows * c.n_q_heads * L.n_split_max * c.head_dim * 4);
@@ -159,7 +159,8 @@ Layout make_layout(const swift_model_config &c) {
     L.hs = take(subs * L.sub_hs * 2);
     L.pss = take(subs * L.sub_pss * 4);
     L.mv_part_capacity = 8192;
-    L.mv_part = take((uint64_t)L.mv_part_capacity * 16 * kMaxBlockRows * 4);
+    L.gemm_part_slots = 16384;
+    L.mv_part = take((uint64_t)std::max(L.mv_part_capacity, L.gemm_part_slots) * 16 * kMaxBlockRows * 4);
     L.mv_counters = take(4096 * 4);
     L.stage_bytes = bf ? std::max(std::max(V * H, F * H), std::max(Q * H, KV * H)) * eb : 0;
     L.stage = take(L.stage_bytes);
@@ -550,6 +551,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
     MacroArgs ma{};
     ma.S = n_sub;
     ma.rows_last = R;
+    ma.part_slots = L.gemm_part_slots;
     auto sub_rows = [&](int sb) { return sb == last ? R : kMaxBlockRows; };
     {
         EmbedRowsArgs ea{};
@@ -616,7 +618,6 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             a.rows = sub_rows(sb);
             a.n_ctx += sb * kMaxBlockRows;
             a.q += sb * L.sub_q;
-            a.q_s += sb * L.sub_q_s;
             a.out_s += sb * L.sub_as;
             int rc = block_attention(x, a, RLC);
             if (rc) return rc;
@@ -631,6 +632,8 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             // keys and values of all rows: the row groups behind the query heads'
             MvArgs m = base_args(y.wqkv + tiled_bytes(Q / 16, H), 2 * KV, H, 2 * KV / 16);
             m.head0 = c.n_q_heads;
+            ma.matrix_rg = (Q + 2 * KV) / 16;
+            ma.first_rg = Q / 16;
             m.in_s = xs;
             m.pss = pss;
             m.n_pss = n_pss;
@@ -639,6 +642,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             m.nb32 = L.nb32;
             if (int rc = run_mv(SWIFT_KC_QKV, EPI_QKV, m)) return rc;
             if (!want_logits) return SWIFT_OK;
+            ma.matrix_rg = ma.first_rg = 0;
             // from here on: the last sub-block's rows and buffers
             tail = true;
             pos0 += last * kMaxBlockRows;
@@ -1022,11 +1026,11 @@ extern "C" int swift_prefill(swift_ctx *x, const int32_t *prompt, int n_prompt, 
         if (prompt[i] < 0 || prompt[i] >= x->c.vocab) return fail(SWIFT_EINVAL, "token id out of range");
     int last_rows = 0;
     if (x->L.tiled) {
-        // bf16 models: macro blocks of up to kMacroSub sub-blocks of 64 rows share one sweep over the weights (a
+        // bf16 models: macro blocks of kMacroSub sub-blocks of 64 rows, then of up to eight, share one sweep over the weights (a
         // blocked matrix product per projection); what is left at the end, if it fits one sub-block, goes through
         // the block kernels
-        const int subs = x->prefill_sub > 0 ? x->prefill_sub : kMacroSub;
         for (int i = 0; i < n_prompt;) {
+            const int subs = x->prefill_sub > 0 ? x->prefill_sub : n_prompt - i >= kMacroSub * kMaxBlockRows ? kMacroSub : 8;
             const int rows = std::min(subs * kMaxBlockRows, n_prompt - i);
             const bool macro = x->prefill_sub >= 0 && rows > kMaxBlockRows;
             const int n_blk = std::min(rows, kMaxBlockRows * (macro ? subs : 1));

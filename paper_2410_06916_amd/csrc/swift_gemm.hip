@@ -257,9 +257,10 @@ __device__ inline void gemm_qkv(const MvArgs &a, int rg0, int r0, int lane, cons
 }
 
 // Which workgroups do what.  Row tiles [0, MTF) are computed whole, one workgroup each per column tile (grid ids below
-// n_full); the rest are split in depth over ksp workgroups of TS k tiles each.
+// n_full); the rest are split in depth over ksp workgroups of TS k tiles each.  fold_rg, fold_TS: a tile that is computed whole
+// adds the sums of its row groups from fold_rg on in parts of fold_TS k tiles all the same (see gemm_sums).
 struct GemmPlan {
-    int MT, NN, MTF, n_full, ksp, TS;
+    int MT, NN, MTF, n_full, ksp, TS, fold_rg, fold_TS;
 };
 
 template <int RGW>
@@ -267,7 +268,7 @@ struct GemmOperands {
     u32x4 av[RGW], bv[4];
 };
 
-template <int EPI, int WN, int RGW>
+template <int EPI, int WN, int RGW, bool FOLD>
 __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan pl) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int WM = 8 / WN, SB = WN / 2;       // wavefronts along the rows; SB sub-blocks side by side
@@ -363,6 +364,25 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // FOLD: the finished parts of the sums, the two terms combined
+    f32x4 done[FOLD ? RGW : 1][2];
+#pragma unroll
+    for (int g = 0; g < (FOLD ? RGW : 1); ++g)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) done[g][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto fold_part = [&]() {
+#pragma unroll
+        for (int g = 0; g < (FOLD ? RGW : 0); ++g)
+            if ((mt * WM + wm) * RGW + g >= pl.fold_rg) {  // (wavefront-uniform)
+                f32x4 v[2];
+                fold_terms(acc[g], col, v);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) done[g][c] += v[c];
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
+
     const unsigned char *a_base = ring + (wm * RGW) * 1024 + lane * 16;
     const unsigned char *b_base = ring + A_BYTES + ws * 8192 + (kg * 128 + 64 * wh + col) * 16;
     // (wavefronts without a sub-block -- an odd sub-block count leaves half of the last column tile empty -- go
@@ -444,18 +464,24 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
             interleave();
             slot = nslot;
         };
-        for (; t + NST + 1 < TF; t += 2) {  // both steps issue a stage
-            steady(o0, o1);
-            steady(o1, o0);
-        }
-        if (t + NST < TF) {  // an odd number of issuing steps: one more, then the operands sit in the other set
-            steady(o0, o1);
-            drain(o1, o0);
-            t += 2;
-        }
-        for (; t < TF; t += 2) {
-            drain(o0, o1);
-            if (t + 1 < TF) drain(o1, o0);
+        for (int end = FOLD ? pl.fold_TS : TF;; end += pl.fold_TS) {  // a part of the sums (an even number of stages but for the last)
+            const int e = min(end, TF), both = min(e, TF - NST - 1);
+            for (; t < both; t += 2) {  // both steps issue a stage
+                steady(o0, o1);
+                steady(o1, o0);
+            }
+            if (t < e && t + NST < TF) {  // an odd number of issuing steps: one more, then the operands sit in the other set
+                steady(o0, o1);
+                drain(o1, o0);
+                t += 2;
+            }
+            for (; t < e; t += 2) {
+                drain(o0, o1);
+                if (t + 1 < e) drain(o1, o0);
+            }
+            if (!FOLD) break;
+            if (e < TF || (ragged && end == TF)) fold_part();
+            if (e == TF) break;
         }
     };
     if (kNorm) norm_ss = gemm_norm_sum(a, ma, sub0);
@@ -514,8 +540,15 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
         }
     };
     __syncthreads();  // the ring is no longer read (and the scales are visible where no step had a barrier)
-    if (KSP == 1) {
-        if (wave_live) finish([&](int g, f32x4(&v)[2]) { fold_terms(acc[g], col, v); });
+    if (FOLD || KSP == 1) {
+        if (wave_live)
+            finish([&](int g, f32x4(&v)[2]) {
+                fold_terms(acc[g], col, v);
+                if (FOLD) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) v[c] = done[g][c] + v[c];
+                }
+            });
         return;
     }
     // ---- depth split over workgroups.  Every wavefront publishes its results, the two terms combined, as
@@ -560,19 +593,26 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int EPI, int WN, int RGW>
-hipError_t launch_gemm_t(const MvArgs &a, const MacroArgs &ma, const GemmPlan &pl, hipStream_t s) {
+template <int EPI, int WN, int RGW, bool FOLD>
+hipError_t launch_gemm_f(const MvArgs &a, const MacroArgs &ma, const GemmPlan &pl, hipStream_t s) {
     static bool attr_set = false;
     const size_t lds = kRingBytes + 128 * 4 + kNormFloats * 4;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemm<EPI, WN, RGW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_gemm<EPI, WN, RGW, FOLD>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int tail = pl.MT - pl.MTF;
     const int grid = pl.n_full + (tail * pl.ksp + 7) / 8 * 8 * pl.NN;
-    hipLaunchKernelGGL((k_gemm<EPI, WN, RGW>), dim3(grid), dim3(512), lds, s, a, ma, pl);
+    hipLaunchKernelGGL((k_gemm<EPI, WN, RGW, FOLD>), dim3(grid), dim3(512), lds, s, a, ma, pl);
     return hipGetLastError();
+}
+constexpr int kFoldMaxRgw = 6;  // (beside more accumulators, the finished parts do not fit the registers)
+template <int EPI, int WN, int RGW>
+hipError_t launch_gemm_t(const MvArgs &a, const MacroArgs &ma, const GemmPlan &pl, hipStream_t s) {
+    if constexpr (RGW <= kFoldMaxRgw)
+        if (pl.fold_TS > 0) return launch_gemm_f<EPI, WN, RGW, true>(a, ma, pl, s);
+    return launch_gemm_f<EPI, WN, RGW, false>(a, ma, pl, s);
 }
 
 // Tilings: wavefronts along the columns (4: two sub-blocks side by side, 2: one) and row groups per wavefront.  Codes 1..4:
@@ -598,28 +638,66 @@ constexpr GemmCost kGemmCosts[kGemmCodes + 1] = {{0, 0},       {0.286, 5.4}, {0.
                                                 {0.425, 4.8}, {0.329, 5.0}, {0.445, 7.3}, {0.594, 6.7}, {0.347, 5.1}};
 constexpr double kPartBytesPerUs = 1.43e6;  // publishing and adding the parts of tiles split in depth
 
-// The plan of a tiling with its last tiles split ksp ways, and what it costs; false if the partial results would not fit
-// the scratch or a part would hold fewer than 16 k tiles.
-bool gemm_plan(const MvArgs &a, const MacroArgs &ma, int n_cu, int code, int ksp, GemmPlan &pl, double &us) {
+// The order of the sums.  Row groups from `first` on are summed in parts of TS k tiles (each from zero, the two terms combined,
+// then the parts in order), the others in one go.  It is a function of the matrix and the number of sub-blocks alone, not of
+// the tile shape or of who computes what, so that the cache entries that a prompt leaves are the same bits whatever the plan below
+// makes of them (a sampled continuation may hang on them); macro blocks of more than eight sub-blocks follow the order of
+// eight, so that a prompt may be cut into either.  (The order is that of a launch with tiles of 16 .. 256 rows on `a.n_rg` row groups by
+// the costs here, whose last round of workgroups was split in depth.)
+struct GemmSums {
+    int first, parts, TS;
+};
+GemmSums gemm_sums(int n_rg, int T, int S, int n_cu) {
+    static const struct { int wn, rgw; double stage, fixed; } kShapes[6] = {{2, 1, 0.305, 9.0}, {2, 2, 0.37, 10.0}, {2, 3, 0.54, 12.0},
+                                                                            {2, 4, 0.58, 14.0}, {1, 1, 0.26, 8.0},  {1, 2, 0.385, 9.0}};
+    S = std::min(S, 8);
+    GemmSums best{n_rg, 1, T};
+    double least = 1e30;
+    for (const auto &h : kShapes)
+        for (int ksp = 1; ksp <= 4; ++ksp) {
+            const int trg = 8 / h.wn * h.rgw, MT = (n_rg + trg - 1) / trg, NN = (S + h.wn - 1) / h.wn;
+            const int per_round = std::max(1, n_cu / NN / 8) * 8, MTF = ksp == 1 ? MT : MT / per_round * per_round;
+            const int TS = (T + ksp - 1) / ksp, parts = (T + TS - 1) / TS, tail = MT - MTF;
+            double us = (double)((MTF * NN + n_cu - 1) / n_cu) * (T * h.stage + h.fixed);
+            if (tail == 0 || parts == 1) {
+                if (ksp != 1) continue;
+            } else {
+                const int64_t slots = (int64_t)parts * (n_rg - MTF * trg) * S;
+                if (TS < 16 || slots > 8192 || tail * NN * 8 > 4096) continue;
+                us += (double)((tail * NN * parts + n_cu - 1) / n_cu) * (TS * h.stage + h.fixed) + (double)slots * 4096.0 / 1.3e6;
+            }
+            if (us >= least) continue;
+            least = us;
+            best = parts == 1 || tail == 0 ? GemmSums{n_rg, 1, T} : GemmSums{MTF * trg, parts, TS};
+        }
+    return best;
+}
+
+// The plan of a tiling, and what it costs.  Row groups that are summed in parts are either split over workgroups, a part each
+// (fold = false; their first one has to begin a tile, and the partial results have to fit the scratch), or added part by part in the
+// workgroup that computes the whole depth (fold = true; parts of an even number of k tiles, up to six row groups per wavefront).
+bool gemm_plan(const MvArgs &a, const MacroArgs &ma, int n_cu, int code, const GemmSums &sums, bool fold, GemmPlan &pl, double &us) {
     const int wn = kGemmTilings[code].wn, rgw = kGemmTilings[code].rgw, trg = (8 / wn) * rgw, sb = wn / 2;
+    const bool split = sums.parts > 1 && !fold;
+    if (fold && (sums.parts == 1 || (sums.TS & 1) != 0 || rgw > kFoldMaxRgw)) return false;
+    if (split && sums.first % trg != 0) return false;
     pl.MT = (a.n_rg + trg - 1) / trg;
     pl.NN = (ma.S + sb - 1) / sb;
-    const int per_round = std::max(1, n_cu / pl.NN / 8) * 8;  // row tiles of a round (whole dies)
-    const int whole_rounds = pl.MT / per_round;
-    pl.MTF = ksp == 1 ? pl.MT : whole_rounds * per_round;
-    pl.TS = (a.T + ksp - 1) / ksp;
-    pl.ksp = (a.T + pl.TS - 1) / pl.TS;  // parts that hold tiles
+    pl.MTF = split ? sums.first / trg : pl.MT;
+    pl.ksp = sums.parts;
+    pl.TS = sums.TS;
     pl.n_full = (pl.MTF + 7) / 8 * 8 * pl.NN;
+    pl.fold_rg = sums.first;
+    pl.fold_TS = fold ? sums.TS : 0;
     const int tail = pl.MT - pl.MTF;
     const GemmCost c = kGemmCosts[code];
     // (rounds by the fullest die: all column tiles of a row tile, or of one of its parts, are on one)
     auto rounds = [&](int groups) { return (double)(((groups + 7) / 8 * pl.NN + n_cu / 8 - 1) / std::max(1, n_cu / 8)); };
     us = rounds(pl.MTF) * (a.T * c.stage + c.fixed);
-    if (tail == 0 || pl.ksp == 1) return ksp == 1;
-    const double bytes = (double)pl.ksp * (a.n_rg - pl.MTF * trg) * ma.S * 4096.0;
-    us += rounds(tail * pl.ksp) * (pl.TS * c.stage + c.fixed) + bytes / kPartBytesPerUs;
-    return pl.TS >= 16 && a.part && a.counters && (int64_t)pl.ksp * (a.n_rg - pl.MTF * trg) * ma.S <= a.part_capacity &&
-           tail * pl.NN * 8 <= 4096;
+    if (tail == 0) return true;
+    const int64_t slots = (int64_t)pl.ksp * (a.n_rg - sums.first) * ma.S;
+    us += rounds(tail * pl.ksp) * (pl.TS * c.stage + c.fixed) + (double)slots * 4096.0 / kPartBytesPerUs;
+    return a.part && a.counters && slots <= ma.part_slots && tail * pl.NN * 8 <= 4096;
 }
 
 }  // namespace
@@ -629,25 +707,30 @@ hipError_t launch_gemm(int epi, const MvArgs &a, const MacroArgs &ma, int n_cu, 
         (a.K & 7) != 0 || a.T != (a.K + 31) / 32 || a.n_rg < 1 || !a.Wt || !a.in_s || a.tree || a.q_s ||
         (epi == EPI_RESID ? !a.gain_next || !a.pss_out || (a.O & 7) != 0 : !a.pss || a.n_pss < 1))
         return hipErrorInvalidValue;
-    // The tile shape and the depth split that finish first by the measured costs: workgroups come in rounds of one per
+    // The tile shape and the way of adding the parts that finish first by the measured costs: workgroups come in rounds of one per
     // compute unit, and splitting the last round's tiles in depth fills the units that would idle in it, for the price
     // of the parts' results.
+    GemmSums sums = gemm_sums(ma.matrix_rg > 0 ? ma.matrix_rg : a.n_rg, a.T, ma.S, n_cu);
+    sums.first = std::max(0, sums.first - ma.first_rg);
+    if (sums.first >= a.n_rg) sums = GemmSums{a.n_rg, 1, a.T};
     GemmPlan pl{};
     int code = 0;
     double best = 1e30;
-    const int only = tiling_override & 15, parts = tiling_override >> 4;  // (parts: 0 = any)
     for (int c = 1; c <= kGemmCodes; ++c) {
-        if (only && c != only) continue;
-        for (int ksp = 1; ksp <= 4; ++ksp) {
-            if (parts && ksp != parts) continue;
+        if (tiling_override && c != tiling_override) continue;
+        for (const bool fold : {false, true}) {
             GemmPlan p;
             double us;
-            if (!gemm_plan(a, ma, n_cu, c, ksp, p, us) || us >= best) continue;
+            if (!gemm_plan(a, ma, n_cu, c, sums, fold, p, us) || us >= best) continue;
             best = us;
             pl = p;
             code = c;
         }
     }
+    // (a tile shape asked for by a tuning run may not allow the order of the sums: then they are added in one go)
+    if (code == 0 && tiling_override >= 1 && tiling_override <= kGemmCodes &&
+        gemm_plan(a, ma, n_cu, tiling_override, GemmSums{a.n_rg, 1, a.T}, false, pl, best))
+        code = tiling_override;
     if (code == 0) return hipErrorInvalidValue;
 #define SWIFT_GEMM_CASE(E)                                                \
     case E:                                                               \

@@ -304,16 +304,18 @@ int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity);
 // layout; sub-block s is found at the given element strides from sub-block 0's pointers in MvArgs, its rows sit at
 // positions pos0 + 64 s ..
 // (sixteen: the tiles of 1024 rows leave fewer compute units idle in their last round than two times those of 512; 7B, per
-// layer q|k|v + o_proj + gate/up + down_proj 651 us against 2 x 356)
+// layer q|k|v + o_proj + gate/up + down_proj 677 us against 2 x 357)
 constexpr int kMacroSub = 16;
 struct MacroArgs {
     int S;          // sub-blocks, 1..kMacroSub
     int rows_last;  // rows of the last one, 1..64 (the others hold 64)
     int64_t in_s, pss, out_f32, out_s, pss_out;  // strides, in elements of the respective buffer
+    int part_slots;           // capacity of MvArgs::part: row groups x sub-blocks x depth parts, 4 KB each
+    int matrix_rg, first_rg;  // a launch over some row groups of a matrix: those of the whole one (0: this is it), those before
 };
 // epilogue: EPI_QKV, EPI_RESID or EPI_SWIGLU; a.R is ignored, a.RL must be the 64-row bulk layout, a.rp = 64, a.K a
 // multiple of 8; a.q_s is null; a.part and a.counters (4096 words, zero between launches) may be null: no depth split.
-// tiling_override: 0 = automatic, else the tile shape (tuning runs; kGemmTilings) + 16 x the parts of a depth split (0: any).
+// tiling_override: 0 = automatic, else the tile shape (tuning runs; kGemmTilings).
 hipError_t launch_gemm(int epilogue, const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, hipStream_t s);
 
 // x[r] = E[token r] (fp32), split of x * gain_next, partial sums of squares per 16 elements.  More than kMaxBlockRows rows:

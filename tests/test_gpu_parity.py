@@ -247,6 +247,28 @@ def test_prefill_last_layer_of_macro_blocks_against_64_row_blocks(shape):
     g.close()
 
 
+@pytest.mark.parametrize("shape", [si.LLAMA2_7B.with_layers(2), si.LLAMA2_13B.with_layers(2), si.LLAMA2_70B.with_layers(2)],
+                         ids=lambda s: s.name)
+def test_prefill_macro_blocks_of_16_and_8_leave_the_same_bits(shape):
+    """The order in which a prompt's sums are added follows from the matrix alone, not from the tiles or the workgroups that
+    compute them (parts of the depth added inside a workgroup or over several): 1024 rows in one sweep over the weights leave
+    the cache and the logits of two sweeps of 512, bit for bit; so does the part of a prompt past them."""
+    import paper_2410_06916_amd as P
+    g = P.SwiftModel(shape, 1500)
+    g.load_weights(si.iter_weights(shape, 6, "cuda:0", gain_jitter=0.1))
+    for n_prompt in (1024, 1430):
+        prompt = si.uniform_ids(73, n_prompt, shape.vocab)
+        res = []
+        for blocks in (0, 8):
+            g.prefill_blocks(blocks)
+            g.prefill(prompt)
+            res.append([g.read_logits((n_prompt - 1) % 64)] +
+                       [x for layer in range(2) for p in (0, 63, 500, 512, 777, n_prompt - 1) for x in g.read_kv(layer, p)])
+        for a, b in zip(*res):
+            assert np.array_equal(a, b), n_prompt
+    g.close()
+
+
 @pytest.mark.parametrize("shape", [
     si.TINY.with_layers(2),
     si.ModelShape("fp32-wide", 1, 2048, 16, 8, 128, 10240, 384, "fp32", 1e-6),   # 8 rows per workgroup, 4 in down_proj
