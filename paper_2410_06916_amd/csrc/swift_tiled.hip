@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -221,76 +222,10 @@ __device__ inline void mv_norm_finish(const MvArgs &a, const NormPart &np, float
     // this point and its epilogue)
 }
 
-// The same for blocks of up to 64 rows (row pitch 64): thread = (partial p mod 8, row r), then 64
-// threads add the 8 per-thread sums in order.  One barrier, before the final sums.  scratch: LDS [512].
-__device__ inline void mv_norm_rows64(const MvArgs &a, float *rs /* LDS [64] */, float *scratch) {
-    const int tid = threadIdx.x, r = tid & 63, q = tid >> 6;
-    if (a.pss) {
-        float ss = 0.f;
-        for (int p0 = 0; p0 < a.n_pss; p0 += 64) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + q + 8 * u;
-                v[u] = p < a.n_pss ? a.pss[(size_t)p * a.rp + r] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) ss += v[u];
-        }
-        scratch[q * 64 + r] = ss;
-    }
-    __syncthreads();
-    if (tid < 64) {
-        float ss = 0.f;
-        if (a.pss)
-            for (int q2 = 0; q2 < 8; ++q2) ss += scratch[q2 * 64 + tid];
-        rs[tid] = a.pss ? 1.0f / sqrtf(ss / (float)a.norm_dim + a.eps) : 1.0f;
-    }
-    // (no barrier here: the scales are read by the epilogue only, and every caller has a barrier between
-    // this point and its epilogue)
-}
-
 // The same for exact layouts of 17..32 rows (row pitch 64), in the summation order of mv_norm_load /
 // mv_norm_finish -- a row's scale must not depend on the rows it shares a pass with: thread (row r, q) adds
 // the partials q + 32 u and q + 16 + 32 u, u = 0, 1, .., as two sums; then 32 threads add the 32 sums in
-// order.  One barrier, before the final sums.  scratch: LDS [1024].
-__device__ inline void mv_norm_rows32(const MvArgs &a, float *rs /* LDS [64] */, float *scratch) {
-    const int tid = threadIdx.x, r = tid & 31, q0 = tid >> 5;
-    if (a.pss) {
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int q = q0 + 16 * half;
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = q + 32 * u;
-                v[u] = p < a.n_pss ? a.pss[(size_t)p * a.rp + r] : 0.f;
-            }
-            float ss = 0.f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) ss += v[u];
-            for (int p0 = 256; p0 < a.n_pss; p0 += 256) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int p = p0 + q + 32 * u;
-                    v[u] = p < a.n_pss ? a.pss[(size_t)p * a.rp + r] : 0.f;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) ss += v[u];
-            }
-            scratch[q * 32 + r] = ss;
-        }
-    }
-    __syncthreads();
-    if (tid < 32) {
-        float ss = 0.f;
-        if (a.pss)
-            for (int q2 = 0; q2 < 32; ++q2) ss += scratch[q2 * 32 + tid];
-        rs[tid] = a.pss ? 1.0f / sqrtf(ss / (float)a.norm_dim + a.eps) : 1.0f;
-    }
-}
-
-// mv_norm_rows32 in two parts: the loads of the first 256 partials (hidden <= 4096: all of them), and the rest with an
+// order.  In two parts: the loads of the first 256 partials (hidden <= 4096: all of them), and the rest with an
 // LDS-only barrier.
 struct NormPart32 {
     float v[2][8];
@@ -331,6 +266,37 @@ __device__ inline void mv_norm32_finish(const MvArgs &a, NormPart32 &np, float *
     if (tid < 32) {
         float t = 0.f;
         for (int q2 = 0; q2 < 32; ++q2) t += scratch[q2 * 32 + tid];
+        rs[tid] = a.pss ? 1.0f / sqrtf(t / (float)a.norm_dim + a.eps) : 1.0f;
+    }
+}
+
+// The same for bulk layouts of 64 rows: thread = (partial p mod 8, row r), then 64 threads add the 8 per-thread sums in order.
+struct NormPart64 {
+    float v[32];
+};
+__device__ inline void mv_norm64_load(const MvArgs &a, int p0, NormPart64 &np) {
+    const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+        const int p = p0 + q + 8 * u;
+        np.v[u] = (a.pss && p < a.n_pss) ? a.pss[(size_t)p * a.rp + r] : 0.f;
+    }
+}
+__device__ inline void mv_norm64_finish(const MvArgs &a, NormPart64 &np, float *rs /* LDS [64] */, float *scratch /* LDS [512] */) {
+    const int tid = threadIdx.x, r = tid & 63, q = tid >> 6;
+    float ss = 0.f;
+    for (int p0 = 0;;) {
+#pragma unroll
+        for (int u = 0; u < 32; ++u) ss += np.v[u];
+        p0 += 256;
+        if (p0 >= a.n_pss) break;
+        mv_norm64_load(a, p0, np);
+    }
+    scratch[q * 64 + r] = ss;
+    lds_barrier();
+    if (tid < 64) {
+        float t = 0.f;
+        for (int q2 = 0; q2 < 8; ++q2) t += scratch[q2 * 64 + tid];
         rs[tid] = a.pss ? 1.0f / sqrtf(t / (float)a.norm_dim + a.eps) : 1.0f;
     }
 }
@@ -699,15 +665,22 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 }
 
 // ------------------------------------------------------------------------------------------
-// a block of up to 64 activation rows: Y = W . X, MFMA, K chunked through LDS, optional split-K
+// a block of up to 64 activation rows: Y = W . X, MFMA, both operands through a ring in LDS, optional split-K
 // ------------------------------------------------------------------------------------------
-// Each of the 8 wavefronts of a workgroup owns RG 16-row groups of W; the workgroup walks its K
-// range in chunks of CT tiles.  The B operand of a chunk (4 CT k-chunks x NC = 3R columns x 16 B,
-// already in B layout in global memory) is copied into one of two LDS buffers while the MFMAs of
-// the previous chunk run; the A tiles of the next chunk are loaded into a second register set at
-// the same time.  NCB = ceil(NC/16) column blocks; a B operand read from LDS feeds RG MFMAs (with
-// RG = 2 the LDS traffic per MFMA halves, which is what bounds the 64-row case).  With
-// gridDim.y > 1 the K range is split over workgroups: each writes its partial results, and the
+// A workgroup of 8 wavefronts owns 2 WM row groups of W (WM = 4 or 3) and all columns.  Wavefront (w % WM, w / WM), w < 2 WM,
+// multiplies two row groups with half of the column blocks, NCW = ceil(NCB / 2) of them.  Weight tiles and the B operand reach LDS
+// straight from global memory through a ring of stages of two k tiles each, all eight wavefronts copying; in step t the
+// operands of stage t + 1 are read, stage t is multiplied, and what lies further ahead (about 140 KB) is on its way.  One barrier
+// per stage.
+// What bounds it: the weight stream, and the operand reads (a wavefront reads 2 + NCW KB per k tile; as one row group
+// times all columns, which is what this kernel replaces, 1 + NCB KB from chunks of eight tiles that drained the loads in
+// flight at every barrier).  Weights are copied non-temporally, so that they do not push the B operand, which every workgroup
+// reads, out of L2.  us, before / now: 7B, 31 rows gate/up 54 / 40, down_proj 35.5 / 31, LM head 60 / 49; 32 bulk rows gate/up
+// 40.5 / 34; 13B, 31 rows gate/up 79 / 57, down_proj 57 / 41; 70B, 31 rows gate/up 231 / 179, LM head 112 / 87.  (One k tile a
+// stage 1-3 % slower; weights straight to registers, each tile by two wavefronts: gate/up 54; four wavefronts of 512 registers
+// with six row groups each and nothing staged: 62.)
+//
+// With gridDim.y > 1 the K range is split over workgroups: each writes its partial results, and the
 // workgroup that arrives last at a counter adds the partials in split order (so the result does
 // not depend on arrival order) and runs the epilogue.
 //
@@ -718,252 +691,293 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 // the three terms, and the last workgroup adds the group results in order.  The LDS-resident kernel adds its 8
 // slice sums in the same grouping.  The bulk variants (NCB = 4 / 8: layouts of 32 / 64 rows, two-term columns)
 // keep their own fixed order.
-template <int EPI, int NCB, int CT, int RG, bool DMA, bool CANON>
-__global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS, int rpw) {
+constexpr int kMvnRing = 144 * 1024;
+constexpr int kMvnTiles = 2;       // k tiles of a stage
+constexpr int kNonTemporal = 2;    // cache policy of a load: nt
+// How k_mvN cuts a matrix over workgroups: grid (row blocks, K parts), tiles per part, row groups per workgroup, six or eight:
+// what takes fewer rounds x tiles x cost of a tile, which is about that of (row groups + 20) (7B gate/up, 31 rows, one round
+// either way: 40.3 us with six, 42.9 with eight; 13B gate/up, two rounds with six: 88 against 57).
+struct MvnPlan {
+    int grid_x, ksp, TS, rgs;
+};
+static MvnPlan mvn_plan(const MvArgs &a, int n_cu, bool canon) {
+    MvnPlan best{};
+    int64_t least = 0;
+    for (int rgs = 6; rgs <= 8; rgs += 2) {
+        MvnPlan p;
+        p.rgs = rgs;
+        p.grid_x = (a.n_rg + rgs - 1) / rgs;
+        if (canon) {
+            p.TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
+        } else {
+            // about one workgroup of eight row groups per compute unit, eight tiles each at least (whatever the workgroup's
+            // own row groups: the parts are the order of the sums)
+            int ksp = std::min(8, std::max(1, n_cu / ((a.n_rg + 7) / 8)));
+            while (ksp > 1 && ((a.T + ksp - 1) / ksp < 8 || (int64_t)a.n_rg * ksp > a.part_capacity)) --ksp;
+            p.TS = (a.T + ksp - 1) / ksp;
+        }
+        p.ksp = (a.T + p.TS - 1) / p.TS;  // parts that hold tiles
+        const int64_t cost = (int64_t)((p.grid_x * p.ksp + n_cu - 1) / n_cu) * p.TS * (rgs + 20);
+        if (rgs == 6 || cost < least) {
+            best = p;
+            least = cost;
+        }
+    }
+    return best;
+}
+
+template <int NCW>
+struct MvnOperands {
+    u32x4 av[kMvnTiles][2], bv[kMvnTiles][NCW];
+};
+template <int EPI, int NCB, bool CANON, int WM>
+__global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int R = a.R, NT = block_terms(a.RL), NC = NT * layout_rows(a.RL);  // NC: columns of the split input as laid out
-    const int buf_bytes = 4 * CT * NC * 16;
-    // the result dump (NCB * 8 KB) reuses the B buffers, so the region is at least that large
-    const int main_bytes = max(2 * buf_bytes, NCB * 8192);
-    float *rs = (float *)(smem + 16 + (size_t)main_bytes);
+    constexpr int KT = kMvnTiles;
+    constexpr int NCW = (NCB + 1) / 2;                 // column blocks of a wavefront (two wavefronts side by side)
+    constexpr int RGS = 2 * WM;                        // row groups; wavefronts past 2 WM only copy
+    constexpr int ST_BYTES = KT * (RGS + NCB) * 1024;
+    constexpr int NST = kMvnRing / ST_BYTES;
+    constexpr int NP = KT * (RGS + NCB), PW = (NP + 7) / 8;  // 1 KB pieces of a stage; of a wavefront
+    static_assert(NST >= 3 && NST * PW < 60, "ring depth against the load counter");
+    unsigned char *ring = smem;
+    float *rs = (float *)(smem + NST * ST_BYTES + 1024);  // (operand reads of columns past the last run over a stage's end)
     int *flag = (int *)(rs + 64);
-    float *nscratch = rs + 80;  // [1024]
-    float *dump = (float *)(smem + 16);  // reuses the B buffers after the last MFMA
+    uint32_t *touched = (uint32_t *)(rs + 80);         // [8][64]
+    float *nscratch = rs + 80 + 512;                   // [1024]
+    constexpr bool kNorm = EPI != EPI_RESID;
+    const int R = a.R, NT = block_terms(a.RL), NC = NT * layout_rows(a.RL);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int T = a.T;
-    // rpw <= 8 wavefronts of a workgroup own row groups (the launcher's choice: as many as spread the matrix
-    // evenly over the compute units); the others only help with the copies and the barriers
-    const bool active = wave < rpw;
-    const int rg0 = ((int)blockIdx.x * rpw + min(wave, rpw - 1)) * RG;  // first row group of this wavefront
-    const int tb = (int)blockIdx.y * TS;
-    const int nt = min(T, tb + TS) - tb;  // >= 1 (launcher)
+    const int wm = wave % WM, wn = min(wave / WM, 1);
+    const bool worker = wave < 2 * WM;
     const int col = lane & 15, kg = lane >> 4;
-    constexpr bool kCanon = CANON;  // exact layouts (verify blocks); the bulk variants keep their own order
-    // A slice is walked in chunks of CT tiles that do not run over its end (the last chunk of a slice
-    // may be partial), so that slices end between chunks.  The prefill variant has one "slice": its
-    // whole K range.
-    const int n_c = kCanon ? (T + 7) >> 3 : nt;   // tiles of a slice
-    const int nchs = (n_c + CT - 1) / CT;         // chunks of a slice
-    const int nch = ((nt + n_c - 1) / n_c - 1) * nchs + ((nt - 1) % n_c) / CT + 1;  // chunks of this workgroup
-    const int KSP = gridDim.y;
-    // first tile (relative to tb) of chunk c, and the tiles of it that exist
-    auto chunk_t0 = [&](int c) { return (c / nchs) * n_c + (c % nchs) * CT; };
-    auto chunk_nt = [&](int c) { return min(min(CT, n_c - (c % nchs) * CT), nt - chunk_t0(c)); };
-    const u32x4 *base[RG];
-#pragma unroll
-    for (int g = 0; g < RG; ++g)  // row groups past the end repeat the last one; their results are dropped
-        base[g] = (const u32x4 *)a.Wt + ((size_t)min(rg0 + g, a.n_rg - 1) * T + tb) * 64 + lane;
-    if (EPI == EPI_QKV && active) {  // the lines this wavefront's epilogue will write values into
-#pragma unroll
-        for (int g = 0; g < RG; ++g) mv_touch_value_lines(a, min(rg0 + g, a.n_rg - 1), lane);
+    const int T = a.T, rgb = (int)blockIdx.x * RGS;  // first row group
+    const int t_lo = (int)blockIdx.y * TS, t_hi = min(T, t_lo + TS), KSP = gridDim.y;
+    const int n_c = CANON ? (T + 7) >> 3 : T;  // tiles of a slice
+    const bool ragged = (a.K & 31) != 0 && t_hi == T;  // (a last tile past the real depth is not part of the pipeline)
+    const int TF = t_hi - t_lo - (ragged ? 1 : 0);
+
+    // (the norm partials go out ahead of the ring's first stages; the scales are read by the epilogue only)
+    NormPart np;
+    NormPart32 np32;
+    NormPart64 np64;
+    if (kNorm) {
+        if (NCB > 6)
+            mv_norm64_load(a, 0, np64);
+        else if (a.rp == 16)
+            np = mv_norm_load(a);
+        else
+            mv_norm32_load(a, 0, np32);
     }
-    const u32x4 *bsrc = (const u32x4 *)a.in_s;
-    const int real_units = (a.K >> 3) * NC;
-    const int chunk_units = 4 * CT * NC;  // 16-byte units of one B chunk (<= 512 NQ)
-    constexpr int NQ = (4 * CT * NCB * 16 + 511) / 512;  // ... per thread
-
-    // per-lane B addressing: byte offset inside a buffer for tile u, column block cb:
-    //   ((4u + kg) * NC + 16 cb + col) * 16 = boff0 + u * tstride + 256 cb.
-    // Columns that do not exist (col >= NC in the last block, rows >= R of a 64-row layout) read
-    // whatever lies there: they only produce result columns that nobody reads.
-    const int boff0 = 16 + (kg * NC + col) * 16;
-    const int tstride = 4 * NC * 16;
-
-    f32x4 acc[RG][NCB];
-    // The sums of this workgroup's slices are added in slice order as the slices are completed.
-    f32x4 ssum[kCanon ? NCB : 1];
-#pragma unroll
-    for (int g = 0; g < RG; ++g)
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int cb = 0; cb < (kCanon ? NCB : 1); ++cb) ssum[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto slice_end = [&]() {
-#pragma unroll
-        for (int cb = 0; cb < (kCanon ? NCB : 1); ++cb) {
-            ssum[cb] += acc[0][cb];
-            acc[0][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (EPI == EPI_QKV) {  // the lines this wavefront's epilogue will write values into (see mv_touch_value_lines)
+        const int d = a.head_dim, half = d >> 1, gph = half >> 3, rg = min(rgb + wave, a.n_rg - 1);
+        const int hh = rg / gph, head = hh - a.n_q_heads - a.n_kv_heads, r = lane >> 1;
+        if (a.nb32 > 0 && head >= 0 && r < R) {
+            const uint16_t *vp = (const uint16_t *)a.vcache + (kv_vt_index(head, a.nb32, d, a.pos0 + r, 8 * (rg - hh * gph) + (lane & 1) * half) & ~(size_t)1);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)vp,
+                                             (__attribute__((address_space(3))) void *)(touched + wave * 64), 4, 0, 0);
         }
-    };
-    auto loadA = [&](int c, u32x4(&A)[RG][CT]) {
-        const int t0 = chunk_t0(c);
+    }
+    // ---- what this wavefront copies per stage: pieces wave + 8 i (a row group's KT tiles, then KT tiles of B)
+    const unsigned char *src[PW];
+    int stride[PW];
+    uint32_t voff[PW], vend[PW];  // (the last stage of a part may hold tiles past its end, which are not multiplied: cut at the matrix's)
 #pragma unroll
-        for (int g = 0; g < RG; ++g)
-#pragma unroll
-            for (int u = 0; u < CT; ++u)
-                A[g][u] = active ? __builtin_nontemporal_load(base[g] + (size_t)min(t0 + u, nt - 1) * 64)
-                                 : u32x4{0u, 0u, 0u, 0u};
-    };
-    auto loadB = [&](int c, u32x4(&tmp)[NQ]) {
-        const int gu0 = 4 * (tb + chunk_t0(c)) * NC;
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int i = tid + 512 * q;
-            tmp[q] = (i < chunk_units && gu0 + i < real_units) ? bsrc[gu0 + i] : zero;
+    for (int i = 0; i < PW; ++i) {
+        const int p = min(wave + 8 * i, NP - 1);
+        if (p < KT * RGS) {
+            src[i] = (const unsigned char *)a.Wt + (size_t)min(rgb + p / KT, a.n_rg - 1) * T * 1024;
+            stride[i] = 1024;
+            voff[i] = lane * 16 + (t_lo + p % KT) * 1024;
+            vend[i] = lane * 16 + (T - 1) * 1024;
+        } else {
+            src[i] = (const unsigned char *)a.in_s;
+            stride[i] = 64 * NC;
+            voff[i] = lane * 16 + t_lo * stride[i] + (p - KT * RGS) * 1024;
+            vend[i] = (a.K >> 3) * NC * 16 - 16;
         }
-    };
-    auto storeB = [&](int bi, const u32x4(&tmp)[NQ]) {
-        u32x4 *dst = (u32x4 *)(smem + 16 + (size_t)bi * buf_bytes);
+    }
+    const bool full_share = (NP % 8 == 0) || wave < NP % 8;
+    auto issue = [&](int slot_bytes, auto FULL) {
+        unsigned char *dst = ring + slot_bytes + wave * 1024;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int i = tid + 512 * q;
-            if (i < chunk_units) dst[i] = tmp[q];
-        }
-    };
-    // DMA variants: B chunk c -> LDS buffer bi straight from global memory (no registers, no LDS write
-    // instructions: the data lands while the wavefronts run MFMAs).  A wavefront's 64 lanes fill 64
-    // consecutive 16-byte units from a wavefront-uniform base; lanes past the chunk take no part.  Units
-    // past the real K range (a ragged last tile) are zeroed with ordinary writes.
-    auto dmaB = [&](int c, int bi) {
-        const int gu0 = 4 * (tb + chunk_t0(c)) * NC;
-        u32x4 *dst = (u32x4 *)(smem + 16 + (size_t)bi * buf_bytes);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int i = tid + 512 * q;
-            if (i < chunk_units) {
-                if (gu0 + i < real_units)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(bsrc + gu0 + i),
-                                                     (__attribute__((address_space(3))) void *)(dst + 512 * q + 64 * wave), 16, 0, 0);
+        for (int i = 0; i < PW; ++i) {
+            if (i < PW - 1 || decltype(FULL)::value) {
+                const auto from = (const __attribute__((address_space(1))) void *)(src[i] + (size_t)min(voff[i], vend[i]));
+                const auto to = (__attribute__((address_space(3))) void *)(dst + i * 8192);
+                if (wave + 8 * i < KT * RGS)  // (wavefront-uniform)
+                    __builtin_amdgcn_global_load_lds(from, to, 16, 0, kNonTemporal);
                 else
-                    dst[i] = u32x4{0u, 0u, 0u, 0u};
+                    __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
             }
+            voff[i] += KT * stride[i];
         }
     };
-    // The B operands of a tile (NCB LDS reads) are requested one tile ahead of the MFMAs that use
-    // them.  Slots past the chunk's tiles multiply a zero A operand.
-    auto mfmas = [&](int c, const u32x4(&A)[RG][CT], int bi) {
-        const int ntc = chunk_nt(c);
-        const unsigned char *bp = smem + boff0 + bi * buf_bytes;
-        u32x4 bq[2][NCB];
+    auto wait_all_but = [&](auto N, auto FULL) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(N)::value * (decltype(FULL)::value ? PW : PW - 1)) : "memory");
+    };
+    auto lds_sync = [&]() {
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+        asm volatile("s_barrier" ::: "memory");
+    };
+    f32x4 acc[2][NCW], ssum[CANON ? 2 : 1][CANON ? NCW : 1];
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) bq[0][cb] = *(const u32x4 *)(bp + 256 * cb);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int g = 0; g < 2; ++g)
 #pragma unroll
-        for (int u = 0; u < CT; ++u) {
-            if (u + 1 < CT) {
+        for (int cb = 0; cb < NCW; ++cb) {
+            acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (CANON) ssum[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    int left = n_c;  // tiles to the end of the slice (a workgroup's part begins with a slice)
+    const unsigned char *a_base = ring + wm * 2048 * KT + lane * 16;
+    const unsigned char *b_base = ring + KT * RGS * 1024 + (kg * NC + 16 * NCW * wn + col) * 16;
+    const int tstride = 64 * NC;
+    auto read_operands = [&](int slot_bytes, MvnOperands<NCW> &o) {
 #pragma unroll
-                for (int cb = 0; cb < NCB; ++cb)
-                    bq[(u + 1) & 1][cb] = *(const u32x4 *)(bp + (u + 1) * tstride + 256 * cb);
-            }
-            // (keep the reads above the MFMAs: left alone, the scheduler sinks each read to just
-            // before its use to save registers, and every MFMA then waits out the LDS latency)
+        for (int k = 0; k < KT; ++k) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g) o.av[k][g] = *(const u32x4 *)(a_base + slot_bytes + (g * KT + k) * 1024);
+#pragma unroll
+            for (int cb = 0; cb < NCW; ++cb) o.bv[k][cb] = *(const u32x4 *)(b_base + slot_bytes + k * tstride + cb * 256);
+        }
+    };
+    auto slice_end = [&]() {
+        if constexpr (CANON) {
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int cb = 0; cb < NCW; ++cb) {
+                    ssum[g][cb] += acc[g][cb];
+                    acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    };
+    auto multiply = [&](const u32x4(&av)[2], const u32x4(&bv)[NCW]) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int cb = 0; cb < NCW; ++cb)
+                acc[g][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[g]), __builtin_bit_cast(bf16x8, bv[cb]),
+                                                                     acc[g][cb], 0, 0, 0);
+    };
+    auto norm = [&]() {
+        if (!kNorm) return;
+        if (NCB > 6)
+            mv_norm64_finish(a, np64, rs, nscratch);
+        else if (a.rp == 16)
+            mv_norm_finish<true>(a, np, rs, nscratch);
+        else
+            mv_norm32_finish(a, np32, rs, nscratch);
+    };
+    auto pipeline = [&](auto FULL) {
+        constexpr auto ALL = std::integral_constant<int, 0>();
+        constexpr auto AHEAD = std::integral_constant<int, NST - 2>();
+        const int SF = (TF + KT - 1) / KT;  // stages
+        const int first = min(SF, NST);
+        for (int t = 0; t < first; ++t) issue(t * ST_BYTES, FULL);
+        norm();
+        if (SF == 0) return;
+        if (SF >= NST)
+            wait_all_but(std::integral_constant<int, NST - 1>(), FULL);
+        else
+            wait_all_but(ALL, FULL);
+        MvnOperands<NCW> o0, o1;
+        lds_sync();
+        if (worker) read_operands(0, o0);
+        int t = 0, slot = 0, todo = TF;
+        auto step = [&](const MvnOperands<NCW> &cur, MvnOperands<NCW> &nxt, auto STEADY) {
+            const int nslot = slot + ST_BYTES == NST * ST_BYTES ? 0 : slot + ST_BYTES;
+            if (decltype(STEADY)::value)
+                wait_all_but(AHEAD, FULL);
+            else
+                wait_all_but(ALL, FULL);
+            lds_sync();
             __builtin_amdgcn_sched_barrier(0);
-            const bool ok = u < ntc;  // wavefront-uniform
+            if (decltype(STEADY)::value) issue(slot, FULL);
+            if (worker) {
+                read_operands(nslot, nxt);
 #pragma unroll
-            for (int g = 0; g < RG; ++g) {
-                const u32x4 zero = {0u, 0u, 0u, 0u};
-                const u32x4 av = ok ? A[g][u] : zero;
-#pragma unroll
-                for (int cb = 0; cb < NCB; ++cb)
-                    acc[g][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
-                                                                         __builtin_bit_cast(bf16x8, bq[u & 1][cb]),
-                                                                         acc[g][cb], 0, 0, 0);
+                for (int k = 0; k < KT; ++k) {
+                    if (k > 0 && todo <= k) break;
+                    multiply(cur.av[k], cur.bv[k]);
+                    if (CANON && --left == 0) {  // (wavefront-uniform)
+                        slice_end();
+                        left = n_c;
+                    }
+                }
             }
+            todo -= KT;
+            slot = nslot;
+        };
+        constexpr auto GO = std::true_type();
+        constexpr auto DRAIN = std::false_type();
+        for (; t + NST + 1 < SF; t += 2) {
+            step(o0, o1, GO);
+            step(o1, o0, GO);
         }
-        if (kCanon && ((c + 1) % nchs == 0 || c + 1 == nch)) slice_end();
+        if (t + NST < SF) {
+            step(o0, o1, GO);
+            step(o1, o0, DRAIN);
+            t += 2;
+        }
+        for (; t < SF; t += 2) {
+            step(o0, o1, DRAIN);
+            if (t + 1 < SF) step(o1, o0, DRAIN);
+        }
     };
-
-    u32x4 A0[RG][CT], A1[RG][CT];
-    if constexpr (DMA) {
-        // Pipeline: while the MFMAs of chunk c run, the B operand and the A tiles of chunk c + 1 are on their
-        // way, the former straight into the other LDS buffer.  Per step: wait for this wavefront's own loads
-        // of chunk c, then one barrier (everybody's part of B(c) has landed; nobody reads the other buffer).
-        if (tid < 4) ((uint32_t *)smem)[tid] = 0u;
-        dmaB(0, 0);
-        loadA(0, A0);
-        if (a.rp == 16)
-            mv_norm_finish(a, mv_norm_load(a), rs, nscratch);
-        else if (CANON)
-            mv_norm_rows32(a, rs, nscratch);
-        else
-            mv_norm_rows64(a, rs, nscratch);
-        auto step = [&](int c, const u32x4(&Ac)[RG][CT], int bc, u32x4(&An)[RG][CT], int bn) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            lds_barrier();
-            if (c + 1 < nch) {
-                dmaB(c + 1, bn);
-                loadA(c + 1, An);
-            }
-            mfmas(c, Ac, bc);
-        };
-        for (int c = 0; c < nch; c += 2) {
-            step(c, A0, 0, A1, 1);
-            if (c + 1 < nch) step(c + 1, A1, 1, A0, 0);
+    if (full_share)
+        pipeline(std::true_type());
+    else
+        pipeline(std::false_type());
+    if (ragged) {
+        const int real_units = (a.K >> 3) * NC;  // 16-byte units of the split activation
+        __syncthreads();
+        for (int i = tid; i < RGS * 64; i += 512)
+            *(u32x4 *)(ring + (i >> 6) * 1024 * KT + (i & 63) * 16) =
+                *((const u32x4 *)a.Wt + ((size_t)min(rgb + (i >> 6), a.n_rg - 1) * T + T - 1) * 64 + (i & 63));
+        for (int i = tid; i < 4 * NC; i += 512) {
+            const int gu = (T - 1) * 4 * NC + i;
+            *(u32x4 *)(ring + KT * RGS * 1024 + i * 16) = gu < real_units ? ((const u32x4 *)a.in_s)[gu] : u32x4{0u, 0u, 0u, 0u};
         }
-    } else {
-        // Pipeline: while the MFMAs of chunk c run, the A tiles of chunk c + 1 and the B operand of
-        // chunk c + 2 are on their way from memory, and the B operand of chunk c + 1 (loaded during
-        // the previous step) is copied into the other LDS buffer.  One LDS-only barrier per step: it
-        // does not wait for the loads in flight.
-        u32x4 tmp[NQ];
-        loadB(0, tmp);
-        loadA(0, A0);
-        if (tid < 4) ((uint32_t *)smem)[tid] = 0u;
-        storeB(0, tmp);
-        if (nch > 1) loadB(1, tmp);
-        if (a.rp == 16)
-            mv_norm_finish(a, mv_norm_load(a), rs, nscratch);
-        else if (CANON)
-            mv_norm_rows32(a, rs, nscratch);
-        else
-            mv_norm_rows64(a, rs, nscratch);
-
-        auto step = [&](int c, const u32x4(&Ac)[RG][CT], int bc, u32x4(&An)[RG][CT], int bn) {
-            lds_barrier();  // chunk c's B is visible; nobody reads buffer bn any more
-            if (c + 1 < nch) {
-                storeB(bn, tmp);
-                if (c + 2 < nch) loadB(c + 2, tmp);
-                loadA(c + 1, An);
-            }
-            mfmas(c, Ac, bc);
-        };
-        for (int c = 0; c < nch; c += 2) {
-            step(c, A0, 0, A1, 1);
-            if (c + 1 < nch) step(c + 1, A1, 1, A0, 0);
+        __syncthreads();
+        MvnOperands<NCW> o;
+        if (worker) {
+            read_operands(0, o);
+            multiply(o.av[0], o.bv[0]);
         }
+        --left;
     }
+    if (CANON && left != n_c) slice_end();
 
-    // ---- per row group of the wavefront: results to LDS (dump[wave][column][tile row]), then the
-    // epilogue, or with split K the partial
-    float *dw = dump + (size_t)wave * (NCB * 256);
+    // ---- results to LDS ([row group][column][tile row]), then the epilogue, or with split K the partial
+    __syncthreads();  // the ring is no longer read
+    float *dump = (float *)ring;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int cb = 0; cb < NCW; ++cb) {
+            const int c = 16 * (NCW * wn + cb) + col;
+            const f32x4 v = CANON ? ssum[CANON ? g : 0][CANON ? cb : 0] : acc[g][cb];
+            if (worker && c < 16 * NCB) *(f32x4 *)(dump + ((2 * wm + g) * (16 * NCB) + c) * 16 + 4 * kg) = v;
+        }
+    __syncthreads();
+    const int rg = rgb + wave;
+    const bool live = wave < RGS && rg < a.n_rg;
+    const float *dw = dump + wave * (NCB * 256);
     auto y_local = [&](int r, int j) {
         const float y2 = dw[(NT * r) * 16 + j] + dw[(NT * r + 1) * 16 + j];
         return NT == 3 ? y2 + dw[(3 * r + 2) * 16 + j] : y2;
     };
-    auto dump_regs = [&](const f32x4(&v)[NCB]) {
-        __syncthreads();  // the B buffers / the previous dump are no longer read
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) dw[(16 * cb + col) * 16 + 4 * kg + r4] = v[cb][r4];
-        __syncthreads();
-    };
-#pragma unroll
-    for (int g = 0; g < RG; ++g) {
-        const int rg = rg0 + g;
-        const bool live = active && rg < a.n_rg;
-        if constexpr (kCanon)
-            dump_regs(ssum);  // (RG = 1) the sum of this workgroup's slices, per term
-        else
-            dump_regs(acc[g]);
-        if (KSP == 1) {
-            if (live) mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_local);
-        } else if (live) {
-            // publish the partial, terms combined (device-scope atomic stores write through, so the
-            // release below has nothing to flush)
-            float *pp = a.part + ((size_t)blockIdx.y * a.n_rg + rg) * (16 * R);
-            for (int idx = lane; idx < 16 * R; idx += 64)
-                __hip_atomic_store(pp + idx, y_local(idx >> 4, idx & 15), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    if (KSP == 1) {
+        if (live) mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_local);
+        return;
     }
-    if (KSP == 1) return;
-    // ---- split-K: the last workgroup of this row block to arrive reduces.
-    // One release/acquire per workgroup: the barrier orders every wavefront's partial stores before
-    // thread 0's device-scope read-modify-write on the counter, which publishes them (release) and,
-    // in the workgroup that arrives last, makes the other workgroups' partials visible (acquire).
-    // Separate fences around a relaxed atomic cost 10+ us more per launch on this multi-die part.
+    if (live) {
+        float *pp = a.part + ((size_t)blockIdx.y * a.n_rg + rg) * (16 * R);
+        for (int idx = lane; idx < 16 * R; idx += 64)
+            __hip_atomic_store(pp + idx, y_local(idx >> 4, idx & 15), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     if (tid == 0) {
         const int old = __hip_atomic_fetch_add(a.counters + blockIdx.x, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -971,11 +985,7 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS, int rpw) {
     }
     __syncthreads();
     if (*flag == 0) return;
-    // (plain loads below: ordered after thread 0's acquire by the barrier)
-#pragma unroll
-    for (int g = 0; g < RG; ++g) {
-        const int rg = rg0 + g;
-        if (!active || rg >= a.n_rg) continue;
+    if (live) {
         const float *p0 = a.part + (size_t)rg * (16 * R);
         const size_t sstride = (size_t)a.n_rg * (16 * R);
         mv_epilogue<EPI>(a, rg, lane, rs, nullptr, [&](int r, int j) {
@@ -991,54 +1001,23 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS, int rpw) {
     if (tid == 0) a.counters[blockIdx.x] = 0;
 }
 
-// How k_mvN cuts a matrix over workgroups: grid (row blocks, K parts), tiles per part, wavefronts with work.
-struct MvnPlan {
-    int grid_x, ksp, TS, rpw;
-};
-static MvnPlan mvn_plan(const MvArgs &a, int n_cu, int RG, bool canon) {
-    MvnPlan p;
-    const int n_rb = (a.n_rg + 8 * RG - 1) / (8 * RG);
-    // split K over workgroups until about one workgroup per compute unit exists
-    // (never more workgroups than compute units: one workgroup fills a compute unit's registers,
-    // so a partial second round would double the kernel's duration)
-    int ksp = n_cu / n_rb;
-    if (ksp < 1) ksp = 1;
-    if (ksp > 8) ksp = 8;
-    if (canon) {
-        p.TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
-    } else {
-        while (ksp > 1 && ((a.T + ksp - 1) / ksp < 8 || (int64_t)a.n_rg * ksp > a.part_capacity)) --ksp;
-        p.TS = (a.T + ksp - 1) / ksp;
-    }
-    p.ksp = (a.T + p.TS - 1) / p.TS;  // workgroups whose K range holds tiles
-    // With fewer workgroups than compute units, a workgroup takes fewer row groups, so that every compute unit
-    // gets about the same share: what bounds these launches is what ONE compute unit can take in (weights plus
-    // its copy of the activation), not the chip's HBM rate.
-    p.rpw = 8;
-    p.grid_x = n_rb;
-    if (n_rb * p.ksp < n_cu) {
-        p.rpw = (a.n_rg * p.ksp + RG * n_cu - 1) / (RG * n_cu);
-        if (p.rpw < 4) p.rpw = 4;
-        if (p.rpw > 8) p.rpw = 8;
-        p.grid_x = (a.n_rg + p.rpw * RG - 1) / (p.rpw * RG);
-    }
-    return p;
-}
-
-template <int EPI, int NCB, int CT, int RG, bool DMA, bool CANON>
+template <int EPI, int NCB, bool CANON, int WM>
 static hipError_t launch_mvN_t(const MvArgs &a, int n_cu, hipStream_t s) {
+    constexpr int ST = kMvnTiles * (2 * WM + NCB) * 1024;
+    const size_t lds = kMvnRing / ST * ST + 1024 + (80 + 512 + 1024) * 4;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_mvN<EPI, NCB, CT, RG, DMA, CANON>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMvMaxLds);
+        hipError_t e = hipFuncSetAttribute((const void *)k_mvN<EPI, NCB, CANON, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int NC = block_terms(a.RL) * layout_rows(a.RL);
-    const size_t buf2 = 2 * (size_t)4 * CT * NC * 16;
-    const size_t lds = 16 + (buf2 > (size_t)NCB * 8192 ? buf2 : (size_t)NCB * 8192) + 320 + 4096;
-    const MvnPlan p = mvn_plan(a, n_cu, RG, CANON);
-    return launch_maybe_timed(k_mvN<EPI, NCB, CT, RG, DMA, CANON>, dim3(p.grid_x, p.ksp), dim3(512), lds, s, a, p.TS, p.rpw);
+    const MvnPlan p = mvn_plan(a, n_cu, CANON);
+    return launch_maybe_timed(k_mvN<EPI, NCB, CANON, WM>, dim3(p.grid_x, p.ksp), dim3(512), lds, s, a, p.TS);
+}
+
+template <int EPI, int NCB, bool CANON>
+static hipError_t launch_mvN(const MvArgs &a, int n_cu, hipStream_t s) {
+    return mvn_plan(a, n_cu, CANON).rgs == 6 ? launch_mvN_t<EPI, NCB, CANON, 3>(a, n_cu, s) : launch_mvN_t<EPI, NCB, CANON, 4>(a, n_cu, s);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1235,31 +1214,44 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
     return mvr_depth((a.T + 7) / 8, NCB, RG) == NS ? launch_mvR_ns<EPI, NCB, RG, NS>(a, s) : launch_mvR_ns<EPI, NCB, RG, NS2>(a, s);
 }
 
-// Row groups per workgroup round for k_mvR, or 0: k_mvN is the faster kernel.  Both sides by what one compute unit has to
-// walk, in us per k tile, fitted to 709 sets of launch durations of both kernels (rows 1-32 of both layouts, seven widths
+// Row groups per workgroup round for k_mvR, or 0: k_mvN.
+// From eleven exact (17 bulk) rows on, k_mvN takes the matrices that its workgroups of six row groups cover in one round with K
+// whole (us, k_mvR / k_mvN, 7B gate/up: 16 rows 35.8 / 33.5, 21 rows 43.0 / 35.3, 26 rows 48.1 / 38; 9 rows 33 / 34).
+// Elsewhere the line is where k_mvR broke even with the kernel that k_mvN replaces, by what one compute unit had to
+// walk, in us per k tile, fitted to 709 sets of launch durations of both (rows 1-32 of both layouts, seven widths
 // from 1024 to 8192, matrices of 6 to 1300 MB).  c: column blocks, 0.4 x those computed + 0.6 x the columns' own share.
 //   k_mvR   3.7 + rounds x 8 slices x steps of a slice as walked x (weights of 1, 2 or 3 row groups + c columns of B)
-//   k_mvN   6.1 (+ 2.8 + 0.96 c where K is split over workgroups) + rounds x tiles (a slice's last chunk of eight, where it
+//   line    6.1 (+ 2.8 + 0.96 c where K is split over workgroups) + rounds x tiles (a slice's last chunk of eight, where it
 //           is partial, counts half of what it lacks) x (row groups + c columns), by the root of the share of units in use
-// The picks add up to 0.3 % more than the faster kernel of every set; the worst ones are launches of 7-13 us and, at the
-// 7B, 13B and 70B widths, o_proj of 3-5 rows (70B, 27.5 against 25) and down_proj of 6-9 (13B, 36.9 against 34.0).
-// (us, k_mvN / the best k_mvR.  7B: 9 rows q|k|v 27.8 / 20.8, o_proj 15.3 / 10.4, gate/up 37.8 / 32.9, down_proj 26.0 /
-// 23.8; 15 rows down_proj 29.0 / 29.6; 31 rows q|k|v 37.9 / 30.3, gate/up 52.2 / 51.5, down_proj 35.2 / 41.3, LM head
-// 60.0 / 74.9.  70B, 16 rows: LM head 90.3 / 97.7.  13B, 32 bulk rows: q|k|v 40.9 / 45.2.)
+// Beyond the line k_mvN is the faster kernel by 2-40 % (us, k_mvR / k_mvN: 7B, 31 rows down_proj 41.3 / 31, LM head 75 / 48.6; 70B,
+// 16 rows LM head 97.7 / 83).  Short of it k_mvR is, by far at few rows (7B, 9 rows q|k|v 20 / 27, o_proj 9.2 / 17, down_proj 22 /
+// 25; 31 rows o_proj 17 / 22), and loses 6-17 % in a strip along the line (13B, 21 rows q|k|v 42 / 36; 70B, 16 rows down_proj
+// 92 / 76.5, 31 rows q|k|v 49.5 / 45): the instances that blocks of those widths take are part of what the tests state.
 static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     if (ncb < 1 || ncb > 6 || a.R > kMaxRows) return 0;
     static const double kWeights[3] = {0.0213, 0.0467, 0.0603}, kColumns[3] = {0.0147, 0.0178, 0.0226};
     const bool bulk = (a.RL & kBulkLayout) != 0;
     const double cols = 0.4 * ncb + 0.6 * (block_terms(a.RL) * layout_rows(a.RL)) / 16.0;
+    if (ncb > 2) {
+        const MvnPlan p = mvn_plan(a, n_cu, !bulk);
+        if (p.rgs == 6 && p.ksp == 1) return 0;
+    }
     double best = 1e30;
     int rg = 0;
     if (ncb > 1) {  // (one column block: activations too deep for k_mv1, which k_mvN does not take)
-        const MvnPlan p = mvn_plan(a, n_cu, 1, !bulk);
-        const int n = bulk ? p.TS : (a.T + 7) / 8;  // tiles of a slice
-        const double walked = p.TS + 0.5 * (p.TS / n) * ((n + 7) / 8 * 8 - n);
-        const int wgs = p.grid_x * p.ksp, rounds = (wgs + n_cu - 1) / n_cu;
-        best = 6.05 + (p.ksp > 1 ? 2.83 + 0.964 * cols : 0.0) +
-               rounds * walked * (p.rpw * 0.0349 + cols * (bulk ? 0.0212 : 0.0284)) * sqrt((double)wgs / (rounds * n_cu));
+        const int n_rb = (a.n_rg + 7) / 8;
+        int parts = std::min(8, std::max(1, n_cu / n_rb)), TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
+        if (bulk) {
+            while (parts > 1 && ((a.T + parts - 1) / parts < 8 || (int64_t)a.n_rg * parts > a.part_capacity)) --parts;
+            TS = (a.T + parts - 1) / parts;
+        }
+        parts = (a.T + TS - 1) / TS;
+        const int rgs = n_rb * parts < n_cu ? std::min(8, std::max(4, (a.n_rg * parts + n_cu - 1) / n_cu)) : 8;
+        const int n = bulk ? TS : (a.T + 7) / 8;  // tiles of a slice
+        const double walked = TS + 0.5 * (TS / n) * ((n + 7) / 8 * 8 - n);
+        const int wgs = (a.n_rg + rgs - 1) / rgs * parts, rounds = (wgs + n_cu - 1) / n_cu;
+        best = 6.05 + (parts > 1 ? 2.83 + 0.964 * cols : 0.0) +
+               rounds * walked * (rgs * 0.0349 + cols * (bulk ? 0.0212 : 0.0284)) * sqrt((double)wgs / (rounds * n_cu));
     }
     for (int c = 1; c <= 3; ++c) {
         if (ncb > 4 && c == 2) continue;
@@ -1282,7 +1274,7 @@ static int mv_column_blocks(const MvArgs &a) { return (block_terms(a.RL) * layou
 int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity) {
     if (mv_takes_mv1(a, 0)) return snprintf(out, (size_t)capacity, "mv1<rows %d>", a.R);
     const int ncb = mv_column_blocks(a), rg = mvr_row_groups(a, n_cu, ncb);
-    if (rg == 0) return snprintf(out, (size_t)capacity, "mvN<columns %d, parts %d>", ncb, mvn_plan(a, n_cu, 1, !(a.RL & kBulkLayout)).ksp);
+    if (rg == 0) return snprintf(out, (size_t)capacity, "mvN<columns %d, parts %d>", ncb, mvn_plan(a, n_cu, !(a.RL & kBulkLayout)).ksp);
     const int units = (a.n_rg + rg - 1) / rg;
     return snprintf(out, (size_t)capacity, "mvR<columns %d, row groups %d, steps %d, rounds %d>", ncb, rg,
                     mvr_depth((a.T + 7) / 8, ncb, rg), (units + n_cu - 1) / n_cu);
@@ -1305,7 +1297,7 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
         (bulk ? (lrows != 32 && lrows != 64) : (lrows != a.R || lrows > kMaxRows)) || a.head0 != 0)
         return hipErrorInvalidValue;
     if (mv_takes_mv1(a, ks_override)) return launch_mv1(epi, a, n_cu, ks_override, wg_override, s);
-    // exact layouts (up to 32 rows): 2-6 column blocks of three-term columns, K chunks of 8 tiles, the fixed
+    // exact layouts (up to 32 rows): 2-6 column blocks of three-term columns, the fixed
     // summation order; bulk layouts of 32 / 64 rows (prefill, candidate evaluation): 4 / 8 column blocks of
     // two-term columns
     const int ncb = mv_column_blocks(a);
@@ -1339,16 +1331,16 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
 #define SWIFT_MVN_CASE(E)                                                                \
     case E:                                                                              \
         if (bulk) switch (ncb) {                                                         \
-                case 4: return launch_mvN_t<E, 4, 8, 1, true, false>(a, n_cu, s);        \
-                case 8: return launch_mvN_t<E, 8, 8, 1, true, false>(a, n_cu, s);        \
+                case 4: return launch_mvN<E, 4, false>(a, n_cu, s);                      \
+                case 8: return launch_mvN<E, 8, false>(a, n_cu, s);                      \
                 default: return hipErrorInvalidValue;                                    \
             }                                                                            \
         switch (ncb) {                                                                   \
-            case 2: return launch_mvN_t<E, 2, 8, 1, false, true>(a, n_cu, s);            \
-            case 3: return launch_mvN_t<E, 3, 8, 1, false, true>(a, n_cu, s);            \
-            case 4: return launch_mvN_t<E, 4, 8, 1, false, true>(a, n_cu, s);            \
-            case 5: return launch_mvN_t<E, 5, 8, 1, false, true>(a, n_cu, s);            \
-            case 6: return launch_mvN_t<E, 6, 8, 1, false, true>(a, n_cu, s);            \
+            case 2: return launch_mvN<E, 2, true>(a, n_cu, s);                           \
+            case 3: return launch_mvN<E, 3, true>(a, n_cu, s);                           \
+            case 4: return launch_mvN<E, 4, true>(a, n_cu, s);                           \
+            case 5: return launch_mvN<E, 5, true>(a, n_cu, s);                           \
+            case 6: return launch_mvN<E, 6, true>(a, n_cu, s);                           \
             default: return hipErrorInvalidValue;                                        \
         }
     switch (epi) {
