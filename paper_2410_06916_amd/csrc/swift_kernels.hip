@@ -578,8 +578,8 @@ hipError_t launch_attn_decode(int dtype, const AttnArgs &a, int n_cu, hipStream_
 // ------------------------------------------------------------------------------------------
 // greedy choice + confidence:  token = first arg-max, conf = 1 / sum exp(l - max)
 // ------------------------------------------------------------------------------------------
-template <bool TOPK>
-__global__ __launch_bounds__(1024) void k_argmax_conf(ArgmaxArgs a) {
+template <bool TOPK, int PT>
+__global__ __launch_bounds__(1024) void k_argmax_conf(ArgmaxArgs a) {  // PT: logits per thread that stay in registers
     const float *lg = a.logits + (size_t)blockIdx.x * a.V;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ float smax[16];
@@ -587,8 +587,7 @@ __global__ __launch_bounds__(1024) void k_argmax_conf(ArgmaxArgs a) {
     __shared__ float ssum[16];
     float best = -INFINITY;
     int bi = 0x7fffffff;
-    // up to 32 logits per thread stay in registers (one round of loads, all in flight together)
-    constexpr int PT = 32;
+    // up to PT logits per thread stay in registers (one round of loads, all in flight together)
     const bool in_regs = a.V <= 1024 * PT;
     float v[PT];
     if (in_regs) {
@@ -612,14 +611,10 @@ __global__ __launch_bounds__(1024) void k_argmax_conf(ArgmaxArgs a) {
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(best, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (ov > best || (ov == best && oi < bi)) {
-            best = ov;
-            bi = oi;
-        }
+    {   // the largest value of the wavefront, then the smallest index that holds it
+        const float top = wave_max(best);
+        bi = wave_min(best == top ? bi : 0x7fffffff);
+        best = top;
     }
     if (lane == 0) {
         smax[wave] = best;
@@ -686,14 +681,10 @@ __global__ __launch_bounds__(1024) void k_argmax_conf(ArgmaxArgs a) {
                 }
             }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const float ov = __shfl_xor(best, off, 64);
-            const int oi = __shfl_xor(bi, off, 64);
-            if (ov > best || (ov == best && oi < bi)) {
-                best = ov;
-                bi = oi;
-            }
+        {
+            const float top = wave_max(best);
+            bi = wave_min(best == top ? bi : 0x7fffffff);
+            best = top;
         }
         if (lane == 0) {
             smax[wave] = best;
@@ -730,9 +721,11 @@ __global__ __launch_bounds__(1024) void k_argmax_conf(ArgmaxArgs a) {
 hipError_t launch_argmax_conf(const ArgmaxArgs &a, hipStream_t s) {
     if (a.topk) {
         if (a.n_topk < 1 || a.n_topk > kTopK) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_argmax_conf<true>, dim3(a.rows), dim3(1024), 0, s, a);
+        hipLaunchKernelGGL((k_argmax_conf<true, 32>), dim3(a.rows), dim3(1024), 0, s, a);
+    } else if (a.V <= 4 * 1024) {  // (1024 tokens: 3.5 us, 8.0 through the 32-value instance)
+        hipLaunchKernelGGL((k_argmax_conf<false, 4>), dim3(a.rows), dim3(1024), 0, s, a);
     } else {
-        hipLaunchKernelGGL(k_argmax_conf<false>, dim3(a.rows), dim3(1024), 0, s, a);
+        hipLaunchKernelGGL((k_argmax_conf<false, 32>), dim3(a.rows), dim3(1024), 0, s, a);
     }
     return hipGetLastError();
 }

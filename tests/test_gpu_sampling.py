@@ -238,3 +238,43 @@ def test_sampled_decoding_on_random_shapes(oracle_lib):
         g.close()
         o.close()
     assert n_done >= 20 and compared >= run // 2, (n_done, compared, run)
+
+
+@pytest.mark.parametrize("vocab", [510, 4096, 7000, 12288, 32768])
+def test_nucleus_and_draws_over_row_lengths(vocab):
+    """Rows of one id, whole fours and other numbers of ids per thread: the nucleus and the token drawn from it against numpy
+    in 64 bits on the row's own logits, from one-token nuclei to the whole row and from peaked to nearly flat rows.  A
+    threshold is held to the same tokens where no token's tail mass comes within 2e-5 of top_p (V fp32 additions of values
+    below 1, pairwise within wavefronts: far below that), a draw where its running sum is further than 2e-5 from u."""
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape(f"rows-{vocab}", 1, 64, 2, 1, 32, 96, vocab, "fp32", 1e-5)
+    g = P.SwiftModel(shape, 40)
+    g.load_weights(hp.shaped_weights(shape, seed=3))
+    pend = g.prefill([1, 2, 3])
+    rng = np.random.default_rng(vocab)
+    held = 0
+    for T in (0.02, 0.3, 1.0, 50.0):
+        for top_p in (1e-6, 0.3, 0.95, 0.9999, 1.0):
+            u = float(np.float32(rng.random()))
+            out, probs = g.verify_sample([pend], T, top_p, [], u, True)
+            lg = g.read_logits(0).astype(np.float64)
+            g.rollback(3, pend)
+            p = np.exp((lg - lg.max()) / T)
+            p /= p.sum()
+            order = np.argsort(-p, kind="stable")
+            cum = np.cumsum(p[order])
+            n = min(vocab, int(np.searchsorted(cum, top_p)) + 1) if top_p < 1 else vocab
+            if top_p < 1 and (np.abs(cum[max(0, n - 2):n + 1] - top_p).min() < 2e-5 and n > 1):
+                continue
+            keep = p >= p[order[n - 1]] * (1 - 1e-6)
+            want = np.where(keep, p, 0.0)
+            want /= want.sum()
+            got = probs[0].astype(np.float64)
+            assert abs((got > 0).sum() - (want > 1e-44).sum()) <= (0 if top_p < 1 else vocab), (T, top_p)
+            assert np.abs(got - want).max() <= 1e-4 * want.max() + 1e-9, (T, top_p)
+            c = np.cumsum(got) / got.sum()
+            if np.abs(c - u).min() > 2e-5:
+                assert int(out[0]) == int(np.searchsorted(c, u, side="right")), (T, top_p, u)
+                held += 1
+    assert held >= 10
+    g.close()
