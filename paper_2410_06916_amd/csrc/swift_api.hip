@@ -75,7 +75,7 @@ struct Layout {
     int nb32;                         // > 0: values transposed in blocks of 32 slots, nb32 blocks per kv head
     bool mfma_attn;                   // decode / draft / verify attention on the matrix cores (bf16, heads of 64 or 128)
     uint64_t q_s;  // queries as two bf16 terms (matrix-core attention)
-    uint64_t x, q, att, h, logits, part_o, part_ml, out_tok, out_conf, out_topk;
+    uint64_t x, q, att, h, logits, part_o, part_ml, out_tok;
     uint64_t samp_q, samp_p, samp_out;  // speculative sampling: draft and target distributions [16][V], results
     // tiled path: split activations (three bf16 terms, MFMA B layout), RMSNorm partials, split-K scratch
     uint64_t xs, as_, hs, pss, mv_part, mv_counters;
@@ -149,8 +149,6 @@ Layout make_layout(const swift_model_config &c) {
     L.part_o = take((uint64_t)kMaxRows * c.n_q_heads * L.n_split_max * c.head_dim * 4);
     L.part_ml = take((uint64_t)kMaxRows * c.n_q_heads * L.n_split_max * 2 * 4);
     L.out_tok = take(kMaxBlockRows * 4);
-    L.out_conf = take(kMaxBlockRows * 4);
-    L.out_topk = take(kMaxBlockRows * kTopK * 4);
     L.samp_q = take((uint64_t)kMaxRows * V * 4);
     L.samp_p = take((uint64_t)kMaxRows * V * 4);
     L.samp_out = take(256);
@@ -274,9 +272,13 @@ struct swift_ctx {
     bool no_events;     // the current call must not create HIP events (allocation-free entry point)
     std::vector<bool> loaded;  // per tensor slot
     int n_loaded;
-    // pinned host staging for results
+    // pinned host memory that the kernels write results to: tokens and confidences by row, sampled tokens, .. (swift_create)
     int32_t *h_tok;
     float *h_conf;
+    int32_t *h_draw;
+    // the next one-row pass: where its token lies on the device (nullptr: the caller's), and which row its results go to
+    const int32_t *feed;
+    int out_row;
     // decoding state
     int n;            // cache length
     int32_t pending;  // -1 before prefill
@@ -342,6 +344,12 @@ char *kv_base(swift_ctx *x, int layer, int which) {
     return x->base + x->L.kv + (uint64_t)layer * (x->L.kv_k_bytes + x->L.kv_v_bytes) + (which ? x->L.kv_k_bytes : 0);
 }
 
+// The arg-max of rows [0, rows) of the logits; results to rows [x->out_row, ..).
+ArgmaxArgs argmax_args(swift_ctx *x, int rows) {
+    return ArgmaxArgs{dptr<float>(x, x->L.logits), x->c.vocab, rows, dptr<int32_t>(x, x->L.out_tok) + x->out_row, x->h_tok + x->out_row,
+                      x->h_conf + x->out_row, x->want_topk ? x->h_topk : nullptr, kTopK};
+}
+
 // The rows of a token tree: level of each block row, block row of the first candidate of each level (the only
 // one with children).
 typedef TreeTab TreeRows;
@@ -395,7 +403,9 @@ int forward_block_rows(swift_ctx *x, const int32_t *tokens, int R, int pos0, con
     ea.E = x->base + L.embed;
     ea.H = H;
     ea.R = R;
+    ea.V = V;
     memcpy(ea.tokens, tokens, R * sizeof(int32_t));
+    ea.feed = x->feed;
     ea.x = xr;
     HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)R * H * eb, [&] { return launch_embed(c.dtype, ea, s); }));
     for (int l = 0; l < c.n_layers; ++l) {
@@ -439,8 +449,7 @@ int forward_block_rows(swift_ctx *x, const int32_t *tokens, int R, int pos0, con
     }
     if (want_logits) {
         if ((rc = linear(SWIFT_KC_LMHEAD, EPI_LOGITS, L.lm_head, V, H, xr, dptr<float>(x, L.final_norm), lr, V, 0))) return rc;
-        ArgmaxArgs m{lr, V, R, dptr<int32_t>(x, L.out_tok), dptr<float>(x, L.out_conf),
-                     x->want_topk ? dptr<int32_t>(x, L.out_topk) : nullptr, kTopK};
+        const ArgmaxArgs m = argmax_args(x, R);
         HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)R * V * 4, [&] { return launch_argmax_conf(m, s); }));
     }
     return SWIFT_OK;
@@ -558,6 +567,8 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
         ea.E = dptr<uint16_t>(x, L.embed);
         ea.H = H;
         ea.R = last * kMaxBlockRows + R;
+        ea.V = V;
+        ea.feed = x->feed;
         ea.x = xf;
         ea.xs = xs;
         ea.gain_next = gain_of(0);
@@ -743,8 +754,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
     }
 
     if (want_logits) {
-        ArgmaxArgs am{dptr<float>(x, L.logits), V, R, dptr<int32_t>(x, L.out_tok), dptr<float>(x, L.out_conf),
-                      x->want_topk ? dptr<int32_t>(x, L.out_topk) : nullptr, kTopK};
+        const ArgmaxArgs am = argmax_args(x, R);
         HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)R * V * 4, [&] { return launch_argmax_conf(am, s); }));
     }
     return SWIFT_OK;
@@ -782,8 +792,7 @@ int macro_sub_logits(swift_ctx *x, int sb, int rows) {
     m.ld_out = c.vocab;
     HIP_TRY(timed(x, SWIFT_KC_LMHEAD, (uint64_t)m.O * m.K * 2,
                   [&] { return launch_mv(EPI_LOGITS, m, x->n_cu, x->tune_ks[SWIFT_KC_LMHEAD], x->tune_wg[SWIFT_KC_LMHEAD], s); }, true));
-    ArgmaxArgs am{dptr<float>(x, L.logits), c.vocab, rows, dptr<int32_t>(x, L.out_tok), dptr<float>(x, L.out_conf),
-                  x->want_topk ? dptr<int32_t>(x, L.out_topk) : nullptr, kTopK};
+    const ArgmaxArgs am = argmax_args(x, rows);
     HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)rows * c.vocab * 4, [&] { return launch_argmax_conf(am, s); }));
     return SWIFT_OK;
 }
@@ -799,13 +808,26 @@ int forward_block(swift_ctx *x, const int32_t *tokens, int R, int pos0, const ui
     return forward_block_rows(x, tokens, R, pos0, skip, want_logits, reuse_kv, tree);
 }
 
-// Copies rows [0, rows) of the token / confidence results to the pinned staging area and waits.
-int read_results(swift_ctx *x, int rows) {
-    // (tokens and confidences lie kMaxBlockRows words apart on the device and in the staging area alike: one copy)
-    if (x->L.out_conf != x->L.out_tok + kMaxBlockRows * 4 || (char *)x->h_conf != (char *)x->h_tok + kMaxBlockRows * 4)
-        return fail(SWIFT_EINVAL, "result areas are not adjacent");
-    HIP_TRY(hipMemcpyAsync(x->h_tok, dptr<int32_t>(x, x->L.out_tok), (kMaxBlockRows + rows) * 4, hipMemcpyDeviceToHost, x->stream));
+bool is_pinned(const void *p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeHost;
+}
+
+// Waits for the token / confidence results of rows [0, rows), and copies `bytes` from src on the device to dst, if given.  A
+// copy to pinned memory goes out ahead of the one wait; one to pageable memory holds the host up by itself, and longer while the
+// device is still at work than after the wait (a 400 us pass: by 9 us).
+int read_results(swift_ctx *x, int rows, void *dst = nullptr, const void *src = nullptr, size_t bytes = 0) {
+    const bool ahead = dst && is_pinned(dst);
+    if (ahead) HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, x->stream));
     HIP_TRY(hipStreamSynchronize(x->stream));
+    if (dst && !ahead) {
+        HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, x->stream));
+        HIP_TRY(hipStreamSynchronize(x->stream));
+    }
     // a token id is fed back as an embedding row index: never pass on one outside the vocabulary
     for (int i = 0; i < rows; ++i)
         if (x->h_tok[i] < 0 || x->h_tok[i] >= x->c.vocab)
@@ -924,13 +946,16 @@ extern "C" int swift_create(const swift_model_config *cfg, void *device_mem, uin
     x->gemm_rgw = 0;
     x->h_tok = nullptr;
     x->h_conf = nullptr;
-    hipError_t e = hipHostMalloc((void **)&x->h_tok, (2 * kMaxBlockRows + 4 + kTopK) * 4, hipHostMallocDefault);
+    x->feed = nullptr;
+    x->out_row = 0;
+    hipError_t e = hipHostMalloc((void **)&x->h_tok, (3 * kMaxBlockRows + kTopK) * 4, hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess) {
         delete x;
         return fail(SWIFT_EDEVICE, std::string("hipHostMalloc: ") + hipGetErrorString(e));
     }
     x->h_conf = (float *)(x->h_tok + kMaxBlockRows);
-    x->h_topk = x->h_tok + 2 * kMaxBlockRows + 4;
+    x->h_draw = x->h_tok + 2 * kMaxBlockRows;
+    x->h_topk = x->h_tok + 3 * kMaxBlockRows;
 
     // rotary tables: angle = pos * theta^(-2i/d) in fp64, cos/sin rounded to fp32
     const int half = cfg->head_dim / 2;
@@ -1105,6 +1130,20 @@ extern "C" int swift_eval_mask(swift_ctx *x, const uint8_t *skip_mask, const int
     return SWIFT_OK;
 }
 
+namespace {
+// Confidences are never below zero (nor is anything below NaN): the drafting does not hang on them.
+inline bool never_stops(float conf_threshold) { return !(conf_threshold > 0.f); }
+// Draft pass j of a chain: row 0 holds `first` (j = 0) or the token at `feed` on the device; results to row j.
+int draft_pass(swift_ctx *x, int32_t first, int j, const uint8_t *skip_mask, const int32_t *feed) {
+    x->feed = j > 0 ? feed : nullptr;
+    x->out_row = j;
+    const int rc = forward_block(x, &first, 1, x->n + j, skip_mask, true);
+    x->feed = nullptr;
+    x->out_row = 0;
+    return rc;
+}
+}  // namespace
+
 extern "C" int swift_draft_step(swift_ctx *x, const uint8_t *skip_mask, int max_k, float conf_threshold,
                                 int32_t *draft_tokens, float *draft_conf, int *k_out) {
     if (!x || !skip_mask || !k_out) return fail(SWIFT_EINVAL, "null argument");
@@ -1117,7 +1156,22 @@ extern "C" int swift_draft_step(swift_ctx *x, const uint8_t *skip_mask, int max_
     x->k_verify = -1;     // the draft overwrites slots an outstanding verification wrote: its accept must fail
     x->tree_levels = -1;
     x->k_sampled = -1;
-    for (int j = 1; j <= max_k; ++j) {
+    if (max_k > 0 && never_stops(conf_threshold)) {
+        // all passes without a word from the host: each takes the token of the one before from where it was left on the device
+        // (us a call: 7B, 8 tokens 12050 -> 11923; fp32, 4 layers of 256, 4 tokens and their verification 528 -> 444)
+        for (int j = 0; j < max_k; ++j) {
+            int rc = draft_pass(x, prev, j, skip_mask, dptr<int32_t>(x, x->L.out_tok) + j - 1);
+            if (rc) return rc;
+        }
+        int rc = read_results(x, max_k);
+        if (rc) return rc;
+        for (; k < max_k; ++k) {
+            draft_tokens[k] = x->h_tok[k];
+            draft_conf[k] = x->h_conf[k];
+            x->st.draft_passes++;
+        }
+    }
+    for (int j = k + 1; j <= max_k; ++j) {
         int rc = forward_block(x, &prev, 1, x->n + j - 1, skip_mask, true);
         if (rc) return rc;
         rc = read_results(x, 1);
@@ -1137,13 +1191,8 @@ namespace {
 int verify_impl(swift_ctx *x, const int32_t *tokens, int k, int32_t *target_tokens, float *logits_out) {
     int rc = forward_block(x, tokens, k + 1, x->n, nullptr, true);
     if (rc) return rc;
-    rc = read_results(x, k + 1);
+    rc = read_results(x, k + 1, logits_out, dptr<float>(x, x->L.logits), (size_t)(k + 1) * x->c.vocab * 4);
     if (rc) return rc;
-    if (logits_out) {
-        HIP_TRY(hipMemcpyAsync(logits_out, dptr<float>(x, x->L.logits), (size_t)(k + 1) * x->c.vocab * 4,
-                               hipMemcpyDeviceToHost, x->stream));
-        HIP_TRY(hipStreamSynchronize(x->stream));
-    }
     for (int i = 0; i <= k; ++i) {
         x->vtokens[i] = tokens[i];
         x->targets[i] = x->h_tok[i];
@@ -1287,7 +1336,6 @@ extern "C" int swift_draft_step_topk(swift_ctx *x, const uint8_t *skip_mask, int
         int rc = forward_block(x, &prev, 1, x->n + j - 1, skip_mask, true);
         x->want_topk = false;
         if (rc) return rc;
-        HIP_TRY(hipMemcpyAsync(x->h_topk, dptr<int32_t>(x, x->L.out_topk), kTopK * 4, hipMemcpyDeviceToHost, x->stream));
         rc = read_results(x, 1);
         if (rc) return rc;
         const float p = x->h_conf[0];
@@ -1328,13 +1376,8 @@ extern "C" int swift_verify_tree(swift_ctx *x, const int32_t *tokens, const int 
     if (x->n + rows > x->c.max_seq) return fail(SWIFT_ECAPACITY, "block would run past the cache capacity");
     int rc = forward_block(x, tokens, rows, x->n, nullptr, true, false, &t);
     if (rc) return rc;
-    rc = read_results(x, rows);
+    rc = read_results(x, rows, logits_out, dptr<float>(x, x->L.logits), (size_t)rows * x->c.vocab * 4);
     if (rc) return rc;
-    if (logits_out) {
-        HIP_TRY(hipMemcpyAsync(logits_out, dptr<float>(x, x->L.logits), (size_t)rows * x->c.vocab * 4, hipMemcpyDeviceToHost,
-                               x->stream));
-        HIP_TRY(hipStreamSynchronize(x->stream));
-    }
     for (int r = 0; r < rows; ++r) {
         x->vtokens[r] = tokens[r];
         x->targets[r] = x->h_tok[r];
@@ -1432,10 +1475,9 @@ extern "C" int swift_prefill_sample(swift_ctx *x, const int32_t *prompt, int n_p
     const int last_row = (n_prompt - 1) % block;
     rc = warp_rows(x, last_row, 1, temperature, top_p, x->L.samp_p, 0);
     if (rc) return rc;
-    HIP_TRY(launch_draw(dptr<float>(x, x->L.samp_p), x->c.vocab, u, dptr<int32_t>(x, x->L.samp_out), x->stream));
-    HIP_TRY(hipMemcpyAsync(x->h_topk, dptr<int32_t>(x, x->L.samp_out), 4, hipMemcpyDeviceToHost, x->stream));
+    HIP_TRY(launch_draw(dptr<float>(x, x->L.samp_p), x->c.vocab, u, dptr<int32_t>(x, x->L.samp_out), x->h_draw, x->stream));
     HIP_TRY(hipStreamSynchronize(x->stream));
-    x->pending = x->h_topk[0];
+    x->pending = x->h_draw[0];
     *first_token = x->pending;
     return SWIFT_OK;
 }
@@ -1457,23 +1499,24 @@ extern "C" int swift_draft_step_sample(swift_ctx *x, const uint8_t *skip_mask, i
     x->k_verify = -1;     // the draft overwrites slots an outstanding verification wrote: its accept must fail
     x->tree_levels = -1;
     x->k_sampled = -1;
-    for (int j = 1; j <= max_k; ++j) {
-        rc = forward_block(x, &prev, 1, x->n + j - 1, skip_mask, true);
+    const bool chain = never_stops(conf_threshold);  // (as in swift_draft_step)
+    int32_t *drawn = dptr<int32_t>(x, x->L.samp_out);
+    for (int j = 0; j < max_k; ++j) {
+        rc = draft_pass(x, prev, j, skip_mask, drawn);
         if (rc) return rc;
-        rc = warp_rows(x, 0, 1, temperature, top_p, x->L.samp_q, k);
+        rc = warp_rows(x, 0, 1, temperature, top_p, x->L.samp_q, j);
         if (rc) return rc;
-        HIP_TRY(launch_draw(dptr<float>(x, x->L.samp_q) + (size_t)k * x->c.vocab, x->c.vocab, u[j - 1],
-                            dptr<int32_t>(x, x->L.samp_out), x->stream));
-        HIP_TRY(hipMemcpyAsync(x->h_topk, dptr<int32_t>(x, x->L.samp_out), 4, hipMemcpyDeviceToHost, x->stream));
-        rc = read_results(x, 1);
+        HIP_TRY(launch_draw(dptr<float>(x, x->L.samp_q) + (size_t)j * x->c.vocab, x->c.vocab, u[j], drawn, x->h_draw + j, x->stream));
+        if (chain && j + 1 < max_k) continue;
+        rc = read_results(x, j + 1);
         if (rc) return rc;
-        prev = x->h_topk[0];
-        draft_tokens[k] = prev;
-        draft_conf[k] = x->h_conf[0];
-        x->sampled[k] = prev;
-        ++k;
-        x->st.draft_passes++;
-        if (x->h_conf[0] < conf_threshold) break;
+        for (; k <= j; ++k) {
+            draft_tokens[k] = x->h_draw[k];
+            draft_conf[k] = x->h_conf[k];
+            x->sampled[k] = x->h_draw[k];
+            x->st.draft_passes++;
+        }
+        if (x->h_conf[j] < conf_threshold) break;
     }
     x->k_sampled = k;
     *k_out = k;
@@ -1511,23 +1554,17 @@ extern "C" int swift_verify_sample(swift_ctx *x, const int32_t *tokens, int k, f
         sa.u_accept[i] = u_accept[i];
     }
     sa.u_final = u_final;
-    sa.out = dptr<int32_t>(x, x->L.samp_out);
+    sa.out = x->h_draw;
     HIP_TRY(timed(x, SWIFT_KC_OTHER, (uint64_t)x->c.vocab * 8, [&] { return launch_spec_accept(sa, x->stream); }));
-    HIP_TRY(hipMemcpyAsync(x->h_topk, dptr<int32_t>(x, x->L.samp_out), 8, hipMemcpyDeviceToHost, x->stream));
-    rc = read_results(x, k + 1);
+    rc = read_results(x, k + 1, probs_out, dptr<float>(x, x->L.samp_p), (size_t)(k + 1) * x->c.vocab * 4);
     if (rc) return rc;
-    if (probs_out) {
-        HIP_TRY(hipMemcpyAsync(probs_out, dptr<float>(x, x->L.samp_p), (size_t)(k + 1) * x->c.vocab * 4, hipMemcpyDeviceToHost,
-                               x->stream));
-        HIP_TRY(hipStreamSynchronize(x->stream));
-    }
-    const int m = x->h_topk[0];
+    const int m = x->h_draw[0];
     if (m < 0 || m > k) return fail(SWIFT_EDEVICE, "acceptance kernel returned an impossible count");
     for (int i = 0; i < m; ++i) emitted[i] = tokens[1 + i];
-    emitted[m] = x->h_topk[1];
+    emitted[m] = x->h_draw[1];
     *n_emitted = m + 1;
     x->n += m + 1;
-    x->pending = x->h_topk[1];
+    x->pending = x->h_draw[1];
     x->k_verify = -1;
     x->tree_levels = -1;
     x->k_sampled = -1;

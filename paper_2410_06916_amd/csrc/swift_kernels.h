@@ -73,8 +73,9 @@ hipError_t launch_gemv(int dtype, int epilogue, const GemvArgs &a, int n_cu, hip
 
 struct EmbedArgs {
     const void *E;  // [V][H]
-    int H, R;
+    int H, R, V;
     int32_t tokens[kMaxBlockRows];
+    const int32_t *feed;  // nullptr, or where row 0's token lies on the device (see EmbedRowsArgs)
     float *x;  // [R][H]
 };
 hipError_t launch_embed(int dtype, const EmbedArgs &a, hipStream_t s);
@@ -151,9 +152,11 @@ constexpr int kTopK = 10;  // candidates kept per row (SWIFT_TOPK)
 struct ArgmaxArgs {
     const float *logits;  // [rows][V]
     int V, rows;
-    int32_t *tokens;      // [rows]
-    float *conf;          // [rows]
-    int32_t *topk;        // nullptr, or [rows][kTopK]: the n_topk largest logits' indices, largest first,
+    // [rows] each.  `next` stays on the device (a following pass may take its token from there: EmbedRowsArgs::feed); tokens and
+    // confidences go straight to the host's pinned memory, where they are read once the stream has been waited for.
+    int32_t *next, *tokens;
+    float *conf;
+    int32_t *topk;        // nullptr, or [rows][kTopK] (pinned host memory too): the n_topk largest logits' indices, largest first,
     int n_topk;           //   equal values in index order (topk[0] is the arg-max)
 };
 hipError_t launch_argmax_conf(const ArgmaxArgs &a, hipStream_t s);
@@ -169,8 +172,8 @@ struct WarpArgs {
     float *probs;         // [rows][V]
 };
 hipError_t launch_warp(const WarpArgs &a, hipStream_t s);
-// out[0] = the first token j with probs[0] + .. + probs[j] > u * (sum of probs), 0 <= u < 1
-hipError_t launch_draw(const float *probs, int V, float u, int32_t *out, hipStream_t s);
+// out[0] (on the device) = host_out[0] (pinned) = the first token j with probs[0] + .. + probs[j] > u * (sum of probs), 0 <= u < 1
+hipError_t launch_draw(const float *probs, int V, float u, int32_t *out, int32_t *host_out, hipStream_t s);
 // Keep / replace rule over a verified block of k draft tokens x[i] drawn from q[i] (rows of [.][V]), target
 // distributions p[0..k]: out[0] = number of tokens kept, out[1] = the token that follows them.
 struct SpecAcceptArgs {
@@ -179,7 +182,7 @@ struct SpecAcceptArgs {
     int32_t x[kMaxRows];
     float u_accept[kMaxRows];
     float u_final;
-    int32_t *out;
+    int32_t *out;  // [2], pinned host memory
 };
 hipError_t launch_spec_accept(const SpecAcceptArgs &a, hipStream_t s);
 
@@ -322,8 +325,11 @@ hipError_t launch_gemm(int epilogue, const MvArgs &a, const MacroArgs &ma, int n
 // those of a macro block, row r at row r % 64 of sub-block r / 64, found at the given element strides.
 struct EmbedRowsArgs {
     const uint16_t *E;  // [V][H] bf16 row-major
-    int H, R;
+    int H, R, V;
     int RL;             // layout code of xs: block_row_layout
+    // nullptr, or where row 0's token lies on the device: written by the launches before this one, in [0, V) by construction
+    // (clamped all the same: it indexes E)
+    const int32_t *feed;
     float *x;           // [R][H]
     uint16_t *xs;       // [H/8][3 RL][8]
     const float *gain_next;

@@ -214,13 +214,14 @@ hipError_t launch_gemv(int dtype, int epi, const GemvArgs &a, int n_cu, hipStrea
 template <typename T>
 __global__ void k_embed(EmbedArgs a) {
     const int r = blockIdx.y;
-    const typename T::elem *row = (const typename T::elem *)a.E + (size_t)a.tokens[r] * a.H;
+    const int tok = a.feed ? min(max(a.feed[0], 0), a.V - 1) : a.tokens[r];
+    const typename T::elem *row = (const typename T::elem *)a.E + (size_t)tok * a.H;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.H; i += gridDim.x * blockDim.x)
         a.x[(size_t)r * a.H + i] = T::load1(row + i);
 }
 
 hipError_t launch_embed(int dtype, const EmbedArgs &a, hipStream_t s) {
-    if (dtype != F32 || a.R < 1 || a.R > kMaxBlockRows) return hipErrorInvalidValue;  // (bf16 models: launch_embed_rows)
+    if (dtype != F32 || a.R < 1 || a.R > kMaxBlockRows || (a.feed && a.R != 1)) return hipErrorInvalidValue;  // (bf16 models: launch_embed_rows)
     hipLaunchKernelGGL(k_embed<F32T>, dim3((a.H + 255) / 256, a.R), dim3(256), 0, s, a);
     return hipGetLastError();
 }
@@ -645,6 +646,7 @@ __global__ __launch_bounds__(1024) void k_argmax_conf(ArgmaxArgs a) {  // PT: lo
     if (tid == 0) {
         float t = 0.f;
         for (int w = 0; w < 16; ++w) t += ssum[w];
+        a.next[blockIdx.x] = bi;
         a.tokens[blockIdx.x] = bi;
         a.conf[blockIdx.x] = 1.0f / t;
     }

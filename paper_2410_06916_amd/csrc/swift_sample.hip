@@ -231,12 +231,15 @@ __global__ __launch_bounds__(kThreads) void k_warp(WarpArgs a) {
 }
 #undef SWIFT_EACH
 
-// out[0] = a draw from probs (one row) with the uniform u
-__global__ __launch_bounds__(kThreads) void k_draw(const float *probs, int V, float u, int32_t *out) {
+// out[0] = host_out[0] = a draw from probs (one row) with the uniform u
+__global__ __launch_bounds__(kThreads) void k_draw(const float *probs, int V, float u, int32_t *out, int32_t *host_out) {
     __shared__ float sh[16];
     __shared__ int shi[32];
     const int tok = block_draw(RowWeights{probs}, V, u, sh, shi, nullptr);
-    if (threadIdx.x == 0) out[0] = tok;
+    if (threadIdx.x == 0) {
+        out[0] = tok;
+        host_out[0] = tok;
+    }
 }
 
 // The keep / replace rule over a verified block: draft token x_i (drawn from q_i) is kept iff
@@ -279,9 +282,9 @@ hipError_t launch_warp(const WarpArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_draw(const float *probs, int V, float u, int32_t *out, hipStream_t s) {
+hipError_t launch_draw(const float *probs, int V, float u, int32_t *out, int32_t *host_out, hipStream_t s) {
     if (V < 1 || !(u >= 0.f && u < 1.f)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_draw, dim3(1), dim3(kThreads), 0, s, probs, V, u, out);
+    hipLaunchKernelGGL(k_draw, dim3(1), dim3(kThreads), 0, s, probs, V, u, out, host_out);
     return hipGetLastError();
 }
 

@@ -110,7 +110,8 @@ __global__ __launch_bounds__(256) void k_embed_rows(EmbedRowsArgs a, EmbedTokens
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = 0.f;
     if (ok) {
-        const u32x4 e = *(const u32x4 *)(a.E + (size_t)tok.id[r] * a.H + 8 * c);
+        const int id = a.feed ? min(max(a.feed[0], 0), a.V - 1) : tok.id[r];
+        const u32x4 e = *(const u32x4 *)(a.E + (size_t)id * a.H + 8 * c);
         const f32x4 g0 = *(const f32x4 *)(a.gain_next + 8 * c), g1 = *(const f32x4 *)(a.gain_next + 8 * c + 4);
         float *x = a.x + sub * a.sub_x + (size_t)rs * a.H + 8 * c;
         u32x4 t[3];
@@ -151,7 +152,7 @@ static hipError_t launch_embed_rows_n(const EmbedRowsArgs &a, const int32_t *tok
 }
 
 hipError_t launch_embed_rows(const EmbedRowsArgs &a, const int32_t *tokens, hipStream_t s) {
-    if (a.R < 1 || (a.H & 7) != 0) return hipErrorInvalidValue;
+    if (a.R < 1 || (a.H & 7) != 0 || (a.feed && a.R != 1)) return hipErrorInvalidValue;
     if (a.R <= kMaxBlockRows) return launch_embed_rows_n<kMaxBlockRows>(a, tokens, s);
     for (int r0 = 0; r0 < a.R; r0 += kEmbedRows) {
         EmbedRowsArgs b = a;

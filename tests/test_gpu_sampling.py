@@ -278,3 +278,35 @@ def test_nucleus_and_draws_over_row_lengths(vocab):
                 held += 1
     assert held >= 10
     g.close()
+
+
+@pytest.mark.parametrize("shape", [hp.SMALL_GQA, hp.SMALL_GQA_BF16], ids=lambda s: s.name)
+def test_drafting_without_a_threshold_equals_pass_by_pass(shape):
+    """A threshold that no confidence can fall below sends all draft passes out at once, each taking its token from the device;
+    one that none of these does (1e-30) waits for every token.  Same tokens, confidences, logits, cache and counts, greedy and
+    sampled, 1 to 31 tokens, NaN and negative thresholds included."""
+    import paper_2410_06916_amd as P
+    g = P.SwiftModel(shape, 64)
+    g.load_weights(hp.shaped_weights(shape, seed=9))
+    mask = np.zeros(2 * shape.n_layers, np.uint8)
+    mask[1] = 1
+    u = np.random.default_rng(1).random(31).astype(np.float32)
+    res = []
+    for thr in (1e-30, 0.0, -1.0, float("nan")):
+        pend = g.prefill(si.uniform_ids(3, 9, shape.vocab))
+        out = []
+        for k in (1, 2, 31):
+            tok, conf = g.draft_step(mask, k, thr)
+            out += [tok, conf, g.read_logits(0), *g.read_kv(0, 9 + k - 1)]
+            tok, conf = g.draft_step_sample(mask, k, thr, 0.8, 0.9, u[:k])
+            em, pr = g.verify_sample(np.concatenate([[pend], tok]), 0.8, 0.9, u[:k], 0.5, True)
+            g.rollback(9, pend)
+            out += [tok, conf, em, pr]
+        out.append(np.array([g.stats()["draft_passes"]]))
+        res.append(out)
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert np.array_equal(a, b)
+    tok, conf = g.draft_step(mask, 0, 0.0)
+    assert tok.size == 0 and conf.size == 0
+    g.close()
