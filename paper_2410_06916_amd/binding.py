@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import threading
+import weakref
 from typing import Dict, Optional, Sequence
 
 import numpy as np
@@ -168,6 +170,37 @@ def pass_bytes(cfg: ModelConfig, skip: Optional[np.ndarray], n_ctx: int, rows: i
     return n.value
 
 
+# Rows of logits or probabilities that a call returns lie in pinned memory, which the device writes to at the link's rate (31 rows of
+# 32000: 80 us, 230 into pageable memory), from torch's caching host allocator: an array's memory goes back there with the
+# array.  What callers hold on to is bounded: past _PINNED_MAX bytes, and for less than _PINNED_MIN, rows are pageable.
+_PINNED_MIN, _PINNED_MAX = 1 << 16, 1 << 28
+_pinned_bytes = 0
+_pinned_lock = threading.Lock()
+
+
+def _pinned_count(n: int) -> bool:
+    """Takes (n > 0) or gives back (n < 0) pinned bytes; False if there is no room for them."""
+    global _pinned_bytes
+    with _pinned_lock:
+        if n > 0 and _pinned_bytes + n > _PINNED_MAX:
+            return False
+        _pinned_bytes += n
+        return True
+
+
+def _host_rows(torch, rows: int, width: int) -> np.ndarray:
+    n = 4 * rows * width
+    if n >= _PINNED_MIN and _pinned_count(n):
+        try:
+            a = torch.empty((rows, width), dtype=torch.float32, pin_memory=True).numpy()
+        except BaseException:
+            _pinned_count(-n)
+            raise
+        weakref.finalize(a, _pinned_count, -n).atexit = False
+        return a
+    return np.empty((rows, width), np.float32)
+
+
 class SwiftModel:
     """One context: device arena (a torch uint8 tensor), stream (torch's current stream of the
     device at construction) and the C-ABI calls."""
@@ -243,7 +276,7 @@ class SwiftModel:
         t = np.ascontiguousarray(tokens, np.int32)
         k = t.size - 1
         tgt = np.zeros(k + 1, np.int32)
-        lg = np.empty((k + 1, self.cfg.vocab), np.float32) if want_logits else None
+        lg = _host_rows(self.torch, k + 1, self.cfg.vocab) if want_logits else None
         _chk(lib().swift_verify(self._h, _p(t, C.c_int32), k, _p(tgt, C.c_int32),
                                 _p(lg, C.c_float) if want_logits else None), "swift_verify")
         return tgt, lg
@@ -253,7 +286,7 @@ class SwiftModel:
         t = np.ascontiguousarray(tokens, np.int32)
         k = t.size - 1
         tgt = np.zeros(k + 1, np.int32)
-        lg = np.empty((k + 1, self.cfg.vocab), np.float32) if want_logits else None
+        lg = _host_rows(self.torch, k + 1, self.cfg.vocab) if want_logits else None
         _chk(lib().swift_verify_static(self._h, _p(t, C.c_int32), k, _p(tgt, C.c_int32),
                                        _p(lg, C.c_float) if want_logits else None), "swift_verify_static")
         return tgt, lg
@@ -284,7 +317,7 @@ class SwiftModel:
         rows = np.concatenate([[self.pending]] + [np.asarray(l, np.int32) for l in levels]).astype(np.int32)
         width = np.array([len(l) for l in levels], np.intc)
         tgt = np.zeros(rows.size, np.int32)
-        lg = np.empty((rows.size, self.cfg.vocab), np.float32) if want_logits else None
+        lg = _host_rows(self.torch, rows.size, self.cfg.vocab) if want_logits else None
         _chk(lib().swift_verify_tree(self._h, _p(rows, C.c_int32), _p(width, C.c_int) if len(levels) else None,
                                      len(levels), _p(tgt, C.c_int32), _p(lg, C.c_float) if want_logits else None),
              "swift_verify_tree")
@@ -326,7 +359,7 @@ class SwiftModel:
         assert ua.size >= k
         em = np.zeros(k + 1, np.int32)
         n = C.c_int()
-        pr = np.empty((k + 1, self.cfg.vocab), np.float32) if want_probs else None
+        pr = _host_rows(self.torch, k + 1, self.cfg.vocab) if want_probs else None
         _chk(lib().swift_verify_sample(self._h, _p(t, C.c_int32), k, temperature, top_p,
                                        _p(ua, C.c_float) if k else None, u_final, _p(em, C.c_int32), C.byref(n),
                                        _p(pr, C.c_float) if want_probs else None), "swift_verify_sample")

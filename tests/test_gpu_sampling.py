@@ -310,3 +310,33 @@ def test_drafting_without_a_threshold_equals_pass_by_pass(shape):
     tok, conf = g.draft_step(mask, 0, 0.0)
     assert tok.size == 0 and conf.size == 0
     g.close()
+
+
+def test_returned_rows_outlive_later_calls_and_their_pinned_memory_is_bounded(monkeypatch):
+    """Logits that a call has returned stay what they were while later calls return theirs, from pinned memory up to a bound
+    and from pageable memory past it; the bound counts only what is still held."""
+    import gc
+    import paper_2410_06916_amd as P
+    from paper_2410_06916_amd import binding as B
+    shape = si.ModelShape("pinned", 1, 64, 2, 1, 32, 96, 33002, "bf16", 1e-5)
+    g = P.SwiftModel(shape, 40)
+    g.load_weights(hp.shaped_weights(shape, seed=2))
+    pend = g.prefill([5, 6, 7])
+    row = 4 * shape.vocab
+    gc.collect()
+    before = B._pinned_bytes
+    monkeypatch.setattr(B, "_PINNED_MAX", before + 3 * row)
+    held = []
+    for i in range(5):
+        held.append(g.verify([pend], True)[1])
+        g.rollback(3, pend)
+        assert B._pinned_bytes == before + min(i + 1, 3) * row
+    assert all(np.array_equal(h, held[0]) for h in held)
+    view = held[0][0, 5:]
+    del held[0], held[0]
+    gc.collect()
+    assert B._pinned_bytes == before + 2 * row      # (the view keeps its array)
+    del view, held
+    gc.collect()
+    assert B._pinned_bytes == before
+    g.close()
