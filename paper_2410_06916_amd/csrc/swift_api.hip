@@ -159,7 +159,7 @@ Layout make_layout(const swift_model_config &c) {
     L.mv_part_capacity = 8192;
     L.gemm_part_slots = 16384;
     L.mv_part = take((uint64_t)std::max(L.mv_part_capacity, L.gemm_part_slots) * 16 * kMaxBlockRows * 4);
-    L.mv_counters = take(4096 * 4);
+    L.mv_counters = take(kMvCounters * 4);
     L.stage_bytes = bf ? std::max(std::max(V * H, F * H), std::max(Q * H, KV * H)) * eb : 0;
     L.stage = take(L.stage_bytes);
     L.total = off;
@@ -1267,7 +1267,7 @@ extern "C" int swift_verify_static(swift_ctx *x, const int32_t *tokens, int k, i
             m.head_dim = d;
             m.part_capacity = x->L.mv_part_capacity;
             const int slots = mv_split_slots(m, x->n_cu);
-            if (slots > kStaticPartSlots || (mt.n_rg + 7) / 8 > (int)(kStaticCounterBytes / 4))
+            if (slots > kStaticPartSlots || (mt.n_rg + 7) / 8 > kMvCounters)
                 return fail(SWIFT_ECAPACITY, "swift_verify_static: a projection of this model needs more split-K scratch "
                                              "than the static array holds; use swift_verify");
         }

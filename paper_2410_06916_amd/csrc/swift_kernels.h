@@ -13,7 +13,8 @@ namespace swift {
 constexpr int kMaxRows = 32;       // rows of one verify block or token tree (SWIFT_MAX_BLOCK)
 constexpr int kMaxBlockRows = 64;  // rows of one prefill block
 // The static scratch array of swift_verify_static: [arrival counters][split-K partial sums][attention partials].
-constexpr size_t kStaticCounterBytes = 4096 * 4;
+constexpr int kMvCounters = 4096;  // arrival counters of the split projections
+constexpr size_t kStaticCounterBytes = kMvCounters * 4;
 constexpr int kStaticPartSlots = 8192;  // row-group-splits of kMaxRows rows, as the arena's area holds for such blocks
 constexpr size_t kStaticPartBytes = (size_t)kStaticPartSlots * 16 * kMaxRows * 4;  // 16 MiB
 constexpr size_t kStaticAttnBytes = SWIFT_STATIC_SCRATCH_BYTES - kStaticCounterBytes - kStaticPartBytes;
@@ -269,7 +270,7 @@ struct MvArgs {
                            // what is left of the fp32 value after hi), the operand form of the matrix-core attention
     // multi-row kernel only: split-K scratch
     float *part;           // [k splits][row group][R][16] fp32 partial results
-    int *counters;         // one per 8-row-group block, zero between launches
+    int *counters;         // [kMvCounters], zero between launches (one per wavefront of a row block)
     int part_capacity;     // row-group-splits the scratch can hold
     int S;                 // set by the launcher
     int kgroup;            // set by the launcher: K slices whose sums are added first (see mv_slice_group)
