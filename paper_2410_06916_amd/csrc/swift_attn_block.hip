@@ -40,10 +40,14 @@ __device__ inline bf16x8 pack_bf16x8(const uint16_t (&v)[8]) {
 // Scores of one half chunk (32 slots) are two MFMA tiles tt = 0, 1; tile row 4 g + i is slot
 // 8 g + 4 tt + i of the half, so that a lane's eight probabilities of the half are slots 8 g .. 8 g + 7:
 // the k range of its B operand in the second product.
-// A prompt macro block (a.sub_rows = 64) is one launch too: blockIdx.z is the sub-block, which is treated as a block
-// of its own whose partial results sit at the macro block's row numbers.
+// A prompt macro block (a.sub_rows = 64) is one launch too: blockIdx.z stands for the sub-block, which is treated as a block
+// of its own whose partial results sit at the macro block's row numbers.  Later sub-blocks reach further back and take longer,
+// so the order in which they are handed out is theirs from the last one on (they start first, the short ones fill what is left); where
+// all workgroups are resident at once, two to a compute unit, only the first half is handed out so and the second from the
+// first sub-block on, which pairs long ones with short ones (7B, 1024-row macro blocks over 1024-3072 slots: 95.8 us on average in
+// ascending order, 86.5).
 template <int D>
-__global__ __launch_bounds__(256, 2) void k_attn_block(AttnArgs am, int chunk) {
+__global__ __launch_bounds__(256, 2) void k_attn_block(AttnArgs am, int chunk, int paired) {
     constexpr int DC = D / 32;   // k steps of a score tile
     constexpr int DT = D / 16;   // 16-row tiles of O^T
     constexpr int PPR = D / 8;   // 16-byte pieces per cache row
@@ -54,12 +58,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_block(AttnArgs am, int chunk) {
     __shared__ __align__(16) uint16_t Vt[D * VP];
 
     AttnArgs a = am;
-    const int row_base = (int)blockIdx.z * 64;  // first row of this sub-block in the macro block
+    const int n_sub = gridDim.z, zb = blockIdx.z, first = paired ? (n_sub + 1) / 2 : n_sub;
+    const int sub = zb < first ? n_sub - 1 - zb : zb - first;
+    const int row_base = sub * 64;  // first row of this sub-block in the macro block
     if (am.sub_rows) {
         a.rows = min(64, am.rows - row_base);
         a.n_ctx = am.n_ctx + row_base;
-        a.q = am.q + (size_t)blockIdx.z * am.sub_q;
-        if (am.out_s) a.out_s = am.out_s + (size_t)blockIdx.z * am.sub_out_s;
+        a.q = am.q + (size_t)sub * am.sub_q;
+        if (am.out_s) a.out_s = am.out_s + (size_t)sub * am.sub_out_s;
     }
     const int head = blockIdx.x, sp = blockIdx.y, n_split = gridDim.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, g = lane >> 4;
@@ -280,10 +286,11 @@ hipError_t launch_attn_block(const AttnArgs &a, int n_cu, hipStream_t s) {
     const int n_split = (ctx + chunk - 1) / chunk;
     if ((int64_t)n_split * a.rows > (int64_t)kMaxRows * a.max_split) return hipErrorInvalidValue;
     const dim3 grid(a.n_q_heads, n_split, n_sub), block(256);
+    const int paired = a.n_q_heads * n_split * n_sub <= 2 * n_cu;
     if (a.head_dim == 128)
-        hipLaunchKernelGGL(k_attn_block<128>, grid, block, 0, s, a, chunk);
+        hipLaunchKernelGGL(k_attn_block<128>, grid, block, 0, s, a, chunk, paired);
     else
-        hipLaunchKernelGGL(k_attn_block<64>, grid, block, 0, s, a, chunk);
+        hipLaunchKernelGGL(k_attn_block<64>, grid, block, 0, s, a, chunk, paired);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_split == 1) return e;
     return launch_attn_combine(a, chunk, n_split, s);
