@@ -94,6 +94,22 @@ __device__ inline void am_write(const AttnArgs &a, int row, int e, float y) {
     }
 }
 
+// Four consecutive elements, the first a multiple of four.
+__device__ inline void am_write4(const AttnArgs &a, int row, int e, const f32x4 &y) {
+    if (a.out) *(f32x4 *)(a.out + (size_t)row * a.n_q_heads * a.head_dim + e) = y;
+    if (a.out_s) {
+        uint16_t t[3][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) split3(y[i], t[0][i], t[1][i], t[2][i]);
+        const int ocode = a.out_rows ? a.out_rows : a.rows, orows = layout_rows(ocode), nt = block_terms(ocode);
+        uint16_t *p = a.out_s + ((size_t)(e >> 3) * (nt * orows) + nt * row) * 8 + (e & 7);
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k < nt) *(u32x2 *)(p + 8 * k) = u32x2{pack2(t[k][0], t[k][1]), pack2(t[k][2], t[k][3])};
+    }
+}
+
 // Lane layout of v_mfma_f32_16x16x32_bf16 (C = A B): lane = 16 g + col.
 //   A (16 x 32): row col,    k = 8 g .. 8 g + 7        B (32 x 16): column col, k = 8 g .. 8 g + 7
 //   C (16 x 16): column col, rows 4 g .. 4 g + 3
@@ -205,31 +221,41 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
             for (int t = 0; t < 2; ++t) qop[c][t] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(qp + t * D + 32 * c));
     }
     // ---- the own slots of the rows that are finished here (prefix inside the first range), requested before
-    // the prefix is walked so that their latency is not paid at the end: scores by whole wavefronts into LDS,
-    // the value elements each thread will need in the last phase into registers
-    constexpr int kOwnMax = 16 * D / 256;  // elements per thread in the last phase with four wavefronts
+    // the prefix is walked so that their latency is not paid at the end: what this wavefront's scores need (16 / NW members,
+    // by whole wavefronts, lane l elements 2 l and 2 l + 1; reduced after the walk) and the value elements each thread will need
+    // in the last phase.
+    constexpr int kOwnMax = 16 * D / 4 / 256;  // units of four elements per thread in the last phase with four wavefronts
     float *s_own = am_sh + (size_t)NW * (16 * (MP + 2));
-    float v_own[kOwnMax];
+    // (trees: registers for two scores and one unit, all there are with eight wavefronts; what four need beyond them is read late)
+    constexpr int kScores = TREE ? 2 : 4, kUnits = TREE ? 1 : kOwnMax;
+    uint32_t v_own[kUnits][4];
+    float q_own[kScores][2];
+    uint32_t k_own[kScores];
+    // (member of score i: the last wavefronts have the fewest chunks to walk)
+    auto own_member = [&](int i) { return NW - 1 - wave + NW * i; };
+    auto load_own_values = [&](int u, uint32_t(&v)[4]) {
+        const int idx = tid + u * (int)blockDim.x, mm = idx / (D / 4), dd = 4 * (idx - mm * (D / 4));
+        const bool here = mm < 16 && m0 + mm < M_total && am_prefix_end<TREE>(a, (m0 + mm) / group) <= range;
+        const int own = here ? am_own_slot<TREE>(a, (m0 + mm) / group) : 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = here ? vt[((size_t)(own >> 3) * D + dd + i) * 8 + (own & 7)] : 0u;
+    };
+    auto own_here = [&](int mm) { return mm < 16 && m0 + mm < M_total && am_prefix_end<TREE>(a, (m0 + mm) / group) <= range; };
     if (sp == 0) {
-        // (member mm by wavefront NW - 1 - mm % NW: the last wavefronts have the fewest chunks to walk)
-        for (int mm = NW - 1 - wave; mm < 16; mm += NW) {
-            const int m = m0 + mm;
-            if (m >= M_total) continue;
+#pragma unroll
+        for (int i = 0; i < kScores; ++i) {
+            const int mm = own_member(i), m = m0 + mm;
+            q_own[i][0] = q_own[i][1] = 0.f;
+            k_own[i] = 0u;
+            if (!own_here(mm) || 2 * lane >= D) continue;  // (else finished by the combine kernel)
             const int row = m / group, head = m - row * group;
-            if (am_prefix_end<TREE>(a, row) > range) continue;  // finished by the combine kernel
-            const float sc = am_own_score(a.q + ((size_t)row * nq + kvh * group + head) * D,
-                                          kc + (size_t)am_own_slot<TREE>(a, row) * D, D, lane, scale);
-            if (lane == 0) s_own[mm] = sc;
+            const float *q = a.q + ((size_t)row * nq + kvh * group + head) * D + 2 * lane;
+            q_own[i][0] = q[0];
+            q_own[i][1] = q[1];
+            k_own[i] = *(const uint32_t *)(kc + (size_t)am_own_slot<TREE>(a, row) * D + 2 * lane);
         }
 #pragma unroll
-        for (int u = 0; u < kOwnMax; ++u) {
-            const int idx = tid + u * (int)blockDim.x, mm = idx / D, dd = idx - mm * D, m = m0 + mm;
-            v_own[u] = 0.f;
-            if (idx < 16 * D && m < M_total && am_prefix_end<TREE>(a, m / group) <= range) {
-                const int own = am_own_slot<TREE>(a, m / group);
-                v_own[u] = am_bf(vt[((size_t)(own >> 3) * D + dd) * 8 + (own & 7)]);
-            }
-        }
+        for (int u = 0; u < kUnits; ++u) load_own_values(u, v_own[u]);
     }
 
     // ---- this wavefront's chunks: every NW-th of the range, folded in order.  The keys of the next chunk are
@@ -292,21 +318,39 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
     // range with their own slot, or leave the range's partial result for k_attn_mfma_combine
     l_run += __shfl_xor(l_run, 16, 64);
     l_run += __shfl_xor(l_run, 32, 64);
+    if (sp == 0) {
+#pragma unroll
+        for (int i = kScores; i < 4; ++i) {
+            const int mm = own_member(i), m = m0 + mm;
+            if (!own_here(mm)) continue;
+            const int row = m / group, head = m - row * group;
+            const float sc = am_own_score(a.q + ((size_t)row * nq + kvh * group + head) * D,
+                                          kc + (size_t)am_own_slot<TREE>(a, row) * D, D, lane, scale);
+            if (lane == 0) s_own[mm] = sc;
+        }
+#pragma unroll
+        for (int i = 0; i < kScores; ++i) {
+            const int mm = own_member(i);
+            if (!own_here(mm)) continue;  // (wavefront-uniform)
+            const float sc = fmaf(q_own[i][1], am_bf((uint16_t)(k_own[i] >> 16)), fmaf(q_own[i][0], am_bf((uint16_t)k_own[i]), 0.f));
+            const float sum = wave_sum(sc) * scale;
+            if (lane == 0) s_own[mm] = sum;
+        }
+    }
     float *wbase = am_sh + (size_t)wave * (16 * (MP + 2));
     if (g == 0) {
         wbase[col] = m_run;
         wbase[16 + col] = l_run;
     }
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) wbase[32 + col * MP + 16 * dt + 4 * g + i] = o[dt][i];
+    for (int dt = 0; dt < DT; ++dt) *(f32x4 *)(wbase + 32 + col * MP + 16 * dt + 4 * g) = o[dt];
     __syncthreads();
+    // (a thread takes four elements of a member: the wavefronts' weights are worked out once for them)
 #pragma unroll
     for (int u = 0; u < kOwnMax; ++u) {
         const int idx = tid + u * (int)blockDim.x;
-        if (idx >= 16 * D) break;
-        const int mm = idx / D, dd = idx - mm * D;
+        if (idx >= 16 * D / 4) break;
+        const int mm = idx / (D / 4), dd = 4 * (idx - mm * (D / 4));
         const int m = m0 + mm;
         if (m >= M_total) continue;
         const int row = m / group, head = m - row * group;
@@ -315,20 +359,27 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
         if (sp >= max(nsr, 1)) continue;
         float mn = -INFINITY;
         for (int w = 0; w < NW; ++w) mn = fmaxf(mn, am_sh[(size_t)w * (16 * (MP + 2)) + mm]);
-        float ls = 0.f, os = 0.f;
+        float ls = 0.f;
+        f32x4 os = {0.f, 0.f, 0.f, 0.f};
         for (int w = 0; w < NW; ++w) {
             const float *wb = am_sh + (size_t)w * (16 * (MP + 2));
             const float mw = wb[mm];
             const float cw = mw == -INFINITY ? 0.f : __expf(mw - mn);
             ls += wb[16 + mm] * cw;
-            os += wb[32 + mm * MP + dd] * cw;
+            os += *(const f32x4 *)(wb + 32 + mm * MP + dd) * cw;
         }
         const int qh = kvh * group + head;
         if (nsr <= 1) {
-            am_write(a, row, qh * D + dd, am_finish(mn, ls, os, s_own[mm], v_own[u]));
+            f32x4 y;
+            uint32_t late[4];
+            if (u >= kUnits) load_own_values(u, late);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                y[i] = am_finish(mn, ls, os[i], s_own[mm], am_bf((uint16_t)(u < kUnits ? v_own[u < kUnits ? u : 0][i] : late[i])));
+            am_write4(a, row, qh * D + dd, y);
         } else {
             const size_t slot = ((size_t)row * nq + qh) * n_split + sp;
-            a.part_o[slot * D + dd] = os;
+            *(f32x4 *)(a.part_o + slot * D + dd) = os;
             if (dd == 0) {
                 a.part_ml[slot * 2] = mn;
                 a.part_ml[slot * 2 + 1] = ls;
