@@ -107,7 +107,7 @@ Layout make_layout(const swift_model_config &c) {
     };
     const bool bf = c.dtype == SWIFT_BF16;
     // bf16 models run on the tiled MFMA kernels (a depth too large for the LDS-resident kernel goes
-    // through the K-chunked block kernel, whatever the row count)
+    // through the block kernels, whatever the row count)
     L.tiled = bf;
     L.tiled_h = L.tiled_q = L.tiled_f = L.tiled;
     L.embed = take(V * H * eb);

@@ -676,8 +676,8 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 // What bounds it: the weight stream, and the operand reads (a wavefront reads 2 + NCW KB per k tile; as one row group
 // times all columns, which is what this kernel replaces, 1 + NCB KB from chunks of eight tiles that drained the loads in
 // flight at every barrier).  Weights are copied non-temporally, so that they do not push the B operand, which every workgroup
-// reads, out of L2.  us, before / now: 7B, 31 rows gate/up 54 / 40, down_proj 35.5 / 31, LM head 60 / 49; 32 bulk rows gate/up
-// 40.5 / 34; 13B, 31 rows gate/up 79 / 57, down_proj 57 / 41; 70B, 31 rows gate/up 231 / 179, LM head 112 / 87.  (One k tile a
+// reads, out of L2.  us, before / now: 7B, 31 rows gate/up 54 / 40, down_proj 35.5 / 28, LM head 60 / 48; 32 bulk rows gate/up
+// 40.5 / 34; 13B, 31 rows gate/up 79 / 57, down_proj 57 / 39; 70B, 31 rows gate/up 231 / 179, LM head 112 / 86.  (One k tile a
 // stage 1-3 % slower; weights straight to registers, each tile by two wavefronts: gate/up 54; four wavefronts of 512 registers
 // with six row groups each and nothing staged: 62.)
 //
@@ -1236,8 +1236,8 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
 //   k_mvR   3.7 + rounds x 8 slices x steps of a slice as walked x (weights of 1, 2 or 3 row groups + c columns of B)
 //   line    6.1 (+ 2.8 + 0.96 c where K is split over workgroups) + rounds x tiles (a slice's last chunk of eight, where it
 //           is partial, counts half of what it lacks) x (row groups + c columns), by the root of the share of units in use
-// Beyond the line k_mvN is the faster kernel by 2-40 % (us, k_mvR / k_mvN: 7B, 31 rows down_proj 41.3 / 31, LM head 75 / 48.6; 70B,
-// 16 rows LM head 97.7 / 83).  Short of it k_mvR is, by far at few rows (7B, 9 rows q|k|v 20 / 27, o_proj 9.2 / 17, down_proj 22 /
+// Beyond the line k_mvN is the faster kernel by 2-40 % (us, k_mvR / k_mvN: 7B, 31 rows down_proj 41.3 / 28, LM head 75 / 48; 70B,
+// 16 rows LM head 97.7 / 82).  Short of it k_mvR is, by far at few rows (7B, 9 rows q|k|v 20 / 27, o_proj 9.2 / 17, down_proj 22 /
 // 25; 31 rows o_proj 17 / 22), and loses 6-17 % in a strip along the line (13B, 21 rows q|k|v 42 / 36; 70B, 16 rows down_proj
 // 92 / 76.5, 31 rows q|k|v 49.5 / 45): the instances that blocks of those widths take are part of what the tests state.
 static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
