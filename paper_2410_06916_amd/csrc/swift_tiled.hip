@@ -685,7 +685,7 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 // one that arrives last at the row group's counter adds the partials in split order (so the result does
 // not depend on arrival order) and runs the epilogue.
 //
-// CANON (exact layouts: verify blocks of up to 32 rows, 2-6 column blocks) reproduces the LDS-resident kernel
+// CANON (exact layouts: verify blocks of up to 32 rows, 2-6 column blocks; mvn_canon) reproduces the LDS-resident kernel
 // bit for bit: the K range of a row group is cut into the same 8 slices of ceil(T/8) tiles, a slice is
 // accumulated from zero tile by tile, a workgroup covers a group of 8, 4, 2 or 1 whole slices (mv_slice_group: a
 // function of the matrix alone, not of the row count) and adds their sums per term in slice order, combines
@@ -764,7 +764,7 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
     NormPart32 np32;
     NormPart64 np64;
     if (kNorm) {
-        if (NCB > 6)
+        if (!CANON)  // (the bulk layouts' own order)
             mv_norm64_load(a, 0, np64);
         else if (a.rp == 16)
             np = mv_norm_load(a);
@@ -864,7 +864,7 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
     };
     auto norm = [&]() {
         if (!kNorm) return;
-        if (NCB > 6)
+        if (!CANON)
             mv_norm64_finish(a, np64, rs, nscratch);
         else if (a.rp == 16)
             mv_norm_finish<true>(a, np, rs, nscratch);
@@ -1240,15 +1240,11 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
 // 16 rows LM head 97.7 / 82).  Short of it k_mvR is, by far at few rows (7B, 9 rows q|k|v 20 / 27, o_proj 9.2 / 17, down_proj 22 /
 // 25; 31 rows o_proj 17 / 22), and loses 6-17 % in a strip along the line (13B, 21 rows q|k|v 42 / 36; 70B, 16 rows down_proj
 // 92 / 76.5, 31 rows q|k|v 49.5 / 45): the instances that blocks of those widths take are part of what the tests state.
-static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
+static int mvr_line(const MvArgs &a, int n_cu, int ncb) {
     if (ncb < 1 || ncb > 6 || a.R > kMaxRows) return 0;
     static const double kWeights[3] = {0.0213, 0.0467, 0.0603}, kColumns[3] = {0.0147, 0.0178, 0.0226};
     const bool bulk = (a.RL & kBulkLayout) != 0;
     const double cols = 0.4 * ncb + 0.6 * (block_terms(a.RL) * layout_rows(a.RL)) / 16.0;
-    if (ncb > 2) {
-        const MvnPlan p = mvn_plan(a, n_cu, !bulk);
-        if (p.rgs == 6 && p.ksp == 1) return 0;
-    }
     double best = 1e30;
     int rg = 0;
     if (ncb > 1) {  // (one column block: activations too deep for k_mv1, which k_mvN does not take)
@@ -1277,6 +1273,16 @@ static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     }
     return rg;
 }
+static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
+    if (ncb > 2 && ncb <= 6) {
+        const MvnPlan p = mvn_plan(a, n_cu, true);
+        if (p.rgs == 6 && p.ksp == 1) return 0;
+    }
+    return mvr_line(a, n_cu, ncb);
+}
+// Whether k_mvN adds the eight slices: exact layouts, and bulk ones of 32 rows short of the line (K whole there), whose sums are
+// k_mvR's then, so that which kernel is the faster one does not decide what a short prompt leaves in the cache.
+static bool mvn_canon(const MvArgs &a, int n_cu, int ncb) { return !(a.RL & kBulkLayout) || mvr_line(a, n_cu, ncb) != 0; }
 
 // Small blocks (in their own exact layout) whose whole activation fits in LDS take the single-pass kernel.
 static bool mv_takes_mv1(const MvArgs &a, int ks_override) {
@@ -1287,7 +1293,7 @@ static int mv_column_blocks(const MvArgs &a) { return (block_terms(a.RL) * layou
 int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity) {
     if (mv_takes_mv1(a, 0)) return snprintf(out, (size_t)capacity, "mv1<rows %d>", a.R);
     const int ncb = mv_column_blocks(a), rg = mvr_row_groups(a, n_cu, ncb);
-    if (rg == 0) return snprintf(out, (size_t)capacity, "mvN<columns %d, parts %d>", ncb, mvn_plan(a, n_cu, !(a.RL & kBulkLayout)).ksp);
+    if (rg == 0) return snprintf(out, (size_t)capacity, "mvN<columns %d, parts %d>", ncb, mvn_plan(a, n_cu, mvn_canon(a, n_cu, ncb)).ksp);
     const int units = (a.n_rg + rg - 1) / rg;
     return snprintf(out, (size_t)capacity, "mvR<columns %d, row groups %d, steps %d, rounds %d>", ncb, rg,
                     mvr_depth((a.T + 7) / 8, ncb, rg), (units + n_cu - 1) / n_cu);
@@ -1341,10 +1347,11 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
 #undef SWIFT_MVR_RG
         return hipErrorInvalidValue;
     }
+    const bool canon = mvn_canon(a, n_cu, ncb);
 #define SWIFT_MVN_CASE(E)                                                                \
     case E:                                                                              \
         if (bulk) switch (ncb) {                                                         \
-                case 4: return launch_mvN<E, 4, false>(a, n_cu, s);                      \
+                case 4: return canon ? launch_mvN<E, 4, true>(a, n_cu, s) : launch_mvN<E, 4, false>(a, n_cu, s); \
                 case 8: return launch_mvN<E, 8, false>(a, n_cu, s);                      \
                 default: return hipErrorInvalidValue;                                    \
             }                                                                            \
