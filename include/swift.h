@@ -353,6 +353,13 @@ int swift_debug_attn_path(swift_ctx *ctx, int rows, int tree, char *out, int cap
 int swift_debug_projection_path(const swift_model_config *cfg, int n_cu, int kernel_class, int rows, int exact, char *out,
                                 int capacity);
 
+/* Names the launch of the blocked matrix product that a projection (kernel_class as above, but _LMHEAD) of a bf16 model takes in a
+ * prompt macro block of sub_blocks (2..16) sub-blocks of 64 rows, e.g. "gemm<tile 6, parts 2, workgroups>": tile shape, parts of
+ * the depth, where they are added ("inside" a workgroup, over "workgroups", or "whole").  last_layer != 0: the last layer's
+ * SWIFT_KC_QKV launch, which covers the keys' and values' rows of all sub-blocks.  Host only; for tests. */
+int swift_debug_prompt_path(const swift_model_config *cfg, int n_cu, int kernel_class, int sub_blocks, int last_layer, char *out,
+                            int capacity);
+
 /* Overrides the launch shape of the tiled single-row projection kernel of one class: wavefronts
  * that share a 16-row group (0 = automatic, else 1, 2, 4 or 8) and workgroups (0 = automatic).
  * Results do not depend on it bit for bit only within one setting; it exists for tuning runs. */

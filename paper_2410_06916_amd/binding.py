@@ -108,6 +108,7 @@ def lib():
     L.swift_debug_prefill.argtypes = [vp, C.c_int, C.c_int]
     L.swift_debug_attn_path.argtypes = [vp, C.c_int, C.c_int, C.c_char_p, C.c_int]
     L.swift_debug_projection_path.argtypes = [C.POINTER(ModelConfig), C.c_int, C.c_int, C.c_int, C.c_int, C.c_char_p, C.c_int]
+    L.swift_debug_prompt_path.argtypes = [C.POINTER(ModelConfig), C.c_int, C.c_int, C.c_int, C.c_int, C.c_char_p, C.c_int]
     L.swift_profile_class.argtypes = [vp, C.c_int]
     L.swift_profile_read.argtypes = [vp, C.POINTER(C.c_int64), C.POINTER(C.c_double), C.POINTER(C.c_uint64)]
     _lib = L
@@ -155,6 +156,14 @@ def projection_path(cfg: ModelConfig, name: str, rows: int, exact: bool = True, 
     buf = C.create_string_buffer(96)
     _chk(lib().swift_debug_projection_path(C.byref(cfg), n_cu, KERNEL_CLASSES[name], rows, 1 if exact else 0, buf, 96),
          "swift_debug_projection_path")
+    return buf.value.decode()
+
+
+def prompt_path(cfg: ModelConfig, name: str, sub_blocks: int, last_layer: bool = False, n_cu: int = 256) -> str:
+    """Name of the launch that projection `name` takes in a prompt macro block (see swift_debug_prompt_path)."""
+    buf = C.create_string_buffer(96)
+    _chk(lib().swift_debug_prompt_path(C.byref(cfg), n_cu, KERNEL_CLASSES[name], sub_blocks, 1 if last_layer else 0, buf, 96),
+         "swift_debug_prompt_path")
     return buf.value.decode()
 
 

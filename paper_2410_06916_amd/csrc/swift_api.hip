@@ -81,7 +81,7 @@ struct Layout {
     uint64_t xs, as_, hs, pss, mv_part, mv_counters;
     // elements from one sub-block of a prompt macro block to the next, per activation buffer
     uint64_t sub_x, sub_q, sub_xs, sub_as, sub_hs, sub_pss;
-    int mv_part_capacity, gemm_part_slots;
+    int mv_part_capacity;
     uint64_t stage, stage_bytes;  // staging for host tensors that are re-tiled on the device
     uint64_t total;
     int n_split_max;
@@ -93,6 +93,8 @@ struct Layout {
 inline uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 // bytes of a tiled [rows][K] bf16 matrix whose row groups hold `rows_per_group` matrix rows... (16 tile rows)
 inline uint64_t tiled_bytes(uint64_t n_rg, uint64_t K) { return n_rg * ceil_div(K, 32) * 1024; }
+
+constexpr int kGemmPartSlots = 16384;  // MacroArgs::part_slots of the arena's scratch
 
 Layout make_layout(const swift_model_config &c) {
     Layout L;
@@ -157,8 +159,7 @@ Layout make_layout(const swift_model_config &c) {
     L.hs = take(subs * L.sub_hs * 2);
     L.pss = take(subs * L.sub_pss * 4);
     L.mv_part_capacity = 8192;
-    L.gemm_part_slots = 16384;
-    L.mv_part = take((uint64_t)std::max(L.mv_part_capacity, L.gemm_part_slots) * 16 * kMaxBlockRows * 4);
+    L.mv_part = take((uint64_t)std::max(L.mv_part_capacity, kGemmPartSlots) * 16 * kMaxBlockRows * 4);
     L.mv_counters = take(kMvCounters * 4);
     L.stage_bytes = bf ? std::max(std::max(V * H, F * H), std::max(Q * H, KV * H)) * eb : 0;
     L.stage = take(L.stage_bytes);
@@ -488,6 +489,25 @@ int block_attention(swift_ctx *x, const AttnArgs &at, int RLC) {
     return SWIFT_OK;
 }
 
+// The launch that gives a macro block its last layer's keys and values, from the arguments m of the whole fused q|k|v matrix: the row
+// groups behind the query heads', or the whole matrix (queries that nobody reads) where no plan for those row groups alone adds
+// their sums in the matrix's order (head counts that leave the first row group summed in parts off every tile's edge, and
+// parts of an odd number of k tiles: 125 heads of 64 without grouping, hidden 8000, 1024 rows).
+void last_layer_rows(const swift_model_config &c, int n_cu, MvArgs &m, MacroArgs &ma) {
+    const int first = c.n_q_heads * c.head_dim / 16;
+    MvArgs kv = m;
+    if (kv.Wt) kv.Wt = (const char *)kv.Wt + tiled_bytes(first, kv.K);
+    kv.O -= 16 * first;
+    kv.n_rg -= first;
+    kv.head0 = c.n_q_heads;
+    MacroArgs kva = ma;
+    kva.matrix_rg = m.n_rg;
+    kva.first_rg = first;
+    if (!gemm_keeps_order(kv, kva, n_cu)) return;
+    m = kv;
+    ma = kva;
+}
+
 // ---- tiled bf16 path: a block of R rows (tokens[0..R) at positions pos0..pos0+R-1) through the
 // network in one sweep over the weights.  Row r attends cache slots [0, pos0 + r].
 // tree: the rows are those of a token tree (R <= 16): row r goes to slot pos0 + r, is rotated for position
@@ -560,7 +580,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
     MacroArgs ma{};
     ma.S = n_sub;
     ma.rows_last = R;
-    ma.part_slots = L.gemm_part_slots;
+    ma.part_slots = kGemmPartSlots;
     auto sub_rows = [&](int sb) { return sb == last ? R : kMaxBlockRows; };
     {
         EmbedRowsArgs ea{};
@@ -640,11 +660,11 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
         const LayerOff &y = L.layers[l];
         const float *gnext = gain_of(i + 1);
         if (i == tail_stage) {
-            // keys and values of all rows: the row groups behind the query heads'
-            MvArgs m = base_args(y.wqkv + tiled_bytes(Q / 16, H), 2 * KV, H, 2 * KV / 16);
-            m.head0 = c.n_q_heads;
-            ma.matrix_rg = (Q + 2 * KV) / 16;
-            ma.first_rg = Q / 16;
+            // keys and values of all rows
+            MvArgs m = base_args(y.wqkv, Q + 2 * KV, H, (Q + 2 * KV) / 16);
+            last_layer_rows(c, x->n_cu, m, ma);
+            m.out_f32 = qf;
+            m.ld_out = Q;
             m.in_s = xs;
             m.pss = pss;
             m.n_pss = n_pss;
@@ -1687,6 +1707,23 @@ extern "C" int swift_debug_attn_path(swift_ctx *x, int rows, int tree, char *out
     return SWIFT_OK;
 }
 
+namespace {
+// Sizes of a projection: O, K, T, n_rg.
+int projection_sizes(const swift_model_config &c, int kernel_class, MvArgs &m) {
+    const int H = c.hidden, Q = c.n_q_heads * c.head_dim, KV = c.n_kv_heads * c.head_dim, F = c.ffn;
+    switch (kernel_class) {
+        case SWIFT_KC_QKV: m.O = Q + 2 * KV, m.K = H, m.n_rg = m.O / 16; break;
+        case SWIFT_KC_OPROJ: m.O = H, m.K = Q, m.n_rg = (H + 15) / 16; break;
+        case SWIFT_KC_GATEUP: m.O = 2 * F, m.K = H, m.n_rg = (F + 7) / 8; break;
+        case SWIFT_KC_DOWN: m.O = H, m.K = F, m.n_rg = (H + 15) / 16; break;
+        case SWIFT_KC_LMHEAD: m.O = c.vocab, m.K = H, m.n_rg = (c.vocab + 15) / 16; break;
+        default: return fail(SWIFT_EINVAL, "not a projection");
+    }
+    m.T = (m.K + 31) / 32;
+    return SWIFT_OK;
+}
+}  // namespace
+
 extern "C" int swift_debug_projection_path(const swift_model_config *cfg, int n_cu, int kernel_class, int rows, int exact,
                                           char *out, int capacity) {
     if (!out || capacity < 1 || n_cu < 1 || rows < 1 || rows > (exact ? kMaxRows : kMaxBlockRows))
@@ -1694,23 +1731,36 @@ extern "C" int swift_debug_projection_path(const swift_model_config *cfg, int n_
     int rc = swift_check_config(cfg);
     if (rc) return rc;
     if (cfg->dtype != SWIFT_BF16) return fail(SWIFT_EINVAL, "fp32 models have one projection kernel");
-    const int H = cfg->hidden, Q = cfg->n_q_heads * cfg->head_dim, KV = cfg->n_kv_heads * cfg->head_dim, F = cfg->ffn;
     MvArgs m{};
-    switch (kernel_class) {
-        case SWIFT_KC_QKV: m.O = Q + 2 * KV, m.K = H, m.n_rg = m.O / 16; break;
-        case SWIFT_KC_OPROJ: m.O = H, m.K = Q, m.n_rg = (H + 15) / 16; break;
-        case SWIFT_KC_GATEUP: m.O = 2 * F, m.K = H, m.n_rg = (F + 7) / 8; break;
-        case SWIFT_KC_DOWN: m.O = H, m.K = F, m.n_rg = (H + 15) / 16; break;
-        case SWIFT_KC_LMHEAD: m.O = cfg->vocab, m.K = H, m.n_rg = (cfg->vocab + 15) / 16; break;
-        default: return fail(SWIFT_EINVAL, "not a projection");
-    }
-    m.T = (m.K + 31) / 32;
+    if ((rc = projection_sizes(*cfg, kernel_class, m))) return rc;
     m.R = rows;
     m.RL = block_row_layout(rows, exact != 0);
     m.rp = block_row_pitch(rows);
     m.head_dim = cfg->head_dim;
     m.part_capacity = make_layout(*cfg).mv_part_capacity;
     mv_path_name(m, n_cu, out, capacity);
+    return SWIFT_OK;
+}
+
+extern "C" int swift_debug_prompt_path(const swift_model_config *cfg, int n_cu, int kernel_class, int sub_blocks, int last_layer,
+                                       char *out, int capacity) {
+    if (!out || capacity < 1 || n_cu < 1 || sub_blocks < 2 || sub_blocks > kMacroSub || kernel_class == SWIFT_KC_LMHEAD ||
+        (last_layer && kernel_class != SWIFT_KC_QKV))
+        return fail(SWIFT_EINVAL, "bad argument");
+    int rc = swift_check_config(cfg);
+    if (rc) return rc;
+    if (cfg->dtype != SWIFT_BF16) return fail(SWIFT_EINVAL, "fp32 models have one projection kernel");
+    MvArgs m{};
+    if ((rc = projection_sizes(*cfg, kernel_class, m))) return rc;
+    float part;
+    int counter;
+    m.part = &part;  // (nothing is launched: only that they are there counts)
+    m.counters = &counter;
+    MacroArgs ma{};
+    ma.S = sub_blocks;
+    ma.part_slots = kGemmPartSlots;
+    if (last_layer) last_layer_rows(*cfg, n_cu, m, ma);
+    gemm_path_name(m, ma, n_cu, out, capacity);
     return SWIFT_OK;
 }
 

@@ -26,6 +26,7 @@
 // workgroups each: every wavefront publishes its results, and of the wavefronts that share a piece of a tile the one
 // that arrives last adds them in part order and runs the epilogue.
 #include <math.h>
+#include <stdio.h>
 
 #include <algorithm>
 #include <type_traits>
@@ -700,21 +701,15 @@ bool gemm_plan(const MvArgs &a, const MacroArgs &ma, int n_cu, int code, const G
     return a.part && a.counters && slots <= ma.part_slots && tail * pl.NN * 8 <= 4096;
 }
 
-}  // namespace
-
-hipError_t launch_gemm(int epi, const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, hipStream_t s) {
-    if (ma.S < 1 || ma.S > kMacroSub || ma.rows_last < 1 || ma.rows_last > 64 || a.RL != (64 | kBulkLayout) || a.rp != 64 ||
-        (a.K & 7) != 0 || a.T != (a.K + 31) / 32 || a.n_rg < 1 || !a.Wt || !a.in_s || a.tree || a.q_s ||
-        (epi == EPI_RESID ? !a.gain_next || !a.pss_out || (a.O & 7) != 0 : !a.pss || a.n_pss < 1))
-        return hipErrorInvalidValue;
-    // The tile shape and the way of adding the parts that finish first by the measured costs: workgroups come in rounds of one per
-    // compute unit, and splitting the last round's tiles in depth fills the units that would idle in it, for the price
-    // of the parts' results.
-    GemmSums sums = gemm_sums(ma.matrix_rg > 0 ? ma.matrix_rg : a.n_rg, a.T, ma.S, n_cu);
-    sums.first = std::max(0, sums.first - ma.first_rg);
-    if (sums.first >= a.n_rg) sums = GemmSums{a.n_rg, 1, a.T};
-    GemmPlan pl{};
-    int code = 0;
+// The plan with the least cost: the tile shape and the way of adding the parts that finish first, among those that keep the order
+// of the sums.  Workgroups come in rounds of one per compute unit, and splitting the last round's tiles in depth fills the units
+// that would idle in it, for the price of the parts' results.  code 0: none keeps it.
+struct GemmChoice {
+    int code;
+    GemmPlan pl;
+};
+GemmChoice gemm_choose(const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, const GemmSums &sums) {
+    GemmChoice ch{};
     double best = 1e30;
     for (int c = 1; c <= kGemmCodes; ++c) {
         if (tiling_override && c != tiling_override) continue;
@@ -723,14 +718,43 @@ hipError_t launch_gemm(int epi, const MvArgs &a, const MacroArgs &ma, int n_cu, 
             double us;
             if (!gemm_plan(a, ma, n_cu, c, sums, fold, p, us) || us >= best) continue;
             best = us;
-            pl = p;
-            code = c;
+            ch = GemmChoice{c, p};
         }
     }
-    // (a tile shape asked for by a tuning run may not allow the order of the sums: then they are added in one go)
-    if (code == 0 && tiling_override >= 1 && tiling_override <= kGemmCodes &&
-        gemm_plan(a, ma, n_cu, tiling_override, GemmSums{a.n_rg, 1, a.T}, false, pl, best))
-        code = tiling_override;
+    return ch;
+}
+// The order of the sums of a launch's row groups: that of their matrix.
+GemmSums launch_sums(const MvArgs &a, const MacroArgs &ma, int n_cu) {
+    GemmSums sums = gemm_sums(ma.matrix_rg > 0 ? ma.matrix_rg : a.n_rg, a.T, ma.S, n_cu);
+    sums.first = std::max(0, sums.first - ma.first_rg);
+    return sums.first >= a.n_rg ? GemmSums{a.n_rg, 1, a.T} : sums;
+}
+
+}  // namespace
+
+bool gemm_keeps_order(const MvArgs &a, const MacroArgs &ma, int n_cu) {
+    return gemm_choose(a, ma, n_cu, 0, launch_sums(a, ma, n_cu)).code != 0;
+}
+
+int gemm_path_name(const MvArgs &a, const MacroArgs &ma, int n_cu, char *out, int capacity) {
+    const GemmChoice ch = gemm_choose(a, ma, n_cu, 0, launch_sums(a, ma, n_cu));
+    if (ch.code == 0) return snprintf(out, (size_t)capacity, "none");
+    const GemmPlan &p = ch.pl;
+    return snprintf(out, (size_t)capacity, "gemm<tile %d, parts %d, %s>", ch.code, p.fold_TS > 0 || p.MTF < p.MT ? p.ksp : 1,
+                    p.fold_TS > 0 ? "inside" : p.MTF < p.MT ? "workgroups" : "whole");
+}
+
+hipError_t launch_gemm(int epi, const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, hipStream_t s) {
+    if (ma.S < 1 || ma.S > kMacroSub || ma.rows_last < 1 || ma.rows_last > 64 || a.RL != (64 | kBulkLayout) || a.rp != 64 ||
+        (a.K & 7) != 0 || a.T != (a.K + 31) / 32 || a.n_rg < 1 || !a.Wt || !a.in_s || a.tree || a.q_s ||
+        (epi == EPI_RESID ? !a.gain_next || !a.pss_out || (a.O & 7) != 0 : !a.pss || a.n_pss < 1))
+        return hipErrorInvalidValue;
+    GemmChoice ch = gemm_choose(a, ma, n_cu, tiling_override, launch_sums(a, ma, n_cu));
+    // (a tile shape asked for by a tuning run, or scratch that is not there, may not allow the order: then the sums are added in one go,
+    // which every shape can)
+    if (ch.code == 0) ch = gemm_choose(a, ma, n_cu, tiling_override, GemmSums{a.n_rg, 1, a.T});
+    const int code = ch.code;
+    const GemmPlan &pl = ch.pl;
     if (code == 0) return hipErrorInvalidValue;
 #define SWIFT_GEMM_CASE(E)                                                \
     case E:                                                               \

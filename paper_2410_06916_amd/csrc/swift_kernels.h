@@ -318,9 +318,15 @@ struct MacroArgs {
     int matrix_rg, first_rg;  // a launch over some row groups of a matrix: those of the whole one (0: this is it), those before
 };
 // epilogue: EPI_QKV, EPI_RESID or EPI_SWIGLU; a.R is ignored, a.RL must be the 64-row bulk layout, a.rp = 64, a.K a
-// multiple of 8; a.q_s is null; a.part and a.counters (4096 words, zero between launches) may be null: no depth split.
-// tiling_override: 0 = automatic, else the tile shape (tuning runs; kGemmTilings).
+// multiple of 8; a.q_s is null; a.part and a.counters (4096 words, zero between launches) may be null: no split over workgroups.
+// tiling_override: 0 = automatic, else the tile shape (tuning runs; kGemmTilings).  Never refused for its sizes: where no plan adds
+// the sums in the matrix's order, they are added in one go.
 hipError_t launch_gemm(int epilogue, const MvArgs &a, const MacroArgs &ma, int n_cu, int tiling_override, hipStream_t s);
+// Whether launch_gemm finds a plan for this launch that adds its sums in the matrix's order (gemm_sums); reads the sizes of a
+// and ma, and whether a.part and a.counters are there.
+bool gemm_keeps_order(const MvArgs &a, const MacroArgs &ma, int n_cu);
+// Names that plan, e.g. "gemm<tile 6, parts 2, workgroups>": tile shape, depth parts, where they are added; "none" if there is none.
+int gemm_path_name(const MvArgs &a, const MacroArgs &ma, int n_cu, char *out, int capacity);
 
 // x[r] = E[token r] (fp32), split of x * gain_next, partial sums of squares per 16 elements.  More than kMaxBlockRows rows:
 // those of a macro block, row r at row r % 64 of sub-block r / 64, found at the given element strides.

@@ -247,6 +247,27 @@ def test_prefill_last_layer_of_macro_blocks_against_64_row_blocks(shape):
     g.close()
 
 
+def test_prefill_of_a_head_count_off_every_tile_edge():
+    """125 heads of 64: at 16 sub-blocks the row groups of the last layer's keys and values alone have no plan in the order of
+    their matrix's sums, so the whole matrix goes through.  Against the same prompt in 64-row blocks, and bit for bit against
+    two sweeps of 512 rows."""
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape("heads-125", 2, 8000, 125, 125, 64, 64, 96, "bf16", 1e-5)
+    g = P.SwiftModel(shape, 1100)
+    g.load_weights(si.iter_weights(shape, 6, "cuda:0", gain_jitter=0.1))
+    prompt = si.uniform_ids(74, 1024, shape.vocab)
+    res = []
+    for blocks in (-1, 0, 8):
+        g.prefill_blocks(blocks)
+        g.prefill(prompt)
+        res.append((g.read_logits(63), [x for p in (0, 63, 64, 511, 1023) for x in g.read_kv(1, p)]))
+    assert hp.rel_err_rowmax(res[1][0], res[0][0])[0] <= 2e-3
+    for a, b in zip(res[0][1], res[1][1]):
+        assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(a) + 2.0 ** -10 * np.abs(a).max())
+    assert np.array_equal(res[1][0], res[2][0]) and all(np.array_equal(a, b) for a, b in zip(res[1][1], res[2][1]))
+    g.close()
+
+
 @pytest.mark.parametrize("shape", [si.LLAMA2_7B.with_layers(2), si.LLAMA2_13B.with_layers(2), si.LLAMA2_70B.with_layers(2)],
                          ids=lambda s: s.name)
 def test_prefill_macro_blocks_of_16_and_8_leave_the_same_bits(shape):

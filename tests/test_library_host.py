@@ -205,6 +205,39 @@ def test_projection_kernel_of_a_block_is_the_faster_one(P, width):
         B.projection_path(cfg, "qkv", 33)
 
 
+@pytest.mark.parametrize("head_dim", [16, 32, 64, 128])
+def test_every_prompt_launch_has_a_plan_in_the_matrix_order(P, head_dim):
+    """The blocked matrix product finds a plan that keeps the order of the sums for every head count, grouping and depth and
+    2..16 sub-blocks: for whole matrices, and for the last layer's keys and values (their row groups alone, or else the whole
+    matrix).  125 and 117 heads of 64, 107 at hidden 4096 and many heads of 32 and 16 have none for the row groups alone."""
+    from paper_2410_06916_amd import binding as B
+    L = P.lib()
+    out = C.create_string_buffer(96)
+
+    def path(cfg, kc, subs, last, n_cu):
+        assert L.swift_debug_prompt_path(C.byref(cfg), n_cu, B.KERNEL_CLASSES[kc], subs, last, out, 96) == 0
+        return out.value
+    for n_q in range(1, 641):
+        if 4 * n_q * head_dim > 160 * 1024 - 1024:
+            break
+        for hidden in {max(8, n_q * head_dim), 1016, 4096, 8000}:
+            for group in (1, 8 if n_q % 8 == 0 else 1):
+                cfg = B.make_config(si.ModelShape("plan", 1, hidden, n_q, n_q // group, head_dim, 8 * n_q + 8, 96, "bf16", 1e-5), 2048)
+                for subs in (2, 3, 5, 7, 8, 9, 11, 15, 16):
+                    whole, last = path(cfg, "qkv", subs, 0, 256), path(cfg, "qkv", subs, 1, 256)
+                    assert whole != b"none" and last != b"none", (n_q, hidden, group, subs)
+                    for kc in ("oproj", "gateup", "down"):
+                        assert path(cfg, kc, subs, 0, 256) != b"none", (kc, n_q, hidden, group, subs)
+    for n_cu in (32, 64, 128, 208, 304):
+        for n_q in (8, 32, 107, 125):
+            cfg = B.make_config(si.ModelShape("plan", 1, 8000, n_q, n_q, 64, 11008, 96, "bf16", 1e-5), 2048)
+            for subs in range(2, 17):
+                for kc in ("qkv", "oproj", "gateup", "down"):
+                    assert path(cfg, kc, subs, 0, n_cu) != b"none", (n_cu, kc, n_q, subs)
+    assert L.swift_debug_prompt_path(C.byref(cfg), 256, B.KERNEL_CLASSES["lmhead"], 4, 0, out, 96) == -1
+    assert L.swift_debug_prompt_path(C.byref(cfg), 256, B.KERNEL_CLASSES["qkv"], 17, 0, out, 96) == -1
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
