@@ -181,7 +181,9 @@ def pass_bytes(cfg: ModelConfig, skip: Optional[np.ndarray], n_ctx: int, rows: i
 
 # Rows of logits or probabilities that a call returns lie in pinned memory, which the device writes to at the link's rate (31 rows of
 # 32000: 80 us, 230 into pageable memory), from torch's caching host allocator: an array's memory goes back there with the
-# array.  What callers hold on to is bounded: past _PINNED_MAX bytes, and for less than _PINNED_MIN, rows are pageable.
+# array.  What callers hold on to is bounded: past _PINNED_MAX bytes, for less than _PINNED_MIN, and where no pinned memory can be
+# had, rows are pageable.  (The allocator hands out powers of two and keeps freed blocks for the next arrays of the
+# process, so at most twice _PINNED_MAX stays pinned for each power of two that row counts ask for.)
 _PINNED_MIN, _PINNED_MAX = 1 << 16, 1 << 28
 _pinned_bytes = 0
 _pinned_lock = threading.Lock()
@@ -202,11 +204,14 @@ def _host_rows(torch, rows: int, width: int) -> np.ndarray:
     if n >= _PINNED_MIN and _pinned_count(n):
         try:
             a = torch.empty((rows, width), dtype=torch.float32, pin_memory=True).numpy()
+        except RuntimeError:
+            _pinned_count(-n)
         except BaseException:
             _pinned_count(-n)
             raise
-        weakref.finalize(a, _pinned_count, -n).atexit = False
-        return a
+        else:
+            weakref.finalize(a, _pinned_count, -n).atexit = False
+            return a
     return np.empty((rows, width), np.float32)
 
 

@@ -238,6 +238,25 @@ def test_every_prompt_launch_has_a_plan_in_the_matrix_order(P, head_dim):
     assert L.swift_debug_prompt_path(C.byref(cfg), 256, B.KERNEL_CLASSES["qkv"], 17, 0, out, 96) == -1
 
 
+def test_returned_rows_are_pageable_where_no_pinned_memory_can_be_had(P):
+    """A failed pinned allocation gives its bytes back and falls to pageable memory; an interrupt does not."""
+    from paper_2410_06916_amd import binding as B
+
+    class NoPinned:
+        float32 = None
+        error = RuntimeError("out of pinned memory")
+
+        def empty(self, *args, **kwargs):
+            raise self.error
+    before = B._pinned_bytes
+    a = B._host_rows(NoPinned(), 31, 32000)
+    assert a.shape == (31, 32000) and a.dtype == np.float32 and B._pinned_bytes == before
+    NoPinned.error = KeyboardInterrupt()
+    with pytest.raises(KeyboardInterrupt):
+        B._host_rows(NoPinned(), 31, 32000)
+    assert B._pinned_bytes == before
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
