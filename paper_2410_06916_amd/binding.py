@@ -1,6 +1,7 @@
 """ctypes binding of libswift_hip.so: same names as the C ABI, argument marshalling only."""
 from __future__ import annotations
 
+import collections
 import ctypes as C
 import os
 import threading
@@ -187,30 +188,49 @@ def pass_bytes(cfg: ModelConfig, skip: Optional[np.ndarray], n_ctx: int, rows: i
 _PINNED_MIN, _PINNED_MAX = 1 << 16, 1 << 28
 _pinned_bytes = 0
 _pinned_lock = threading.Lock()
+_pinned_returned = collections.deque()  # bytes of dead arrays that are not taken off _pinned_bytes yet
 
 
-def _pinned_count(n: int) -> bool:
-    """Takes (n > 0) or gives back (n < 0) pinned bytes; False if there is no room for them."""
+def _pinned_settle():
+    """Takes returned bytes off the count, unless somebody holds the lock: they do, once they have let go of it."""
+    global _pinned_bytes
+    while _pinned_returned and _pinned_lock.acquire(blocking=False):
+        try:
+            while _pinned_returned:
+                _pinned_bytes -= _pinned_returned.popleft()
+        finally:
+            _pinned_lock.release()
+
+
+def _pinned_give_back(n: int):
+    """Never waits: a collection may run this as a finaliser in a thread that holds the lock."""
+    _pinned_returned.append(n)
+    _pinned_settle()
+
+
+def _pinned_take(n: int) -> bool:
+    """Counts n bytes; False if there is no room for them."""
     global _pinned_bytes
     with _pinned_lock:
-        if n > 0 and _pinned_bytes + n > _PINNED_MAX:
-            return False
-        _pinned_bytes += n
-        return True
+        room = _pinned_bytes + n <= _PINNED_MAX
+        if room:
+            _pinned_bytes += n
+    _pinned_settle()
+    return room
 
 
 def _host_rows(torch, rows: int, width: int) -> np.ndarray:
     n = 4 * rows * width
-    if n >= _PINNED_MIN and _pinned_count(n):
+    if n >= _PINNED_MIN and _pinned_take(n):
         try:
             a = torch.empty((rows, width), dtype=torch.float32, pin_memory=True).numpy()
         except RuntimeError:
-            _pinned_count(-n)
+            _pinned_give_back(n)
         except BaseException:
-            _pinned_count(-n)
+            _pinned_give_back(n)
             raise
         else:
-            weakref.finalize(a, _pinned_count, -n).atexit = False
+            weakref.finalize(a, _pinned_give_back, n).atexit = False
             return a
     return np.empty((rows, width), np.float32)
 

@@ -257,6 +257,35 @@ def test_returned_rows_are_pageable_where_no_pinned_memory_can_be_had(P):
     assert B._pinned_bytes == before
 
 
+def test_a_returned_array_may_die_in_a_thread_that_counts(P):
+    """A collection that starts while a thread holds the count's lock may finalise an array in that very thread: it must
+    not wait for the lock, and its bytes are taken off once the lock is free.  Many threads: nothing is lost."""
+    import threading
+    from paper_2410_06916_amd import binding as B
+    before = B._pinned_bytes
+    assert B._pinned_take(1000) and B._pinned_take(24)
+
+    def die_inside():
+        with B._pinned_lock:
+            B._pinned_give_back(1000)
+    t = threading.Thread(target=die_inside, daemon=True)
+    t.start()
+    t.join(10)
+    assert not t.is_alive()
+    B._pinned_give_back(24)
+    assert B._pinned_bytes == before
+
+    def work():
+        for i in range(2000):
+            assert B._pinned_take(i)
+            B._pinned_give_back(i)
+    ts = [threading.Thread(target=work) for _ in range(8)]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    assert B._pinned_bytes == before and not B._pinned_returned
+    assert not B._pinned_take(B._PINNED_MAX + 1 - before)
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
