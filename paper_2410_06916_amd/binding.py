@@ -320,7 +320,7 @@ class SwiftModel:
         t = np.ascontiguousarray(tokens, np.int32)
         k = t.size - 1
         tgt = np.zeros(k + 1, np.int32)
-        lg = _host_rows(self.torch, k + 1, self.cfg.vocab) if want_logits else None
+        lg = np.empty((k + 1, self.cfg.vocab), np.float32) if want_logits else None  # (this call allocates nothing the device sees)
         _chk(lib().swift_verify_static(self._h, _p(t, C.c_int32), k, _p(tgt, C.c_int32),
                                        _p(lg, C.c_float) if want_logits else None), "swift_verify_static")
         return tgt, lg

@@ -93,6 +93,24 @@ def test_static_scratch_verify_against_oracle_and_limits(oracle_lib):
     g.close()
 
 
+def test_static_verification_pins_no_host_memory():
+    """The rows that verify_static returns are ordinary memory: the call leaves the count of pinned allocations alone, where
+    verify takes one for rows of this size."""
+    import torch
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape("static-rows", 1, 64, 2, 1, 32, 96, 33004, "bf16", 1e-5)
+    g = P.SwiftModel(shape, 40)
+    g.load_weights(hp.shaped_weights(shape, seed=2))
+    pend = g.prefill([5, 6, 7])
+    _, want = g.verify([pend, 3], True)
+    assert torch.from_numpy(want).is_pinned()
+    g.rollback(3, pend)
+    _, got = g.verify_static([pend, 3], True)
+    assert not torch.from_numpy(got).is_pinned()
+    assert np.array_equal(got, want)
+    g.close()
+
+
 @pytest.mark.parametrize("heads,kv", [(32, 4), (64, 8), (46, 23)])
 def test_static_scratch_holds_full_blocks_of_fp32_models_over_short_caches(heads, kv):
     """fp32 models take the row-at-a-time attention, whose shortest ranges follow from what a slot costs: with many query
