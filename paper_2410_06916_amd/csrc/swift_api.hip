@@ -1287,7 +1287,7 @@ extern "C" int swift_verify_static(swift_ctx *x, const int32_t *tokens, int k, i
             m.head_dim = d;
             m.part_capacity = x->L.mv_part_capacity;
             const int slots = mv_split_slots(m, x->n_cu);
-            if (slots > kStaticPartSlots || (mt.n_rg + 7) / 8 > kMvCounters)
+            if (slots > kStaticPartSlots || (mt.n_rg + 7) / 8 > kMvCounters || mv_split_counters(m, x->n_cu) > kMvCounters)
                 return fail(SWIFT_ECAPACITY, "swift_verify_static: a projection of this model needs more split-K scratch "
                                              "than the static array holds; use swift_verify");
         }

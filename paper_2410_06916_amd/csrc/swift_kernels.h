@@ -300,6 +300,8 @@ hipError_t launch_mv(int epilogue, MvArgs a, int n_cu, int ks_override, int wg_o
 // Row-group-splits of `part` (16 * R floats each) that launch_mv writes for a block of up to 16 rows
 // described by `a` (0: the launch splits K inside workgroups only and uses neither `part` nor `counters`).
 int mv_split_slots(const MvArgs &a, int n_cu);
+// Arrival counters that goes with: one per wavefront of a workgroup that covers all columns, in each row block.
+int mv_split_counters(const MvArgs &a, int n_cu);
 // Writes the name of the kernel instance launch_mv takes for `a` into out; returns the length snprintf reports.  Host only.
 int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity);
 

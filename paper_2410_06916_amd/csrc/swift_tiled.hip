@@ -728,6 +728,8 @@ static MvnPlan mvn_plan(const MvArgs &a, int n_cu, bool canon) {
     return best;
 }
 
+static int mvn_counters(const MvnPlan &p) { return p.ksp > 1 ? p.grid_x * 8 : 0; }
+
 template <int NCW>
 struct MvnOperands {
     u32x4 av[kMvnTiles][2], bv[kMvnTiles][NCW];
@@ -1024,7 +1026,7 @@ static hipError_t launch_mvN_t(const MvArgs &a, int n_cu, hipStream_t s) {
         attr_set = true;
     }
     const MvnPlan p = mvn_plan(a, n_cu, CANON);
-    if (p.ksp > 1 && p.grid_x * 8 > kMvCounters) return hipErrorInvalidValue;
+    if (mvn_counters(p) > kMvCounters) return hipErrorInvalidValue;
     return launch_maybe_timed(k_mvN<EPI, NCB, CANON, WM>, dim3(p.grid_x, p.ksp), dim3(512), lds, s, a, p.TS);
 }
 
@@ -1307,6 +1309,11 @@ int mv_split_slots(const MvArgs &a, int n_cu) {
     const int TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
     const int ksp = (a.T + TS - 1) / TS;
     return ksp > 1 ? ksp * a.n_rg : 0;
+}
+
+int mv_split_counters(const MvArgs &a, int n_cu) {
+    if (mv_split_slots(a, n_cu) == 0) return 0;
+    return mvn_counters(mvn_plan(a, n_cu, mvn_canon(a, n_cu, mv_column_blocks(a))));
 }
 
 hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_override, hipStream_t s) {

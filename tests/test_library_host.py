@@ -205,6 +205,23 @@ def test_projection_kernel_of_a_block_is_the_faster_one(P, width):
         B.projection_path(cfg, "qkv", 33)
 
 
+def test_arrival_counters_cover_every_split_block_projection(P):
+    """A block projection that is split in depth has an arrival counter for each of the eight wavefronts of a workgroup of six or
+    eight row groups: for every matrix that is split (at 256 compute units: up to 1024 row groups) they fit the 4096 counters
+    of the arena and of the static scratch."""
+    from paper_2410_06916_amd import binding as B
+    split = set()
+    for n_rg in list(range(1, 1500, 7)) + [2000, 4096, 32767]:
+        for hidden in (64, 1016, 4096, 8192):
+            cfg = B.make_config(si.ModelShape("counters", 1, hidden, 4, 4, 64, 8, 16 * n_rg, "bf16", 1e-5), 64)
+            for rows, exact in ((6, True), (16, True), (32, True), (64, False)):
+                name = B.projection_path(cfg, "lmhead", rows, exact)
+                if name.startswith("mvN") and not name.endswith("parts 1>"):
+                    split.add(n_rg)
+                    assert (n_rg + 5) // 6 * 8 <= 4096, (n_rg, hidden, rows, name)
+    assert len(split) > 50 and max(split) > 900
+
+
 @pytest.mark.parametrize("head_dim", [16, 32, 64, 128])
 def test_every_prompt_launch_has_a_plan_in_the_matrix_order(P, head_dim):
     """The blocked matrix product finds a plan that keeps the order of the sums for every head count, grouping and depth and
