@@ -247,6 +247,48 @@ def test_prefill_last_layer_of_macro_blocks_against_64_row_blocks(shape):
     g.close()
 
 
+@pytest.mark.parametrize("hidden,ffn,heads,kv,d,subs,projection,path", [
+    # tile shapes that the tuning interface does not offer: 96, 160 and 224 rows x 256 columns, 192 x 128
+    (72, 1240, 32, 32, 128, 3, "qkv", "gemm<tile 7, parts 1, whole>"),
+    (1456, 184, 16, 16, 32, 11, "qkv", "gemm<tile 7, parts 2, workgroups>"),
+    (168, 1432, 24, 24, 128, 8, "qkv", "gemm<tile 8, parts 1, whole>"),
+    (3320, 3360, 4, 1, 32, 3, "gateup", "gemm<tile 8, parts 3, workgroups>"),
+    (232, 736, 32, 32, 64, 16, "qkv", "gemm<tile 9, parts 1, whole>"),
+    (3848, 1256, 4, 2, 32, 11, "gateup", "gemm<tile 9, parts 3, workgroups>"),
+    (104, 128, 48, 48, 64, 5, "qkv", "gemm<tile 10, parts 1, whole>"),
+    (3608, 5296, 4, 4, 64, 3, "down", "gemm<tile 10, parts 4, workgroups>"),
+    # parts added inside the workgroup
+    (3416, 272, 24, 24, 32, 11, "qkv", "gemm<tile 1, parts 3, inside>"),
+    (3536, 4112, 16, 16, 32, 11, "gateup", "gemm<tile 2, parts 4, inside>"),
+    (1520, 1496, 48, 48, 128, 16, "qkv", "gemm<tile 3, parts 3, inside>"),
+    (968, 392, 4, 1, 32, 16, "gateup", "gemm<tile 5, parts 2, inside>"),
+    (3632, 1288, 4, 1, 64, 11, "gateup", "gemm<tile 7, parts 3, inside>"),
+    (976, 8240, 24, 6, 32, 8, "gateup", "gemm<tile 8, parts 2, inside>"),
+], ids=lambda v: v.replace("gemm<", "").replace(">", "").replace(", ", "-").replace(" ", "") if isinstance(v, str) else None)
+def test_prefill_tiles_and_parts_with_a_ragged_depth(hidden, ffn, heads, kv, d, subs, projection, path):
+    """Launches of the blocked matrix product that only the launcher's own choice reaches, each over a depth that is not a multiple
+    of the 32-deep k tile (8, 16 and 24 over) and with a last sub-block of 37 rows, against the same prompt in 64-row blocks.  Bounds as
+    for the depth split."""
+    import paper_2410_06916_amd as P
+    from paper_2410_06916_amd import binding as B
+    shape = si.ModelShape("ragged-tiles", 2, hidden, heads, kv, d, ffn, 96, "bf16", 1e-5)
+    n_prompt = 64 * subs - 27
+    g = P.SwiftModel(shape, n_prompt + 8)
+    assert B.prompt_path(g.cfg, projection, subs) == path
+    g.load_weights(si.iter_weights(shape, 6, "cuda:0", gain_jitter=0.1))
+    prompt = si.uniform_ids(75, n_prompt, shape.vocab)
+    res = []
+    for blocks in (-1, 0):
+        g.prefill_blocks(blocks)
+        g.prefill(prompt)
+        res.append((np.stack([g.read_logits(r) for r in range(37)]),
+                    [x for layer in range(2) for p in list(range(0, n_prompt, 29)) + [n_prompt - 1] for x in g.read_kv(layer, p)]))
+    assert np.all(hp.rel_err_rowmax(res[1][0], res[0][0]) <= 2e-3)
+    for a, b in zip(res[0][1], res[1][1]):
+        assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(a) + 2.0 ** -10 * np.abs(a).max())
+    g.close()
+
+
 def test_prefill_of_a_head_count_off_every_tile_edge():
     """125 heads of 64: at 16 sub-blocks the row groups of the last layer's keys and values alone have no plan in the order of
     their matrix's sums, so the whole matrix goes through.  Against the same prompt in 64-row blocks, and bit for bit against
