@@ -629,8 +629,8 @@ constexpr GemmTiling kGemmTilings[kGemmCodes + 1] = {{0, 0}, {4, 2}, {4, 4}, {4,
 
 // What a workgroup costs, measured with all compute units at work (7B, 13B and 70B shapes, 128-1024 rows): us per k tile, and us
 // per workgroup for its start, the first stages' arrival and the epilogue.  Over 105 launches (profiles/blocked_product_sweep.txt)
-// the shapes and splits chosen by them add up to 0.3 % more than the fastest of each launch; single launches up to 11 % (13B
-// q|k|v).  (A 256 x 256 tile's matrix instructions take 0.54 us per k tile at 1.9 GHz; a whole chip of them is held to less by
+// the shapes and splits chosen by them, were any order of the sums allowed, add up to 0.3 % more than the fastest of each launch;
+// single launches up to 11 % (13B q|k|v).  With the order kept (gemm_sums) it is 3.2 %.  (A 256 x 256 tile's matrix instructions take 0.54 us per k tile at 1.9 GHz; a whole chip of them is held to less by
 // its power, 1.6 PFLOP/s.)
 struct GemmCost {
     double stage, fixed;
@@ -643,8 +643,11 @@ constexpr double kPartBytesPerUs = 1.43e6;  // publishing and adding the parts o
 // then the parts in order), the others in one go.  It is a function of the matrix and the number of sub-blocks alone, not of
 // the tile shape or of who computes what, so that the cache entries that a prompt leaves are the same bits whatever the plan below
 // makes of them (a sampled continuation may hang on them); macro blocks of more than eight sub-blocks follow the order of
-// eight, so that a prompt may be cut into either.  (The order is that of a launch with tiles of 16 .. 256 rows on `a.n_rg` row groups by
-// the costs here, whose last round of workgroups was split in depth.)
+// eight, so that a prompt may be cut into either.  The shapes and costs below are those of a launcher of earlier kernels, whose last round
+// of workgroups was split in depth: they stand for nothing but the order it left, which caches and continuations follow.
+// What it costs: row groups summed in parts exclude tiles whose edges do not meet the first of them, and, inside a workgroup, tiles of more
+// than kFoldMaxRgw row groups per wavefront (7B gate/up, 1024 rows: 309 us, 280 with 256 x 256 tiles; k|v of 70B at 6-8
+// sub-blocks 69, 43-47).
 struct GemmSums {
     int first, parts, TS;
 };

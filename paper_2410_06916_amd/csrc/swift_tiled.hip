@@ -676,7 +676,7 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 // What bounds it: the weight stream, and the operand reads (a wavefront reads 2 + NCW KB per k tile; as one row group
 // times all columns, which is what this kernel replaces, 1 + NCB KB from chunks of eight tiles that drained the loads in
 // flight at every barrier).  Weights are copied non-temporally, so that they do not push the B operand, which every workgroup
-// reads, out of L2.  us, before / now: 7B, 31 rows gate/up 54 / 40, down_proj 35.5 / 28, LM head 60 / 48; 32 bulk rows gate/up
+// reads, out of L2.  us, before / now, launches back to back: 7B, 31 rows gate/up 54 / 40, down_proj 35.5 / 28 (30 in a pass), LM head 60 / 48; 32 bulk rows gate/up
 // 40.5 / 34; 13B, 31 rows gate/up 79 / 57, down_proj 57 / 39; 70B, 31 rows gate/up 231 / 179, LM head 112 / 86.  (One k tile a
 // stage 1-3 % slower; weights straight to registers, each tile by two wavefronts: gate/up 54; four wavefronts of 512 registers
 // with six row groups each and nothing staged: 62.)
@@ -1229,19 +1229,14 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
     return mvr_depth((a.T + 7) / 8, NCB, RG) == NS ? launch_mvR_ns<EPI, NCB, RG, NS>(a, s) : launch_mvR_ns<EPI, NCB, RG, NS2>(a, s);
 }
 
-// Row groups per workgroup round for k_mvR, or 0: k_mvN.
-// From eleven exact (17 bulk) rows on, k_mvN takes the matrices that its workgroups of six row groups cover in one round with K
-// whole (us, k_mvR / k_mvN, 7B gate/up: 16 rows 35.8 / 33.5, 21 rows 43.0 / 35.3, 26 rows 48.1 / 38; 9 rows 33 / 34).
-// Elsewhere the line is where k_mvR broke even with the kernel that k_mvN replaces, by what one compute unit had to
+// A line between small blocks and large ones: row groups per workgroup round for k_mvR short of it, 0 beyond.  Two things hang on
+// it: which kernel exact blocks take (mvr_row_groups), and how bulk blocks of 32 rows add their sums (mvn_canon).
+// It is where k_mvR broke even with the kernel that k_mvN replaces, by what one compute unit had to
 // walk, in us per k tile, fitted to 709 sets of launch durations of both (rows 1-32 of both layouts, seven widths
 // from 1024 to 8192, matrices of 6 to 1300 MB).  c: column blocks, 0.4 x those computed + 0.6 x the columns' own share.
 //   k_mvR   3.7 + rounds x 8 slices x steps of a slice as walked x (weights of 1, 2 or 3 row groups + c columns of B)
 //   line    6.1 (+ 2.8 + 0.96 c where K is split over workgroups) + rounds x tiles (a slice's last chunk of eight, where it
 //           is partial, counts half of what it lacks) x (row groups + c columns), by the root of the share of units in use
-// Beyond the line k_mvN is the faster kernel by 2-40 % (us, k_mvR / k_mvN: 7B, 31 rows down_proj 41.3 / 28, LM head 75 / 48; 70B,
-// 16 rows LM head 97.7 / 82).  Short of it k_mvR is, by far at few rows (7B, 9 rows q|k|v 20 / 27, o_proj 9.2 / 17, down_proj 22 /
-// 25; 31 rows o_proj 17 / 22), and loses 6-17 % in a strip along the line (13B, 21 rows q|k|v 42 / 36; 70B, 16 rows down_proj
-// 92 / 76.5, 31 rows q|k|v 49.5 / 45): the instances that blocks of those widths take are part of what the tests state.
 static int mvr_line(const MvArgs &a, int n_cu, int ncb) {
     if (ncb < 1 || ncb > 6 || a.R > kMaxRows) return 0;
     static const double kWeights[3] = {0.0213, 0.0467, 0.0603}, kColumns[3] = {0.0147, 0.0178, 0.0226};
@@ -1275,6 +1270,15 @@ static int mvr_line(const MvArgs &a, int n_cu, int ncb) {
     }
     return rg;
 }
+// Row groups per workgroup round for k_mvR, or 0: k_mvN.  From eleven exact (17 bulk) rows on, k_mvN takes the matrices that its
+// workgroups of six row groups cover in one round with K whole (us, k_mvR / k_mvN, 7B gate/up: 16 rows 35.8 / 33.5, 21 rows 43.0 /
+// 35.3, 26 rows 48.1 / 38; 9 rows 33 / 34); elsewhere what lies beyond the line.
+// The line prices the predecessor of k_mvN, so it is not where today's two kernels break even (both timed at the 7B, 13B and 70B
+// widths, 6-32 rows: profiles/block_projection_sweep.txt, third table).  Beyond it k_mvN is faster throughout (us, k_mvR / k_mvN: 7B, 31
+// rows down_proj 41.8 / 28.2, LM head 75 / 47.5; 13B, 24 rows gate/up 82 / 54).  Short of it k_mvR is where the matrix is narrow or
+// the rows few (7B, 9 rows q|k|v 20.4 / 23.5, 31 rows o_proj 17 / 20), and k_mvN would be by up to 32 % in a strip along it (13B, 18 rows LM
+// head 72.8 / 55.1, 9 rows gate/up 54.9 / 46.9, 21 rows q|k|v 42 / 34.5; 7B, 13 rows down_proj 28.6 / 23.1; 70B, 18 rows gate/up 187 / 160,
+// 16 rows down_proj 93 / 75): 3.5 % over all launches of the table.  Exact blocks come out the same bits either way.
 static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     if (ncb > 2 && ncb <= 6) {
         const MvnPlan p = mvn_plan(a, n_cu, true);
@@ -1283,7 +1287,8 @@ static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     return mvr_line(a, n_cu, ncb);
 }
 // Whether k_mvN adds the eight slices: exact layouts, and bulk ones of 32 rows short of the line (K whole there), whose sums are
-// k_mvR's then, so that which kernel is the faster one does not decide what a short prompt leaves in the cache.
+// k_mvR's then.  This is an order of sums and no rule about speed: a short prompt's cache entries hang on it, whichever kernel
+// runs, so it stays where it is if the choice between the kernels moves.
 static bool mvn_canon(const MvArgs &a, int n_cu, int ncb) { return !(a.RL & kBulkLayout) || mvr_line(a, n_cu, ncb) != 0; }
 
 // Small blocks (in their own exact layout) whose whole activation fits in LDS take the single-pass kernel.

@@ -175,8 +175,9 @@ def test_prefill_block_sizes_against_oracle(oracle_lib):
 
 @pytest.mark.parametrize("subs,rgw", [(-1, 0)] + [(s_, r_) for s_ in (2, 3, 8) for r_ in (1, 2, 3, 4, 5, 6)])
 def test_prefill_tilings_against_oracle(oracle_lib, subs, rgw):
-    """Every tile shape of the blocked matrix product (1..4 row groups per wavefront on two sub-blocks, 1 or 2 on
-    one: another ring depth and another share of the copies per wavefront each) and macro blocks of 2, 3 and 8 sub-blocks, against the one
+    """The tile shapes of the blocked matrix product that a caller can ask for (2, 4, 6 or 8 row groups per wavefront on two
+    sub-blocks, 2 or 4 on one: another ring depth and another share of the copies per wavefront each; the other four: the test of
+    tiles and parts with a ragged depth) and macro blocks of 2, 3 and 8 sub-blocks, against the one
     64-row block per sweep that the same prompts take with subs = -1; heads of 64 (attention on the matrix
     cores inside the macro block), a row count that leaves row groups past the end of every tile height."""
     shape = si.ModelShape("macro-d64", 2, 224, 4, 2, 64, 344, 300, "bf16", 1e-5)
@@ -542,7 +543,7 @@ def test_candidate_evaluation_against_oracle(oracle_lib, case):
                 g.prefill_blocks(0)
                 assert np.array_equal(pb, po) and mb == mo, (case, gamma, mi, "64-row blocks")
                 if case == "7b-width-long-window":
-                    # every tile shape of the blocked matrix product (with two sub-blocks the matrices of few rows
+                    # every tile shape of the blocked matrix product that can be asked for (with two sub-blocks the matrices of few rows
                     # split the depth over workgroups under each of them)
                     for tiling in range(1, 7):
                         g.prefill_blocks(0, tiling)

@@ -167,8 +167,8 @@ def test_projection_kernels_hold_their_windows_in_registers(P):
 
 
 _R = "mvR<columns %d, row groups %d"
-# (kernel class, rows) -> the kernel that was the faster one by 4 % and more, each launch timed on the MI355X
-_FASTER_PROJECTION = {
+# (kernel class, rows) -> the kernel that is taken
+_PROJECTION_KERNEL = {
     "7b": {("qkv", 9): _R % (2, 3), ("oproj", 9): _R % (2, 1), ("gateup", 9): _R % (2, 3), ("down", 9): _R % (2, 1),
            ("down", 11): _R % (3, 1), ("qkv", 31): _R % (6, 3), ("oproj", 31): _R % (6, 1), ("down", 31): "mvN", ("lmhead", 31): "mvN",
            ("lmhead", 19): "mvN", ("down", 5): _R % (1, 1)},
@@ -180,23 +180,25 @@ _FASTER_PROJECTION = {
             ("down", 31): "mvN", ("gateup", 31): "mvN", ("oproj", 31): "mvN"},
 }
 # the same for candidate-evaluation and prompt blocks of 17-32 rows (two terms per row: four column blocks)
-_FASTER_PROJECTION_BULK = {
+_PROJECTION_KERNEL_BULK = {
     "7b": {"qkv": _R % (4, 3), "oproj": _R % (4, 1), "lmhead": "mvN"},
     "13b": {"qkv": "mvN", "oproj": _R % (4, 2), "gateup": "mvN", "down": "mvN", "lmhead": "mvN"},
     "70b": {"qkv": _R % (4, 3), "oproj": _R % (4, 2), "down": "mvN", "lmhead": "mvN"},
 }
 
 
-@pytest.mark.parametrize("width", sorted(_FASTER_PROJECTION))
-def test_projection_kernel_of_a_block_is_the_faster_one(P, width):
-    """The rule that chooses between the two block projection kernels, against launch durations of both (7B, 13B and 70B
-    widths, 256 compute units; profiles/block_projection_sweep.txt holds all of them)."""
+@pytest.mark.parametrize("width", sorted(_PROJECTION_KERNEL))
+def test_projection_kernel_of_a_block(P, width):
+    """Which of the two block projection kernels is taken on either side of the line between them (7B, 13B and 70B widths, 256
+    compute units).  The line was fitted to launch durations of k_mvR and of the kernel before k_mvN, and most entries are the
+    faster of those two by 4 % and more; against today's k_mvN some along the line are not (13B gate/up and LM head at nine rows:
+    profiles/block_projection_sweep.txt, third table).  Results of exact blocks do not hang on it."""
     from paper_2410_06916_amd import binding as B
     cfg = B.make_config({"7b": si.LLAMA2_7B, "13b": si.LLAMA2_13B, "70b": si.LLAMA2_70B}[width], 777)
-    for (name, rows), want in _FASTER_PROJECTION[width].items():
+    for (name, rows), want in _PROJECTION_KERNEL[width].items():
         got = B.projection_path(cfg, name, rows)
         assert got.startswith(want), (name, rows, got)
-    for name, want in _FASTER_PROJECTION_BULK[width].items():
+    for name, want in _PROJECTION_KERNEL_BULK[width].items():
         got = B.projection_path(cfg, name, 32, exact=False)
         assert got.startswith(want), (name, "bulk", got)
     with pytest.raises(P.SwiftError):
