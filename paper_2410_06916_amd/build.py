@@ -16,9 +16,10 @@ HEADERS = ["swift_kernels.h", "swift_device.h", "swift_attn.h", "swift_mv.h", os
 STAMP = os.path.join(HERE, "libswift_hip.srchash")
 OBJ = os.path.join(HERE, "_build")
 
-# packed-fp32 instruction selection is switched off for all device code
+# packed-fp32 instruction selection is switched off for all device code; the leading scalar arguments of a kernel are in registers
+# when its wavefronts start
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-Wall", "-Wno-unused-result",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def lib_path() -> str:

@@ -37,6 +37,17 @@ __device__ inline void split3(float v, uint16_t &hi, uint16_t &mid, uint16_t &lo
     lo = (uint16_t)f32_to_bf16_rne_finite(r2);
 }
 
+// The same for a product a * b: what is left after hi comes from the unrounded product (spelt out, so that it is the same in every kernel).
+__device__ inline void split3(float a, float b, uint16_t &hi, uint16_t &mid, uint16_t &lo) {
+    const uint32_t h = f32_to_bf16_rne_finite(a * b);
+    const float r1 = fmaf(a, b, -__uint_as_float(h << 16));
+    const uint32_t m = f32_to_bf16_rne_finite(r1);
+    const float r2 = r1 - __uint_as_float(m << 16);
+    hi = (uint16_t)h;
+    mid = (uint16_t)m;
+    lo = (uint16_t)f32_to_bf16_rne_finite(r2);
+}
+
 // Exchanges the odd 16-lane rows of a with the even ones of b.
 __device__ inline void swap16(uint32_t &a, uint32_t &b) {
     const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
@@ -56,6 +67,33 @@ __device__ inline uint32_t pack2(uint32_t lo, uint32_t hi) { return lo | (hi << 
 // load and store of the wavefront (its release fence covers global memory), which would drain a
 // window of weight loads that is deliberately kept in flight across the barrier.
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The struct argument at byte `at` of the kernel's arguments, through a pointer the compiler cannot see behind: its fields are read
+// where they are used, and what the kernel does before waits for none of them.
+template <typename A>
+__device__ inline const A &late_args(int at) {
+    auto p = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const A *)(const __attribute__((address_space(4))) A *)(p + at);
+}
+
+// Copies 4 or 16 bytes per lane from global memory straight to LDS: lane l's go to byte BYTES * l of dst (wavefront-uniform).
+// NT: non-temporal.  Waiting for it (vmcnt) is the caller's business.
+template <int BYTES, bool NT = false>
+__device__ inline void to_lds(const void *src, void *dst) {
+    const auto from = (const __attribute__((address_space(1))) void *)src;
+    const auto to = (__attribute__((address_space(3))) void *)dst;
+    if constexpr (BYTES == 4) {
+        __builtin_amdgcn_global_load_lds(from, to, 4, 0, 0);
+    } else if constexpr (NT) {
+        __builtin_amdgcn_global_load_lds(from, to, 16, 0, 2);
+    } else {
+        __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+    }
+}
+
+// Keeps a loaded word that nobody uses from being optimised away (and is where it is waited for).
+__device__ inline void keep_alive(uint32_t w) { asm volatile("" ::"v"(w)); }
 
 struct F32T {
     static constexpr int VEC = 4;  // elements per 16-byte load
@@ -107,6 +145,15 @@ __device__ inline float wave_reduce(float v, Op op) {
 }
 __device__ inline float wave_sum(float v) {
     return wave_reduce(v, [](float x, float y) { return x + y; });
+}
+// The sum of v^2 over a row of 16 lanes, in the row's first lane: that lane's sum of an exchange with lane ^ 8, ^ 4, ^ 2, ^ 1 (one
+// rounding in the first sum: a fused multiply-add, spelt out so that it is the same in every kernel; for lanes 0 to 3, rotating
+// by 12 is ^ 4).
+__device__ inline float row_sum_of_squares(float v) {
+    float s = fmaf(v, v, dpp_move<0x128>(v * v));
+    s += dpp_move<0x12C>(s);
+    s += dpp_move<0x4E>(s);
+    return s + dpp_move<0xB1>(s);
 }
 __device__ inline float wave_max(float v) {
     return wave_reduce(v, [](float x, float y) { return fmaxf(x, y); });

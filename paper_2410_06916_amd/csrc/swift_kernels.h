@@ -241,24 +241,46 @@ hipError_t launch_tile_weights(const TileArgs &a, hipStream_t s);
 // (x * gain of the next consumer) and, per 16-row group, the partial sums of squares of x, so the
 // consumer only adds up the partials (fixed order) to get the RMSNorm scale 1/sqrt(mean x^2 + eps)
 // and applies it to its results (W.(x*g) * scale == W.(x*scale*g) up to fp32 rounding).
+//
+// A pointer to device memory that the compiler knows as such wherever the struct that holds it was read from (it finds that out
+// by itself for the arguments of a kernel, not behind late_args; through generic pointers a kernel waits for all its loads at once).
+template <typename T>
+struct DevPtr {
+    T *p;
+    __host__ __device__ DevPtr &operator=(T *q) {
+        p = q;
+        return *this;
+    }
+    __host__ __device__ operator T *() const {
+#ifdef __HIP_DEVICE_COMPILE__
+        return (T *)(__attribute__((address_space(1))) T *)p;
+#else
+        return p;
+#endif
+    }
+    template <typename U>
+    __host__ __device__ explicit operator U *() const {
+        return (U *)(T *)*this;
+    }
+};
 struct MvArgs {
-    const void *Wt;        // tiled weights
+    DevPtr<const void> Wt; // tiled weights
     int O, K, T, n_rg;     // real rows / depth, k-tiles, row groups
     int R;                 // activation rows, 1..64
     int RL;                // layout code of the split layouts (in_s, out_s): block_row_layout
                            // (columns of rows that do not exist hold garbage that no result depends on)
-    const uint16_t *in_s;  // split input [K/8][3 RL][8]
-    const float *pss;      // [n_pss][rp] partial sums of squares of the producer, or nullptr: no norm
+    DevPtr<const uint16_t> in_s;  // split input [K/8][3 RL][8]
+    DevPtr<const float> pss;  // [n_pss][rp] partial sums of squares of the producer, or nullptr: no norm
     int n_pss, norm_dim;
     int rp;                // row pitch of pss and pss_out: 16 for blocks of up to 16 rows, else 64
     float eps;
-    float *out_f32;        // QKV: q [R][ld_out]; LOGITS: logits [R][ld_out]; RESID: x [R][ld_out] (in/out)
+    DevPtr<float> out_f32; // QKV: q [R][ld_out]; LOGITS: logits [R][ld_out]; RESID: x [R][ld_out] (in/out)
     int ld_out;
-    uint16_t *out_s;       // SWIGLU: split h [F/8][3 RL][8]; RESID: split of x*gain_next [O/8][3 RL][8]
-    const float *gain_next;  // RESID: [O]
-    float *pss_out;        // RESID: [n_rg][rp]
-    void *kcache, *vcache;   // QKV: this layer's [n_kv][max_seq][d]
-    const float *cos_tab, *sin_tab;  // QKV: [max_seq][d/2]
+    DevPtr<uint16_t> out_s;  // SWIGLU: split h [F/8][3 RL][8]; RESID: split of x*gain_next [O/8][3 RL][8]
+    DevPtr<const float> gain_next;  // RESID: [O]
+    DevPtr<float> pss_out; // RESID: [n_rg][rp]
+    DevPtr<void> kcache, vcache;  // QKV: this layer's [n_kv][max_seq][d]
+    DevPtr<const float> cos_tab, sin_tab;  // QKV: [max_seq][d/2]
     int pos0, max_seq, head_dim, n_q_heads, n_kv_heads;
     int head0;             // QKV, blocked matrix product only: the fused matrix's head that row group 0 belongs to
     // QKV: row r's keys/values go to slot pos0 + r; it is rotated for position pos0 + r, or, for the rows
@@ -266,11 +288,11 @@ struct MvArgs {
     int tree;
     uint8_t depth[kMaxRows];
     int nb32;              // QKV: > 0: the values go to the grouped layout (kv_vt_index), nb32 32-slot chunks per head
-    uint16_t *q_s;         // QKV: nullptr, or [R][n_q][2][d]: the rotated queries once more, as two bf16 terms (hi, then
+    DevPtr<uint16_t> q_s;  // QKV: nullptr, or [R][n_q][2][d]: the rotated queries once more, as two bf16 terms (hi, then
                            // what is left of the fp32 value after hi), the operand form of the matrix-core attention
     // multi-row kernel only: split-K scratch
-    float *part;           // [k splits][row group][R][16] fp32 partial results
-    int *counters;         // [kMvCounters], zero between launches (one per wavefront of a row block)
+    DevPtr<float> part;    // [k splits][row group][R][16] fp32 partial results
+    DevPtr<int> counters;  // [kMvCounters], zero between launches (one per wavefront of a row block)
     int part_capacity;     // row-group-splits the scratch can hold
     int S;                 // set by the launcher
     int kgroup;            // set by the launcher: K slices whose sums are added first (see mv_slice_group)

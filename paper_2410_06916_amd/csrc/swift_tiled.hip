@@ -17,6 +17,9 @@
 
 namespace swift {
 
+constexpr int kNonTemporal = 2;  // cache policies: nt; sc1
+constexpr int kDeviceScope = 16;
+
 // Events for the next projection launch (see set_launch_events in swift_kernels.h).
 static thread_local hipEvent_t g_ev_start = nullptr, g_ev_stop = nullptr;
 void set_launch_events(hipEvent_t start, hipEvent_t stop) {
@@ -170,104 +173,79 @@ hipError_t launch_embed_rows(const EmbedRowsArgs &a, const int32_t *tokens, hipS
 // ------------------------------------------------------------------------------------------
 // shared pieces of the projection kernels
 // ------------------------------------------------------------------------------------------
-// RMSNorm scale per block row from the producer's partial sums of squares [n_pss][16].  All 512
-// threads load (thread = (partial p mod 32, row r)); mv_norm_load issues the first eight loads per
-// thread (enough for 256 partials, hidden <= 4096) so that the caller can put them ahead of the
-// weight loads; mv_norm_finish adds the rest, then 16 threads add the 32 per-lane sums in order:
-// the summation order is fixed.  One barrier, before the final sums.  (Full barriers: LDS-only ones, which would leave the
-// caller's first weight loads in flight, measured 0.3 us slower per launch.)
+// RMSNorm scale per block row from the producer's partial sums of squares.  A kernel requests the first 256 partials of its rows
+// (hidden <= 4096: all of them) ahead of its weights and adds them up once the weights are on their way: no branches
+// and no use of a loaded value in between (a partial past the last is the last one again, left out of the sum later), since a
+// wait there would hold the weights up.  The summation order is fixed.  One barrier, which orders LDS only, before the final sums.
+//
+// Up to 16 rows (row pitch 16): thread (q = t / 16, row r = t % 16) adds the partials q + 32 u in order of u, then 16 threads
+// add the 32 sums in order.
 struct NormPart {
     float v[8];
 };
-__device__ inline NormPart mv_norm_load(const MvArgs &a) {
+__device__ inline NormPart mv_norm_load(const MvArgs &a, int p0 = 0) {
     NormPart np;
-    const int tid = threadIdx.x, r = tid & 15, q = tid >> 4;
+    const uint32_t at = threadIdx.x + 16 * p0, end = 16 * a.n_pss - 1;  // partial p of row r is word 16 p + r
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int p = q + 32 * u;
-        np.v[u] = (a.pss && p < a.n_pss) ? a.pss[(size_t)p * a.rp + r] : 0.f;
-    }
+    for (int u = 0; u < 8; ++u) np.v[u] = *(const float *)((const char *)a.pss + 4 * min(at + 512 * u, end));
     return np;
 }
-template <bool LDS_ONLY = false>
-__device__ inline void mv_norm_finish(const MvArgs &a, const NormPart &np, float *rs /* LDS [16] */,
-                                      float *scratch /* LDS [512] */) {
-    const int tid = threadIdx.x, r = tid & 15, q = tid >> 4;
-    if (a.pss) {
-        float ss = 0.f;
+__device__ inline void mv_norm_finish(const MvArgs &a, const NormPart &np, float *rs /* LDS [16] */, float *scratch /* LDS [512] */) {
+    const int tid = threadIdx.x, q = tid >> 4;
+    float ss = 0.f;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) ss += np.v[u];
-        for (int p0 = 256; p0 < a.n_pss; p0 += 256) {
-            float v[8];
+    for (int u = 0; u < 8; ++u) ss += q + 32 * u < a.n_pss ? np.v[u] : 0.f;
+    for (int p0 = 256; p0 < a.n_pss; p0 += 256) {
+        const NormPart more = mv_norm_load(a, p0);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int p = p0 + q + 32 * u;
-                v[u] = p < a.n_pss ? a.pss[(size_t)p * a.rp + r] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) ss += v[u];
-        }
-        scratch[q * 16 + r] = ss;
+        for (int u = 0; u < 8; ++u) ss += p0 + q + 32 * u < a.n_pss ? more.v[u] : 0.f;
     }
-    if (LDS_ONLY)
-        lds_barrier();
-    else
-        __syncthreads();
+    scratch[tid] = ss;
+    lds_barrier();
     if (tid < 16) {
-        float ss = 0.f;
-        if (a.pss)
-            for (int q2 = 0; q2 < 32; ++q2) ss += scratch[q2 * 16 + tid];
-        rs[tid] = a.pss ? 1.0f / sqrtf(ss / (float)a.norm_dim + a.eps) : 1.0f;
+        float t = 0.f;
+#pragma unroll
+        for (int q2 = 0; q2 < 32; ++q2) t += scratch[q2 * 16 + tid];
+        rs[tid] = 1.0f / sqrtf(t / (float)a.norm_dim + a.eps);
     }
     // (no barrier here: the scales are read by the epilogue only, and every caller has a barrier between
     // this point and its epilogue)
 }
 
-// The same for exact layouts of 17..32 rows (row pitch 64), in the summation order of mv_norm_load /
-// mv_norm_finish -- a row's scale must not depend on the rows it shares a pass with: thread (row r, q) adds
-// the partials q + 32 u and q + 16 + 32 u, u = 0, 1, .., as two sums; then 32 threads add the 32 sums in
-// order.  In two parts: the loads of the first 256 partials (hidden <= 4096: all of them), and the rest with an
-// LDS-only barrier.
+// The same for exact layouts of 17..32 rows (row pitch 64), in the same order -- a row's scale must not depend on the rows it
+// shares a pass with: thread (row r, q) adds the partials q + 32 u and q + 16 + 32 u as two sums; then 32 threads add the 32 sums
+// in order.
 struct NormPart32 {
     float v[2][8];
 };
-__device__ inline void mv_norm32_load(const MvArgs &a, int p0, NormPart32 &np) {
-    const int tid = threadIdx.x, r = tid & 31, q0 = tid >> 5;
+__device__ inline NormPart32 mv_norm32_load(const MvArgs &a, int p0 = 0) {
+    NormPart32 np;
+    const uint32_t r = threadIdx.x & 31, at = 64 * (p0 + (threadIdx.x >> 5)) + r, end = 64 * (a.n_pss - 1) + r;
 #pragma unroll
     for (int half = 0; half < 2; ++half)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int p = p0 + q0 + 16 * half + 32 * u;
-            np.v[half][u] = (a.pss && p < a.n_pss) ? a.pss[(size_t)p * a.rp + r] : 0.f;
-        }
+        for (int u = 0; u < 8; ++u) np.v[half][u] = *(const float *)((const char *)a.pss + 4 * min(at + 64 * (16 * half + 32 * u), end));
+    return np;
 }
-__device__ inline void mv_norm32_finish(const MvArgs &a, NormPart32 &np, float *rs /* LDS [32] */, float *scratch /* LDS [1024] */) {
+__device__ inline void mv_norm32_finish(const MvArgs &a, const NormPart32 &np, float *rs /* LDS [32] */, float *scratch /* LDS [1024] */) {
     const int tid = threadIdx.x, r = tid & 31, q0 = tid >> 5;
     float ss[2] = {0.f, 0.f};
-    for (int p0 = 0;;) {
+    auto add = [&](int p0, const NormPart32 &n) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            float t = 0.f;
-            if (p0 == 0) {
+        for (int half = 0; half < 2; ++half)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t += np.v[half][u];
-                ss[half] = t;
-            } else {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) ss[half] += np.v[half][u];
-            }
-        }
-        p0 += 256;
-        if (p0 >= a.n_pss) break;
-        mv_norm32_load(a, p0, np);
-    }
+            for (int u = 0; u < 8; ++u) ss[half] += p0 + q0 + 16 * half + 32 * u < a.n_pss ? n.v[half][u] : 0.f;
+    };
+    add(0, np);
+    for (int p0 = 256; p0 < a.n_pss; p0 += 256) add(p0, mv_norm32_load(a, p0));
     scratch[q0 * 32 + r] = ss[0];
     scratch[(q0 + 16) * 32 + r] = ss[1];
     lds_barrier();
     if (tid < 32) {
         float t = 0.f;
+#pragma unroll
         for (int q2 = 0; q2 < 32; ++q2) t += scratch[q2 * 32 + tid];
-        rs[tid] = a.pss ? 1.0f / sqrtf(t / (float)a.norm_dim + a.eps) : 1.0f;
+        rs[tid] = 1.0f / sqrtf(t / (float)a.norm_dim + a.eps);
     }
 }
 
@@ -275,30 +253,29 @@ __device__ inline void mv_norm32_finish(const MvArgs &a, NormPart32 &np, float *
 struct NormPart64 {
     float v[32];
 };
-__device__ inline void mv_norm64_load(const MvArgs &a, int p0, NormPart64 &np) {
-    const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
+__device__ inline NormPart64 mv_norm64_load(const MvArgs &a, int p0 = 0) {
+    NormPart64 np;
+    const uint32_t at = threadIdx.x + 64 * p0, end = 64 * (a.n_pss - 1) + (threadIdx.x & 63);  // partial p of row r is word 64 p + r
 #pragma unroll
-    for (int u = 0; u < 32; ++u) {
-        const int p = p0 + q + 8 * u;
-        np.v[u] = (a.pss && p < a.n_pss) ? a.pss[(size_t)p * a.rp + r] : 0.f;
-    }
+    for (int u = 0; u < 32; ++u) np.v[u] = *(const float *)((const char *)a.pss + 4 * min(at + 512 * u, end));
+    return np;
 }
-__device__ inline void mv_norm64_finish(const MvArgs &a, NormPart64 &np, float *rs /* LDS [64] */, float *scratch /* LDS [512] */) {
-    const int tid = threadIdx.x, r = tid & 63, q = tid >> 6;
+__device__ inline void mv_norm64_finish(const MvArgs &a, const NormPart64 &np, float *rs /* LDS [64] */, float *scratch /* LDS [512] */) {
+    const int tid = threadIdx.x, q = tid >> 6;
     float ss = 0.f;
-    for (int p0 = 0;;) {
+    auto add = [&](int p0, const NormPart64 &n) {
 #pragma unroll
-        for (int u = 0; u < 32; ++u) ss += np.v[u];
-        p0 += 256;
-        if (p0 >= a.n_pss) break;
-        mv_norm64_load(a, p0, np);
-    }
-    scratch[q * 64 + r] = ss;
+        for (int u = 0; u < 32; ++u) ss += p0 + q + 8 * u < a.n_pss ? n.v[u] : 0.f;
+    };
+    add(0, np);
+    for (int p0 = 256; p0 < a.n_pss; p0 += 256) add(p0, mv_norm64_load(a, p0));
+    scratch[tid] = ss;
     lds_barrier();
     if (tid < 64) {
         float t = 0.f;
+#pragma unroll
         for (int q2 = 0; q2 < 8; ++q2) t += scratch[q2 * 64 + tid];
-        rs[tid] = a.pss ? 1.0f / sqrtf(t / (float)a.norm_dim + a.eps) : 1.0f;
+        rs[tid] = 1.0f / sqrtf(t / (float)a.norm_dim + a.eps);
     }
 }
 
@@ -329,29 +306,38 @@ static int mv_slice_group(const MvArgs &a, int n_cu) {
 // each taking a contiguous slice of its k-tiles, so a workgroup works on G = 8/KS row groups at a
 // time and the slices (and the three terms) are added in LDS in a fixed order.  Every wavefront
 // keeps a rolling window of NS (10..16) 1 KB tile loads in flight, walked in blocks of NS slots (the
-// launcher picks the depth that cuts the slice with the fewest unused slots); the first window is
-// issued before the activation is staged, and the window rolls on from one round into the next.
+// launcher picks the depth that cuts the slice with the fewest unused slots), and the window rolls on from one round into the next.
+// What bounds it: the weight stream (6.9 TB/s on large matrices) and about 3 us of start and end per launch.  The start: what the
+// first loads need travels in the kernel's leading arguments, which are in registers when a wavefront starts; the activation, the
+// residual values and the rotary rows go straight to LDS, and loads go out without a branch or a wait between them (a slice is a
+// buffer: past its end it reads nothing).  The end: residual values that are there already, and slice sums read all at once in
+// the last round.  us, before / now (launches back to back, 7B): one row o_proj 8.8 / 7.8, down_proj 16.8 / 16.3, LM head 41.0 /
+// 40.4; two rows down_proj 18.3 / 16.9; five rows q|k|v 22.5 / 20.6, o_proj 10.7 / 9.0, gate/up 32.0 / 31.1, LM head 44.0 / 43.1;
+// 13B, one row gate/up 44.3 / 43.2, down_proj 25.8 / 24.3.  7B gate/up of one row stays at 29.7.
+// LDS beyond mv1_lds_bytes: the touched lines and what rounds the rotary rows up to whole copies.
+constexpr size_t kMv1MoreLds = 256 + 512;
+__host__ __device__ inline int mv1_rot_pitch(int R, int head_dim) { return (R * (head_dim >> 1) + 63) & ~63; }
 template <int EPI, int KS, int NS>
-__global__ __launch_bounds__(512, 4) void k_mv1(MvArgs a) {  // 4 wavefronts per SIMD: <= 128 VGPRs, two workgroups per CU
+__global__ __launch_bounds__(512, 4) void k_mv1(const unsigned char *Wt, const unsigned char *in_s, int T, int K, int R, int n_rg, int W,
+                                                 int S, MvArgs rest) {  // 4 wavefronts per SIMD: <= 128 VGPRs, two workgroups per CU
+    constexpr int rest_at = 40;  // byte offset of `rest` among the arguments
     extern __shared__ __align__(16) unsigned char smem[];
-    const int R = a.R, NC = 3 * R;
-    // LDS: [16 B zeros][4T chunks x NC x 8 bf16][2 x 8 wavefronts x NC x 16 fp32][16 scales][512 scratch][R x d rotary]
-    float *red = (float *)(smem + 16 + (size_t)a.T * 64 * NC);
+    const int NC = 3 * R;
+    // LDS: [16 B zeros][4T chunks x NC x 8 bf16][2 x 8 wavefronts x NC x 16 fp32][16 scales][512 scratch][64 touched][R x d rotary]
+    float *red = (float *)(smem + 16 + (size_t)T * 64 * NC);
     float *rs = red + 2 * 8 * 16 * NC;
     float *nscratch = rs + 16;
-    float *rot = nscratch + 512;  // per block row: [d/2 cos | d/2 sin] at that row's position
+    float *touched = nscratch + 512;  // [64]
+    float *rot = touched + 64;        // [R][d/2] cosines, then sines (at mv1_rot_pitch), of the block rows' positions
     constexpr int G = 8 / KS;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront-uniform from here on
     const int g = wave / KS, ks = wave - g * KS;
-    const int T = a.T;
     const int n = (T + KS - 1) / KS;           // k-tiles per wavefront and row group
     const int t0 = min(ks * n, T - 1);
     const int nv = max(0, min(n, T - ks * n)); // ... of which exist
-    const int nvm1 = max(nv - 1, 0);
-    const u32x4 *Wt = (const u32x4 *)a.Wt;
-    const int W = a.n_wg;
     if (EPI == EPI_QKV && (int)blockIdx.x >= W) {
+        const MvArgs &a = late_args<MvArgs>(rest_at);
         // Cache warm-up for the attention launch that follows: warm-up workgroup p reads the committed keys
         // and values of the kv heads congruent to p.  Workgroups go to the dies round-robin by index, and the
         // attention kernel's workgroup for head g has index g (+ a multiple of 8 per further row), so with
@@ -386,7 +372,7 @@ __global__ __launch_bounds__(512, 4) void k_mv1(MvArgs a) {  // 4 wavefronts per
         if ((x.x & x.y & x.z & x.w) == 0xffffffffu && a.pf_rows < 0) ((volatile uint32_t *)smem)[0] = x.x;
         return;
     }
-    const int last_rg = a.n_rg - 1;
+    const int last_rg = n_rg - 1;
     const int col = lane & 15, kg = lane >> 4;
     // byte address of this lane's B chunk for tile t: boff + t * bstride; lanes of columns >= NC
     // (and slots past the wavefront's slice) read the zero chunk at address 0
@@ -394,8 +380,14 @@ __global__ __launch_bounds__(512, 4) void k_mv1(MvArgs a) {  // 4 wavefronts per
     const int bstride = col < NC ? 64 * NC : 0;
 
     u32x4 buf[NS];
-    const u32x4 *base = nullptr;
-    auto load_slot = [&](int i) { return __builtin_nontemporal_load(base + (size_t)min(i, nvm1) * 64); };
+    // (the slice as a buffer: slots past its end read nothing and give zeros)
+    const uint32_t lane16 = lane * 16;
+    __amdgpu_buffer_rsrc_t slice;
+    auto set_slice = [&](int seg) {
+        const int rg = min((seg * W + (int)blockIdx.x) * G + g, last_rg);
+        slice = __builtin_amdgcn_make_buffer_rsrc((void *)(Wt + ((size_t)rg * T + t0) * 1024), 0, nv * 1024, 0x00020000);
+    };
+    auto load_slot = [&](int i) { return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(slice, lane16, i * 1024, kNonTemporal)); };
     auto mma_slot = [&](int i, const u32x4 &av, f32x4 &acc, int live_mask) {
         const int m = (i < nv) ? live_mask : 0;              // all ones or zero, wavefront-uniform
         const int addr = (boff + (t0 + i) * bstride) & m;
@@ -403,89 +395,56 @@ __global__ __launch_bounds__(512, 4) void k_mv1(MvArgs a) {  // 4 wavefronts per
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv),
                                                       acc, 0, 0, 0);
     };
-    auto prime = [&](int seg) {
-        const int rg = min((seg * W + (int)blockIdx.x) * G + g, last_rg);
-        base = Wt + ((size_t)rg * T + t0) * 64 + lane;
+    // ---- the split activation goes straight to LDS (the producer kernel already wrote it in B layout).  Everything that the
+    // prologue and the first epilogue need is requested ahead of the weights (loads return in order), and the barrier at the end
+    // orders LDS only: the MFMAs start on the first tiles while the rest of the window is on its way.
+    const uint32_t real_bytes = (uint32_t)(K >> 3) * NC * 16, all_bytes = (uint32_t)T * 64 * NC;
+    for (uint32_t p = wave * 1024; p < real_bytes; p += 8192)  // (the last piece runs on into the slice sums' place)
+        to_lds<16>(in_s + min(p + lane16, real_bytes - 16), smem + 16 + p);
+    __builtin_amdgcn_sched_barrier(0);
+    const MvArgs &a = late_args<MvArgs>(rest_at);
+    NormPart np;
+    if (EPI != EPI_RESID) np = mv_norm_load(a);
+    // the residual values that the first round's epilogue adds to (R <= 5: two passes) and their gains, to LDS: wavefronts 0, 1 and 2
+    auto *resid = (__attribute__((address_space(3))) float *)nscratch;
+    if (EPI == EPI_RESID && G == 1 && wave < 3) {
+        const int row = min(16 * min((int)blockIdx.x, last_rg) + col, a.O - 1);
+        const float *from = wave < 2 ? a.out_f32 + (size_t)min(4 * wave + kg, R - 1) * a.ld_out + row : a.gain_next + row;
+        to_lds<4>(from, nscratch + 64 * wave);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    set_slice(0);
 #pragma unroll
-        for (int u = 0; u < NS; ++u) buf[u] = load_slot(u);
-    };
-
-    // ---- stage the split activation (a plain copy: the producer kernel already wrote it in B
-    // layout).  Its loads, and those of the norm partials, go out ahead of the weight loads so
-    // that they return first; the first weight window is in flight while LDS is filled.
-    {
-        const u32x4 *src = (const u32x4 *)a.in_s;
-        u32x4 *dst = (u32x4 *)(smem + 16);
-        const int n_units = T * 4 * NC, real_units = (a.K >> 3) * NC;
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-        // The residual projections read their norm partials ahead of the weight window and wait for them
-        // with an LDS-only barrier, so that the MFMAs start on the first tiles while the rest of the window
-        // is still on its way (o_proj 10.7 -> 10.4 us, down_proj 19.0 -> 18.2 us); the other epilogues measured
-        // slower that way (q|k|v by 2.7 us) and keep the full barrier.
-        constexpr bool kEarlyNorm = EPI == EPI_RESID;
-        NormPart np;
-        auto side_loads = [&]() {
-            if (tid < 4) ((uint32_t *)smem)[tid] = 0u;
-            if (EPI == EPI_QKV) {
-                // the lines the epilogues of this workgroup's rounds will write values into (wavefront s: round s)
-                if (wave < a.S)
-                    for (int gg = 0; gg < G; ++gg) mv_touch_value_lines(a, min((wave * W + (int)blockIdx.x) * G + gg, last_rg), lane);
-                const int d = a.head_dim, half = d >> 1;
-                for (int i = tid; i < R * half; i += 512) {
-                    const int r = i / half, e = i - r * half;
-                    rot[r * d + e] = a.cos_tab[(size_t)mv_rope_pos(a, r) * half + e];
-                    rot[r * d + half + e] = a.sin_tab[(size_t)mv_rope_pos(a, r) * half + e];
-                }
-            }
-        };
-        if (n_units <= 4 * 512) {  // depth <= 5461 for one row: four loads per thread cover it
-            u32x4 tmp[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = tid + 512 * q;
-                tmp[q] = i < real_units ? src[i] : zero;
-            }
-            if (kEarlyNorm) np = mv_norm_load(a);
-            prime(0);
-            side_loads();
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = tid + 512 * q;
-                if (i < n_units) dst[i] = tmp[q];
-            }
-        } else {
-            u32x4 tmp[9];
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                const int i = tid + 512 * q;
-                tmp[q] = i < real_units ? src[i] : zero;
-            }
-            if (kEarlyNorm) np = mv_norm_load(a);
-            prime(0);
-            side_loads();
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                const int i = tid + 512 * q;
-                if (i < n_units) dst[i] = tmp[q];
-            }
-            for (int i0 = 9 * 512; i0 < n_units; i0 += 4 * 512) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = i0 + tid + 512 * q;
-                    tmp[q] = i < real_units ? src[i] : zero;
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = i0 + tid + 512 * q;
-                    if (i < n_units) dst[i] = tmp[q];
-                }
-            }
+    for (int u = 0; u < NS; ++u) buf[u] = load_slot(u);
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < 4) ((uint32_t *)smem)[tid] = 0u;
+    if (EPI == EPI_QKV) {
+        // behind the window, to LDS: the rotary rows (wavefront w: elements 64 w .. of [row][d/2]), and a word of each line that the
+        // epilogues of this workgroup's rounds will write values into (wavefront s: round s; see mv_value_line)
+        const int half = a.head_dim >> 1, lg_half = __builtin_ctz(half), i = min(tid, R * half - 1);
+        if (64 * wave < R * half) {
+            const uint32_t at = ((uint32_t)mv_rope_pos(a, i >> lg_half) << lg_half) + (i & (half - 1));
+            to_lds<4>(a.cos_tab + at, rot + 64 * wave);
+            to_lds<4>(a.sin_tab + at, rot + mv1_rot_pitch(R, a.head_dim) + 64 * wave);
         }
-        if (!kEarlyNorm) np = mv_norm_load(a);
-        mv_norm_finish<kEarlyNorm>(a, np, rs, nscratch);
+        if (G == 1 && wave < S) {
+            const uint32_t *line = mv_value_line(a, min(wave * W + (int)blockIdx.x, last_rg), lane);
+            if (line) to_lds<4>(line, touched);
+        }
+    }
+    // (the activation has arrived: what was requested after it may be on its way)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NS) : "memory");
+    if (EPI != EPI_RESID)
+        mv_norm_finish(a, np, rs, nscratch);
+    else
+        lds_barrier();
+    if ((K & 31) != 0) {  // zeros past the real depth
+        for (uint32_t i = real_bytes + tid * 16; i < all_bytes; i += 8192) *(u32x4 *)(smem + 16 + i) = u32x4{0u, 0u, 0u, 0u};
+        lds_barrier();
     }
 
-    for (int seg = 0; seg < a.S; ++seg) {
+    auto round = [&](int seg, auto LAST) {
+        constexpr bool kLast = decltype(LAST)::value;
         const int rg = (seg * W + (int)blockIdx.x) * G + g;
         const bool live = rg <= last_rg;
         const int live_mask = live ? -1 : 0;
@@ -501,10 +460,9 @@ __global__ __launch_bounds__(512, 4) void k_mv1(MvArgs a) {  // 4 wavefronts per
                 buf[u] = load_slot((b + 1) * NS + u);
             }
         }
-        if (seg + 1 < a.S) {
+        if (!kLast) {
             // the window rolls on into the next round's row group: the stream never drains
-            const int rgn = min(((seg + 1) * W + (int)blockIdx.x) * G + g, last_rg);
-            base = Wt + ((size_t)rgn * T + t0) * 64 + lane;
+            set_slice(seg + 1);
 #pragma unroll
             for (int u = 0; u < NS; ++u) {
                 mma_slot((nb16 - 1) * NS + u, buf[u], acc, live_mask);
@@ -518,37 +476,72 @@ __global__ __launch_bounds__(512, 4) void k_mv1(MvArgs a) {  // 4 wavefronts per
         // ---- end of the row group: every wavefront parks its NC result columns in LDS; one
         // wavefront per row group adds terms and K slices and runs the epilogue
         float *rp = red + (size_t)(seg & 1) * (8 * 16 * NC);
-        if (col < NC) {
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) rp[(wave * NC + col) * 16 + 4 * kg + r4] = acc[r4];
-        }
+        if (col < NC) *(f32x4 *)(rp + (wave * NC + col) * 16 + 4 * kg) = acc;
+        if (EPI == EPI_QKV && seg == 0)  // (the rotary rows have arrived)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLast ? 0 : NS) : "memory");
         lds_barrier();  // (the next round's tile loads stay in flight)
-        if (!live || ks != 0) continue;
-        mv_epilogue<EPI>(a, rg, lane, rs, EPI == EPI_QKV ? rot : nullptr, [&](int r, int j) {
-            // Slice sums are added per term in groups of kgroup slices (slice order), the three
-            // terms of a group are combined, and the groups are added in order.  (Rolled loops: this
-            // runs in one wavefront per row group while the load window stays in registers.)
-            const int kgroup = a.kgroup;
-            const float *w = rp + (g * KS * NC + 3 * r) * 16 + j;
-            const int ss = NC * 16;  // from one slice to the next
-            float y = 0.f;
+        if (!live || ks != 0) return;
+        // Slice sums are added per term in groups of kgroup slices (slice order), the three terms of a group are combined, and the
+        // groups are added in order.
+        const int kgroup = a.kgroup, ss = NC * 16;  // ss: from one slice to the next
+        const float *w0 = rp + g * KS * ss;
+        if constexpr (!kLast) {
+            // (rolled loops: this runs in one wavefront per row group while the load window stays in registers)
+            mv_epilogue<EPI>(a, rg, lane, rs, EPI == EPI_QKV ? rot : nullptr, [&](int r, int j) {
+                const float *w = w0 + 3 * r * 16 + j;
+                float y = 0.f;
 #pragma unroll 1
-            for (int k0 = 0; k0 < KS; k0 += kgroup) {
-                float hi = w[0], mid = w[16], lo = w[32];
-                w += ss;
-#pragma unroll 1
-                for (int k2 = 1; k2 < kgroup; ++k2) {
-                    hi += w[0];
-                    mid += w[16];
-                    lo += w[32];
+                for (int k0 = 0; k0 < KS; k0 += kgroup) {
+                    float hi = w[0], mid = w[16], lo = w[32];
                     w += ss;
+#pragma unroll 1
+                    for (int k2 = 1; k2 < kgroup; ++k2) {
+                        hi += w[0];
+                        mid += w[16];
+                        lo += w[32];
+                        w += ss;
+                    }
+                    const float gs = (hi + mid) + lo;
+                    y = k0 == 0 ? gs : y + gs;
                 }
-                const float gs = (hi + mid) + lo;
-                y = k0 == 0 ? gs : y + gs;
+                return y;
+            });
+            return;
+        }
+        // (the last round: the window's registers are free, all slice sums are read at once)
+        auto y_last = [&](int r, int j) {
+            const float *w = w0 + 3 * r * 16 + j;
+            float v[KS][3];
+#pragma unroll
+            for (int k = 0; k < KS; ++k)
+#pragma unroll
+                for (int t = 0; t < 3; ++t) v[k][t] = w[k * ss + 16 * t];
+            float y = 0.f, sum[3];
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const bool first = (k & (kgroup - 1)) == 0;  // (a power of two)
+#pragma unroll
+                for (int t = 0; t < 3; ++t) sum[t] = first ? v[k][t] : sum[t] + v[k][t];
+                if (((k + 1) & (kgroup - 1)) == 0) {
+                    const float gs = (sum[0] + sum[1]) + sum[2];
+                    y = k < kgroup ? gs : y + gs;
+                }
             }
             return y;
-        });
-    }
+        };
+        if constexpr (EPI == EPI_RESID) {
+            Residuals<2> X;
+            if (G == 1 && S == 1)
+                X = Residuals<2>{{resid[lane], resid[64 + lane]}, resid[128 + lane]};
+            else
+                X = mv_residuals<2>(a, rg, lane);
+            mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_last, 0, 1, X);
+        } else {
+            mv_epilogue<EPI>(a, rg, lane, rs, EPI == EPI_QKV ? rot : nullptr, y_last);
+        }
+    };
+    for (int seg = 0; seg + 1 < S; ++seg) round(seg, std::false_type());
+    round(S - 1, std::true_type());
 }
 
 template <int EPI, int KS, int NS>
@@ -556,11 +549,12 @@ static hipError_t launch_mv1_t(const MvArgs &a, int grid, size_t lds, hipStream_
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void *)k_mv1<EPI, KS, NS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)kMvMaxLds);
+                                           (int)(kMvMaxLds + kMv1MoreLds));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    return launch_maybe_timed(k_mv1<EPI, KS, NS>, dim3(grid), dim3(512), lds, s, a);
+    return launch_maybe_timed(k_mv1<EPI, KS, NS>, dim3(grid), dim3(512), lds + kMv1MoreLds, s, (const unsigned char *)a.Wt,
+                              (const unsigned char *)a.in_s, a.T, a.K, a.R, a.n_rg, a.n_wg, a.S, a);
 }
 
 static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int wg_override, hipStream_t s) {
@@ -680,6 +674,9 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 // 40.5 / 34; 13B, 31 rows gate/up 79 / 57, down_proj 57 / 39; 70B, 31 rows gate/up 231 / 179, LM head 112 / 86.  (One k tile a
 // stage 1-3 % slower; weights straight to registers, each tile by two wavefronts: gate/up 54; four wavefronts of 512 registers
 // with six row groups each and nothing staged: 62.)
+// Residual values are requested together, before the count that decides who adds the parts; read one by one in the last wavefront's
+// epilogue, a dependent load per pass of four rows, they made up to 7 us of a launch (64 bulk rows o_proj 24.1 / 19.6, down_proj 36.5 /
+// 29.5; 31 rows down_proj 27.7 / 25.6; 13B, 31 rows o_proj 22.3 / 19.0, 64 bulk rows down_proj 44.7 / 37.6).
 //
 // With gridDim.y > 1 the K range is split over workgroups: each wavefront writes the partial results of one row group, and the
 // one that arrives last at the row group's counter adds the partials in split order (so the result does
@@ -694,8 +691,6 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
 // keep their own fixed order.
 constexpr int kMvnRing = 144 * 1024;
 constexpr int kMvnTiles = 2;       // k tiles of a stage
-constexpr int kNonTemporal = 2;    // cache policies: nt; sc1
-constexpr int kDeviceScope = 16;
 // How k_mvN cuts a matrix over workgroups: grid (row blocks, K parts), tiles per part, row groups per workgroup, six or eight:
 // what takes fewer rounds x tiles x cost of a tile, which is about that of (row groups + 20) (7B gate/up, 31 rows, one round
 // either way: 40.3 us with six, 42.9 with eight; 13B gate/up, two rounds with six: 88 against 57).
@@ -767,20 +762,15 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
     NormPart64 np64;
     if (kNorm) {
         if (!CANON)  // (the bulk layouts' own order)
-            mv_norm64_load(a, 0, np64);
-        else if (a.rp == 16)
+            np64 = mv_norm64_load(a);
+        else if (NCB <= 3)
             np = mv_norm_load(a);
         else
-            mv_norm32_load(a, 0, np32);
+            np32 = mv_norm32_load(a);
     }
-    if (EPI == EPI_QKV) {  // the lines this wavefront's epilogue will write values into (see mv_touch_value_lines)
-        const int d = a.head_dim, half = d >> 1, gph = half >> 3, rg = min(rgb + wave, a.n_rg - 1);
-        const int hh = rg / gph, head = hh - a.n_q_heads - a.n_kv_heads, r = lane >> 1;
-        if (a.nb32 > 0 && head >= 0 && r < R) {
-            const uint16_t *vp = (const uint16_t *)a.vcache + (kv_vt_index(head, a.nb32, d, a.pos0 + r, 8 * (rg - hh * gph) + (lane & 1) * half) & ~(size_t)1);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)vp,
-                                             (__attribute__((address_space(3))) void *)(touched + wave * 64), 4, 0, 0);
-        }
+    if (EPI == EPI_QKV) {  // the lines this wavefront's epilogue will write values into (see mv_value_line)
+        const uint32_t *line = mv_value_line(a, min(rgb + wave, a.n_rg - 1), lane);
+        if (line) to_lds<4>(line, touched + wave * 64);
     }
     // ---- what this wavefront copies per stage: pieces wave + 8 i (a row group's KT tiles, then KT tiles of B)
     const unsigned char *src[PW];
@@ -807,12 +797,11 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
 #pragma unroll
         for (int i = 0; i < PW; ++i) {
             if (i < PW - 1 || decltype(FULL)::value) {
-                const auto from = (const __attribute__((address_space(1))) void *)(src[i] + (size_t)min(voff[i], vend[i]));
-                const auto to = (__attribute__((address_space(3))) void *)(dst + i * 8192);
+                const unsigned char *from = src[i] + (size_t)min(voff[i], vend[i]);
                 if (wave + 8 * i < KT * RGS)  // (wavefront-uniform)
-                    __builtin_amdgcn_global_load_lds(from, to, 16, 0, kNonTemporal);
+                    to_lds<16, true>(from, dst + i * 8192);
                 else
-                    __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+                    to_lds<16>(from, dst + i * 8192);
             }
             voff[i] += KT * stride[i];
         }
@@ -868,8 +857,8 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
         if (!kNorm) return;
         if (!CANON)
             mv_norm64_finish(a, np64, rs, nscratch);
-        else if (a.rp == 16)
-            mv_norm_finish<true>(a, np, rs, nscratch);
+        else if (NCB <= 3)
+            mv_norm_finish(a, np, rs, nscratch);
         else
             mv_norm32_finish(a, np32, rs, nscratch);
     };
@@ -972,8 +961,13 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
         const float y2 = dw[(NT * r) * 16 + j] + dw[(NT * r + 1) * 16 + j];
         return NT == 3 ? y2 + dw[(3 * r + 2) * 16 + j] : y2;
     };
+    constexpr int kPasses = (NCB == 8 ? 64 : NCB > 3 ? 32 : 16) / 4;  // of an epilogue of as many rows as the columns hold
     if (KSP == 1) {
-        if (live) mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_local);
+        if (!live) return;
+        if constexpr (EPI == EPI_RESID)
+            mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_local, 0, 1, mv_residuals<kPasses>(a, rg, lane));
+        else
+            mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_local);
         return;
     }
     // ---- every wavefront publishes its row group's partial, terms combined, and counts itself in; of the KSP wavefronts with the
@@ -991,6 +985,9 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
         if (NT == 3) y = y + *(const f32x4 *)(d + 32);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, y), part, part_off(blockIdx.y, i), 0, kDeviceScope);
     }
+    // (the residual values are requested with the stores on their way, in case this wavefront is the last)
+    Residuals<EPI == EPI_RESID ? kPasses : 1> X;
+    if (EPI == EPI_RESID) X = mv_residuals<EPI == EPI_RESID ? kPasses : 1>(a, rg, lane);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     int *counter = a.counters + blockIdx.x * 8 + wave;
     int arrived = 0;
@@ -1011,7 +1008,11 @@ __global__ __launch_bounds__(512) void k_mvN(MvArgs a, int TS) {
     // (one wavefront's LDS instructions are carried out in order: only the compiler has to keep it)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    mv_epilogue<EPI>(a, rg, lane, rs, nullptr, [&](int r, int j) { return dm[r * 16 + j]; });
+    auto y_sum = [&](int r, int j) { return dm[r * 16 + j]; };
+    if constexpr (EPI == EPI_RESID)
+        mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_sum, 0, 1, X);
+    else
+        mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y_sum);
     if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -1042,12 +1043,17 @@ static hipError_t launch_mvN(const MvArgs &a, int n_cu, hipStream_t s) {
 // of NS steps (a step: the tile of each of the RG row groups and the NCB column blocks of B that meet it), and the slice
 // sums are added in LDS in the one fixed order.  B is not staged: it comes straight from L2, which holds it (27 columns x
 // 4096: 221 KB) and delivers 128 B/ns to a compute unit that takes in about 26 B/ns of weights, so that nothing couples
-// the wavefronts between the ends of a round.
+// the wavefronts between the ends of a round.  Slices of W and B are buffers, whose loads cost no address arithmetic and past whose
+// ends nothing is read; residual values are requested ahead of the weights.  us, before / now: 7B, 9 rows o_proj 10.2 / 9.7, down_proj
+// 23.4 / 22.2; 32 bulk rows q|k|v 25.0 / 23.8, o_proj 13.9 / 13.0; 13B, 9 rows o_proj 16.0 / 14.7, gate/up 54.6 / 53.4; 16 rows o_proj
+// 18.9 / 17.6.
 // (the slice sums of two rounds, where LDS holds them: one barrier a round)
 template <int NCB, int RG>
 constexpr bool kMvrTwoBuffers = 2 * 8 * RG * 16 * NCB * 16 * 4 <= 150 * 1024;
 template <int EPI, int NCB, int RG, int NS>
-__global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
+__global__ __launch_bounds__(512) void k_mvR(const unsigned char *Wt, const unsigned char *in_s, int T, int K, int NC, int n_rg, int W, int S,
+                                              MvArgs rest) {
+    constexpr int rest_at = 40;  // byte offset of `rest` among the arguments
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int NCP = 16 * NCB;                 // columns as computed
     constexpr int kRed = 8 * RG * NCP * 16;       // floats of one round's slice sums
@@ -1056,61 +1062,70 @@ __global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
     float *rs = red + (kTwo ? 2 : 1) * kRed;      // [32]
     float *nscratch = rs + 32;                    // [1024]
     constexpr bool kNorm = EPI != EPI_RESID;
-    const int NT = block_terms(a.RL), NC = NT * layout_rows(a.RL);
     const int tid = threadIdx.x, lane = tid & 63;
     const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, kg = lane >> 4;
-    const int T = a.T;
     const int n = (T + 7) >> 3;                // k tiles of a slice
     const int t0 = min(ks * n, T - 1);
     const int nv = max(0, min(n, T - ks * n)); // ... of which exist
-    const int nvm1 = max(nv - 1, 0);
-    const int W = a.n_wg, last_rg = a.n_rg - 1;
-    const u32x4 *Wt = (const u32x4 *)a.Wt;
-    const unsigned char *bb = (const unsigned char *)a.in_s;
-    // this lane's byte offset of B for tile t0 (columns past NC read what lies there: results nobody reads); in a ragged
-    // last tile the lanes past the real depth read its last chunk, and meet zero weights
-    const uint32_t bstride = 64u * NC;
-    const uint32_t boff = ((uint32_t)(4 * t0 + kg) * NC + col) * 16u;
-    const uint32_t bmax = ((uint32_t)((a.K >> 3) - 1) * NC + col) * 16u;
-
+    const int last_rg = n_rg - 1;
+    // Slices of W and of B as buffers: steps past a slice's end, and lanes past the real depth in a ragged last tile, read nothing
+    // and get zeros (columns past the last read what lies behind: results nobody reads).
+    const uint32_t lane16 = lane * 16, b_at = (uint32_t)(kg * NC + col) * 16, b_step = 64u * NC;
+    const uint32_t b_end = (uint32_t)(K >> 3) * NC * 16;
+    const __amdgpu_buffer_rsrc_t b_slice =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(in_s + (size_t)t0 * b_step), 0, min(nv * b_step, b_end - t0 * b_step), 0x00020000);
+    __amdgpu_buffer_rsrc_t slice[RG];
     u32x4 A[NS][RG], B[NS][NCB];
-    const u32x4 *base[RG];
     auto load_step = [&](int i, u32x4(&Av)[RG], u32x4(&Bv)[NCB]) {
-        const int ii = min(i, nvm1);
 #pragma unroll
-        for (int g = 0; g < RG; ++g) Av[g] = __builtin_nontemporal_load(base[g] + (size_t)ii * 64);
-        const uint32_t off = min(boff + (uint32_t)ii * bstride, bmax);
+        for (int g = 0; g < RG; ++g)
+            Av[g] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(slice[g], lane16, i * 1024, kNonTemporal));
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) Bv[cb] = *(const u32x4 *)(bb + off + 256 * cb);
+        for (int cb = 0; cb < NCB; ++cb)
+            Bv[cb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b_slice, b_at + 256 * cb, i * b_step, 0));
     };
-    auto set_base = [&](int seg) {
+    auto set_slices = [&](int seg) {
 #pragma unroll
         for (int g = 0; g < RG; ++g) {
             const int rg = min((seg * W + (int)blockIdx.x) * RG + g, last_rg);
-            base[g] = Wt + ((size_t)rg * T + t0) * 64 + lane;
+            slice[g] = __builtin_amdgcn_make_buffer_rsrc((void *)(Wt + ((size_t)rg * T + t0) * 1024), 0, nv * 1024, 0x00020000);
         }
     };
     // (the norm partials go out first; the scales are read by the epilogue only, so an LDS-only barrier will do)
+    const MvArgs &a = late_args<MvArgs>(rest_at);
+    constexpr int share = 8 / RG;  // wavefronts per row group in the epilogue
+    constexpr int kPasses = ((NCB <= 3 ? 16 : 32) / 4 + share - 1) / share;  // a wavefront's share of an epilogue of up to 16 / 32 rows
+    const int eg = min(ks / share, RG - 1);  // this wavefront's row group there
     NormPart np;
     NormPart32 np32;
     if (kNorm) {
-        if (a.rp == 16)
+        if (NCB <= 3)  // (up to 16 rows: row pitch 16)
             np = mv_norm_load(a);
         else
-            mv_norm32_load(a, 0, np32);
+            np32 = mv_norm32_load(a);
     }
-    set_base(0);
+    constexpr bool kAhead = EPI == EPI_RESID && RG * NCB < 15;  // (no registers left in the largest)
+    Residuals<kPasses> X;
+    if (kAhead) X = mv_residuals<kPasses>(a, min((int)blockIdx.x * RG + eg, last_rg), lane, ks - eg * share, share);
+    __builtin_amdgcn_sched_barrier(0);
+    set_slices(0);
 #pragma unroll
     for (int u = 0; u < NS; ++u) load_step(u, A[u], B[u]);
-    if (EPI == EPI_QKV) {
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t v_line[RG];
+#pragma unroll
+    for (int g = 0; g < RG; ++g) {
         // the lines the epilogues of this workgroup's rounds will write values into (wavefront s: round s)
-        if (ks < a.S)
-            for (int g = 0; g < RG; ++g) mv_touch_value_lines(a, min((ks * W + (int)blockIdx.x) * RG + g, last_rg), lane);
+        v_line[g] = 0u;
+        if (EPI == EPI_QKV && ks < S) {
+            const uint32_t *line = mv_value_line(a, min((ks * W + (int)blockIdx.x) * RG + g, last_rg), lane);
+            if (line) v_line[g] = *line;
+        }
     }
     if (kNorm) {
-        if (a.rp == 16)
-            mv_norm_finish<true>(a, np, rs, nscratch);
+        if (NCB <= 3)
+            mv_norm_finish(a, np, rs, nscratch);
         else
             mv_norm32_finish(a, np32, rs, nscratch);
     }
@@ -1126,7 +1141,7 @@ __global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
                                                                      acc[g][cb], 0, 0, 0);
     };
     const int nb = (n + NS - 1) / NS;
-    for (int seg = 0; seg < a.S; ++seg) {
+    for (int seg = 0; seg < S; ++seg) {
 #pragma unroll
         for (int g = 0; g < RG; ++g)
 #pragma unroll
@@ -1138,9 +1153,9 @@ __global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
                 load_step((b + 1) * NS + u, A[u], B[u]);
             }
         }
-        if (seg + 1 < a.S) {
+        if (seg + 1 < S) {
             // the window rolls on into the next round's row groups: the stream never drains
-            set_base(seg + 1);
+            set_slices(seg + 1);
 #pragma unroll
             for (int u = 0; u < NS; ++u) {
                 mma_step((nb - 1) * NS + u, A[u], B[u]);
@@ -1158,13 +1173,15 @@ __global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) *(f32x4 *)(rp + ((ks * RG + g) * NCP + 16 * cb + col) * 16 + 4 * kg) = acc[g][cb];
         lds_barrier();  // (the next round's loads stay in flight)
-        constexpr int share = 8 / RG;              // wavefronts per row group
+        if (EPI == EPI_QKV && seg == 0)
+#pragma unroll
+            for (int g = 0; g < RG; ++g) keep_alive(v_line[g]);
         const int g = ks / share;
         const int rg = (seg * W + (int)blockIdx.x) * RG + g;
         if (g < RG && rg <= last_rg) {
-            mv_epilogue<EPI>(a, rg, lane, rs, nullptr, [&](int r, int j) {
+            auto y = [&](int r, int j) {
                 // (the order of k_mv1: per term in groups of kgroup slices, the terms of a group combined, groups in order)
-                const int kgroup = a.kgroup;
+                const int kgroup = a.kgroup, NT = block_terms(a.RL);
                 const float *w = rp + (g * NCP + NT * r) * 16 + j;
                 constexpr int ss = RG * NCP * 16;  // from one slice to the next
                 float y = 0.f;
@@ -1183,7 +1200,13 @@ __global__ __launch_bounds__(512) void k_mvR(MvArgs a) {
                     y = k0 == 0 ? gs : y + gs;
                 }
                 return y;
-            }, ks - g * share, share);
+            };
+            if constexpr (EPI == EPI_RESID) {
+                if (!kAhead || seg > 0) X = mv_residuals<kPasses>(a, rg, lane, ks - g * share, share);
+                mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y, ks - g * share, share, X);
+            } else {
+                mv_epilogue<EPI>(a, rg, lane, rs, nullptr, y, ks - g * share, share);
+            }
         }
     }
 }
@@ -1217,7 +1240,8 @@ static hipError_t launch_mvR_ns(const MvArgs &a, hipStream_t s) {
         attr_set = true;
     }
     const size_t lds = (size_t)(kMvrTwoBuffers<NCB, RG> ? 2 : 1) * 8 * RG * 16 * NCB * 16 * 4 + 32 * 4 + 1024 * 4;
-    return launch_maybe_timed(k_mvR<EPI, NCB, RG, NS>, dim3(a.n_wg), dim3(512), lds, s, a);
+    return launch_maybe_timed(k_mvR<EPI, NCB, RG, NS>, dim3(a.n_wg), dim3(512), lds, s, (const unsigned char *)a.Wt,
+                              (const unsigned char *)a.in_s, a.T, a.K, block_terms(a.RL) * layout_rows(a.RL), a.n_rg, a.n_wg, a.S, a);
 }
 template <int EPI, int NCB, int RG>
 static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
@@ -1291,14 +1315,27 @@ static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
 // runs, so it stays where it is if the choice between the kernels moves.
 static bool mvn_canon(const MvArgs &a, int n_cu, int ncb) { return !(a.RL & kBulkLayout) || mvr_line(a, n_cu, ncb) != 0; }
 
-// Small blocks (in their own exact layout) whose whole activation fits in LDS take the single-pass kernel.
-static bool mv_takes_mv1(const MvArgs &a, int ks_override) {
-    return !(a.RL & kBulkLayout) && a.R <= kMvSmallRows && ks_override != 16 && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds;
+// Small blocks (in their own exact layout) whose whole activation fits in LDS ..
+static bool mv_fits_mv1(const MvArgs &a) {
+    return !(a.RL & kBulkLayout) && a.R <= kMvSmallRows && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds;
+}
+// .. take the single-pass kernel, but for two kinds of matrices where k_mvR is faster, in rounds of three row groups per compute
+// unit: those that it covers in one such round and k_mv1 in an uneven one and a half or two (513..768 row groups on 256 units; us,
+// k_mv1 / k_mvR, one row: depth 4096, 520 row groups 18.5 / 14.4, 768 (7B q|k|v) 19.7 / 18.8; depth 2048, 640: 11.0 / 9.9; depth
+// 8192, 640 (70B q|k|v) 33.8 / 28.7; next to them 384: 12.4 / 12.6, 896: 21.0 / 22.7), and deep ones (from 8192 on) whose rounds of three are
+// nine tenths full (depth 8192, 3584 row groups (70B gate/up) 143.6 / 136.7, 1536: 64.1 / 62.2; 2560, five sixths full, 103.6 /
+// 114.3).  The bits are the same either way.
+static bool mv_takes_mv1(const MvArgs &a, int n_cu, int ks_override) {
+    if (!mv_fits_mv1(a) || ks_override == 16) return false;
+    if (ks_override != 0) return true;
+    const int per_round = 3 * n_cu, rounds = (a.n_rg + per_round - 1) / per_round;
+    if (a.n_rg > 2 * n_cu && rounds == 1) return false;
+    return !(a.T >= 256 && a.n_rg > per_round && 10 * a.n_rg >= 9 * rounds * per_round);
 }
 static int mv_column_blocks(const MvArgs &a) { return (block_terms(a.RL) * layout_rows(a.RL) + 15) / 16; }
 
 int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity) {
-    if (mv_takes_mv1(a, 0)) return snprintf(out, (size_t)capacity, "mv1<rows %d>", a.R);
+    if (mv_takes_mv1(a, n_cu, 0)) return snprintf(out, (size_t)capacity, "mv1<rows %d>", a.R);
     const int ncb = mv_column_blocks(a), rg = mvr_row_groups(a, n_cu, ncb);
     if (rg == 0) return snprintf(out, (size_t)capacity, "mvN<columns %d, parts %d>", ncb, mvn_plan(a, n_cu, mvn_canon(a, n_cu, ncb)).ksp);
     const int units = (a.n_rg + rg - 1) / rg;
@@ -1308,7 +1345,7 @@ int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity) {
 
 int mv_split_slots(const MvArgs &a, int n_cu) {
     if (a.RL & kBulkLayout) return a.part_capacity;  // (bulk layouts: not needed by callers)
-    if (mv_takes_mv1(a, 0)) return 0;
+    if (mv_fits_mv1(a)) return 0;
     // (what k_mvN needs, also where k_mvR, which needs none, is the faster kernel: what a caller's scratch has to hold does
     // not hang on a rule about speed)
     const int TS = ((a.T + 7) / 8) * mv_slice_group(a, n_cu);
@@ -1325,13 +1362,15 @@ hipError_t launch_mv(int epi, MvArgs a, int n_cu, int ks_override, int wg_overri
     const bool bulk = (a.RL & kBulkLayout) != 0;
     const int lrows = layout_rows(a.RL);
     if (a.R < 1 || a.R > kMaxBlockRows || (a.rp != 16 && a.rp != 64) || a.R > a.rp || a.R > lrows ||
-        (bulk ? (lrows != 32 && lrows != 64) : (lrows != a.R || lrows > kMaxRows)) || a.head0 != 0)
+        (bulk ? (lrows != 32 && lrows != 64) : (lrows != a.R || lrows > kMaxRows)) || a.head0 != 0 ||
+        (epi != EPI_RESID && (!a.pss || a.n_pss < 1)))
         return hipErrorInvalidValue;
-    if (mv_takes_mv1(a, ks_override)) return launch_mv1(epi, a, n_cu, ks_override, wg_override, s);
+    if (mv_takes_mv1(a, n_cu, ks_override)) return launch_mv1(epi, a, n_cu, ks_override, wg_override, s);
     // exact layouts (up to 32 rows): 2-6 column blocks of three-term columns, the fixed
     // summation order; bulk layouts of 32 / 64 rows (prefill, candidate evaluation): 4 / 8 column blocks of
     // two-term columns
     const int ncb = mv_column_blocks(a);
+    if ((a.rp == 16) != (ncb <= 3)) return hipErrorInvalidValue;  // (three column blocks: up to 16 rows)
     if (const int rg = mvr_row_groups(a, n_cu, ncb)) {
 #define SWIFT_MVR_RG(E, N)                                          \
     case N:                                                         \
