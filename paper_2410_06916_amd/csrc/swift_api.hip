@@ -725,6 +725,7 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
             a.part_o = x->scr.part_o;
             a.part_ml = x->scr.part_ml;
             a.max_split = L.n_split_max;
+            a.counters = x->scr.mv_counters;
             a.nb32 = L.nb32;
             a.q_s = dptr<uint16_t>(x, L.q_s);
             a.out = nullptr;

@@ -15,7 +15,7 @@
 //    range's chunks round-robin, each folding its chunks in order into a running (max, sum, weighted values)
 //    with S^T = K Q^T and O^T += V^T P^T (queries and probabilities as two bf16 terms each: relative error
 //    2^-17 against the 2^-9 of the bf16 keys and values; fp32 sums); the wavefronts' results are merged in
-//    wavefront order, the ranges' in range order (k_attn_mfma_combine);
+//    wavefront order, the ranges' in range order (by the last workgroup of a head, or k_attn_mfma_combine);
 //  * the row's own slot (its key and value, written to the cache by the projection kernel of the same pass)
 //    is merged last, in fp32 vector arithmetic.  For a tree row the prefix beyond the committed slots is
 //    the first candidates of the levels above it: one mapping for all rows, so tree rows share the loads
@@ -32,7 +32,9 @@ namespace swift {
 
 namespace {
 
-constexpr int kAmPad = 4;  // floats of padding per member row of the merge area
+constexpr int kAmPad = 4;         // floats of padding per member row of the merge area
+constexpr int kDeviceScope = 16;  // cache policy sc1
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ inline bf16x8 am_pack(const uint16_t (&v)[8]) {
     u32x4 u;
@@ -81,6 +83,18 @@ __device__ inline float am_finish(float mn, float ls, float os, float s_own, flo
     return (os * c1 + c2 * v_own) / (ls * c1 + c2);
 }
 
+// Folds the next range's (max m, sum l, weighted value o) into a running merge.  (A range's maximum is -inf only if its rows see
+// nothing there.)
+template <typename V>
+__device__ inline void am_fold(float &mn, float &ls, V &os, float m, float l, const V &o) {
+    const float m2 = fmaxf(mn, m);
+    const float c1 = mn == -INFINITY ? 0.f : __expf(mn - m2);
+    const float c2 = m == -INFINITY ? 0.f : __expf(m - m2);
+    ls = ls * c1 + l * c2;
+    os = os * c1 + o * c2;
+    mn = m2;
+}
+
 __device__ inline void am_write(const AttnArgs &a, int row, int e, float y) {
     if (a.out) a.out[(size_t)row * a.n_q_heads * a.head_dim + e] = y;
     if (a.out_s) {
@@ -103,7 +117,6 @@ __device__ inline void am_write4(const AttnArgs &a, int row, int e, const f32x4 
         for (int i = 0; i < 4; ++i) split3(y[i], t[0][i], t[1][i], t[2][i]);
         const int ocode = a.out_rows ? a.out_rows : a.rows, orows = layout_rows(ocode), nt = block_terms(ocode);
         uint16_t *p = a.out_s + ((size_t)(e >> 3) * (nt * orows) + nt * row) * 8 + (e & 7);
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             if (k < nt) *(u32x2 *)(p + 8 * k) = u32x2{pack2(t[k][0], t[k][1]), pack2(t[k][2], t[k][3])};
@@ -116,31 +129,30 @@ __device__ inline void am_write4(const AttnArgs &a, int row, int e, const f32x4 
 // Scores of a 32-slot chunk are two tiles tt = 0, 1; tile row 4 g + i is slot 8 g + 4 tt + i of the chunk, so
 // that a lane's eight probabilities are slots 8 g .. 8 g + 7: the k range of its B operand in O^T = V^T P^T.
 //
-// Workgroup (kv head, cache range sp, member tile z), blockDim.x / 64 wavefronts.  range: slots per workgroup, a
-// multiple of 32.  hi_all: end of the longest prefix of the block.
-template <int D, bool TREE>
-__global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi_all) {
+// Workgroup (kv head, cache range sp, member tile z), NW wavefronts.  range: slots per workgroup, a multiple of 32.  hi_all: end of the
+// longest prefix of the block.  lg_group: log2 of the query heads per kv head.  MERGE: rows whose prefix spans several ranges are
+// finished in this launch, by the workgroup that arrives last at their (kv head, member tile); else by k_attn_mfma_combine.
+//
+// What bounds it at short contexts: a chain of latencies (launch, first loads, chunks, merge).  So the arguments of the first loads
+// are the kernel's leading ones, which are in registers at its start, and nothing on the way to the first product waits for a load
+// that is not part of it (100 slots, one row: 5.8 us, 4.5 without such waits and with the wavefronts' results read all at once).
+template <int D, bool TREE, int NW, bool MERGE>
+__global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache, const uint16_t *vcache, const uint16_t *q_s, int max_seq,
+                                                          int nb32, int range, int hi_all, int rows, int lg_group, AttnArgs a) {
     constexpr int DC = D / 32;      // k steps of a score tile
     constexpr int DT = D / 16;      // 16-row tiles of O^T
     constexpr int MP = D + kAmPad;  // pitch of a member's values in the merge area
     extern __shared__ __align__(16) float am_sh[];
-    const int kvh = blockIdx.x, sp = blockIdx.y, n_split = gridDim.y;
+    const int kvh = blockIdx.x, sp = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int NW = blockDim.x >> 6;
-    const int nq = a.n_q_heads, group = nq / a.n_kv_heads;
-    const int M_total = a.rows * group;
+    const int M_total = rows << lg_group;
     const int m0 = 16 * blockIdx.z;  // first member of this workgroup's tile; member m = (row m / group, head m % group)
     const int lo = sp * range, hi = min(hi_all, lo + range);
     const float scale = 1.0f / sqrtf((float)D);
-    const uint16_t *kc = (const uint16_t *)a.kcache + (size_t)kvh * a.max_seq * D;
-    const uint16_t *vt = (const uint16_t *)a.vcache + (size_t)kvh * a.nb32 * D * 32;
+    const uint16_t *kc = kcache + (size_t)kvh * max_seq * D;
+    const uint16_t *vt = vcache + (size_t)kvh * nb32 * D * 32;
 
-    // ---- this lane's member (column col of the tile)
-    const int mem = m0 + col;
-    const bool mem_ok = mem < M_total;
-    const int mrow = mem_ok ? mem / group : 0, mhead = mem_ok ? mem - mrow * group : 0;
-    const int lim = mem_ok ? min(am_prefix_end<TREE>(a, mrow), lo + range) : 0;  // the prefix slots it sees here
     // ---- operands of a chunk, straight from the cache in MFMA A layout
     // Chunks that lie below safe_end hold 32 prefix slots that sit where their numbers say: keys as stored,
     // values one 16-byte load per eight slots.  In the chunk in which the longest prefix ends, the keys of the
@@ -165,21 +177,6 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
             const uint16_t *vp = vt + ((size_t)(4 * c + g) * D + col) * 8;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) vA[dt] = *(const u32x4 *)(vp + dt * (16 * 8));
-            if (!plain) {
-                // the chunk in which the longest prefix ends: the slots past it are zeroed in the registers
-                const int n_ok = hi_all - (32 * c + 8 * g);  // slots of this lane's eight that belong to the prefix
-                const uint32_t m0 = n_ok >= 2 ? 0xffffffffu : n_ok == 1 ? 0x0000ffffu : 0u;
-                const uint32_t m1 = n_ok >= 4 ? 0xffffffffu : n_ok == 3 ? 0x0000ffffu : 0u;
-                const uint32_t m2 = n_ok >= 6 ? 0xffffffffu : n_ok == 5 ? 0x0000ffffu : 0u;
-                const uint32_t m3 = n_ok >= 8 ? 0xffffffffu : n_ok == 7 ? 0x0000ffffu : 0u;
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) {
-                    vA[dt].x &= m0;
-                    vA[dt].y &= m1;
-                    vA[dt].z &= m2;
-                    vA[dt].w &= m3;
-                }
-            }
         } else {
             // a tree's chunks beyond the committed slots: slot by slot through the mapping
             int ps[8];
@@ -192,6 +189,23 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
                 for (int j = 0; j < 8; ++j) e[j] = vt[((size_t)(ps[j] >> 3) * D + 16 * dt + col) * 8 + (ps[j] & 7)];
                 vA[dt] = __builtin_bit_cast(u32x4, am_pack(e));
             }
+        }
+    };
+    // (at their use, so that nothing waits for them earlier)
+    auto mask_values = [&](int c, u32x4(&vA)[DT]) {
+        if (TREE || 32 * (c + 1) <= safe_end) return;
+        // the chunk in which the longest prefix ends: the slots past it are zeroed in the registers
+        const int n_ok = hi_all - (32 * c + 8 * g);  // slots of this lane's eight that belong to the prefix
+        const uint32_t m0 = n_ok >= 2 ? 0xffffffffu : n_ok == 1 ? 0x0000ffffu : 0u;
+        const uint32_t m1 = n_ok >= 4 ? 0xffffffffu : n_ok == 3 ? 0x0000ffffu : 0u;
+        const uint32_t m2 = n_ok >= 6 ? 0xffffffffu : n_ok == 5 ? 0x0000ffffu : 0u;
+        const uint32_t m3 = n_ok >= 8 ? 0xffffffffu : n_ok == 7 ? 0x0000ffffu : 0u;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+            vA[dt].x &= m0;
+            vA[dt].y &= m1;
+            vA[dt].z &= m2;
+            vA[dt].w &= m3;
         }
     };
 
@@ -210,53 +224,57 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
         load_values(c, vA);
     }
 
-    // query operands: two bf16 terms per value (relative error 2^-17; the keys they meet are bf16), written in
-    // this form by the projection kernel
+    // query operands of this lane's member (column col of the tile): two bf16 terms per value (relative error 2^-17; the keys they
+    // meet are bf16), written in this form by the projection kernel
+    const int nq = a.n_q_heads, group = 1 << lg_group;
+    const int mem = min(m0 + col, M_total - 1), mrow = mem >> lg_group, mhead = mem & (group - 1);
     bf16x8 qop[DC][2];
     {
-        const uint16_t *qp = a.q_s + ((size_t)(mrow * nq + kvh * group + mhead) * 2) * D + 8 * g;
+        const uint16_t *qp = q_s + ((size_t)(mrow * nq + kvh * group + mhead) * 2) * D + 8 * g;
 #pragma unroll
         for (int c = 0; c < DC; ++c)
 #pragma unroll
             for (int t = 0; t < 2; ++t) qop[c][t] = __builtin_bit_cast(bf16x8, *(const u32x4 *)(qp + t * D + 32 * c));
     }
-    // ---- the own slots of the rows that are finished here (prefix inside the first range), requested before
+    const int lim = m0 + col < M_total ? min(am_prefix_end<TREE>(a, mrow), lo + range) : 0;  // the prefix slots it sees here
+
+    // ---- the rows' own slots (MERGE: any workgroup may be the one that finishes a row), requested before
     // the prefix is walked so that their latency is not paid at the end: what this wavefront's scores need (16 / NW members,
     // by whole wavefronts, lane l elements 2 l and 2 l + 1; reduced after the walk) and the value elements each thread will need
-    // in the last phase, four in a row.  (With one element a thread at a time there, and the scores reduced before the walk, a launch
-    // at 512-770 slots took 15.5 us at 9 rows, 20.3 for a tree of 31, 17.6 for 32 evaluation rows; so 13.8, 16.9 and 14.4.)
-    constexpr int kOwnMax = 16 * D / 4 / 256;  // units of four elements per thread in the last phase with four wavefronts
+    // in the last phase, four in a row, each as the word that holds it.
+    constexpr int kUnits = (16 * D / 4 + 64 * NW - 1) / (64 * NW);  // units of four elements per thread in the last phase
+    constexpr int kScores = 16 / NW;
     float *s_own = am_sh + (size_t)NW * (16 * (MP + 2));
-    // (trees: registers for two scores and one unit, all there are with eight wavefronts; what four need beyond them is read late)
-    constexpr int kScores = TREE ? 2 : 4, kUnits = TREE ? 1 : kOwnMax;
+    const bool finishes = MERGE || sp == 0;
+    const int n_here = finishes ? min(16, M_total - m0) : 0;  // members that may be finished here
+    // (member of score i: the last wavefronts have the fewest chunks to walk)
+    auto own_member = [&](int i) { return NW - 1 - wave + NW * i; };
+    auto unit_member = [&](int u) { return (tid + u * 64 * NW) / (D / 4); };
+    auto unit_elem = [&](int u) { return 4 * ((tid + u * 64 * NW) % (D / 4)); };
     uint32_t v_own[kUnits][4];
     float q_own[kScores][2];
     uint32_t k_own[kScores];
-    // (member of score i: the last wavefronts have the fewest chunks to walk)
-    auto own_member = [&](int i) { return NW - 1 - wave + NW * i; };
-    auto load_own_values = [&](int u, uint32_t(&v)[4]) {
-        const int idx = tid + u * (int)blockDim.x, mm = idx / (D / 4), dd = 4 * (idx - mm * (D / 4));
-        const bool here = mm < 16 && m0 + mm < M_total && am_prefix_end<TREE>(a, (m0 + mm) / group) <= range;
-        const int own = here ? am_own_slot<TREE>(a, (m0 + mm) / group) : 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = here ? vt[((size_t)(own >> 3) * D + dd + i) * 8 + (own & 7)] : 0u;
-    };
-    auto own_here = [&](int mm) { return mm < 16 && m0 + mm < M_total && am_prefix_end<TREE>(a, (m0 + mm) / group) <= range; };
-    if (sp == 0) {
-#pragma unroll
-        for (int i = 0; i < kScores; ++i) {
-            const int mm = own_member(i), m = m0 + mm;
-            q_own[i][0] = q_own[i][1] = 0.f;
-            k_own[i] = 0u;
-            if (!own_here(mm) || 2 * lane >= D) continue;  // (else finished by the combine kernel)
-            const int row = m / group, head = m - row * group;
+    for (int i = 0; i < kScores; ++i) {
+        q_own[i][0] = q_own[i][1] = 0.f;
+        k_own[i] = 0u;
+        const int mm = own_member(i), row = (m0 + mm) >> lg_group, head = (m0 + mm) & (group - 1);
+        if (mm >= n_here) continue;  // (wavefront-uniform)
+        if (2 * lane < D) {
             const float *q = a.q + ((size_t)row * nq + kvh * group + head) * D + 2 * lane;
             q_own[i][0] = q[0];
             q_own[i][1] = q[1];
             k_own[i] = *(const uint32_t *)(kc + (size_t)am_own_slot<TREE>(a, row) * D + 2 * lane);
         }
+    }
+    if (finishes) {
 #pragma unroll
-        for (int u = 0; u < kUnits; ++u) load_own_values(u, v_own[u]);
+        for (int u = 0; u < kUnits; ++u) {
+            const int row = min(m0 + unit_member(u), M_total - 1) >> lg_group, own = am_own_slot<TREE>(a, row);
+            const uint16_t *vp = vt + ((size_t)(own >> 3) * D + unit_elem(u)) * 8 + (own & 6);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v_own[u][i] = *(const uint32_t *)(vp + 8 * i);
+        }
     }
 
     // ---- this wavefront's chunks: every NW-th of the range, folded in order.  The keys of the next chunk are
@@ -284,8 +302,7 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
                 mx = fmaxf(mx, v);
             }
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = column_reduce(mx, [](float x, float y) { return fmaxf(x, y); });
         const float mn = fmaxf(m_run, mx);
         const float ms = mn == -INFINITY ? 0.f : mn;  // nothing live yet: every exponential below is 0
         const float corr = __expf(m_run - ms);
@@ -302,6 +319,7 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
         const bf16x8 phi = am_pack(ph), plo = am_pack(pl);
         l_run = l_run * corr + ps;
         m_run = mn;
+        mask_values(c, vA);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
             o[dt] *= corr;
@@ -316,27 +334,15 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
     }
 
     // ---- merge the wavefronts (in wavefront order), then finish the rows whose prefix ends in the first
-    // range with their own slot, or leave the range's partial result for k_attn_mfma_combine
-    l_run += __shfl_xor(l_run, 16, 64);
-    l_run += __shfl_xor(l_run, 32, 64);
-    if (sp == 0) {
+    // range with their own slot, or leave the range's partial result
+    l_run = column_reduce(l_run, [](float x, float y) { return x + y; });
 #pragma unroll
-        for (int i = kScores; i < 4; ++i) {
-            const int mm = own_member(i), m = m0 + mm;
-            if (!own_here(mm)) continue;
-            const int row = m / group, head = m - row * group;
-            const float sc = am_own_score(a.q + ((size_t)row * nq + kvh * group + head) * D,
-                                          kc + (size_t)am_own_slot<TREE>(a, row) * D, D, lane, scale);
-            if (lane == 0) s_own[mm] = sc;
-        }
-#pragma unroll
-        for (int i = 0; i < kScores; ++i) {
-            const int mm = own_member(i);
-            if (!own_here(mm)) continue;  // (wavefront-uniform)
-            const float sc = fmaf(q_own[i][1], am_bf((uint16_t)(k_own[i] >> 16)), fmaf(q_own[i][0], am_bf((uint16_t)k_own[i]), 0.f));
-            const float sum = wave_sum(sc) * scale;
-            if (lane == 0) s_own[mm] = sum;
-        }
+    for (int i = 0; i < kScores; ++i) {
+        const int mm = own_member(i);
+        if (mm >= n_here) continue;  // (wavefront-uniform)
+        const float sc = fmaf(q_own[i][1], am_bf((uint16_t)(k_own[i] >> 16)), fmaf(q_own[i][0], am_bf((uint16_t)k_own[i]), 0.f));
+        const float sum = wave_sum(sc) * scale;
+        if (lane == 0) s_own[mm] = sum;
     }
     float *wbase = am_sh + (size_t)wave * (16 * (MP + 2));
     if (g == 0) {
@@ -346,45 +352,102 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnArgs a, int range, int hi
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) *(f32x4 *)(wbase + 32 + col * MP + 16 * dt + 4 * g) = o[dt];
     __syncthreads();
+    auto finish = [&](int u, int row, int qh, float mn, float ls, const f32x4 &os) {
+        const int shift = (am_own_slot<TREE>(a, row) & 1) * 16;
+        f32x4 y;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = am_finish(mn, ls, os[i], s_own[unit_member(u)], am_bf((uint16_t)(v_own[u][i] >> shift)));
+        am_write4(a, row, qh * D + unit_elem(u), y);
+    };
+    const int n_split = gridDim.y;
+    const __amdgpu_buffer_rsrc_t part_o = __builtin_amdgcn_make_buffer_rsrc(a.part_o, 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t part_ml = __builtin_amdgcn_make_buffer_rsrc(a.part_ml, 0, 0x7fffffff, 0x00020000);
     // (a thread takes four elements of a member: the wavefronts' weights are worked out once for them)
 #pragma unroll
-    for (int u = 0; u < kOwnMax; ++u) {
-        const int idx = tid + u * (int)blockDim.x;
-        if (idx >= 16 * D / 4) break;
-        const int mm = idx / (D / 4), dd = 4 * (idx - mm * (D / 4));
-        const int m = m0 + mm;
-        if (m >= M_total) continue;
-        const int row = m / group, head = m - row * group;
+    for (int u = 0; u < kUnits; ++u) {
+        const int mm = unit_member(u), dd = unit_elem(u), m = m0 + mm;
+        if (mm >= 16 || m >= M_total) continue;
+        const int row = m >> lg_group, qh = kvh * group + (m & (group - 1));
         const int pe = am_prefix_end<TREE>(a, row);
         const int nsr = (pe + range - 1) / range;  // ranges the row's prefix reaches (0: an empty prefix)
         if (sp >= max(nsr, 1)) continue;
-        float mn = -INFINITY;
-        for (int w = 0; w < NW; ++w) mn = fmaxf(mn, am_sh[(size_t)w * (16 * (MP + 2)) + mm]);
-        float ls = 0.f;
-        f32x4 os = {0.f, 0.f, 0.f, 0.f};
+        float mw[NW], lw[NW], mn = -INFINITY;
+        f32x4 ow[NW];
+#pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float *wb = am_sh + (size_t)w * (16 * (MP + 2));
-            const float mw = wb[mm];
-            const float cw = mw == -INFINITY ? 0.f : __expf(mw - mn);
-            ls += wb[16 + mm] * cw;
-            os += *(const f32x4 *)(wb + 32 + mm * MP + dd) * cw;
+            mw[w] = wb[mm];
+            lw[w] = wb[16 + mm];
+            ow[w] = *(const f32x4 *)(wb + 32 + mm * MP + dd);
         }
-        const int qh = kvh * group + head;
-        if (nsr <= 1) {
-            f32x4 y;
-            uint32_t late[4];
-            if (u >= kUnits) load_own_values(u, late);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                y[i] = am_finish(mn, ls, os[i], s_own[mm], am_bf((uint16_t)(u < kUnits ? v_own[u < kUnits ? u : 0][i] : late[i])));
-            am_write4(a, row, qh * D + dd, y);
+        for (int w = 0; w < NW; ++w) mn = fmaxf(mn, mw[w]);
+        float ls = 0.f;
+        f32x4 os = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float cw = mw[w] == -INFINITY ? 0.f : __expf(mw[w] - mn);
+            ls += lw[w] * cw;
+            os += ow[w] * cw;
+        }
+        if (nsr <= 1) {
+            finish(u, row, qh, mn, ls, os);
         } else {
             const size_t slot = ((size_t)row * nq + qh) * n_split + sp;
-            *(f32x4 *)(a.part_o + slot * D + dd) = os;
-            if (dd == 0) {
-                a.part_ml[slot * 2] = mn;
-                a.part_ml[slot * 2 + 1] = ls;
+            if constexpr (MERGE) {
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, os), part_o, (uint32_t)((slot * D + dd) * 4), 0, kDeviceScope);
+                if (dd == 0)
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(mn), __float_as_uint(ls)}, part_ml, (uint32_t)(slot * 8), 0,
+                                                          kDeviceScope);
+            } else {
+                *(f32x4 *)(a.part_o + slot * D + dd) = os;
+                if (dd == 0) {
+                    a.part_ml[slot * 2] = mn;
+                    a.part_ml[slot * 2 + 1] = ls;
+                }
             }
+        }
+    }
+    if constexpr (MERGE) {
+        if (n_split == 1) return;
+        // ---- the workgroup that arrives last merges the ranges, in range order.  Partial results are stored and loaded at device
+        // scope (written through, read past this die's L2): once a workgroup's stores are acknowledged, a relaxed count
+        // publishes them, and no cache is written back or invalidated.
+        __shared__ int arrived;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        int *counter = a.counters + kvh * (int)gridDim.z + (int)blockIdx.z;
+        if (tid == 0) arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (arrived != n_split - 1) return;
+        asm volatile("" ::: "memory");
+        if (tid == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            const int mm = unit_member(u), dd = unit_elem(u), m = m0 + mm;
+            if (mm >= 16 || m >= M_total) continue;
+            const int row = m >> lg_group, qh = kvh * group + (m & (group - 1));
+            const int nsr = (am_prefix_end<TREE>(a, row) + range - 1) / range;
+            if (nsr <= 1) continue;
+            const uint32_t base = (uint32_t)(((size_t)row * nq + qh) * n_split);
+            float mn = -INFINITY, ls = 0.f;
+            f32x4 os = {0.f, 0.f, 0.f, 0.f};
+            for (int s0 = 0; s0 < nsr; s0 += 8) {
+                u32x2 ml[8];
+                u32x4 ov[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const uint32_t slot = base + (uint32_t)min(s0 + k, nsr - 1);
+                    ml[k] = __builtin_amdgcn_raw_buffer_load_b64(part_ml, slot * 8, 0, kDeviceScope);
+                    ov[k] = __builtin_amdgcn_raw_buffer_load_b128(part_o, (slot * D + dd) * 4, 0, kDeviceScope);
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (s0 + k >= nsr) break;
+                    am_fold(mn, ls, os, __uint_as_float(ml[k].x), __uint_as_float(ml[k].y), __builtin_bit_cast(f32x4, ov[k]));
+                }
+            }
+            finish(u, row, qh, mn, ls, os);
         }
     }
 }
@@ -423,13 +486,7 @@ __global__ __launch_bounds__(128) void k_attn_mfma_combine(AttnArgs a, int range
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             if (s0 + u >= nsr) break;
-            // running merge in range order (a range's maximum is -inf only if its rows see nothing there)
-            const float m2 = fmaxf(mn, m8[u]);
-            const float c1 = mn == -INFINITY ? 0.f : __expf(mn - m2);
-            const float c2 = m8[u] == -INFINITY ? 0.f : __expf(m8[u] - m2);
-            ls = ls * c1 + l8[u] * c2;
-            os = os * c1 + o8[u] * c2;
-            mn = m2;
+            am_fold(mn, ls, os, m8[u], l8[u], o8[u]);
         }
     }
     if (tid < 64) {
@@ -442,26 +499,41 @@ __global__ __launch_bounds__(128) void k_attn_mfma_combine(AttnArgs a, int range
 }
 
 // The launch shape.  Everything that shapes a row's arithmetic (wavefronts per workgroup, slots per range)
-// follows from the cache capacity and the head count alone.
+// follows from the cache capacity and the head counts alone.
 struct AmPlan {
     int nw;        // wavefronts per workgroup
     int range;     // cache slots per workgroup
     int hi_all;    // end of the longest prefix of the block
     int n_split;   // ranges that prefix reaches
     int n_tiles;   // member tiles (16 members each) = workgroups per (kv head, range)
+    bool merge;    // the ranges are merged in the same launch
 };
 AmPlan am_plan(const AttnArgs &a, int n_cu) {
     AmPlan p{};
-    // Short caches of many-headed models: one workgroup per kv head walks the whole prefix (no partial results,
-    // no second launch), with eight wavefronts to have enough loads in flight; otherwise the capacity is cut
-    // into enough ranges for about two workgroups per compute unit with one member tile.
-    const bool single = attn_uses_head_kernel(a.max_seq, a.n_kv_heads);
-    p.nw = single ? 8 : 4;
-    int want = single ? 1 : (2 * n_cu + a.n_kv_heads - 1) / a.n_kv_heads;
-    if (want > a.max_split) want = a.max_split;
-    if (want < 1) want = 1;
-    // (whole chunks; a range need not hold the same number of chunks for every wavefront)
-    p.range = std::max(32 * p.nw, ((a.max_seq + want - 1) / want + 31) / 32 * 32);
+    // Short caches of many-headed models: workgroups of eight wavefronts, ranges of a chunk each, merged by the last workgroup of a
+    // head.  (us a launch, 32 heads of 128, cold caches; before: one workgroup per head and range, three to six chunks in a row
+    // per wavefront.  640 slots: one row 10.2 / 8.5, 9 rows 12.8 / 9.6, 31 rows 13.6 / 10.6; 1400 slots: 21.5 / 11.7, 21.3 / 11.8, 21.8 /
+    // 19.5; one range as before, with this kernel 10.2, 11.9, 12.5 and 21.0, 20.6, 21.5; ranges of 128 with four wavefronts: 14 at 9
+    // rows and 640 slots; ranges of 512: 10.8, 11.8, 12.7 and 13.6, 13.2, 14.3; merged by a launch of its own: 10.5, 11.6, 12.6 and
+    // 12.6, 12.4, 18.1.  40 heads, 1100 slots, 31 rows: 18.4 / 19.3, the one case that lost: more workgroups than units.)  Where a
+    // full block's partial results would not fit the static scratch, one range.
+    p.merge = attn_uses_head_kernel(a.max_seq, a.n_kv_heads);
+    if (p.merge) {
+        p.nw = 8;
+        p.range = 256;
+        const size_t slots = (size_t)kMaxRows * a.n_q_heads * ((a.max_seq + p.range - 1) / p.range);
+        if (slots * (a.head_dim + 2) * 4 + 256 > kStaticAttnBytes) p.range = (a.max_seq + 31) / 32 * 32;
+    } else {
+        // otherwise the capacity is cut into enough ranges for about two workgroups per compute unit with one member tile, and a
+        // launch of its own merges them (7B, 8150 slots: 30.4 us for both, one row; 9 rows 31.2.  By the last workgroup, 16 ranges
+        // of 9 rows: 40)
+        p.nw = 4;
+        int want = (2 * n_cu + a.n_kv_heads - 1) / a.n_kv_heads;
+        if (want > a.max_split) want = a.max_split;
+        if (want < 1) want = 1;
+        // (whole chunks; a range need not hold the same number of chunks for every wavefront)
+        p.range = std::max(32 * p.nw, ((a.max_seq + want - 1) / want + 31) / 32 * 32);
+    }
     if (a.tree) {
         int deepest = 0;
         for (int r = 0; r < a.rows; ++r) deepest = std::max(deepest, (int)a.tt.depth[(a.row_base + r) & (kMaxRows - 1)]);
@@ -497,29 +569,41 @@ hipError_t launch_attn_mfma(const AttnArgs &a, int n_cu, hipStream_t s) {
                : (a.n_ctx < 1 || a.n_ctx - 1 + a.rows > a.max_seq))
         return hipErrorInvalidValue;
     const AmPlan p = am_plan(a, n_cu);
-    if (p.n_split > a.max_split) return hipErrorInvalidValue;
+    const int group = a.n_q_heads / a.n_kv_heads;
+    if (p.n_split > a.max_split || (group & (group - 1)) != 0 ||
+        (p.merge && p.n_split > 1 && (!a.counters || a.n_kv_heads * p.n_tiles > kMvCounters)))
+        return hipErrorInvalidValue;
     const int D = a.head_dim;
     const size_t lds = ((size_t)p.nw * 16 * (D + kAmPad + 2) + 16) * sizeof(float);
     const dim3 grid(a.n_kv_heads, p.n_split, p.n_tiles), block(64 * p.nw);
-#define SWIFT_AM(DD, TR)                                                                                        \
+    const int lg_group = __builtin_ctz(a.n_q_heads / a.n_kv_heads);
+#define SWIFT_AM(DD, TR, WV, MG)                                                                                \
     do {                                                                                                        \
         static bool attr_set = false;                                                                           \
         if (!attr_set) {                                                                                        \
-            hipError_t e = hipFuncSetAttribute((const void *)k_attn_mfma<DD, TR>,                               \
+            hipError_t e = hipFuncSetAttribute((const void *)k_attn_mfma<DD, TR, WV, MG>,                       \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);          \
             if (e != hipSuccess) return e;                                                                      \
             attr_set = true;                                                                                    \
         }                                                                                                       \
-        hipLaunchKernelGGL((k_attn_mfma<DD, TR>), grid, block, lds, s, a, p.range, p.hi_all);                   \
+        hipLaunchKernelGGL((k_attn_mfma<DD, TR, WV, MG>), grid, block, lds, s, (const uint16_t *)a.kcache,      \
+                           (const uint16_t *)a.vcache, a.q_s, a.max_seq, a.nb32, p.range, p.hi_all, a.rows, lg_group, a); \
     } while (0)
-    if (D == 128) {
-        if (a.tree) SWIFT_AM(128, true); else SWIFT_AM(128, false);
-    } else {
-        if (a.tree) SWIFT_AM(64, true); else SWIFT_AM(64, false);
+#define SWIFT_AM_D(DD)                                                                                          \
+    if (p.nw == 8) {                                                                                            \
+        if (a.tree) SWIFT_AM(DD, true, 8, true); else SWIFT_AM(DD, false, 8, true);                             \
+    } else {                                                                                                    \
+        if (a.tree) SWIFT_AM(DD, true, 4, false); else SWIFT_AM(DD, false, 4, false);                           \
     }
+    if (D == 128) {
+        SWIFT_AM_D(128)
+    } else {
+        SWIFT_AM_D(64)
+    }
+#undef SWIFT_AM_D
 #undef SWIFT_AM
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.n_split == 1) return e;
+    if (e != hipSuccess || p.n_split == 1 || p.merge) return e;
     const dim3 cgrid(a.n_q_heads, a.rows);
     if (a.tree)
         hipLaunchKernelGGL(k_attn_mfma_combine<true>, cgrid, dim3(128), 0, s, a, p.range, p.n_split);

@@ -143,6 +143,14 @@ __device__ inline float wave_reduce(float v, Op op) {
     v = op(v, dpp_move<0x4E>(v));    // quad_perm [2,3,0,1]
     return op(v, dpp_move<0xB1>(v)); // quad_perm [1,0,3,2]
 }
+// The lanes of one matrix column (l, l ^ 16, l ^ 32, l ^ 48), in the order of an exchange with lane ^ 16, ^ 32.
+template <typename Op>
+__device__ inline float column_reduce(float v, Op op) {
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
 __device__ inline float wave_sum(float v) {
     return wave_reduce(v, [](float x, float y) { return x + y; });
 }

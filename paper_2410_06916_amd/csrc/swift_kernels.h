@@ -90,6 +90,7 @@ struct AttnArgs {
     float *part_o;                // [rows][n_q][n_split][d]   unnormalised partial outputs
     float *part_ml;               // [rows][n_q][n_split][2]   running max, running sum
     int max_split;                // splits the partial buffers can hold
+    int *counters;                // matrix-core attention: nullptr, or [kMvCounters] arrival counters, zero between launches
     float *out;                   // fp32 [rows][n_q][d], or nullptr
     uint16_t *out_s;              // bf16 term split [n_q*d/8][terms * layout rows][8], or nullptr
     int out_rows;                 // layout code (block_row_layout) of the block out_s belongs to (0: an exact layout
