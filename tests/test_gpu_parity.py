@@ -1270,3 +1270,42 @@ def test_full_size_workloads_are_lossless_on_gpu(name, n_prompt, n_new):
     out, trace = P.generate_swift(g, prompt, n_new, np.zeros_like(mask), w.max_k, 0.0)
     assert np.array_equal(out, ar) and all(t["m"] == len(t["draft"]) for t in trace)
     g.close()
+
+
+@pytest.mark.parametrize("d,q_heads,prompt", [(128, 24, 250), (128, 24, 255), (128, 24, 256), (64, 48, 505), (128, 24, 771)])
+def test_rows_across_merged_attention_ranges(oracle_lib, d, q_heads, prompt):
+    """Short caches of 24 and more kv heads: ranges of 256 slots, merged by the last workgroup of a head and member tile.  Blocks
+    whose rows end in different ranges, prefixes that end at, before and after a range's edge, one and several member tiles: rows
+    equal the same tokens decoded alone bit for bit, three calls in a row (the arrival counters are zero again), also from the
+    static scratch, and a tree's rows equal the chain's; logits within the bf16 tolerance of the oracle's."""
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape("merged-ranges", 2, 256, q_heads, 24, d, 256, 512, "bf16", 1e-5)
+    weights, cap = hp.shaped_weights(shape, seed=5), 820
+    g, o = P.SwiftModel(shape, cap), oracle_lib.Oracle(shape, cap, threads=4)
+    g.load_weights(weights)
+    o.set_weights(weights)
+    ids = si.uniform_ids(6, prompt, shape.vocab)
+    assert g.prefill(ids) == o.prefill(ids)[0]
+    assert "8 wavefronts, range 256" in g.attn_path(1)
+    n0, t0 = g.cache_len, g.pending
+    toks, rows = [t0], []
+    for _ in range(32):
+        tgt, lg = g.verify([g.pending], True)
+        g.accept()
+        toks.append(int(tgt[0]))
+        rows.append(lg[0].copy())
+    want = o.verify(toks[:32], True)[1]
+    assert np.all(hp.rel_err_rowmax(np.stack(rows), want) <= 2e-2)
+    for R in (2, 7, 9, 16, 32):
+        for call in (g.verify, g.verify, g.verify_static):
+            g.rollback(n0, t0)
+            tgt, lg = call(toks[:R], True)
+            assert [int(x) for x in tgt] == toks[1:R + 1]
+            assert np.array_equal(lg, np.stack(rows[:R])), (d, prompt, R)
+    g.rollback(n0, t0)
+    levels = [np.array([t, (t + 1) % shape.vocab, (t + 2) % shape.vocab], np.int32) for t in toks[1:9]]
+    lg = g.verify_tree(levels, True)[1]
+    spine = [0] + [1 + 3 * i for i in range(8)]  # the pending token and each level's first candidate
+    assert np.array_equal(lg[spine], np.stack(rows[:9]))
+    g.close()
+    o.close()
