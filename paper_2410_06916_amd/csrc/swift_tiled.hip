@@ -1214,12 +1214,13 @@ __global__ __launch_bounds__(512) void k_mvR(const unsigned char *Wt, const unsi
 // Steps in flight per wavefront: what 256 registers hold beside the accumulators (3 x 6 tiles: two steps, three spill).
 constexpr int mvr_steps(int ncb, int rg) {
     const int n = ((rg * ncb >= 18 ? 144 : rg * ncb >= 8 ? 184 : 200) - 4 * rg * ncb) / (4 * (rg + ncb));
-    return n > 10 ? 10 : n;
+    const int most = rg == 1 && ncb <= 2 ? 11 : 10;
+    return n > most ? most : n;
 }
 
 // A second depth for slices that the first one cuts badly (slots past the end of a slice load its last tile again): 16, 20,
 // 32 and 43 tiles are 2 x 8, 2 x 10 or 5 x 4, 4 x 8 and 5 x 9 or 11 x 4.
-constexpr int mvr_other_steps(int ns) { return ns > 8 ? 8 : ns == 8 ? 7 : ns > 4 ? 4 : ns == 3 ? 2 : ns; }
+constexpr int mvr_other_steps(int ns) { return ns > 10 ? 11 : ns > 8 ? 8 : ns == 8 ? 7 : ns > 4 ? 4 : ns == 3 ? 2 : ns; }
 // The better of the two depths for a slice of n tiles, and the steps of the slice as walked with it.
 static int mvr_depth(int n, int ncb, int rg) {
     const int a = mvr_steps(ncb, rg), b = mvr_other_steps(a);
