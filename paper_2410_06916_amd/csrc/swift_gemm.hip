@@ -45,19 +45,29 @@ constexpr int kNormFloats = 2 * 16 * 64;  // scratch of gemm_norm_scales
 
 // RMSNorm scales of the workgroup's two sub-blocks: rs[64 wn + r].  Thread (wn, q, r4) adds the partials q, q + 16,
 // .. of rows 4 r4 .. 4 r4 + 3 of sub-block wn (16 loads of 16 bytes in flight at a time); then one thread per row
-// adds the sixteen sums in order.  The partials are read ahead of the ring's first stages, so that they do not queue
-// behind 140 KB of tiles; the scales are read by the epilogue only, so no barrier here waits for more than LDS.
-__device__ inline f32x4 gemm_norm_sum(const MvArgs &a, const MacroArgs &ma, int sub0) {
+// adds the sixteen sums in order.  The first 256 partials are requested ahead of the ring's first stages, so that they do not queue
+// behind 140 KB of tiles, and added up once those are on their way; the scales are read by the epilogue only, so no barrier here waits for
+// more than LDS.
+struct GemmNorm {
+    f32x4 v[16];
+};
+__device__ inline GemmNorm gemm_norm_load(const MvArgs &a, const MacroArgs &ma, int sub0, int p0 = 0) {
     const int tid = threadIdx.x, q = (tid >> 4) & 15;
     const float *p = a.pss + (size_t)min(sub0 + (tid >> 8), ma.S - 1) * ma.pss + 4 * (tid & 15);
+    GemmNorm n;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) n.v[u] = *(const f32x4 *)(p + (size_t)min(p0 + q + 16 * u, a.n_pss - 1) * a.rp);
+    return n;
+}
+__device__ inline f32x4 gemm_norm_sum(const MvArgs &a, const MacroArgs &ma, int sub0, const GemmNorm &first) {
+    const int q = (threadIdx.x >> 4) & 15;
     f32x4 ss = {0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < a.n_pss; p0 += 256) {
-        f32x4 v[16];
+    auto add = [&](int p0, const GemmNorm &n) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = *(const f32x4 *)(p + (size_t)min(p0 + q + 16 * u, a.n_pss - 1) * a.rp);
-#pragma unroll
-        for (int u = 0; u < 16; ++u) ss += p0 + q + 16 * u < a.n_pss ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int u = 0; u < 16; ++u) ss += p0 + q + 16 * u < a.n_pss ? n.v[u] : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    add(0, first);
+    for (int p0 = 256; p0 < a.n_pss; p0 += 256) add(p0, gemm_norm_load(a, ma, sub0, p0));
     return ss;
 }
 __device__ inline void gemm_norm_scales(const MvArgs &a, const f32x4 &ss, float *rs, float *scratch) {
@@ -152,8 +162,7 @@ __device__ inline void gemm_resid(const MvArgs &a, int rg0, int r0, int lane, YF
                 if (ok) *(f32x4 *)(a.out_f32 + (size_t)r * a.ld_out + row) = xn;
                 store_split(a.out_s, 2 * rg + (kg >> 1), r, kg, ok, xn * gain[g]);
                 float ss = in ? (xn[0] * xn[0] + xn[1] * xn[1]) + (xn[2] * xn[2] + xn[3] * xn[3]) : 0.f;
-                ss += __shfl_xor(ss, 16, 64);
-                ss += __shfl_xor(ss, 32, 64);
+                ss = column_reduce(ss, [](float x, float y) { return x + y; });
                 if (kg == 0 && r < a.R) a.pss_out[(size_t)rg * a.rp + r] = ss;
             }
         }
@@ -279,6 +288,7 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     constexpr int NST = kRingBytes / ST_BYTES;   // stages of the ring
     constexpr int NP = TRG + 8 * SB;              // 1 KB pieces of a stage
     constexpr int PW = (NP + 7) / 8;              // pieces a wavefront copies per stage (PW - 1 past the remainder)
+    constexpr bool kLateNorm = !FOLD && RGW != 7 && !(EPI == EPI_QKV && RGW == 8);  // (the others have no registers for the partials behind the first requests)
     constexpr bool kNorm = EPI != EPI_RESID;      // the input is a normalised one: scales from the producer's partial sums
     static_assert(NST >= 3 && NST * PW < 64, "ring depth against the load counter");
     unsigned char *ring = smem;
@@ -360,17 +370,17 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     };
 
     f32x4 acc[RGW][4];
+    f32x4 done[FOLD ? RGW : 1][2];  // FOLD: the finished parts of the sums, the two terms combined
+    auto clear = [&]() {            // (once the registers of the norm partials are free)
 #pragma unroll
-    for (int g = 0; g < RGW; ++g)
+        for (int g = 0; g < RGW; ++g)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // FOLD: the finished parts of the sums, the two terms combined
-    f32x4 done[FOLD ? RGW : 1][2];
+            for (int cb = 0; cb < 4; ++cb) acc[g][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int g = 0; g < (FOLD ? RGW : 1); ++g)
+        for (int g = 0; g < (FOLD ? RGW : 1); ++g)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) done[g][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < 2; ++c) done[g][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
     auto fold_part = [&]() {
 #pragma unroll
         for (int g = 0; g < (FOLD ? RGW : 0); ++g)
@@ -386,8 +396,6 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
 
     const unsigned char *a_base = ring + (wm * RGW) * 1024 + lane * 16;
     const unsigned char *b_base = ring + A_BYTES + ws * 8192 + (kg * 128 + 64 * wh + col) * 16;
-    // (wavefronts without a sub-block -- an odd sub-block count leaves half of the last column tile empty -- go
-    // through the motions on the last sub-block's data; their results are dropped)
     auto read_operands = [&](int slot_bytes, GemmOperands<RGW> &o) {
 #pragma unroll
         for (int g = 0; g < RGW; ++g) o.av[g] = *(const u32x4 *)(a_base + slot_bytes + g * 1024);
@@ -423,26 +431,53 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     // register set, and the matrix cores work on stage t meanwhile.  `slot`: byte offset of stage t's ring slot.
     // The loop body is kept free of conditions: a wavefront issues at most one scalar instruction every few cycles,
     // and whatever the loop needs beyond the matrix instructions is paid for in full.
+    GemmNorm np;
     f32x4 norm_ss = {0.f, 0.f, 0.f, 0.f};
-    auto pipeline = [&](auto FULL) {
-        constexpr auto ALL = std::integral_constant<int, 0>();
-        constexpr auto AHEAD = std::integral_constant<int, NST - 2>();  // stages t + 2 .. t + NST - 1 may stay in flight
+    auto start = [&](auto FULL) {  // requests the first stages and waits for the first one
+        const int first = min(TF, NST);
         if (TF >= NST) {
 #pragma unroll
             for (int t = 0; t < NST; ++t) issue(t * ST_BYTES, FULL);
-            if (kNorm) gemm_norm_scales(a, norm_ss, rs, nscratch);
-            wait_all_but(std::integral_constant<int, NST - 1>(), FULL);
         } else {
-            for (int t = 0; t < TF; ++t) issue(t * ST_BYTES, FULL);
-            if (kNorm) gemm_norm_scales(a, norm_ss, rs, nscratch);
-            if (TF == 0) return;
-            wait_all_but(ALL, FULL);
+            for (int t = 0; t < first; ++t) issue(t * ST_BYTES, FULL);
         }
+        if (kNorm && kLateNorm) norm_ss = gemm_norm_sum(a, ma, sub0, np);
+        if (kNorm) gemm_norm_scales(a, norm_ss, rs, nscratch);
+        if (TF >= NST)
+            wait_all_but(std::integral_constant<int, NST - 1>(), FULL);
+        else
+            wait_all_but(std::integral_constant<int, 0>(), FULL);
+    };
+    auto next_slot = [&](int sl) { return sl + ST_BYTES == NST * ST_BYTES ? 0 : sl + ST_BYTES; };
+    constexpr auto ALL = std::integral_constant<int, 0>();
+    constexpr auto AHEAD = std::integral_constant<int, NST - 2>();  // stages t + 2 .. t + NST - 1 may stay in flight
+    // A wavefront whose half of a sub-block holds no row copies its share and keeps the others' barriers, no more (its products cost
+    // the others power and LDS: 13 rows in the last of 4 sub-blocks, 13B: gate/up 133.7 / 130.5 us, down_proj 86.6 / 83.9, q|k|v 92.0 /
+    // 88.6; of 2, 70B gate/up 238 / 214).
+    auto copy_only = [&](auto FULL) {
+        start(FULL);
+        if (TF == 0) return;
+        lds_sync();
+        for (int t = 0, slot = 0; t < TF; ++t) {
+            if (t + NST < TF) {
+                wait_all_but(AHEAD, FULL);
+                lds_sync();
+                issue(slot, FULL);
+            } else {
+                wait_all_but(ALL, FULL);
+                lds_sync();
+            }
+            slot = next_slot(slot);
+        }
+    };
+    auto pipeline = [&](auto FULL) {
+        start(FULL);
+        clear();
+        if (TF == 0) return;
         GemmOperands<RGW> o0, o1;
         lds_sync();
         read_operands(0, o0);
         int t = 0, slot = 0;
-        auto next_slot = [&](int sl) { return sl + ST_BYTES == NST * ST_BYTES ? 0 : sl + ST_BYTES; };
         auto steady = [&](const GemmOperands<RGW> &cur, GemmOperands<RGW> &nxt) {
             const int nslot = next_slot(slot);
             wait_all_but(AHEAD, FULL);
@@ -485,11 +520,23 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
             if (e == TF) break;
         }
     };
-    if (kNorm) norm_ss = gemm_norm_sum(a, ma, sub0);
-    if (full_share)
+    const int sub = min(sub0 + ws, ma.S - 1), r0 = 32 * wh;  // the wavefront's sub-block, and its rows of it: r0 .. r0 + 31
+    const bool wave_live = sub0 + ws < ma.S && r0 < (sub == ma.S - 1 ? ma.rows_last : 64);
+    if (kNorm) {
+        np = gemm_norm_load(a, ma, sub0);
+        if (!kLateNorm) norm_ss = gemm_norm_sum(a, ma, sub0, np);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!wave_live) {
+        if (full_share)
+            copy_only(std::true_type());
+        else
+            copy_only(std::false_type());
+    } else if (full_share) {
         pipeline(std::true_type());
-    else
+    } else {
         pipeline(std::false_type());
+    }
     if (ragged) {
         // the ragged tile: copied with ordinary loads, zeros past the real depth (a piece lies wholly inside or
         // wholly outside it), into the first ring slot
@@ -505,51 +552,54 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
             }
         }
         __syncthreads();
-        GemmOperands<RGW> o;
-        read_operands(0, o);
-        multiply(o);
+        if (wave_live) {
+            GemmOperands<RGW> o;
+            read_operands(0, o);
+            multiply(o);
+        }
     }
 
     // ---- epilogue on the sub-block's own buffers
-    const int sub = min(sub0 + ws, ma.S - 1), r0 = 32 * wh;  // the wavefront's rows of it: r0 .. r0 + 31
+    __syncthreads();  // the ring is no longer read (and the scales are visible where no step had a barrier)
+    if (!wave_live) return;
     MvArgs as = a;
     as.R = sub == ma.S - 1 ? ma.rows_last : 64;
     as.pos0 = a.pos0 + 64 * sub;
     if (a.out_f32) as.out_f32 = a.out_f32 + (size_t)sub * ma.out_f32;
     if (a.out_s) as.out_s = a.out_s + (size_t)sub * ma.out_s;
     if (a.pss_out) as.pss_out = a.pss_out + (size_t)sub * ma.pss_out;
-    const bool wave_live = sub0 + ws < ma.S && r0 < as.R;
     const int rg0 = (mt * WM + wm) * RGW;
-    auto finish = [&](auto y) {
+    // (the epilogue of G row groups from rg1 on; y(g, v): finished sums of the g-th of them)
+    auto finish = [&](auto G, int rg1, auto y) {
+        constexpr int kG = decltype(G)::value;
         if (EPI == EPI_RESID) {
-            gemm_resid<RGW>(as, rg0, r0, lane, y);
+            gemm_resid<kG>(as, rg1, r0, lane, y);
         } else {
             float sc[2];
 #pragma unroll
             for (int c = 0; c < 2; ++c) sc[c] = rs[64 * ws + r0 + gemm_row(c, col)];
             if (EPI == EPI_QKV) {
-                gemm_qkv<RGW>(as, rg0, r0, lane, sc, (uint16_t *)ring + (size_t)wave * 1024, y);
+                gemm_qkv<kG>(as, rg1, r0, lane, sc, (uint16_t *)ring + (size_t)wave * 1024, y);
             } else {
 #pragma unroll
-                for (int g = 0; g < RGW; ++g) {
-                    if (rg0 + g >= a.n_rg) break;
+                for (int g = 0; g < kG; ++g) {
+                    if (rg1 + g >= a.n_rg) break;
                     f32x4 v[2];
                     y(g, v);
-                    gemm_swiglu(as, rg0 + g, r0, lane, sc, v);
+                    gemm_swiglu(as, rg1 + g, r0, lane, sc, v);
                 }
             }
         }
     };
-    __syncthreads();  // the ring is no longer read (and the scales are visible where no step had a barrier)
+    constexpr auto WHOLE = std::integral_constant<int, RGW>();
     if (FOLD || KSP == 1) {
-        if (wave_live)
-            finish([&](int g, f32x4(&v)[2]) {
-                fold_terms(acc[g], col, v);
-                if (FOLD) {
+        finish(WHOLE, rg0, [&](int g, f32x4(&v)[2]) {
+            fold_terms(acc[g], col, v);
+            if (FOLD) {
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) v[c] = done[g][c] + v[c];
-                }
-            });
+                for (int c = 0; c < 2; ++c) v[c] = done[g][c] + v[c];
+            }
+        });
         return;
     }
     // ---- depth split over workgroups.  Every wavefront publishes its results, the two terms combined, as
@@ -561,7 +611,6 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     // relaxed count publishes them, and no cache has to be written back or invalidated.  (One counter per workgroup,
     // 8-byte stores and an acquire-release count cost 25-30 us per launch; this ~10.)
     const int rgt0 = rg0 - pl.MTF * TRG, n_rgt = a.n_rg - pl.MTF * TRG;  // row groups of the split tiles
-    if (!wave_live) return;
     const __amdgpu_buffer_rsrc_t part = __builtin_amdgcn_make_buffer_rsrc(a.part, 0, 0x7fffffff, 0x00020000);
     auto part_off = [&](int k2, int g, int c) { return (uint32_t)((((k2 * n_rgt + rgt0 + g) * ma.S + sub) * 4 + 2 * wh + c) * 1024 + lane * 16); };
 #pragma unroll
@@ -579,18 +628,33 @@ __global__ __launch_bounds__(512) void k_gemm(MvArgs a, MacroArgs ma, GemmPlan p
     if (lane == 0) arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__builtin_amdgcn_readfirstlane(arrived) != KSP - 1) return;
     asm volatile("" ::: "memory");
-    finish([&](int g, f32x4(&v)[2]) {
-        if (rg0 + g >= a.n_rg) return;
+    // (the parts of two row groups are requested together: one by one, each was a round trip of its own.  us, before / now: 13B, 4
+    // sub-blocks o_proj 41 / 37; 7B, 2 sub-blocks o_proj 21.8 / 20.5)
+    auto batch = [&](auto G, int g0) {
+        constexpr int kG = decltype(G)::value;
+        f32x4 w[4][kG][2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) v[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(0, g, c), 0, kDeviceScope));
-        for (int k2 = 1; k2 < KSP; ++k2) {
-            f32x4 w[2];
+        for (int k2 = 0; k2 < 4; ++k2)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) w[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(k2, g, c), 0, kDeviceScope));
+            for (int g = 0; g < kG; ++g)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) v[c] += w[c];
-        }
-    });
+                for (int c = 0; c < 2; ++c)
+                    if (k2 < KSP && rg0 + g0 + g < a.n_rg)  // (wavefront-uniform)
+                        w[k2][g][c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, part_off(k2, g0 + g, c), 0, kDeviceScope));
+        finish(G, rg0 + g0, [&](int g, f32x4(&v)[2]) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                v[c] = w[0][g][c];
+#pragma unroll
+                for (int k2 = 1; k2 < 4; ++k2)
+                    if (k2 < KSP) v[c] += w[k2][g][c];
+            }
+        });
+    };
+    constexpr int kB = RGW < 2 || (EPI == EPI_QKV && RGW == 8) ? 1 : 2;
+#pragma unroll 1
+    for (int g0 = 0; g0 + kB <= RGW; g0 += kB) batch(std::integral_constant<int, kB>(), g0);
+    if constexpr (RGW % kB != 0) batch(std::integral_constant<int, 1>(), RGW - 1);
     if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
