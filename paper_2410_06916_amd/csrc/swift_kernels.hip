@@ -38,64 +38,143 @@ __device__ inline float block_sum_256(float v, float *red /* >= 4 floats of LDS 
 // merges them) instead of 135, a 32-row prompt 23 instead of 860.  A row's
 // products are added in the same order whatever RB is (lane l takes 16-byte chunks l, l + 64, .., then a butterfly), so
 // its result does not depend on the rows it shares a pass with.
+//
+// Inside a launch it is the number of memory latencies in a row.  So everything that does not hang on another load is requested
+// at once, ahead of the norm: the activation rows and gains, the weights of the wavefront's first unit and what its epilogue needs
+// (residual values, rotary angles); the arguments of the first loads are the kernel's leading ones, in registers at its start.
+// (Depths of up to kGemvAhead chunks of 64 lanes, 1024 values for fp32; what lies beyond is read where it is used.)
+constexpr int kGemvAhead = 4;
 template <typename T, int EPI, int RB>
-__global__ __launch_bounds__(kGemvThreads) void k_gemv(GemvArgs a) {
-    extern __shared__ __align__(16) float xs[];  // [RB][K] activations (normalised if gain != null)
+__global__ __launch_bounds__(kGemvThreads) void k_gemv(const void *Wv, const float *xin, const float *gain, int K, int O, int R, GemvArgs a) {
+    extern __shared__ __align__(16) float xs[];  // [RB][K] activations (normalised if gain != null); depths requested ahead: [RB][4] sums
     __shared__ float red[4];
+    constexpr int kAhead = kGemvAhead;           // chunks per lane, and activation values per thread and row, requested ahead
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int K = a.K;
-    const int row0 = (int)blockIdx.y * RB, n_rows = min(RB, a.R - row0);
-
-    // ---- prologue: stage the activation rows in LDS, RMS-normalised when a gain is given (rows past the block: the
-    // last row once more, dropped at the end)
-#pragma unroll
-    for (int rr = 0; rr < RB; ++rr) {
-        const float *xin = a.xin + (size_t)(row0 + min(rr, n_rows - 1)) * K;
-        float *x = xs + (size_t)rr * K;
-        if (a.gain) {
-            float ss = 0.f;
-            for (int i = tid; i < K; i += kGemvThreads) {
-                float v = xin[i];
-                x[i] = v;
-                ss += v * v;
-            }
-            ss = block_sum_256(ss, red);
-            const float r = 1.0f / sqrtf(ss / (float)K + a.eps);
-            for (int i = tid; i < K; i += kGemvThreads) x[i] = x[i] * r * a.gain[i];
-        } else {
-            for (int i = tid; i < K; i += kGemvThreads) x[i] = xin[i];
-        }
-    }
-    __syncthreads();
+    const int row0 = (int)blockIdx.y * RB, n_rows = min(RB, R - row0);
 
     // ---- units of two output rows
-    const int d = a.head_dim, half = d >> 1;
-    const int n_units = a.O >> 1;
+    const int d = a.head_dim, half = d >> 1, lg_half = __builtin_ctz(half);
+    const int n_units = O >> 1;
     const int chunks = K / T::VEC;
-    const typename T::elem *W = (const typename T::elem *)a.W;
-    const int waves_total = gridDim.x * (kGemvThreads / 64);
-
-    for (int u = blockIdx.x * (kGemvThreads / 64) + wave; u < n_units; u += waves_total) {
-        int ra, rb;
+    const typename T::elem *W = (const typename T::elem *)Wv;
+    const int waves_total = gridDim.x * (kGemvThreads / 64), u0 = blockIdx.x * (kGemvThreads / 64) + wave;
+    auto unit_rows = [&](int u, int &ra, int &rb) {
         if (EPI == EPI_QKV) {
-            const int hh = u / half, i = u - hh * half;  // head (q heads, then k heads, then v heads)
+            const int hh = u >> lg_half, i = u - (hh << lg_half);  // head (q heads, then k heads, then v heads)
             ra = hh * d + i;
             rb = ra + half;
         } else {
             ra = 2 * u;
             rb = ra + 1;
         }
+    };
+    // (weights that every row group of a block reads again stay in the caches)
+    auto load_w = [&](const u32x4 *p) { return RB == 1 ? __builtin_nontemporal_load(p) : *p; };
+    const int r = row0 + min(lane, n_rows - 1);  // the row whose results this lane stores
+    float *out = a.out + (size_t)r * a.ld_out;
+    float e0 = 0.f, e1 = 0.f;                    // what the epilogue of a unit needs
+    auto load_side = [&](int u) {
+        if (EPI == EPI_RESID) {
+            e0 = out[2 * u];
+            e1 = out[2 * u + 1];
+        } else if (EPI == EPI_QKV) {
+            const int hh = u >> lg_half, i = u - (hh << lg_half);
+            if (hh < a.n_q_heads + a.n_kv_heads) {
+                const int rpos = a.pos0 + (a.tree ? (int)a.depth[r & (kMaxRows - 1)] : r);
+                e0 = a.cos_tab[(size_t)rpos * half + i];
+                e1 = a.sin_tab[(size_t)rpos * half + i];
+            }
+        }
+    };
+
+    // ---- requests
+    u32x4 wa0[kAhead], wb0[kAhead];
+    {
+        int ra, rb;
+        unit_rows(min(u0, n_units - 1), ra, rb);
+        const u32x4 *wa = (const u32x4 *)(W + (size_t)ra * K), *wb = (const u32x4 *)(W + (size_t)rb * K);
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            if (q * 64 >= chunks) break;  // (uniform)
+            const int c = min(lane + 64 * q, chunks - 1);
+            wa0[q] = load_w(wa + c);
+            wb0[q] = load_w(wb + c);
+        }
+    }
+    // ---- prologue: stage the activation rows in LDS, RMS-normalised when a gain is given (rows past the block: the
+    // last row once more, dropped at the end)
+    const bool ahead = K <= kAhead * kGemvThreads;
+    if (ahead) {
+        float x[RB][kAhead], gv[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            if (q * kGemvThreads >= K) break;
+            const int i = min(tid + kGemvThreads * q, K - 1);
+            if (gain) gv[q] = gain[i];
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr) x[rr][q] = xin[(size_t)(row0 + min(rr, n_rows - 1)) * K + i];
+        }
+        load_side(min(u0, n_units - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        float scale[RB], *sums = xs + (size_t)RB * K;
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) scale[rr] = 1.f;
+        if (gain) {
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr) {
+                float ss = 0.f;
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q)
+                    if (tid + kGemvThreads * q < K) ss = fmaf(x[rr][q], x[rr][q], ss);
+                ss = wave_sum(ss);
+                if (lane == 0) sums[4 * rr + wave] = ss;
+            }
+            lds_barrier();
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr) {
+                const float ss = (sums[4 * rr] + sums[4 * rr + 1]) + (sums[4 * rr + 2] + sums[4 * rr + 3]);
+                scale[rr] = 1.0f / sqrtf(ss / (float)K + a.eps);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int i = tid + kGemvThreads * q;
+            if (i >= K) break;
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr) xs[(size_t)rr * K + i] = gain ? x[rr][q] * scale[rr] * gv[q] : x[rr][q];
+        }
+    } else {
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) {
+            const float *xi = xin + (size_t)(row0 + min(rr, n_rows - 1)) * K;
+            float *x = xs + (size_t)rr * K;
+            if (gain) {
+                float ss = 0.f;
+                for (int i = tid; i < K; i += kGemvThreads) {
+                    float v = xi[i];
+                    x[i] = v;
+                    ss = fmaf(v, v, ss);
+                }
+                ss = block_sum_256(ss, red);
+                const float sc = 1.0f / sqrtf(ss / (float)K + a.eps);
+                for (int i = tid; i < K; i += kGemvThreads) x[i] = x[i] * sc * gain[i];
+            } else {
+                for (int i = tid; i < K; i += kGemvThreads) x[i] = xi[i];
+            }
+        }
+    }
+    lds_barrier();
+
+    for (int u = u0; u < n_units; u += waves_total) {
+        int ra, rb;
+        unit_rows(u, ra, rb);
         const u32x4 *wa = (const u32x4 *)(W + (size_t)ra * K);
         const u32x4 *wb = (const u32x4 *)(W + (size_t)rb * K);
         constexpr int kUnroll = RB == 1 ? 4 : 2;
         float acc_a[RB], acc_b[RB];
 #pragma unroll
         for (int rr = 0; rr < RB; ++rr) acc_a[rr] = acc_b[rr] = 0.f;
-#pragma unroll kUnroll
-        for (int c = lane; c < chunks; c += 64) {
-            // (weights that every row group of a block reads again stay in the caches)
-            const u32x4 va = RB == 1 ? __builtin_nontemporal_load(wa + c) : wa[c];
-            const u32x4 vb = RB == 1 ? __builtin_nontemporal_load(wb + c) : wb[c];
+        auto add = [&](int c, const u32x4 &va, const u32x4 &vb) {
             float fa[T::VEC], fb[T::VEC];
             T::unpack(va, fa);
             T::unpack(vb, fb);
@@ -108,7 +187,15 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(GemvArgs a) {
                     acc_b[rr] = fmaf(fb[j], xp[j], acc_b[rr]);
                 }
             }
+        };
+        int c = lane;
+        if (u == u0) {
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q, c += 64)
+                if (c < chunks) add(c, wa0[q], wb0[q]);
         }
+#pragma unroll kUnroll
+        for (; c < chunks; c += 64) add(c, load_w(wa + c), load_w(wb + c));
         // lane rr ends up with row rr's two sums
         float ya0 = 0.f, yb0 = 0.f;
 #pragma unroll
@@ -119,18 +206,15 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(GemvArgs a) {
                 yb0 = sb;
             }
         }
+        if (u != u0 || !ahead) load_side(u);
         if (lane >= n_rows) continue;
-        const int r = row0 + lane;
-        float *out = a.out + (size_t)r * a.ld_out;
 
         if (EPI == EPI_QKV) {
-            const int hh = u / half, i = u - hh * half;
+            const int hh = u >> lg_half, i = u - (hh << lg_half);
             const int nq = a.n_q_heads, nkv = a.n_kv_heads, pos = a.pos0 + r;
             if (hh < nq + nkv) {  // rotary pair (i, i + d/2)
-                const int rpos = a.pos0 + (a.tree ? (int)a.depth[r & (kMaxRows - 1)] : r);
-                const float c = a.cos_tab[(size_t)rpos * half + i], s = a.sin_tab[(size_t)rpos * half + i];
-                const float ya = ya0 * c - yb0 * s;
-                const float yb = yb0 * c + ya0 * s;
+                const float ya = ya0 * e0 - yb0 * e1;
+                const float yb = yb0 * e0 + ya0 * e1;
                 if (hh < nq) {
                     out[hh * d + i] = ya;
                     out[hh * d + i + half] = yb;
@@ -145,8 +229,8 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(GemvArgs a) {
                 T::store1(vc + i + half, yb0);
             }
         } else if (EPI == EPI_RESID) {
-            out[ra] += ya0;
-            out[rb] += yb0;
+            out[ra] = e0 + ya0;
+            out[rb] = e1 + yb0;
         } else if (EPI == EPI_SWIGLU) {
             out[u] = ya0 / (1.0f + expf(-ya0)) * yb0;
         } else {
@@ -158,7 +242,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(GemvArgs a) {
 
 template <typename T, int EPI, int RB>
 static hipError_t launch_gemv_t(const GemvArgs &a, int n_cu, hipStream_t s) {
-    const size_t lds = (size_t)RB * a.K * sizeof(float);
+    const size_t lds = ((size_t)RB * a.K + (a.K <= kGemvAhead * kGemvThreads ? 4 * RB : 0)) * sizeof(float);
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void *)k_gemv<T, EPI, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -173,7 +257,8 @@ static hipError_t launch_gemv_t(const GemvArgs &a, int n_cu, hipStream_t s) {
     int grid = n_cu * occupancy;
     if (grid > wg_needed) grid = wg_needed;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL((k_gemv<T, EPI, RB>), dim3(grid, (a.R + RB - 1) / RB), dim3(kGemvThreads), lds, s, a);
+    hipLaunchKernelGGL((k_gemv<T, EPI, RB>), dim3(grid, (a.R + RB - 1) / RB), dim3(kGemvThreads), lds, s, a.W, a.xin, a.gain, a.K, a.O,
+                       a.R, a);
     return hipGetLastError();
 }
 
