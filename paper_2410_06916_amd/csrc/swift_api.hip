@@ -703,13 +703,6 @@ int forward_block_tiled(swift_ctx *x, const int32_t *tokens, int R, int pos0, co
                 m.tree = 1;
                 memcpy(m.depth, tree->depth, sizeof(m.depth));
             }
-            // the committed keys/values the attention launch will read: warmed into L2 by spare workgroups of
-            // this launch (one-workgroup-per-head attention only: its workgroup-to-head mapping is what the
-            // warm-up relies on)
-            if (!q_only && attn_uses_head_kernel(c.max_seq, c.n_kv_heads)) {
-                m.pf_heads = c.n_kv_heads;
-                m.pf_rows = pos0;
-            }
             if (int rc = run_mv(SWIFT_KC_QKV, EPI_QKV, m)) return rc;
 
             AttnArgs a{};

@@ -297,11 +297,7 @@ struct MvArgs {
     int part_capacity;     // row-group-splits the scratch can hold
     int S;                 // set by the launcher
     int kgroup;            // set by the launcher: K slices whose sums are added first (see mv_slice_group)
-    // QKV, LDS-resident kernel only: cache lines to pull into the L2 of the die that will run the attention of
-    // kv head g right after this launch (rows [0, pf_rows) of head g's keys and values); pf_heads = 0: none.
-    // n_wg: workgroups that do the projection; pf_first, pf_wgs: first warm-up workgroup and how many (all set by
-    // the launcher)
-    int pf_rows, pf_heads, n_wg, pf_first, pf_wgs;
+    int n_wg;              // set by the launcher: workgroups
 };
 // position block row r of a QKV pass is rotated for
 __host__ __device__ inline int mv_rope_pos(const MvArgs &a, int r) {
