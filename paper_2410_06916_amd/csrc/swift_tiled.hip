@@ -1160,21 +1160,30 @@ __global__ __launch_bounds__(512) void k_mvR(const unsigned char *Wt, const unsi
 // Steps in flight per wavefront: what 256 registers hold beside the accumulators (3 x 6 tiles: two steps, three spill).
 constexpr int mvr_steps(int ncb, int rg) {
     const int n = ((rg * ncb >= 18 ? 144 : rg * ncb >= 8 ? 184 : 200) - 4 * rg * ncb) / (4 * (rg + ncb));
-    const int most = rg == 1 && ncb <= 2 ? 11 : 10;
-    return n > most ? most : n;
+    return n > 10 ? 10 : n;
 }
 
-// A second depth for slices that the first one cuts badly (slots past the end of a slice load its last tile again): 16, 20,
-// 32 and 43 tiles are 2 x 8, 2 x 10 or 5 x 4, 4 x 8 and 5 x 9 or 11 x 4.
-constexpr int mvr_other_steps(int ns) { return ns > 10 ? 11 : ns > 8 ? 8 : ns == 8 ? 7 : ns > 4 ? 4 : ns == 3 ? 2 : ns; }
-// The better of the two depths for a slice of n tiles, and the steps of the slice as walked with it.
+// Other depths for slices that the first one cuts badly.  (A step past a slice's end reads nothing, but it is issued and multiplied, and
+// while it holds its place in the window fewer loads are in flight.)  us, 256 row groups, 9 rows, windows of 8 / 10 / 11 steps: 4 tiles
+// 5.2 / 5.7 / 5.7, 16 tiles (7B o_proj) 9.8 / 10.3 / 10.5, 20: 12.0 / 11.6 / 11.8, 24: 13.3 / 14.0 / 14.5, 28: 15.4 / 15.2 / 15.5, 40: 20.1 /
+// 20.1 / 20.4, 43 (7B down_proj): 22.1 / 22.3 / 21.6.  Eleven steps only for one row group and up to two column blocks.
+constexpr int mvr_other_steps(int ns) { return ns > 8 ? 8 : ns == 8 ? 7 : ns > 4 ? 4 : ns == 3 ? 2 : ns; }
+constexpr int mvr_third_steps(int ncb, int rg) { return rg == 1 && ncb <= 2 ? 11 : mvr_steps(ncb, rg); }
+static int mvr_walked(int n, int steps) { return (n + steps - 1) / steps * steps; }
+// The depth that walks a slice of n tiles in the fewest steps.
 static int mvr_depth(int n, int ncb, int rg) {
-    const int a = mvr_steps(ncb, rg), b = mvr_other_steps(a);
-    return (n + a - 1) / a * a <= (n + b - 1) / b * b ? a : b;
+    const int a = mvr_steps(ncb, rg), b = mvr_other_steps(a), c = mvr_third_steps(ncb, rg);
+    const int d = mvr_walked(n, a) <= mvr_walked(n, b) ? a : b;
+    return mvr_walked(n, c) < mvr_walked(n, d) ? c : d;
 }
-static int mvr_slots(int n, int ncb, int rg) {
-    const int d = mvr_depth(n, ncb, rg);
-    return (n + d - 1) / d * d;
+// The steps of a slice as mvr_line prices them: as its constants were fitted, with the first two depths.  For one row group and up to two
+// column blocks the price is that of eleven steps, and of eight up to 16 tiles.  us, k_mvN or more row groups / one row group in k_mvR, 6-10
+// rows: short of 16 tiles at the shallower price, 3072 x 16 row groups 7.9-8.6 / 6.4-7.4, 4096 x 16 8.7-9.4 / 7.7-8.3; beyond them at the
+// dearer one, 28672 x 256 40-43 / 47-54, 12288 x 184 17.4-19.2 / 19-23.6, 6144 x 88 11-12.4 / 10.4-12.9; 2560 x 640 12.2-12.7 / 14.3-15.
+static int mvr_line_steps(int n, int ncb, int rg) {
+    const int a = mvr_steps(ncb, rg), b = mvr_other_steps(a), c = mvr_third_steps(ncb, rg);
+    if (c != a) return n > 16 ? mvr_walked(n, c) : std::min(mvr_walked(n, c), mvr_walked(n, b));
+    return std::min(mvr_walked(n, a), mvr_walked(n, b));
 }
 
 template <int EPI, int NCB, int RG, int NS>
@@ -1196,8 +1205,12 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
     a.S = (units + n_cu - 1) / n_cu;
     a.n_wg = (units + a.S - 1) / a.S;
     a.kgroup = mv_slice_group(a, n_cu);
-    constexpr int NS = mvr_steps(NCB, RG), NS2 = mvr_other_steps(NS);
-    return mvr_depth((a.T + 7) / 8, NCB, RG) == NS ? launch_mvR_ns<EPI, NCB, RG, NS>(a, s) : launch_mvR_ns<EPI, NCB, RG, NS2>(a, s);
+    constexpr int NS = mvr_steps(NCB, RG), NS2 = mvr_other_steps(NS), NS3 = mvr_third_steps(NCB, RG);
+    switch (mvr_depth((a.T + 7) / 8, NCB, RG)) {
+        case NS: return launch_mvR_ns<EPI, NCB, RG, NS>(a, s);
+        case NS3 == NS ? -1 : NS3: return launch_mvR_ns<EPI, NCB, RG, NS3>(a, s);
+        default: return launch_mvR_ns<EPI, NCB, RG, NS2>(a, s);
+    }
 }
 
 // A line between small blocks and large ones: row groups per workgroup round for k_mvR short of it, 0 beyond.  Two things hang on
@@ -1205,7 +1218,7 @@ static hipError_t launch_mvR_t(MvArgs a, int n_cu, hipStream_t s) {
 // It is where k_mvR broke even with the kernel that k_mvN replaces, by what one compute unit had to
 // walk, in us per k tile, fitted to 709 sets of launch durations of both (rows 1-32 of both layouts, seven widths
 // from 1024 to 8192, matrices of 6 to 1300 MB).  c: column blocks, 0.4 x those computed + 0.6 x the columns' own share.
-//   k_mvR   3.7 + rounds x 8 slices x steps of a slice as walked x (weights of 1, 2 or 3 row groups + c columns of B)
+//   k_mvR   3.7 + rounds x 8 slices x steps of a slice (mvr_line_steps) x (weights of 1, 2 or 3 row groups + c columns of B)
 //   line    6.1 (+ 2.8 + 0.96 c where K is split over workgroups) + rounds x tiles (a slice's last chunk of eight, where it
 //           is partial, counts half of what it lacks) x (row groups + c columns), by the root of the share of units in use
 static int mvr_line(const MvArgs &a, int n_cu, int ncb) {
@@ -1233,7 +1246,7 @@ static int mvr_line(const MvArgs &a, int n_cu, int ncb) {
     for (int c = 1; c <= 3; ++c) {
         if (ncb > 4 && c == 2) continue;
         const int units = (a.n_rg + c - 1) / c, S = (units + n_cu - 1) / n_cu;
-        const double us = 3.68 + (double)S * 8 * mvr_slots((a.T + 7) / 8, ncb, c) * (kWeights[c - 1] + cols * kColumns[c - 1]);
+        const double us = 3.68 + (double)S * 8 * mvr_line_steps((a.T + 7) / 8, ncb, c) * (kWeights[c - 1] + cols * kColumns[c - 1]);
         if (us < best) {
             best = us;
             rg = c;

@@ -207,6 +207,25 @@ def test_projection_kernel_of_a_block(P, width):
         B.projection_path(cfg, "qkv", 33)
 
 
+# hidden size -> steps in flight of k_mvR with one row group and up to two column blocks
+_STEPS = {1024: 8, 2048: 8, 2560: 10, 4096: 8, 5120: 10, 6144: 8, 7168: 10, 8192: 8, 10240: 10, 11008: 11, 13824: 11}
+
+
+def test_steps_in_flight_follow_the_slice(P):
+    """256 row groups at nine rows: slices of 4, 8, 16, 24 and 32 tiles are walked eight steps at a time, those of 10, 20, 28 and 40
+    ten, those of 43 and 54 eleven.  And the line between k_mvR and k_mvN does not move with the
+    deepest window where slices are short: narrow matrices of 6-10 rows stay with k_mvR."""
+    from paper_2410_06916_amd import binding as B
+
+    def path(hidden, n_rg, rows):
+        cfg = B.make_config(si.ModelShape("steps", 1, hidden, 4, 4, 64, 8, 16 * n_rg, "bf16", 1e-5), 64)
+        return B.projection_path(cfg, "lmhead", rows)
+    for hidden, steps in _STEPS.items():
+        assert path(hidden, 256, 9) == f"mvR<columns 2, row groups 1, steps {steps}, rounds 1>", hidden
+    for hidden, n_rg, rows in ((3072, 16, 6), (3072, 40, 10), (3584, 16, 8), (4096, 16, 10)):
+        assert path(hidden, n_rg, rows).startswith("mvR<columns 2, row groups 1"), (hidden, n_rg, rows)
+
+
 def test_arrival_counters_cover_every_split_block_projection(P):
     """A block projection that is split in depth has an arrival counter for each of the eight wavefronts of a workgroup of six or
     eight row groups: for every matrix that is split (at 256 compute units: up to 1024 row groups) they fit the 4096 counters
