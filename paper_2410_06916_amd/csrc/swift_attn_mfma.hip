@@ -24,6 +24,7 @@
 #include <stdio.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "swift_device.h"
 #include "swift_kernels.h"
@@ -75,12 +76,13 @@ __device__ inline float am_own_score(const float *q, const uint16_t *k, int d, i
 }
 
 // Merges the own slot (score s_own, value v_own) into the prefix's (max mn, sum ls, weighted value os) and
-// normalises.  An empty prefix has mn = -inf, ls = os = 0.
+// normalises.  An empty prefix has mn = -inf, ls = os = 0.  (Of two products in a sum one is
+// rounded: which one is spelt out, here and in am_fold.  The compiler's own choice hangs on the instance, and a row's bits would.)
 __device__ inline float am_finish(float mn, float ls, float os, float s_own, float v_own) {
     const float m2 = fmaxf(mn, s_own);
     const float c1 = mn == -INFINITY ? 0.f : __expf(mn - m2);
     const float c2 = __expf(s_own - m2);
-    return (os * c1 + c2 * v_own) / (ls * c1 + c2);
+    return fmaf(c2, v_own, os * c1) / fmaf(ls, c1, c2);
 }
 
 // Folds the next range's (max m, sum l, weighted value o) into a running merge.  (A range's maximum is -inf only if its rows see
@@ -90,8 +92,13 @@ __device__ inline void am_fold(float &mn, float &ls, V &os, float m, float l, co
     const float m2 = fmaxf(mn, m);
     const float c1 = mn == -INFINITY ? 0.f : __expf(mn - m2);
     const float c2 = m == -INFINITY ? 0.f : __expf(m - m2);
-    ls = ls * c1 + l * c2;
-    os = os * c1 + o * c2;
+    ls = fmaf(ls, c1, l * c2);
+    if constexpr (std::is_same_v<V, float>) {
+        os = fmaf(os, c1, o * c2);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) os[i] = fmaf(os[i], c1, o[i] * c2);
+    }
     mn = m2;
 }
 
@@ -241,8 +248,11 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
     // ---- the rows' own slots (MERGE: any workgroup may be the one that finishes a row), requested before
     // the prefix is walked so that their latency is not paid at the end: what this wavefront's scores need (16 / NW members,
     // by whole wavefronts, lane l elements 2 l and 2 l + 1; reduced after the walk) and the value elements each thread will need
-    // in the last phase, four in a row, each as the word that holds it.
+    // in the last phase, four in a row, each as the word that holds it.  (Trees with four wavefronts have no registers for the
+    // second unit's, which are loaded when the unit is finished.  us a launch, spilling three / now, trees of 31: 64 / 8 heads of 128, 100
+    // slots 9.9 / 9.2, 2048 slots 41.2 / 40.6; 32 heads, 60 slots 10.9 / 10.6.)
     constexpr int kUnits = (16 * D / 4 + 64 * NW - 1) / (64 * NW);  // units of four elements per thread in the last phase
+    constexpr int kEarlyUnits = TREE && NW == 4 ? 1 : kUnits;
     constexpr int kScores = 16 / NW;
     float *s_own = am_sh + (size_t)NW * (16 * (MP + 2));
     const bool finishes = MERGE || sp == 0;
@@ -251,7 +261,13 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
     auto own_member = [&](int i) { return NW - 1 - wave + NW * i; };
     auto unit_member = [&](int u) { return (tid + u * 64 * NW) / (D / 4); };
     auto unit_elem = [&](int u) { return 4 * ((tid + u * 64 * NW) % (D / 4)); };
-    uint32_t v_own[kUnits][4];
+    uint32_t v_own[kEarlyUnits][4];
+    auto load_own_values = [&](int u, uint32_t(&v)[4]) {
+        const int row = min(m0 + unit_member(u), M_total - 1) >> lg_group, own = am_own_slot<TREE>(a, row);
+        const uint16_t *vp = vt + ((size_t)(own >> 3) * D + unit_elem(u)) * 8 + (own & 6);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *(const uint32_t *)(vp + 8 * i);
+    };
     float q_own[kScores][2];
     uint32_t k_own[kScores];
 #pragma unroll
@@ -269,12 +285,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
     }
     if (finishes) {
 #pragma unroll
-        for (int u = 0; u < kUnits; ++u) {
-            const int row = min(m0 + unit_member(u), M_total - 1) >> lg_group, own = am_own_slot<TREE>(a, row);
-            const uint16_t *vp = vt + ((size_t)(own >> 3) * D + unit_elem(u)) * 8 + (own & 6);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v_own[u][i] = *(const uint32_t *)(vp + 8 * i);
-        }
+        for (int u = 0; u < kEarlyUnits; ++u) load_own_values(u, v_own[u]);
     }
 
     // ---- this wavefront's chunks: every NW-th of the range, folded in order.  The keys of the next chunk are
@@ -354,9 +365,14 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
     __syncthreads();
     auto finish = [&](int u, int row, int qh, float mn, float ls, const f32x4 &os) {
         const int shift = (am_own_slot<TREE>(a, row) & 1) * 16;
+        uint32_t late[4];
+        if (u >= kEarlyUnits) load_own_values(u, late);
         f32x4 y;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y[i] = am_finish(mn, ls, os[i], s_own[unit_member(u)], am_bf((uint16_t)(v_own[u][i] >> shift)));
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t v = u < kEarlyUnits ? v_own[u < kEarlyUnits ? u : 0][i] : late[i];
+            y[i] = am_finish(mn, ls, os[i], s_own[unit_member(u)], am_bf((uint16_t)(v >> shift)));
+        }
         am_write4(a, row, qh * D + unit_elem(u), y);
     };
     const int n_split = gridDim.y;

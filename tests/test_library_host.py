@@ -137,9 +137,9 @@ def test_new_entry_points_reject_null_contexts_without_a_device(P):
     assert [L.swift_topk_width(p) for p in (0.01, 0.5, 0.51, 0.8, 0.81, 0.95, 0.96, 1.0)] == [10, 10, 5, 5, 3, 3, 1, 1]
 
 
-def test_projection_kernels_hold_their_windows_in_registers(P):
-    """The streaming kernels keep what is in flight in registers: no instance of them spills one (the compiler's own count
-    in the library's gfx950 code objects; each object is a bundle entry: count, then offset, size and name of each)."""
+def _vector_spills():
+    """Kernel name -> vector registers spilled: the compiler's own count in the library's gfx950 code objects (each object is a bundle
+    entry: count, then offset, size and name of each)."""
     import shutil
     import struct
     import subprocess
@@ -161,9 +161,23 @@ def test_projection_kernels_hold_their_windows_in_registers(P):
                 spills.update((k, int(v)) for k, v in re.findall(r"\.name:\s+(_Z\S+).*?\.vgpr_spill_count:\s+(\d+)", notes, re.S))
             p += 24 + n
         at += 24
+    return spills
+
+
+def test_projection_kernels_hold_their_windows_in_registers(P):
+    """The streaming kernels keep what is in flight in registers: no instance of them spills one."""
+    spills = _vector_spills()
     kernels = {k: v for k, v in spills.items() if "k_mvR" in k or "k_gemm" in k}
     assert len(kernels) > 100
     assert not [k for k, v in kernels.items() if v], {k: v for k, v in kernels.items() if v}
+
+
+def test_attention_kernels_hold_their_operands_in_registers(P):
+    """No instance of the matrix-core attention of decode and block rows spills a register: tree blocks with four wavefronts, the
+    fullest, load some of their own values late."""
+    kernels = {k: v for k, v in _vector_spills().items() if "k_attn_mfma" in k}
+    assert len(kernels) >= 8
+    assert not any(kernels.values()), {k: v for k, v in kernels.items() if v}
 
 
 _R = "mvR<columns %d, row groups %d"
