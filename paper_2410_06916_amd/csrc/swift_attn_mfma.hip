@@ -526,15 +526,13 @@ struct AmPlan {
 };
 AmPlan am_plan(const AttnArgs &a, int n_cu) {
     AmPlan p{};
-    // Short caches of many-headed models: workgroups of eight wavefronts, ranges of a chunk each, merged by the last workgroup of a
-    // head.  (us a launch, 32 heads of 128, cold caches; before: one workgroup per head and range, three to six chunks in a row
-    // per wavefront.  640 slots: one row 10.2 / 8.5, 9 rows 12.8 / 9.6, 31 rows 13.6 / 10.6; 1400 slots: 21.5 / 11.7, 21.3 / 11.8, 21.8 /
-    // 19.5; one range as before, with this kernel 10.2, 11.9, 12.5 and 21.0, 20.6, 21.5; ranges of 128 with four wavefronts: 14 at 9
-    // rows and 640 slots; ranges of 512: 10.8, 11.8, 12.7 and 13.6, 13.2, 14.3; merged by a launch of its own: 10.5, 11.6, 12.6 and
-    // 12.6, 12.4, 18.1.  40 heads, 1100 slots, 31 rows: 18.4 / 19.3, the one case that lost: more workgroups than units.)  Where a
-    // full block's partial results would not fit the static scratch, one range.
-    p.merge = attn_uses_head_kernel(a.max_seq, a.n_kv_heads);
-    if (p.merge) {
+    // Short caches of many-headed models: workgroups of eight wavefronts, ranges of a chunk each.  (us a launch, 32 heads of 128, cold caches;
+    // before: one workgroup per head and range, three to six chunks in a row per wavefront.  640 slots: one row 10.2 / 8.5, 9 rows
+    // 12.8 / 9.6, 31 rows 13.6 / 10.6; 1400 slots: 21.5 / 11.7, 21.3 / 11.8, 21.8 / 17.9; one range as before, with this kernel 10.2, 11.9,
+    // 12.5 and 21.0, 20.6, 21.5; ranges of 128 with four wavefronts: 14 at 9 rows and 640 slots; ranges of 512: 10.8, 11.8, 12.7 and
+    // 13.6, 13.2, 14.3.)  Where a full block's partial results would not fit the static scratch, one range.
+    const bool short_cache = attn_uses_head_kernel(a.max_seq, a.n_kv_heads);
+    if (short_cache) {
         p.nw = 8;
         p.range = 256;
         const size_t slots = (size_t)kMaxRows * a.n_q_heads * ((a.max_seq + p.range - 1) / p.range);
@@ -559,6 +557,12 @@ AmPlan am_plan(const AttnArgs &a, int n_cu) {
     }
     p.n_split = std::max(1, (p.hi_all + p.range - 1) / p.range);
     p.n_tiles = (a.rows * (a.n_q_heads / a.n_kv_heads) + 15) / 16;
+    // Short caches: the last workgroup of a head merges its ranges, unless there are more workgroups than compute units and four ranges or
+    // more: those that wait for a unit then arrive late, and a launch of its own is the faster one.  Who merges changes no bit.  us, in
+    // the launch / by one of its own: 192 workgroups (32 heads, 1400 slots, 16 rows) 12.6 / 13.3, 256 (1000 slots, 24 rows) 11.2 /
+    // 12.9, 384 (1400 slots, 31 rows) 19.5 / 17.9, 480 (40 heads, 1500 slots, 31 rows) 23.7 / 20.1; two and three ranges: 192 (640 slots, 31
+    // rows) 10.7 / 12.6, 288 (32 kv heads of two, 520 slots) 11.8 / 13.5, 384 (64 heads) 15.5 / 15.4.
+    p.merge = short_cache && (p.n_split <= 3 || a.n_kv_heads * p.n_split * p.n_tiles <= n_cu);
     return p;
 }
 
@@ -572,8 +576,9 @@ size_t attn_mfma_partial_floats(const AttnArgs &a, int n_cu) {
 
 int attn_mfma_path_name(const AttnArgs &a, int n_cu, char *out, int capacity) {
     const AmPlan p = am_plan(a, n_cu);
-    return snprintf(out, (size_t)capacity, "mfma<d %d, group %d, %d wavefronts, range %d, tiles %d%s>", a.head_dim,
-                    a.n_q_heads / a.n_kv_heads, p.nw, p.range, p.n_tiles, a.tree ? ", tree" : "");
+    return snprintf(out, (size_t)capacity, "mfma<d %d, group %d, %d wavefronts, range %d, tiles %d%s%s>", a.head_dim,
+                    a.n_q_heads / a.n_kv_heads, p.nw, p.range, p.n_tiles, a.tree ? ", tree" : "",
+                    p.nw == 8 && !p.merge ? ", merge launch" : "");
 }
 
 hipError_t launch_attn_mfma(const AttnArgs &a, int n_cu, hipStream_t s) {
@@ -607,7 +612,11 @@ hipError_t launch_attn_mfma(const AttnArgs &a, int n_cu, hipStream_t s) {
     } while (0)
 #define SWIFT_AM_D(DD)                                                                                          \
     if (p.nw == 8) {                                                                                            \
-        if (a.tree) SWIFT_AM(DD, true, 8, true); else SWIFT_AM(DD, false, 8, true);                             \
+        if (p.merge) {                                                                                          \
+            if (a.tree) SWIFT_AM(DD, true, 8, true); else SWIFT_AM(DD, false, 8, true);                         \
+        } else {                                                                                                \
+            if (a.tree) SWIFT_AM(DD, true, 8, false); else SWIFT_AM(DD, false, 8, false);                       \
+        }                                                                                                       \
     } else {                                                                                                    \
         if (a.tree) SWIFT_AM(DD, true, 4, false); else SWIFT_AM(DD, false, 4, false);                           \
     }

@@ -1309,3 +1309,55 @@ def test_rows_across_merged_attention_ranges(oracle_lib, d, q_heads, prompt):
     assert np.array_equal(lg[spine], np.stack(rows[:9]))
     g.close()
     o.close()
+
+
+_MERGED = "mfma<d %d, group %d, 8 wavefronts, range %d, tiles %d%s>"
+
+
+@pytest.mark.parametrize("d,q_heads,kv,cap,prompt,rows,paths", [
+    # five ranges of 40 heads: 200 workgroups merge them in the launch, 400 leave it to one of its own
+    (64, 40, 40, 1300, 1100, 32, {1: _MERGED % (64, 1, 256, 1, ""), 17: _MERGED % (64, 1, 256, 2, ", merge launch")}),
+    # three ranges stay in the launch, and the rows that reach the fourth do not: 32 heads of 128 in pairs
+    (128, 64, 32, 1100, 760, 32, {1: _MERGED % (128, 2, 256, 1, ""), 8: _MERGED % (128, 2, 256, 1, ""),
+                                  32: _MERGED % (128, 2, 256, 4, ", merge launch")}),
+    # all seven ranges of the largest short cache, eight query heads on a kv head
+    (64, 192, 24, 1600, 1560, 32, {1: _MERGED % (64, 8, 256, 1, ""), 4: _MERGED % (64, 8, 256, 2, ", merge launch"),
+                                   32: _MERGED % (64, 8, 256, 16, ", merge launch")}),
+    # a full block's partial results would not fit the static scratch: one range over the whole cache
+    (128, 160, 40, 1600, 700, 32, {1: _MERGED % (128, 4, 1600, 1, ""), 32: _MERGED % (128, 4, 1600, 8, "")}),
+])
+def test_short_cache_attention_of_many_heads(d, q_heads, kv, cap, prompt, rows, paths):
+    """Who merges the ranges of a short cache (the launch itself, or a launch of its own where there are more workgroups than compute
+    units) and whether there are any changes no bit of a row: blocks equal the same tokens decoded alone, also from the static
+    scratch, a tree's first candidates equal the chain.  And the logits are, within the bf16 tolerance, those of a cache past the
+    short ones, whose ranges are cut and merged otherwise."""
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape("many-heads", 1, 256, q_heads, kv, d, 256, 512, "bf16", 1e-5)
+    weights = hp.shaped_weights(shape, seed=5)
+    ids = si.uniform_ids(6, prompt, shape.vocab)
+    g = P.SwiftModel(shape, cap)
+    g.load_weights(weights)
+    first = g.prefill(ids)
+    for R, name in paths.items():
+        assert g.attn_path(R) == name, (R, g.attn_path(R))
+    n0, toks, single = g.cache_len, [g.pending], []
+    for _ in range(rows):
+        tgt, lg = g.verify([g.pending], True)
+        g.accept()
+        toks.append(int(tgt[0]))
+        single.append(lg[0].copy())
+    single = np.stack(single)
+    for R in (2, 8, 17, rows):
+        for call in (g.verify, g.verify_static):
+            g.rollback(n0, toks[0])
+            assert np.array_equal(call(toks[:R], True)[1], single[:R]), R
+    g.rollback(n0, toks[0])
+    levels = [np.array([t, (t + 1) % shape.vocab, (t + 2) % shape.vocab], np.int32) for t in toks[1:11]]
+    spine = [0] + [1 + 3 * i for i in range(10)]
+    assert np.array_equal(g.verify_tree(levels, True)[1][spine], single[:11])
+    g.close()
+    long = P.SwiftModel(shape, 1700)
+    long.load_weights(weights)
+    assert long.prefill(ids) == first and "4 wavefronts" in long.attn_path(1)
+    assert np.all(hp.rel_err_rowmax(single, long.verify(toks[:rows], True)[1]) <= TOL["bf16"])
+    long.close()
