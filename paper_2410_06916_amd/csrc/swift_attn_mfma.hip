@@ -130,6 +130,9 @@ __device__ inline void am_write4(const AttnArgs &a, int row, int e, const f32x4 
     }
 }
 
+// Who merges a row's ranges: a launch of its own; the workgroup that arrives last; the one workgroup that walks them all.
+enum AmMerge : int { kOwnLaunch, kLastWorkgroup, kSerial };
+
 // Lane layout of v_mfma_f32_16x16x32_bf16 (C = A B): lane = 16 g + col.
 //   A (16 x 32): row col,    k = 8 g .. 8 g + 7        B (32 x 16): column col, k = 8 g .. 8 g + 7
 //   C (16 x 16): column col, rows 4 g .. 4 g + 3
@@ -137,13 +140,14 @@ __device__ inline void am_write4(const AttnArgs &a, int row, int e, const f32x4 
 // that a lane's eight probabilities are slots 8 g .. 8 g + 7: the k range of its B operand in O^T = V^T P^T.
 //
 // Workgroup (kv head, cache range sp, member tile z), NW wavefronts.  range: slots per workgroup, a multiple of 32.  hi_all: end of the
-// longest prefix of the block.  lg_group: log2 of the query heads per kv head.  MERGE: rows whose prefix spans several ranges are
-// finished in this launch, by the workgroup that arrives last at their (kv head, member tile); else by k_attn_mfma_combine.
+// longest prefix of the block.  lg_group: log2 of the query heads per kv head.  MERGE: who finishes the rows whose prefix spans several
+// ranges: k_attn_mfma_combine, the workgroup that arrives last at their (kv head, member tile), or the only one there is (range: the
+// whole cache; the ranges in which it walks it, a chunk per wavefront, are those of kLastWorkgroup).
 //
 // What bounds it at short contexts: a chain of latencies (launch, first loads, chunks, merge).  So the arguments of the first loads
 // are the kernel's leading ones, which are in registers at its start, and nothing on the way to the first product waits for a load
 // that is not part of it (100 slots, one row: 5.8 us, 4.5 without such waits and with the wavefronts' results read all at once).
-template <int D, bool TREE, int NW, bool MERGE>
+template <int D, bool TREE, int NW, AmMerge MERGE>
 __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache, const uint16_t *vcache, const uint16_t *q_s, int max_seq,
                                                           int nb32, int range, int hi_all, int rows, int lg_group, AttnArgs a) {
     constexpr int DC = D / 32;      // k steps of a score tile
@@ -254,8 +258,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
     constexpr int kUnits = (16 * D / 4 + 64 * NW - 1) / (64 * NW);  // units of four elements per thread in the last phase
     constexpr int kEarlyUnits = TREE && NW == 4 ? 1 : kUnits;
     constexpr int kScores = 16 / NW;
-    float *s_own = am_sh + (size_t)NW * (16 * (MP + 2));
-    const bool finishes = MERGE || sp == 0;
+    constexpr int kArea = NW * 16 * (MP + 2);  // floats of the merge area; kSerial uses two in turn
+    float *s_own = am_sh + (MERGE == kSerial ? 2 : 1) * kArea;
+    const bool finishes = MERGE != kOwnLaunch || sp == 0;
     const int n_here = finishes ? min(16, M_total - m0) : 0;  // members that may be finished here
     // (member of score i: the last wavefronts have the fewest chunks to walk)
     auto own_member = [&](int i) { return NW - 1 - wave + NW * i; };
@@ -339,30 +344,51 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
         }
         if (more) load_values(c + NW, vA);
     };
-    for (; c < c_end; c += 2 * NW) {
-        step(c, kA, kB);
-        if (c + NW < c_end) step(c + NW, kB, kA);
-    }
-
-    // ---- merge the wavefronts (in wavefront order), then finish the rows whose prefix ends in the first
-    // range with their own slot, or leave the range's partial result
-    l_run = column_reduce(l_run, [](float x, float y) { return x + y; });
+    // ---- merge the wavefronts (in wavefront order): every wavefront parks its (max, sum, weighted values) of a range in LDS ..
+    int area = 0;
+    auto park = [&]() {
+        float *wbase = am_sh + area + wave * (16 * (MP + 2));
+        l_run = column_reduce(l_run, [](float x, float y) { return x + y; });
+        if (g == 0) {
+            wbase[col] = m_run;
+            wbase[16 + col] = l_run;
+        }
 #pragma unroll
-    for (int i = 0; i < kScores; ++i) {
-        const int mm = own_member(i);
-        if (mm >= n_here) continue;  // (wavefront-uniform)
-        const float sc = fmaf(q_own[i][1], am_bf((uint16_t)(k_own[i] >> 16)), fmaf(q_own[i][0], am_bf((uint16_t)k_own[i]), 0.f));
-        const float sum = wave_sum(sc) * scale;
-        if (lane == 0) s_own[mm] = sum;
-    }
-    float *wbase = am_sh + (size_t)wave * (16 * (MP + 2));
-    if (g == 0) {
-        wbase[col] = m_run;
-        wbase[16 + col] = l_run;
-    }
+        for (int dt = 0; dt < DT; ++dt) *(f32x4 *)(wbase + 32 + col * MP + 16 * dt + 4 * g) = o[dt];
+    };
+    // .. and a thread takes four elements of a member: the wavefronts' weights are worked out once for them
+    auto merged = [&](int mm, int dd, float &mn, float &ls, f32x4 &os) {
+        float mw[NW], lw[NW];
+        f32x4 ow[NW];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) *(f32x4 *)(wbase + 32 + col * MP + 16 * dt + 4 * g) = o[dt];
-    __syncthreads();
+        for (int w = 0; w < NW; ++w) {
+            const float *wb = am_sh + area + w * (16 * (MP + 2));
+            mw[w] = wb[mm];
+            lw[w] = wb[16 + mm];
+            ow[w] = *(const f32x4 *)(wb + 32 + mm * MP + dd);
+        }
+        mn = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mn = fmaxf(mn, mw[w]);
+        ls = 0.f;
+        os = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float cw = mw[w] == -INFINITY ? 0.f : __expf(mw[w] - mn);
+            ls += lw[w] * cw;
+            os += ow[w] * cw;
+        }
+    };
+    auto own_scores = [&]() {
+#pragma unroll
+        for (int i = 0; i < kScores; ++i) {
+            const int mm = own_member(i);
+            if (mm >= n_here) continue;  // (wavefront-uniform)
+            const float sc = fmaf(q_own[i][1], am_bf((uint16_t)(k_own[i] >> 16)), fmaf(q_own[i][0], am_bf((uint16_t)k_own[i]), 0.f));
+            const float sum = wave_sum(sc) * scale;
+            if (lane == 0) s_own[mm] = sum;
+        }
+    };
     auto finish = [&](int u, int row, int qh, float mn, float ls, const f32x4 &os) {
         const int shift = (am_own_slot<TREE>(a, row) & 1) * 16;
         uint32_t late[4];
@@ -375,10 +401,63 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
         }
         am_write4(a, row, qh * D + unit_elem(u), y);
     };
+    if constexpr (MERGE == kSerial) {
+        // ---- one range after the other, a chunk of each per wavefront, folded in range order as they come.  The next range's chunk is on
+        // its way while a range is merged: one barrier a range, which orders LDS only, and two merge areas in turn.
+        float r_mn[kUnits], r_ls[kUnits];
+        f32x4 r_os[kUnits];
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            r_mn[u] = -INFINITY;
+            r_ls[u] = 0.f;
+            r_os[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        own_scores();
+        auto one = [&](int sp, const u32x4(&kCur)[2][DC], u32x4(&kNxt)[2][DC]) {
+            m_run = -INFINITY;
+            l_run = 0.f;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (c < c_end) step(c, kCur, kNxt);
+            c += NW;
+            park();
+            lds_barrier();
+#pragma unroll
+            for (int u = 0; u < kUnits; ++u) {
+                const int mm = unit_member(u), m = m0 + mm;
+                if (mm >= 16 || m >= M_total) continue;
+                if (sp * 32 * NW >= am_prefix_end<TREE>(a, m >> lg_group)) continue;  // the row's prefix does not reach this range
+                float mn, ls;
+                f32x4 os;
+                merged(mm, unit_elem(u), mn, ls, os);
+                am_fold(r_mn[u], r_ls[u], r_os[u], mn, ls, os);
+            }
+            area = kArea - area;
+        };
+        const int n = (hi_all + 32 * NW - 1) / (32 * NW);  // ranges
+        for (int sp = 0; sp < n; sp += 2) {
+            one(sp, kA, kB);
+            if (sp + 1 < n) one(sp + 1, kB, kA);
+        }
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            const int mm = unit_member(u), m = m0 + mm;
+            if (mm >= 16 || m >= M_total) continue;
+            finish(u, m >> lg_group, kvh * group + (m & (group - 1)), r_mn[u], r_ls[u], r_os[u]);
+        }
+        return;
+    }
+    for (; c < c_end; c += 2 * NW) {
+        step(c, kA, kB);
+        if (c + NW < c_end) step(c + NW, kB, kA);
+    }
+    // ---- then finish the rows whose prefix ends in the first range with their own slot, or leave the range's partial result
+    park();
+    own_scores();
+    __syncthreads();
     const int n_split = gridDim.y;
     const __amdgpu_buffer_rsrc_t part_o = __builtin_amdgcn_make_buffer_rsrc(a.part_o, 0, 0x7fffffff, 0x00020000);
     const __amdgpu_buffer_rsrc_t part_ml = __builtin_amdgcn_make_buffer_rsrc(a.part_ml, 0, 0x7fffffff, 0x00020000);
-    // (a thread takes four elements of a member: the wavefronts' weights are worked out once for them)
 #pragma unroll
     for (int u = 0; u < kUnits; ++u) {
         const int mm = unit_member(u), dd = unit_elem(u), m = m0 + mm;
@@ -387,30 +466,14 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
         const int pe = am_prefix_end<TREE>(a, row);
         const int nsr = (pe + range - 1) / range;  // ranges the row's prefix reaches (0: an empty prefix)
         if (sp >= max(nsr, 1)) continue;
-        float mw[NW], lw[NW], mn = -INFINITY;
-        f32x4 ow[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float *wb = am_sh + (size_t)w * (16 * (MP + 2));
-            mw[w] = wb[mm];
-            lw[w] = wb[16 + mm];
-            ow[w] = *(const f32x4 *)(wb + 32 + mm * MP + dd);
-        }
-#pragma unroll
-        for (int w = 0; w < NW; ++w) mn = fmaxf(mn, mw[w]);
-        float ls = 0.f;
-        f32x4 os = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float cw = mw[w] == -INFINITY ? 0.f : __expf(mw[w] - mn);
-            ls += lw[w] * cw;
-            os += ow[w] * cw;
-        }
+        float mn, ls;
+        f32x4 os;
+        merged(mm, dd, mn, ls, os);
         if (nsr <= 1) {
             finish(u, row, qh, mn, ls, os);
         } else {
             const size_t slot = ((size_t)row * nq + qh) * n_split + sp;
-            if constexpr (MERGE) {
+            if constexpr (MERGE == kLastWorkgroup) {
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, os), part_o, (uint32_t)((slot * D + dd) * 4), 0, kDeviceScope);
                 if (dd == 0)
                     __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(mn), __float_as_uint(ls)}, part_ml, (uint32_t)(slot * 8), 0,
@@ -424,7 +487,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_attn_mfma(const uint16_t *kcache
             }
         }
     }
-    if constexpr (MERGE) {
+    if constexpr (MERGE == kLastWorkgroup) {
         if (n_split == 1) return;
         // ---- the workgroup that arrives last merges the ranges, in range order.  Partial results are stored and loaded at device
         // scope (written through, read past this die's L2): once a workgroup's stores are acknowledged, a relaxed count
@@ -522,7 +585,7 @@ struct AmPlan {
     int hi_all;    // end of the longest prefix of the block
     int n_split;   // ranges that prefix reaches
     int n_tiles;   // member tiles (16 members each) = workgroups per (kv head, range)
-    bool merge;    // the ranges are merged in the same launch
+    AmMerge merge;
 };
 AmPlan am_plan(const AttnArgs &a, int n_cu) {
     AmPlan p{};
@@ -557,12 +620,23 @@ AmPlan am_plan(const AttnArgs &a, int n_cu) {
     }
     p.n_split = std::max(1, (p.hi_all + p.range - 1) / p.range);
     p.n_tiles = (a.rows * (a.n_q_heads / a.n_kv_heads) + 15) / 16;
-    // Short caches: the last workgroup of a head merges its ranges, unless there are more workgroups than compute units and four ranges or
-    // more: those that wait for a unit then arrive late, and a launch of its own is the faster one.  Who merges changes no bit.  us, in
-    // the launch / by one of its own: 192 workgroups (32 heads, 1400 slots, 16 rows) 12.6 / 13.3, 256 (1000 slots, 24 rows) 11.2 /
-    // 12.9, 384 (1400 slots, 31 rows) 19.5 / 17.9, 480 (40 heads, 1500 slots, 31 rows) 23.7 / 20.1; two and three ranges: 192 (640 slots, 31
-    // rows) 10.7 / 12.6, 288 (32 kv heads of two, 520 slots) 11.8 / 13.5, 384 (64 heads) 15.5 / 15.4.
-    p.merge = short_cache && (p.n_split <= 3 || a.n_kv_heads * p.n_split * p.n_tiles <= n_cu);
+    // Who merges the ranges of a short cache changes no bit.  Up to a workgroup per compute unit: the last one of a head.  Beyond, those that
+    // wait for a unit arrive late; with enough heads and tiles to occupy the units by themselves (three eighths of them) a
+    // workgroup each walks all of its ranges, with fewer a launch of its own merges four ranges and more.  us, last workgroup / own launch /
+    // one for all: 192 workgroups (32 heads, 1400 slots, 16 rows) 12.6 / 13.3 / -, 256 (1000 slots, 24 rows) 11.2 / 12.9 / -; 64 heads x
+    // tiles, 384 (1400 slots, 31 rows) 19.5 / 17.9 / 24.5; 80, 400 (40 heads, 1100 slots) 19.0 / 18.1 / 21.2, 240 (700 slots) 11.1 / 12.7 / -;
+    // 96, 288 and 480 (64 / 32 heads, 500 and 1100 slots, 24 rows) 11.7 / 13.5 / 12.4 and 19.2 / 19.7 / 19.7; 104, 416 (52 heads, 800 slots, 31
+    // rows) - / 18.9 / 16.9; 128, 640 (64 heads, 1100 slots) 28.4 / 25.2 / 21.2; 256, 768 (128 / 32 heads, 600 slots) 27.4 / - / 14.2, 1280
+    // (1100 slots) 44 / 39.4 / 20.2.
+    const int groups = a.n_kv_heads * p.n_tiles;
+    if (!short_cache)
+        p.merge = kOwnLaunch;
+    else if (p.n_split == 1 || groups * p.n_split <= n_cu)
+        p.merge = kLastWorkgroup;
+    else if (8 * groups >= 3 * n_cu)
+        p.merge = kSerial;
+    else
+        p.merge = p.n_split <= 3 ? kLastWorkgroup : kOwnLaunch;
     return p;
 }
 
@@ -578,7 +652,7 @@ int attn_mfma_path_name(const AttnArgs &a, int n_cu, char *out, int capacity) {
     const AmPlan p = am_plan(a, n_cu);
     return snprintf(out, (size_t)capacity, "mfma<d %d, group %d, %d wavefronts, range %d, tiles %d%s%s>", a.head_dim,
                     a.n_q_heads / a.n_kv_heads, p.nw, p.range, p.n_tiles, a.tree ? ", tree" : "",
-                    p.nw == 8 && !p.merge ? ", merge launch" : "");
+                    p.nw != 8 || p.merge == kLastWorkgroup ? "" : p.merge == kSerial ? ", serial" : ", merge launch");
 }
 
 hipError_t launch_attn_mfma(const AttnArgs &a, int n_cu, hipStream_t s) {
@@ -592,33 +666,34 @@ hipError_t launch_attn_mfma(const AttnArgs &a, int n_cu, hipStream_t s) {
     const AmPlan p = am_plan(a, n_cu);
     const int group = a.n_q_heads / a.n_kv_heads;
     if (p.n_split > a.max_split || (group & (group - 1)) != 0 ||
-        (p.merge && p.n_split > 1 && (!a.counters || a.n_kv_heads * p.n_tiles > kMvCounters)))
+        (p.merge == kLastWorkgroup && p.n_split > 1 && (!a.counters || a.n_kv_heads * p.n_tiles > kMvCounters)))
         return hipErrorInvalidValue;
     const int D = a.head_dim;
-    const size_t lds = ((size_t)p.nw * 16 * (D + kAmPad + 2) + 16) * sizeof(float);
-    const dim3 grid(a.n_kv_heads, p.n_split, p.n_tiles), block(64 * p.nw);
+    const size_t lds = ((size_t)(p.merge == kSerial ? 2 : 1) * p.nw * 16 * (D + kAmPad + 2) + 16) * sizeof(float);
+    const dim3 grid(a.n_kv_heads, p.merge == kSerial ? 1 : p.n_split, p.n_tiles), block(64 * p.nw);
+    const int range = p.merge == kSerial ? (a.max_seq + 31) / 32 * 32 : p.range;
     const int lg_group = __builtin_ctz(a.n_q_heads / a.n_kv_heads);
 #define SWIFT_AM(DD, TR, WV, MG)                                                                                \
     do {                                                                                                        \
         static bool attr_set = false;                                                                           \
         if (!attr_set) {                                                                                        \
             hipError_t e = hipFuncSetAttribute((const void *)k_attn_mfma<DD, TR, WV, MG>,                       \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);          \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);         \
             if (e != hipSuccess) return e;                                                                      \
             attr_set = true;                                                                                    \
         }                                                                                                       \
         hipLaunchKernelGGL((k_attn_mfma<DD, TR, WV, MG>), grid, block, lds, s, (const uint16_t *)a.kcache,      \
-                           (const uint16_t *)a.vcache, a.q_s, a.max_seq, a.nb32, p.range, p.hi_all, a.rows, lg_group, a); \
+                           (const uint16_t *)a.vcache, a.q_s, a.max_seq, a.nb32, range, p.hi_all, a.rows, lg_group, a); \
     } while (0)
 #define SWIFT_AM_D(DD)                                                                                          \
-    if (p.nw == 8) {                                                                                            \
-        if (p.merge) {                                                                                          \
-            if (a.tree) SWIFT_AM(DD, true, 8, true); else SWIFT_AM(DD, false, 8, true);                         \
-        } else {                                                                                                \
-            if (a.tree) SWIFT_AM(DD, true, 8, false); else SWIFT_AM(DD, false, 8, false);                       \
-        }                                                                                                       \
+    if (p.merge == kLastWorkgroup) {                                                                            \
+        if (a.tree) SWIFT_AM(DD, true, 8, kLastWorkgroup); else SWIFT_AM(DD, false, 8, kLastWorkgroup);         \
+    } else if (p.merge == kSerial) {                                                                            \
+        if (a.tree) SWIFT_AM(DD, true, 8, kSerial); else SWIFT_AM(DD, false, 8, kSerial);                       \
+    } else if (p.nw == 8) {                                                                                     \
+        if (a.tree) SWIFT_AM(DD, true, 8, kOwnLaunch); else SWIFT_AM(DD, false, 8, kOwnLaunch);                 \
     } else {                                                                                                    \
-        if (a.tree) SWIFT_AM(DD, true, 4, false); else SWIFT_AM(DD, false, 4, false);                           \
+        if (a.tree) SWIFT_AM(DD, true, 4, kOwnLaunch); else SWIFT_AM(DD, false, 4, kOwnLaunch);                 \
     }
     if (D == 128) {
         SWIFT_AM_D(128)
@@ -628,7 +703,7 @@ hipError_t launch_attn_mfma(const AttnArgs &a, int n_cu, hipStream_t s) {
 #undef SWIFT_AM_D
 #undef SWIFT_AM
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.n_split == 1 || p.merge) return e;
+    if (e != hipSuccess || p.n_split == 1 || p.merge != kOwnLaunch) return e;
     const dim3 cgrid(a.n_q_heads, a.rows);
     if (a.tree)
         hipLaunchKernelGGL(k_attn_mfma_combine<true>, cgrid, dim3(128), 0, s, a, p.range, p.n_split);

@@ -1317,18 +1317,18 @@ _MERGED = "mfma<d %d, group %d, 8 wavefronts, range %d, tiles %d%s>"
 @pytest.mark.parametrize("d,q_heads,kv,cap,prompt,rows,paths", [
     # five ranges of 40 heads: 200 workgroups merge them in the launch, 400 leave it to one of its own
     (64, 40, 40, 1300, 1100, 32, {1: _MERGED % (64, 1, 256, 1, ""), 17: _MERGED % (64, 1, 256, 2, ", merge launch")}),
-    # three ranges stay in the launch, and the rows that reach the fourth do not: 32 heads of 128 in pairs
+    # four tiles of 32 heads: a workgroup each walks all ranges of its rows, some of which reach the fourth
     (128, 64, 32, 1100, 760, 32, {1: _MERGED % (128, 2, 256, 1, ""), 8: _MERGED % (128, 2, 256, 1, ""),
-                                  32: _MERGED % (128, 2, 256, 4, ", merge launch")}),
+                                  32: _MERGED % (128, 2, 256, 4, ", serial")}),
     # all seven ranges of the largest short cache, eight query heads on a kv head
     (64, 192, 24, 1600, 1560, 32, {1: _MERGED % (64, 8, 256, 1, ""), 4: _MERGED % (64, 8, 256, 2, ", merge launch"),
-                                   32: _MERGED % (64, 8, 256, 16, ", merge launch")}),
+                                   32: _MERGED % (64, 8, 256, 16, ", serial")}),
     # a full block's partial results would not fit the static scratch: one range over the whole cache
     (128, 160, 40, 1600, 700, 32, {1: _MERGED % (128, 4, 1600, 1, ""), 32: _MERGED % (128, 4, 1600, 8, "")}),
 ])
 def test_short_cache_attention_of_many_heads(d, q_heads, kv, cap, prompt, rows, paths):
-    """Who merges the ranges of a short cache (the launch itself, or a launch of its own where there are more workgroups than compute
-    units) and whether there are any changes no bit of a row: blocks equal the same tokens decoded alone, also from the static
+    """Who merges the ranges of a short cache (the last workgroup of a head, a launch of its own, or the one workgroup that walks them
+    all) and whether there are any changes no bit of a row: blocks equal the same tokens decoded alone, also from the static
     scratch, a tree's first candidates equal the chain.  And the logits are, within the bf16 tolerance, those of a cache past the
     short ones, whose ranges are cut and merged otherwise."""
     import paper_2410_06916_amd as P
