@@ -415,8 +415,8 @@ __global__ __launch_bounds__(512, 4) void k_mv1(const unsigned char *Wt, const u
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 
         const int nb16 = (n + NS - 1) / NS;
-        // (As compiled, the NS reloads of a block go out together behind its last MFMA.  Pinning each
-        // reload behind the MFMA that frees its slot with scheduling barriers measured the same.)
+        // (As compiled, a few reloads of a block follow the MFMA that frees their slot and half of them go out behind the last one.  Pinning
+        // each behind its MFMA with scheduling barriers measured the same.)
         for (int b = 0; b + 1 < nb16; ++b) {
 #pragma unroll
             for (int u = 0; u < NS; ++u) {
@@ -426,10 +426,15 @@ __global__ __launch_bounds__(512, 4) void k_mv1(const unsigned char *Wt, const u
         }
         if (!kLast) {
             // the window rolls on into the next round's row group: the stream never drains
+            // (The last block's addresses are the same in every round.  Kept in registers from round to round, two a slot, they spilled up
+            // to eight, whose reloads waited for the window: LM head of depth 3840 43.3 us, 37.8 with the block's number opaque and no
+            // register spilled in any instance; depth 7680 83.3 / 72.2, q|k|v of 960 row groups of depth 8192 42.2 / 40.9.)
+            int last_block = (nb16 - 1) * NS;
+            asm volatile("" : "+s"(last_block));
             set_slice(seg + 1);
 #pragma unroll
             for (int u = 0; u < NS; ++u) {
-                mma_slot((nb16 - 1) * NS + u, buf[u], acc, live_mask);
+                mma_slot(last_block + u, buf[u], acc, live_mask);
                 buf[u] = load_slot(u);
             }
         } else {

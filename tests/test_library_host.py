@@ -170,6 +170,9 @@ def test_projection_kernels_hold_their_windows_in_registers(P):
     kernels = {k: v for k, v in spills.items() if "k_mvR" in k or "k_gemm" in k}
     assert len(kernels) > 100
     assert not [k for k, v in kernels.items() if v], {k: v for k, v in kernels.items() if v}
+    kernels = {k: v for k, v in spills.items() if "k_mv1" in k or "k_mvN" in k}
+    assert len(kernels) > 50
+    assert not any(kernels.values()), {k: v for k, v in kernels.items() if v}
 
 
 def test_attention_kernels_hold_their_operands_in_registers(P):
