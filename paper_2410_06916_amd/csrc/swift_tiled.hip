@@ -526,22 +526,23 @@ static hipError_t launch_mv1_t(const MvArgs &a, int grid, size_t lds, hipStream_
                               (const unsigned char *)a.in_s, a.T, a.K, a.R, a.n_rg, a.n_wg, a.S, a);
 }
 
-static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int wg_override, hipStream_t s) {
-    const size_t lds = mv1_lds_bytes(a.K, a.R, a.head_dim);
-    if (lds > kMvMaxLds) return hipErrorInvalidValue;
-    // Work split: KS wavefronts per row group, W workgroups, S rounds, chosen so that every
-    // workgroup gets the same number of row groups (a weight stream is only as fast as its
-    // slowest wavefront) with at most 16 wavefronts per compute unit.
-    int occ = (int)((160 * 1024) / (lds + 512));
-    if (occ > 2) occ = 2;
-    if (occ < 1) occ = 1;
-    const int max_wg = n_cu * occ;
-    int best_ks = 8, best_w = 1, best_s = 1;
-    double best_score = 1e30;
+// Workgroups of k_mv1 that share a compute unit, by all that a launch asks for.  (Two planned where one fits make two uneven rounds: gate/up of 384
+// row groups, depth 12576, one row 31.3 us against 26.6; 512, depth 5984, two rows 20.7 against 18.1.)
+static int mv1_per_unit(size_t lds) { return std::max(1, std::min(2, (int)((160 * 1024) / (lds + kMv1MoreLds)))); }
+// Work split: KS wavefronts per row group, W workgroups, S rounds, chosen so that every
+// workgroup gets the same number of row groups (a weight stream is only as fast as its
+// slowest wavefront) with at most 16 wavefronts per compute unit.
+struct Mv1Plan {
+    int ks, W, S;
+};
+static Mv1Plan mv1_plan(const MvArgs &a, int n_cu, int ks_override, int wg_override) {
+    const int max_wg = n_cu * mv1_per_unit(mv1_lds_bytes(a.K, a.R, a.head_dim));
     // Always 8 K slices per row group (unless a tuning run overrides it): the slice boundaries and
     // the order in which slice sums are added define a row's result bit for bit, and the block kernel
     // for 6-16 rows uses the same ones, so that a token's logits do not depend on how many rows
     // share its pass (speculative output == plain greedy output exactly, not just up to rounding).
+    Mv1Plan p{8, 1, 1};
+    double best_score = 1e30;
     for (int ks = 8; ks >= 1; ks /= 2) {
         if (ks != (ks_override ? ks_override : 8)) continue;
         const int G = 8 / ks;
@@ -553,20 +554,25 @@ static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int w
             const double score = waste + (fill < 0.5 ? (0.5 - fill) : 0.0) + 0.002 * S + 0.01 * (8 / ks - 1);
             if (score < best_score) {
                 best_score = score;
-                best_ks = ks;
-                best_w = W;
-                best_s = S;
+                p = Mv1Plan{ks, W, S};
             }
         }
     }
     if (wg_override > 0) {
-        const int G = 8 / best_ks;
-        best_w = wg_override;
-        best_s = (a.n_rg + G * best_w - 1) / (G * best_w);
+        const int G = 8 / p.ks;
+        p.W = wg_override;
+        p.S = (a.n_rg + G * p.W - 1) / (G * p.W);
     }
-    a.S = best_s;
-    a.n_wg = best_w;
-    const int grid = best_w;
+    return p;
+}
+
+static hipError_t launch_mv1(int epi, MvArgs a, int n_cu, int ks_override, int wg_override, hipStream_t s) {
+    const size_t lds = mv1_lds_bytes(a.K, a.R, a.head_dim);
+    if (lds > kMvMaxLds) return hipErrorInvalidValue;
+    const Mv1Plan p = mv1_plan(a, n_cu, ks_override, wg_override);
+    const int best_ks = p.ks, grid = p.W;
+    a.S = p.S;
+    a.n_wg = p.W;
     a.kgroup = best_ks == 8 ? mv_slice_group(a, n_cu) : best_ks;
     // Slots per block of the load window (= loads in flight per wavefront): 16 unless another depth
     // cuts a slice of n tiles with fewer wasted slots (n = 43: 3 x 15 instead of 3 x 16; n = 20:
@@ -1300,7 +1306,10 @@ static bool mv_takes_mv1(const MvArgs &a, int n_cu, int ks_override) {
 static int mv_column_blocks(const MvArgs &a) { return (block_terms(a.RL) * layout_rows(a.RL) + 15) / 16; }
 
 int mv_path_name(const MvArgs &a, int n_cu, char *out, int capacity) {
-    if (mv_takes_mv1(a, n_cu, 0)) return snprintf(out, (size_t)capacity, "mv1<rows %d>", a.R);
+    if (mv_takes_mv1(a, n_cu, 0)) {
+        const Mv1Plan p = mv1_plan(a, n_cu, 0, 0);
+        return snprintf(out, (size_t)capacity, "mv1<rows %d, workgroups %d, rounds %d>", a.R, p.W, p.S);
+    }
     const int ncb = mv_column_blocks(a), rg = mvr_row_groups(a, n_cu, ncb);
     if (rg == 0) return snprintf(out, (size_t)capacity, "mvN<columns %d, parts %d>", ncb, mvn_plan(a, n_cu, mvn_canon(a, n_cu, ncb)).ksp);
     const int units = (a.n_rg + rg - 1) / rg;

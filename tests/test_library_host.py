@@ -243,6 +243,20 @@ def test_steps_in_flight_follow_the_slice(P):
         assert path(hidden, n_rg, rows).startswith("mvR<columns 2, row groups 1"), (hidden, n_rg, rows)
 
 
+def test_rounds_of_the_single_pass_kernel_are_resident(P):
+    """k_mv1's workgroups of a round all run at once: two to a compute unit while the LDS that a launch asks for allows it, else one.  Per row
+    count: the last depth of which two fit, and the next two, whose plan has to reckon with all that a launch asks for."""
+    from paper_2410_06916_amd import binding as B
+    for rows, fits in ((1, 12544), (2, 5952), (3, 3776)):
+        for hidden, per_unit in ((fits, 2), (fits + 32, 1), (fits + 64, 1)):
+            for n_rg in (384, 512, 1024):
+                cfg = B.make_config(si.ModelShape("resident", 1, hidden, 4, 4, 128, 8, 16 * n_rg, "bf16", 1e-5), 64)
+                name = B.projection_path(cfg, "lmhead", rows)
+                m = re.fullmatch(r"mv1<rows (\d), workgroups (\d+), rounds (\d+)>", name)
+                assert m, name
+                assert int(m[2]) <= 256 * per_unit and (per_unit == 1 or int(m[2]) > 256), (rows, hidden, n_rg, name)
+
+
 def test_arrival_counters_cover_every_split_block_projection(P):
     """A block projection that is split in depth has an arrival counter for each of the eight wavefronts of a workgroup of six or
     eight row groups: for every matrix that is split (at 256 compute units: up to 1024 row groups) they fit the 4096 counters
