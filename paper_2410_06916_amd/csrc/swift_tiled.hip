@@ -1291,17 +1291,22 @@ static bool mv_fits_mv1(const MvArgs &a) {
     return !(a.RL & kBulkLayout) && a.R <= kMvSmallRows && mv1_lds_bytes(a.K, a.R, a.head_dim) <= kMvMaxLds;
 }
 // .. take the single-pass kernel, but for two kinds of matrices where k_mvR is faster, in rounds of three row groups per compute
-// unit: those that it covers in one such round and k_mv1 in an uneven one and a half or two (513..768 row groups on 256 units; us,
-// k_mv1 / k_mvR, one row: depth 4096, 520 row groups 18.5 / 14.4, 768 (7B q|k|v) 19.7 / 18.8; depth 2048, 640: 11.0 / 9.9; depth
-// 8192, 640 (70B q|k|v) 33.8 / 28.7; next to them 384: 12.4 / 12.6, 896: 21.0 / 22.7), and deep ones (from 8192 on) whose rounds of three are
-// nine tenths full (depth 8192, 3584 row groups (70B gate/up) 143.6 / 136.7, 1536: 64.1 / 62.2; 2560, five sixths full, 103.6 /
-// 114.3).  The bits are the same either way.
+// unit.  (All figures: us, k_mv1 / k_mvR; gate/up, the others within 3 % of its ratios.)
+//  * 513..768 row groups on 256 units, which it covers in one such round and k_mv1 in an uneven one and a half or two.  One row: depth
+//    2048, 640 row groups 11.3 / 9.9; 4096, 520: 18.2 / 15.2, 768: 19.5 / 19.0; 5120, 768: 22.6 / 22.8; 8192, 640: 33.3 / 28.6; next to them
+//    4096, 896: 20.9 / 22.7.  Where the activation leaves k_mv1 one workgroup a unit its rounds are even enough: three rows at depth
+//    5120, 576: 17.6 / 18.9, 704: 20.5 / 21.4; 6144, 576: 20.2 / 21.8, 768: 25.6 / 26.0; two at 7168, 576: 22.7 / 24.3.  Not so at the depths that
+//    k_mvR walks in full windows of eight: three rows at 4096, 544: 16.0 / 15.0, 768: 19.4 / 18.8; two at 8192, 544: 26.7 / 25.9, 768: 34.3 / 33.4.
+//  * deep ones (8192 to 10240) whose rounds of three are nine tenths full: one row, 8192, 1536: 63.3 / 62.3, 3584: 140.8 / 136.1, two rows
+//    145.8 / 135.7; 10240, 3584: 170.3 / 169.0; 12288, 1536: 89.5 / 91.8, 2304: 130.7 / 133.2.
+// The bits are the same either way.
 static bool mv_takes_mv1(const MvArgs &a, int n_cu, int ks_override) {
     if (!mv_fits_mv1(a) || ks_override == 16) return false;
     if (ks_override != 0) return true;
     const int per_round = 3 * n_cu, rounds = (a.n_rg + per_round - 1) / per_round;
-    if (a.n_rg > 2 * n_cu && rounds == 1) return false;
-    return !(a.T >= 256 && a.n_rg > per_round && 10 * a.n_rg >= 9 * rounds * per_round);
+    if (a.n_rg > 2 * n_cu && rounds == 1)
+        return a.T > 128 && a.T < 256 && mv1_per_unit(mv1_lds_bytes(a.K, a.R, a.head_dim)) == 1;
+    return !(a.T >= 256 && a.T <= 320 && a.n_rg > per_round && 10 * a.n_rg >= 9 * rounds * per_round);
 }
 static int mv_column_blocks(const MvArgs &a) { return (block_terms(a.RL) * layout_rows(a.RL) + 15) / 16; }
 

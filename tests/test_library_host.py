@@ -257,6 +257,18 @@ def test_rounds_of_the_single_pass_kernel_are_resident(P):
                 assert int(m[2]) <= 256 * per_unit and (per_unit == 1 or int(m[2]) > 256), (rows, hidden, n_rg, name)
 
 
+def test_which_kernel_takes_one_to_five_rows(P):
+    """513-768 row groups go to k_mvR, but not where k_mv1 has a compute unit to itself at depths between 4096 and 8192 (three rows at
+    5120, two at 6144), and deep matrices in nearly full rounds of three only up to a depth of 10240."""
+    from paper_2410_06916_amd import binding as B
+    for hidden, n_rg, rows, kernel in ((4096, 512, 1, "mv1"), (4096, 520, 1, "mvR"), (4096, 768, 5, "mvR"), (4096, 776, 1, "mv1"),
+                                       (5120, 640, 2, "mvR"), (5120, 640, 3, "mv1"), (5120, 768, 4, "mv1"), (6144, 576, 1, "mvR"),
+                                       (6144, 576, 2, "mv1"), (7168, 768, 3, "mv1"), (8192, 640, 2, "mvR"), (8192, 3584, 2, "mvR"),
+                                       (8192, 2560, 1, "mv1"), (10240, 3584, 1, "mvR"), (12288, 3072, 1, "mv1")):
+        cfg = B.make_config(si.ModelShape("few-rows", 1, hidden, 4, 4, 64, 8, 16 * n_rg, "bf16", 1e-5), 64)
+        assert B.projection_path(cfg, "lmhead", rows).startswith(kernel), (hidden, n_rg, rows)
+
+
 def test_arrival_counters_cover_every_split_block_projection(P):
     """A block projection that is split in depth has an arrival counter for each of the eight wavefronts of a workgroup of six or
     eight row groups: for every matrix that is split (at 256 compute units: up to 1024 row groups) they fit the 4096 counters
