@@ -68,13 +68,36 @@ __device__ inline uint32_t pack2(uint32_t lo, uint32_t hi) { return lo | (hi << 
 // window of weight loads that is deliberately kept in flight across the barrier.
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// The struct argument at byte `at` of the kernel's arguments, through a pointer the compiler cannot see behind: its fields are read
-// where they are used, and what the kernel does before waits for none of them.
-template <typename A>
-__device__ inline const A &late_args(int at) {
+// The type of a kernel's last argument and the byte where it lies among them all: each at the next multiple of its alignment.
+template <typename F>
+struct KernelArgs;
+template <typename... A>
+struct KernelArgs<void (*)(A...)> {
+    static constexpr int last_at() {
+        size_t at = 0, last = 0;
+        ((last = (at + alignof(A) - 1) / alignof(A) * alignof(A), at = last + sizeof(A)), ...);
+        return (int)last;
+    }
+    template <typename... T>
+    struct Last;
+    template <typename T>
+    struct Last<T> {
+        using type = T;
+    };
+    template <typename T, typename... R>
+    struct Last<T, R...> : Last<R...> {};
+    using last = typename Last<A...>::type;
+};
+static_assert(KernelArgs<void (*)(char *, int, char, int, double)>::last_at() == 24, "");
+
+// The struct that is the last argument of kernel F (a pointer type), through a pointer the compiler cannot see behind: its fields are
+// read where they are used, and what the kernel does before waits for none of them.
+template <typename F>
+__device__ inline const typename KernelArgs<F>::last &late_args() {
+    using A = typename KernelArgs<F>::last;
     auto p = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
-    return *(const A *)(const __attribute__((address_space(4))) A *)(p + at);
+    return *(const A *)(const __attribute__((address_space(4))) A *)(p + KernelArgs<F>::last_at());
 }
 
 // Copies 4 or 16 bytes per lane from global memory straight to LDS: lane l's go to byte BYTES * l of dst (wavefront-uniform).

@@ -320,7 +320,6 @@ __host__ __device__ inline int mv1_rot_pitch(int R, int head_dim) { return (R * 
 template <int EPI, int KS, int NS>
 __global__ __launch_bounds__(512, 4) void k_mv1(const unsigned char *Wt, const unsigned char *in_s, int T, int K, int R, int n_rg, int W,
                                                  int S, MvArgs rest) {  // 4 wavefronts per SIMD: <= 128 VGPRs, two workgroups per CU
-    constexpr int rest_at = 40;  // byte offset of `rest` among the arguments
     extern __shared__ __align__(16) unsigned char smem[];
     const int NC = 3 * R;
     // LDS: [16 B zeros][4T chunks x NC x 8 bf16][2 x 8 wavefronts x NC x 16 fp32][16 scales][512 scratch][64 touched][R x d rotary]
@@ -366,7 +365,7 @@ __global__ __launch_bounds__(512, 4) void k_mv1(const unsigned char *Wt, const u
     for (uint32_t p = wave * 1024; p < real_bytes; p += 8192)  // (the last piece runs on into the slice sums' place)
         to_lds<16>(in_s + min(p + lane16, real_bytes - 16), smem + 16 + p);
     __builtin_amdgcn_sched_barrier(0);
-    const MvArgs &a = late_args<MvArgs>(rest_at);
+    const MvArgs &a = late_args<decltype(&k_mv1<EPI, KS, NS>)>();
     NormPart np;
     if (EPI != EPI_RESID) np = mv_norm_load(a);
     // the residual values that the first round's epilogue adds to (R <= 5: two passes) and their gains, to LDS: wavefronts 0, 1 and 2
@@ -1010,7 +1009,6 @@ constexpr bool kMvrTwoBuffers = 2 * 8 * RG * 16 * NCB * 16 * 4 <= 150 * 1024;
 template <int EPI, int NCB, int RG, int NS>
 __global__ __launch_bounds__(512) void k_mvR(const unsigned char *Wt, const unsigned char *in_s, int T, int K, int NC, int n_rg, int W, int S,
                                               MvArgs rest) {
-    constexpr int rest_at = 40;  // byte offset of `rest` among the arguments
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int NCP = 16 * NCB;                 // columns as computed
     constexpr int kRed = 8 * RG * NCP * 16;       // floats of one round's slice sums
@@ -1050,7 +1048,7 @@ __global__ __launch_bounds__(512) void k_mvR(const unsigned char *Wt, const unsi
         }
     };
     // (the norm partials go out first; the scales are read by the epilogue only, so an LDS-only barrier will do)
-    const MvArgs &a = late_args<MvArgs>(rest_at);
+    const MvArgs &a = late_args<decltype(&k_mvR<EPI, NCB, RG, NS>)>();
     constexpr int share = 8 / RG;  // wavefronts per row group in the epilogue
     constexpr int kPasses = ((NCB <= 3 ? 16 : 32) / 4 + share - 1) / share;  // a wavefront's share of an epilogue of up to 16 / 32 rows
     const int eg = min(ks / share, RG - 1);  // this wavefront's row group there
