@@ -37,7 +37,8 @@ __device__ inline void split3(float v, uint16_t &hi, uint16_t &mid, uint16_t &lo
     lo = (uint16_t)f32_to_bf16_rne_finite(r2);
 }
 
-// The same for a product a * b: what is left after hi comes from the unrounded product (spelt out, so that it is the same in every kernel).
+// The same for a product a * b: what is left after hi comes from the unrounded product (spelt out, so that it is the same in every
+// kernel), so that the three terms are within 2^-26 of that, and need not add up to the fp32 value of a * b.
 __device__ inline void split3(float a, float b, uint16_t &hi, uint16_t &mid, uint16_t &lo) {
     const uint32_t h = f32_to_bf16_rne_finite(a * b);
     const float r1 = fmaf(a, b, -__uint_as_float(h << 16));

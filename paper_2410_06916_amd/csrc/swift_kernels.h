@@ -21,8 +21,8 @@ constexpr size_t kStaticAttnBytes = SWIFT_STATIC_SCRATCH_BYTES - kStaticCounterB
 // How the split activations of a block are laid out: a code that holds the rows the layout is pitched for and
 // how many bf16 terms an fp32 activation is split into.
 //  * exact layouts (draft, verify and tree blocks of up to kMaxRows rows; any block of up to 16 rows): pitched for
-//    the block's own row count, three terms (hi + mid + lo is the value exactly) and one fixed summation order,
-//    so that a row's result does not depend on the rows it shares a pass with;
+//    the block's own row count, three terms (see split3: the value exactly, or a product to 2^-26) and one fixed
+//    summation order, so that a row's result does not depend on the rows it shares a pass with;
 //  * bulk layouts (prefill blocks and candidate evaluation windows of more than 16 rows): pitched for 32 or 64
 //    rows, the first two terms only (relative error 2^-17 per element): a third less to stage, read and
 //    multiply, and no promise about the order.
@@ -131,9 +131,10 @@ constexpr int kAttnMfmaMaxRows = 32;
 hipError_t launch_attn_mfma(const AttnArgs &a, int n_cu, hipStream_t s);
 int attn_mfma_path_name(const AttnArgs &a, int n_cu, char *out, int capacity);
 size_t attn_mfma_partial_floats(const AttnArgs &a, int n_cu);
-// True when the attention of a block runs on the one-workgroup-per-(kv head, row) kernel (no partial
-// buffers: one launch may then cover any number of rows); false: the split kernel, at most kMaxRows
-// rows per launch.  Depends on the cache capacity and the head count only.
+// Short caches of models with enough kv heads to occupy the chip with a single row.  The row-at-a-time kernels give a (kv head, row) one
+// workgroup there (no partial buffers: one launch may then cover any number of rows; elsewhere ranges, at most kMaxRows rows per launch);
+// the matrix-core kernel takes workgroups of eight wavefronts and ranges of 256 slots, with partial results and arrival counters (see
+// am_plan).  Depends on the cache capacity and the head count only.
 inline bool attn_uses_head_kernel(int max_seq, int n_kv_heads) { return max_seq <= 1600 && n_kv_heads >= 24; }
 hipError_t launch_attn_decode(int dtype, const AttnArgs &a, int n_cu, hipStream_t s);
 // Writes the name of the kernel instance launch_attn_decode would take for `a` (e.g. "split<bf16, group 1,
@@ -235,14 +236,15 @@ struct TileArgs {
 hipError_t launch_tile_weights(const TileArgs &a, hipStream_t s);
 
 // Activations between the tiled kernels.  An fp32 activation vector of R rows (tokens) that
-// feeds a projection is kept as three bf16 terms per value (value = hi + mid + lo exactly), laid
+// feeds a projection is kept as three bf16 terms per value (hi + mid + lo is the value exactly where it
+// is an fp32 number, and a product of two to 2^-26: split3), laid
 // out as the MFMA B operand: [K/8 chunks][NC = 3R columns][8 k] bf16, column 3r + term (bulk
 // layouts: the first two terms, NC = 2 x 32 or 2 x 64 columns, column 2r + term; block_terms).  The
 // residual stream itself stays fp32 [R][H]; the kernel that updates it also writes the split of
 // (x * gain of the next consumer) and, per 16-row group, the partial sums of squares of x, so the
 // consumer only adds up the partials (fixed order) to get the RMSNorm scale 1/sqrt(mean x^2 + eps)
 // and applies it to its results (W.(x*g) * scale == W.(x*scale*g) up to fp32 rounding).
-//
+
 // A pointer to device memory that the compiler knows as such wherever the struct that holds it was read from (it finds that out
 // by itself for the arguments of a kernel, not behind late_args; through generic pointers a kernel waits for all its loads at once).
 template <typename T>

@@ -368,7 +368,8 @@ __global__ __launch_bounds__(512, 4) void k_mv1(const unsigned char *Wt, const u
     const MvArgs &a = late_args<decltype(&k_mv1<EPI, KS, NS>)>();
     NormPart np;
     if (EPI != EPI_RESID) np = mv_norm_load(a);
-    // the residual values that the first round's epilogue adds to (R <= 5: two passes) and their gains, to LDS: wavefronts 0, 1 and 2
+    // the residual values of the first round's row group (R <= 5: two passes) and their gains, to LDS: wavefronts 0, 1 and 2.  Used where
+    // it is the only round; the epilogues of several rounds read their own.  (Left out there: 1024 row groups, depth 4096 22.8 / 22.9 us.)
     auto *resid = (__attribute__((address_space(3))) float *)nscratch;
     if (EPI == EPI_RESID && G == 1 && wave < 3) {
         const int row = min(16 * min((int)blockIdx.x, last_rg) + col, a.O - 1);
@@ -1172,8 +1173,8 @@ constexpr int mvr_steps(int ncb, int rg) {
     return n > 10 ? 10 : n;
 }
 
-// Other depths for slices that the first one cuts badly.  (A step past a slice's end reads nothing, but it is issued and multiplied, and
-// while it holds its place in the window fewer loads are in flight.)  us, 256 row groups, 9 rows, windows of 8 / 10 / 11 steps: 4 tiles
+// Other depths for slices that the first one cuts badly.  (A step past a slice's end reads nothing and is not multiplied, but it is
+// requested, and while it holds its place in the window fewer loads are in flight.)  us, 256 row groups, 9 rows, windows of 8 / 10 / 11 steps: 4 tiles
 // 5.2 / 5.7 / 5.7, 16 tiles (7B o_proj) 9.8 / 10.3 / 10.5, 20: 12.0 / 11.6 / 11.8, 24: 13.3 / 14.0 / 14.5, 28: 15.4 / 15.2 / 15.5, 40: 20.1 /
 // 20.1 / 20.4, 43 (7B down_proj): 22.1 / 22.3 / 21.6.  Eleven steps only for one row group and up to two column blocks.
 constexpr int mvr_other_steps(int ns) { return ns > 8 ? 8 : ns == 8 ? 7 : ns > 4 ? 4 : ns == 3 ? 2 : ns; }
