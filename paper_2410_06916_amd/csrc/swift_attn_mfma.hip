@@ -15,7 +15,8 @@
 //    range's chunks round-robin, each folding its chunks in order into a running (max, sum, weighted values)
 //    with S^T = K Q^T and O^T += V^T P^T (queries and probabilities as two bf16 terms each: relative error
 //    2^-17 against the 2^-9 of the bf16 keys and values; fp32 sums); the wavefronts' results are merged in
-//    wavefront order, the ranges' in range order (by the last workgroup of a head, or k_attn_mfma_combine);
+//    wavefront order, the ranges' in range order (by the last workgroup of a head, by one workgroup that walks them all, or by
+//    k_attn_mfma_combine: the same bits);
 //  * the row's own slot (its key and value, written to the cache by the projection kernel of the same pass)
 //    is merged last, in fp32 vector arithmetic.  For a tree row the prefix beyond the committed slots is
 //    the first candidates of the levels above it: one mapping for all rows, so tree rows share the loads

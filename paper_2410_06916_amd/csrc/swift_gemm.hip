@@ -46,8 +46,8 @@ constexpr int kNormFloats = 2 * 16 * 64;  // scratch of gemm_norm_scales
 // RMSNorm scales of the workgroup's two sub-blocks: rs[64 wn + r].  Thread (wn, q, r4) adds the partials q, q + 16,
 // .. of rows 4 r4 .. 4 r4 + 3 of sub-block wn (16 loads of 16 bytes in flight at a time); then one thread per row
 // adds the sixteen sums in order.  The first 256 partials are requested ahead of the ring's first stages, so that they do not queue
-// behind 140 KB of tiles, and added up once those are on their way; the scales are read by the epilogue only, so no barrier here waits for
-// more than LDS.
+// behind 140 KB of tiles, and added up once those are on their way, where registers allow (kLateNorm; else before); the scales are read by
+// the epilogue only, so no barrier here waits for more than LDS.
 struct GemmNorm {
     f32x4 v[16];
 };

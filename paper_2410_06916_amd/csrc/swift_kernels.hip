@@ -42,13 +42,17 @@ __device__ inline float block_sum_256(float v, float *red /* >= 4 floats of LDS 
 // Inside a launch it is the number of memory latencies in a row.  So everything that does not hang on another load is requested
 // at once, ahead of the norm: the activation rows and gains, the weights of the wavefront's first unit and what its epilogue needs
 // (residual values, rotary angles); the arguments of the first loads are the kernel's leading ones, in registers at its start.
-// (Depths of up to kGemvAhead chunks of 64 lanes, 1024 values for fp32; what lies beyond is read where it is used.)
+// (AHEAD: depths of up to kGemvAhead chunks of 64 lanes, 1024 values for fp32.  Of a deeper matrix only the first unit's weights are requested
+// ahead of the norm, and not by pairs of rows, whose loop the values in registers hold up.  us, with / without: pairs, down_proj 4096 x
+// 11008, 3 rows 123 / 94, 32 rows 999 / 846, o_proj of 1536, 3 rows 7.3 / 6.4; eight rows, gate/up 11008 x 4096, 5 rows 190 / 211, 5504 x 2048, 32
+// rows 167 / 176; four, o_proj 4096 x 5504, 32 rows 275 / 280; one, q|k|v 9.5 / 10.5.)
 constexpr int kGemvAhead = 4;
-template <typename T, int EPI, int RB>
+template <typename T, int EPI, int RB, bool AHEAD>
 __global__ __launch_bounds__(kGemvThreads) void k_gemv(const void *Wv, const float *xin, const float *gain, int K, int O, int R, GemvArgs a) {
     extern __shared__ __align__(16) float xs[];  // [RB][K] activations (normalised if gain != null); depths requested ahead: [RB][4] sums
     __shared__ float red[4];
     constexpr int kAhead = kGemvAhead;           // chunks per lane, and activation values per thread and row, requested ahead
+    constexpr bool kFirst = AHEAD || RB != 2;    // the first unit's weights among them
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row0 = (int)blockIdx.y * RB, n_rows = min(RB, R - row0);
 
@@ -89,7 +93,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(const void *Wv, const flo
 
     // ---- requests
     u32x4 wa0[kAhead], wb0[kAhead];
-    {
+    if constexpr (kFirst) {
         int ra, rb;
         unit_rows(min(u0, n_units - 1), ra, rb);
         const u32x4 *wa = (const u32x4 *)(W + (size_t)ra * K), *wb = (const u32x4 *)(W + (size_t)rb * K);
@@ -103,8 +107,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(const void *Wv, const flo
     }
     // ---- prologue: stage the activation rows in LDS, RMS-normalised when a gain is given (rows past the block: the
     // last row once more, dropped at the end)
-    const bool ahead = K <= kAhead * kGemvThreads;
-    if (ahead) {
+    if constexpr (AHEAD) {
         float x[RB][kAhead], gv[kAhead];
 #pragma unroll
         for (int q = 0; q < kAhead; ++q) {
@@ -189,7 +192,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(const void *Wv, const flo
             }
         };
         int c = lane;
-        if (u == u0) {
+        if (kFirst && u == u0) {
 #pragma unroll
             for (int q = 0; q < kAhead; ++q, c += 64)
                 if (c < chunks) add(c, wa0[q], wb0[q]);
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(const void *Wv, const flo
                 yb0 = sb;
             }
         }
-        if (u != u0 || !ahead) load_side(u);
+        if (!AHEAD || u != u0) load_side(u);
         if (lane >= n_rows) continue;
 
         if (EPI == EPI_QKV) {
@@ -240,12 +243,12 @@ __global__ __launch_bounds__(kGemvThreads) void k_gemv(const void *Wv, const flo
     }
 }
 
-template <typename T, int EPI, int RB>
-static hipError_t launch_gemv_t(const GemvArgs &a, int n_cu, hipStream_t s) {
-    const size_t lds = ((size_t)RB * a.K + (a.K <= kGemvAhead * kGemvThreads ? 4 * RB : 0)) * sizeof(float);
+template <typename T, int EPI, int RB, bool AHEAD>
+static hipError_t launch_gemv_ta(const GemvArgs &a, int n_cu, hipStream_t s) {
+    const size_t lds = ((size_t)RB * a.K + (AHEAD ? 4 * RB : 0)) * sizeof(float);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gemv<T, EPI, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        hipError_t e = hipFuncSetAttribute((const void *)k_gemv<T, EPI, RB, AHEAD>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            160 * 1024 - 64);
         if (e != hipSuccess) return e;
         attr_set = true;
@@ -257,9 +260,14 @@ static hipError_t launch_gemv_t(const GemvArgs &a, int n_cu, hipStream_t s) {
     int grid = n_cu * occupancy;
     if (grid > wg_needed) grid = wg_needed;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL((k_gemv<T, EPI, RB>), dim3(grid, (a.R + RB - 1) / RB), dim3(kGemvThreads), lds, s, a.W, a.xin, a.gain, a.K, a.O,
+    hipLaunchKernelGGL((k_gemv<T, EPI, RB, AHEAD>), dim3(grid, (a.R + RB - 1) / RB), dim3(kGemvThreads), lds, s, a.W, a.xin, a.gain, a.K, a.O,
                        a.R, a);
     return hipGetLastError();
+}
+
+template <typename T, int EPI, int RB>
+static hipError_t launch_gemv_t(const GemvArgs &a, int n_cu, hipStream_t s) {
+    return a.K <= kGemvAhead * kGemvThreads ? launch_gemv_ta<T, EPI, RB, true>(a, n_cu, s) : launch_gemv_ta<T, EPI, RB, false>(a, n_cu, s);
 }
 
 hipError_t launch_gemv(int dtype, int epi, const GemvArgs &a, int n_cu, hipStream_t s) {

@@ -1361,3 +1361,27 @@ def test_short_cache_attention_of_many_heads(d, q_heads, kv, cap, prompt, rows, 
     assert long.prefill(ids) == first and "4 wavefronts" in long.attn_path(1)
     assert np.all(hp.rel_err_rowmax(single, long.verify(toks[:rows], True)[1]) <= TOL["bf16"])
     long.close()
+
+
+@pytest.mark.parametrize("hidden,ffn", [(1024, 1032), (1032, 1024), (264, 16384)])
+def test_fp32_depths_around_what_is_requested_ahead(oracle_lib, hidden, ffn):
+    """The fp32 projections request a whole activation row ahead up to a depth of 1024 values, and past it the first weights, but not for
+    pairs of rows (all that LDS takes of 16384): rows of blocks equal the same tokens decoded alone, and the oracle's logits."""
+    import paper_2410_06916_amd as P
+    shape = si.ModelShape("fp32-ahead", 2, hidden, 4, 2, 64, ffn, 256, "fp32", 1e-5)
+    o, g = _pair(oracle_lib, shape, hp.shaped_weights(shape, seed=21), 80, threads=8)
+    prompt = si.uniform_ids(5, 20, shape.vocab)
+    first = g.prefill(prompt)
+    assert o.prefill(prompt)[0] == first
+    toks, single = [first], []
+    for _ in range(9):
+        tgt, lg = g.verify([g.pending], True)
+        g.accept()
+        toks.append(int(tgt[0]))
+        single.append(lg[0])
+    for rows in (2, 3, 5, 9):
+        g.rollback(20, first)
+        assert np.array_equal(g.verify(toks[:rows], True)[1], np.stack(single[:rows])), rows
+    assert np.all(hp.rel_err_rowmax(np.stack(single), o.verify(toks[:9], True)[1]) <= TOL["fp32"])
+    g.close()
+    o.close()
