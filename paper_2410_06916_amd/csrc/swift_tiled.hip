@@ -1265,14 +1265,15 @@ static int mvr_line(const MvArgs &a, int n_cu, int ncb) {
     return rg;
 }
 // Row groups per workgroup round for k_mvR, or 0: k_mvN.  From eleven exact (17 bulk) rows on, k_mvN takes the matrices that its
-// workgroups of six row groups cover in one round with K whole (us, k_mvR / k_mvN, 7B gate/up: 16 rows 35.8 / 33.5, 21 rows 43.0 /
-// 35.3, 26 rows 48.1 / 38; 9 rows 33 / 34); elsewhere what lies beyond the line.
-// The line prices the predecessor of k_mvN, so it is not where today's two kernels break even (both timed at the 7B, 13B and 70B
-// widths, 6-32 rows: profiles/block_projection_sweep.txt, third table).  Beyond it k_mvN is faster throughout (us, k_mvR / k_mvN: 7B, 31
-// rows down_proj 41.8 / 28.2, LM head 75 / 47.5; 13B, 24 rows gate/up 82 / 54).  Short of it k_mvR is where the matrix is narrow or
-// the rows few (7B, 9 rows q|k|v 20.4 / 23.5, 31 rows o_proj 17 / 20), and k_mvN would be by up to 32 % in a strip along it (13B, 18 rows LM
-// head 72.8 / 55.1, 9 rows gate/up 54.9 / 46.9, 21 rows q|k|v 42 / 34.5; 7B, 13 rows down_proj 28.6 / 23.1; 70B, 18 rows gate/up 187 / 160,
-// 16 rows down_proj 93 / 75): 3.5 % over all launches of the table.  Exact blocks come out the same bits either way.
+// workgroups of six row groups cover in one round with K whole (us, k_mvR / k_mvN, 7B gate/up: 16 rows 35.9 / 33.3, 21 rows 41.4 /
+// 34.5, 26 rows 46.8 / 37.4; 9 rows 32.2 / 32.7); elsewhere what lies beyond the line.
+// The line prices the predecessor of k_mvN, and steps past a slice's end as if they carried traffic, so it is not where today's two kernels
+// break even (both timed at the 7B, 13B and 70B widths, 6-32 rows: profiles/block_projection_sweep.txt, third table).  Beyond it k_mvN is
+// faster throughout (us, k_mvR / k_mvN: 7B, 31 rows down_proj 40.0 / 25.1, LM head 75.3 / 49.5; 13B, 24 rows gate/up 79.5 / 54.3).
+// Short of it k_mvR is where the matrix is narrow or the rows few (7B, 9 rows q|k|v 20.0 / 22.9, o_proj 9.7 / 13.3), and k_mvN would be by up
+// to 28 % in a strip along it (13B, 18 rows LM head 71.0 / 55.4, 9 rows gate/up 53.6 / 46.5, 21 rows q|k|v 41.0 / 33.5; 7B, 13 rows down_proj
+// 26.3 / 21.9; 70B, 18 rows gate/up 183.9 / 156.6, 16 rows down_proj 90.7 / 73.7): 3.3 % over all launches of the table.  Exact blocks come
+// out the same bits either way.
 static int mvr_row_groups(const MvArgs &a, int n_cu, int ncb) {
     if (ncb > 2 && ncb <= 6) {
         const MvnPlan p = mvn_plan(a, n_cu, true);
